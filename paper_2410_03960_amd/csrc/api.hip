@@ -368,6 +368,7 @@ int run_fused_kv(Run &r, const bf16_t *hidden, bool rstd_ready, Timer &tm) {
   g.A = hidden; g.lda = m.hidden; g.M = (int32_t)r.L.T; g.N = c->P * 2 * kvd; g.K = m.hidden;
   g.W = c->kv_pack; g.ldw = m.hidden; g.wpack = c->kvf_pack;   // gains are folded into kv_pack; rstd is applied in the epilogue
   g.rstd = r.at<float>(r.L.rstd); g.cos_sin = r.at<float2>(r.L.cos_sin);
+  g.partial = r.at<float>(r.L.skpart); g.partial_bytes = SKINNY_PARTIAL_BYTES;
   g.head_dim = m.head_dim; g.q_dim = m.n_q_heads * m.head_dim; g.kv_dim = kvd;
   g.slots = r.at<int64_t>(r.L.slots); g.cache = (bf16_t *)r.kv->data;
   g.cache_layer_stride = r.layer_stride; g.cache_kv_stride = r.plane; g.first_cache_layer = c->l;
@@ -418,8 +419,10 @@ int tail_gemm(const swiftkv_ctx *c, const bf16_t *A, int M, int N, int K, const 
   g.A = A; g.lda = K; g.M = M; g.K = K; g.ldw = K; g.C = C;
   if (epi == EPI_SWIGLU) { g.wtab = gu_tab; g.N = 2 * N; g.ldc = N; }
   else { g.W = W; g.N = N; g.ldc = N; }
+  g.partial = partial; g.partial_bytes = SKINNY_PARTIAL_BYTES;
+  if (epi == EPI_RESID) g.n_splits_out = n_splits_out;
   (void)c;
-  return launch_gemm(g, epi, 2, st);
+  return launch_gemm(g, epi, M < 1024 ? 0 : 2, st);
 }
 
 }  // namespace
@@ -707,15 +710,29 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   // (a) Fragment-order weights (large batches): the residual epilogue of the O / down GEMM leaves, next to
   //     the fp32 residual stream, ab = bf16(h * gain of the next norm) and the rows' sums of squares; the
   //     next projection reads ab and applies 1/rms as a row factor in its own epilogue.  No pass over h.
-  // (b) Otherwise one kernel per norm turns fp32 rows into normed bf16 rows.
-  const bool packed = !few_rows && c->have_wpack && T >= 1024;
+  // (b) Otherwise one kernel per norm turns fp32 rows into normed bf16 rows; it also adds up the K splits a
+  //     residual GEMM left behind, so (b) is taken whenever the O or the down GEMM is better off split.
+  const bool wpacked = !few_rows && c->have_wpack;   // the large GEMMs read the fragment-order copies
+  const auto resid_params = [&](const bf16_t *A, int K, const bf16_t *W, const bf16_t *wpack) {
+    GemmParams g{};
+    g.A = A; g.lda = K; g.M = T; g.N = d; g.K = K; g.W = W; g.ldw = K; g.C = h; g.ldc = d; g.wpack = wpacked ? wpack : nullptr;
+    g.partial = skp; g.partial_bytes = SKINNY_PARTIAL_BYTES;
+    return g;
+  };
+  bool packed = wpacked && T >= 1024;   // form (a)
+  if (packed) {
+    int32_t ns;
+    GemmParams go = resid_params(ob, qd, c->wo[0], c->wo_pack[0]), gd = resid_params(zb, m.ffn, c->wdown[0], c->down_pack[0]);
+    go.n_splits_out = gd.n_splits_out = &ns;
+    packed = plan_gemm_mid(go, EPI_RESID).n_splits == 1 && plan_gemm_mid(gd, EPI_RESID).n_splits == 1;
+  }
   const int n_ssq = d / 64;
   if (packed) {
     tm.begin(TC_NORM);
     launch_rmsnorm_rows(h, c->norm1[0], ab, T, d, m.rms_eps, rstd, st);
     tm.end();
   }
-  // Few-row batches: a residual GEMM that split K leaves the sum of its splits to the RMSNorm pass that
+  // Without form (a) a residual GEMM that split K leaves the sum of its splits to the RMSNorm pass that
   // reads the residual rows next (h_pend = number of splits waiting in skp; 1 = none).
   int32_t h_pend = 1;
   for (int j = 0; j < c->l; ++j) {
@@ -749,7 +766,8 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     } else {
       GemmParams g{};
       g.A = ab; g.lda = d; g.M = T; g.N = qd + 2 * kvd; g.K = d;
-      g.wtab = c->qkv_tab[j]; g.ldw = d; g.wpack = packed ? c->qkv_pack[j] : nullptr; g.rstd = packed ? rstd : nullptr;
+      g.wtab = c->qkv_tab[j]; g.ldw = d; g.wpack = wpacked ? c->qkv_pack[j] : nullptr; g.rstd = packed ? rstd : nullptr;
+      g.partial = skp; g.partial_bytes = SKINNY_PARTIAL_BYTES;
       g.cos_sin = r.at<float2>(r.L.cos_sin);
       g.head_dim = m.head_dim; g.q_dim = qd; g.kv_dim = kvd;
       g.q_out = qb; g.k_out = kb; g.v_out = vb;
@@ -822,9 +840,9 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       if (tail_gemm(c, ob, T, d, qd, c->wo[j], nullptr, nullptr, h, EPI_RESID, skp, st, &h_pend)) return fail(SWIFTKV_EHIP, "O GEMM launch failed");
       tm.end();
     } else {
-      GemmParams g{};
-      g.A = ob; g.lda = qd; g.M = T; g.N = d; g.K = qd; g.W = c->wo[j]; g.ldw = qd; g.C = h; g.ldc = d;
-      if (packed) { g.wpack = c->wo_pack[j]; g.hb = ab; g.hb_gain = c->norm2[j]; g.ssq = ssq; }
+      GemmParams g = resid_params(ob, qd, c->wo[j], c->wo_pack[j]);
+      if (packed) { g.hb = ab; g.hb_gain = c->norm2[j]; g.ssq = ssq; }
+      else g.n_splits_out = &h_pend;
       tm.begin(TC_O);
       if (launch_gemm(g, EPI_RESID, 0, st) != 0) return fail(SWIFTKV_EHIP, "O GEMM launch failed");
       tm.end();
@@ -846,17 +864,18 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       {
         GemmParams g{};
         g.A = ab; g.lda = d; g.M = T; g.N = 2 * m.ffn; g.K = d; g.wtab = c->gu_tab[j]; g.ldw = d;
-        g.wpack = packed ? c->gu_pack[j] : nullptr; g.rstd = packed ? rstd : nullptr;
-        g.C = zb; g.ldc = m.ffn;
+        g.wpack = wpacked ? c->gu_pack[j] : nullptr; g.rstd = packed ? rstd : nullptr;
+        g.C = zb; g.ldc = m.ffn; g.partial = skp; g.partial_bytes = SKINNY_PARTIAL_BYTES;
         tm.begin(TC_GATEUP);
         if (launch_gemm(g, EPI_SWIGLU, 0, st) != 0) return fail(SWIFTKV_EHIP, "gate/up GEMM launch failed");
         tm.end();
       }
       {
-        GemmParams g{};
-        g.A = zb; g.lda = m.ffn; g.M = T; g.N = d; g.K = m.ffn; g.W = c->wdown[j]; g.ldw = m.ffn; g.C = h; g.ldc = d;
+        GemmParams g = resid_params(zb, m.ffn, c->wdown[j], c->down_pack[j]);
         if (packed) {   // the next reader of h: the next layer's input norm, or (gain one) the fused K/V projection
-          g.wpack = c->down_pack[j]; g.hb = ab; g.hb_gain = j + 1 < c->l ? c->norm1[j + 1] : nullptr; g.ssq = ssq;
+          g.hb = ab; g.hb_gain = j + 1 < c->l ? c->norm1[j + 1] : nullptr; g.ssq = ssq;
+        } else if (j + 1 < c->l || c->P > 0) {   // (else the tail reads h without a norm pass in between)
+          g.n_splits_out = &h_pend;
         }
         tm.begin(TC_DOWN);
         if (launch_gemm(g, EPI_RESID, 0, st) != 0) return fail(SWIFTKV_EHIP, "down GEMM launch failed");
@@ -980,7 +999,7 @@ int swiftkv_op_gemm_packed(const void *A, const void *W, void *w_packed, void *C
   GemmParams g{};
   g.A = (const bf16_t *)A; g.lda = K; g.M = M; g.N = N; g.K = K; g.W = (const bf16_t *)W; g.ldw = K; g.C = C; g.ldc = N;
   g.wpack = (const bf16_t *)w_packed;
-  if (launch_gemm(g, EPI_STORE_BF16, 27, st)) return fail(SWIFTKV_EHIP, "gemm launch failed");
+  if (launch_gemm(g, EPI_STORE_BF16, 0, st)) return fail(SWIFTKV_EHIP, "gemm launch failed");
   return check_launch("packed-weight gemm");
 }
 

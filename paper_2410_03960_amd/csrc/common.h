@@ -70,7 +70,8 @@ enum GemmEpi {
   EPI_RESID = 2,       // C fp32 [M, ldc] += acc  (in place on the residual stream, which is kept in fp32)
   EPI_SWIGLU = 3,      // virtual N = 2*ffn in 16-row gate/up interleave; C bf16 [M, ffn]
   EPI_QKV = 4,         // rstd row scale, RoPE on q/k columns, q/k/v to separate row-major buffers
-  EPI_KV = 5           // rstd row scale, RoPE on K columns, paged scatter (bf16) or staging (+absmax)
+  EPI_KV = 5,          // rstd row scale, RoPE on K columns, paged scatter (bf16) or staging (+absmax)
+  EPI_PARTIAL = 6      // fp32 partial sums of one K split (a finishing pass or the consumer adds them up)
 };
 
 struct GemmParams {
@@ -108,13 +109,33 @@ struct GemmParams {
   const bf16_t *hb_gain;
   float *ssq;
   int32_t raster_gm;           // m tiles per rasterisation group (0 = default)
+  // K splits (launch_gemm_mid): scratch for the splits' partial sums, [split][M][N] fp32, or null (K is never split)
+  float *partial;
+  size_t partial_bytes;
+  int32_t *n_splits_out;       // HOST, or null.  Given (RESID only), the consumer of C adds the splits: their number goes here
+                               // (1 = C is final) and C is untouched when it is larger; null = C is always final
+  int32_t n_splits, split_steps;   // set by launch_gemm_mid: K splits and 64-wide k steps of each
 };
 
 // Matrix-instruction rate on given operand data, nothing else in the loop: `iters` x 16 independent
 // v_mfma_f32_32x32x16_bf16 per wave, 4 waves per workgroup, one workgroup per CU.
 int launch_mfma_rate(const bf16_t *operands, float *sink, int32_t n_workgroups, int32_t iters, hipStream_t st);
 int launch_gemm(const GemmParams &p, int epi, int variant, hipStream_t st);
-bool gemm_uses_packed_weights(const GemmParams &p);
+// Choice of kernel, tile height and K splits for more than 80 rows (gemm_mid.hip).
+enum MidKernel {
+  MID_NONE = 0,    // not a shape of these kernels
+  MID_WREG = 1,    // packed weights, activations by LDS-DMA (gemm_wreg.hip)
+  MID_PACKED = 2,  // packed weights, activations staged through registers: short tiles, two workgroups per CU
+  MID_ROWS = 3     // row-major weights
+};
+struct MidPlan {
+  MidKernel kernel;
+  int fm, n_splits, split_steps;   // tile = 32 fm rows x 256 columns; K splits and 64-wide k steps of each
+  double cost;                     // estimated time in us, adding the splits up included
+};
+MidPlan plan_gemm_mid(const GemmParams &p, int epi);
+int launch_gemm_mid(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st);
+int launch_gemm_wreg(const GemmParams &p, int epi, int fm, hipStream_t st);
 
 // skinny (weight-streaming) GEMM for M <= 80 rows
 struct SkinnyParams {

@@ -243,7 +243,7 @@ int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows,
   if (rows <= 0) return 0;
   const dim3 grid((rows + 3) / 4), block(256);
   const float inv_d = 1.0f / (float)d;
-  if (rows <= 256 && d % 1024 == 0 && d / 1024 <= 8) {   // few rows: a workgroup per row, K splits added on the way
+  if ((rows <= 256 || n_splits > 1) && d % 1024 == 0 && d / 1024 <= 8) {   // few rows, or K splits to add on the way: a workgroup per row
 #define SKV_RMS_WG(CQ_)                                                                                            \
   case CQ_:                                                                                                        \
     hipLaunchKernelGGL(rmsnorm_row_wg_kernel<CQ_>, dim3(rows), block, 0, st, (float4 *)h, gain, (uint2 *)out, rows, eps, inv_d, rstd_out, \

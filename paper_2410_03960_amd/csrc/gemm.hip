@@ -19,7 +19,6 @@
 // rows each), which lets [W_Q;W_K;W_V], the 16-row interleave of W_gate/W_up and
 // the concatenated [W_K;W_V] of all AcrossKV group leaders be consumed in place.
 #include "common.h"
-#include <type_traits>
 
 namespace {
 
@@ -691,436 +690,10 @@ int launch_one(const GemmParams &p, hipStream_t st) {
   return 0;
 }
 
-// ---------------------------------------------------------------------------
-// Main loop that keeps the weight operand out of LDS.  The weights are static, so
-// they can be stored once in MFMA fragment order (`wpack`: for every block of 32
-// output rows and 16 k values, the 1 KB that the 64 lanes hold as first operand,
-// lane i at byte 16*i).  A wave then fetches its weight fragments with fully
-// coalesced 16-byte-per-lane loads straight into registers, four 64-wide k steps
-// ahead, and LDS carries the activations only: five stages of 256 rows x 128
-// bytes, filled by LDS-DMA in whole 128-byte row pieces, three steps ahead.
-// The four waves sit side by side along N (wave tile 256 x 64), so no weight byte
-// is loaded twice; every wave reads all of the activation tile from LDS (the same
-// LDS read volume as a 2 x 2 arrangement of 128 x 128 wave tiles, half the LDS
-// writes, half the LDS-DMA requests).  One barrier per 64-wide step, placed
-// before the last 16-wide sub-step, where the next step's activations are first
-// read.  Needs K % 256 == 0 (four register slots, statically indexed) and
-// N % 256 == 0.
-template <int EPI, int FM, bool NORM_OUT = false>   // NORM_OUT (RESID only): also the next projection's bf16 operand and the rows' sums of squares
-__device__ __forceinline__ void gemm_epilogue_n64(const GemmParams &p, floatx16 (&acc)[2][FM], const int m_base,
-                                                  const int n_base, const int lane, unsigned char *slab) {
-  // acc[bn][bm][4*jg + e] is C[m_base + bm*32 + l32][n_base + bn*32 + 8*jg + 4*g + e].  32 rows at a
-  // time go through a per-wave LDS slab (row stride padded by 16 bytes) and leave as 16-byte stores
-  // in which consecutive lanes cover a contiguous row segment.
-  const int l32 = lane & 31, g = lane >> 5;
-  if constexpr (EPI == EPI_RESID) {
-    // C (fp32, the residual stream) += acc.  Optionally also the bf16 operand of the next projection,
-    // hb = bf16(C_new * gain of that projection's RMSNorm), and the sum of squares of C_new over this
-    // wave's 64 columns (the consumer's epilogue applies 1/rms as a row factor).
-    constexpr int RS = 64 * 4 + 16;                // fp32 row stride in bytes
-    float *cbase = (float *)p.C + n_base;
-    const int ch = lane & 7, r8 = lane >> 3;       // this lane's 8 columns, its row inside a group of 8
-    float gv[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
-    if (NORM_OUT && p.hb_gain) {
-      const uint4 gq = *(const uint4 *)(p.hb_gain + n_base + ch * 8);
-      gv[0] = bf16lo(gq.x); gv[1] = bf16hi(gq.x); gv[2] = bf16lo(gq.y); gv[3] = bf16hi(gq.y);
-      gv[4] = bf16lo(gq.z); gv[5] = bf16hi(gq.z); gv[6] = bf16lo(gq.w); gv[7] = bf16hi(gq.w);
-    }
-    // The residual rows are requested for half of the wave tile at a time (128 registers; the operand
-    // registers of the main loop are free by now), all of a half before its first store: loads and stores
-    // share one counter, so a load issued between stores would wait for the stores before it.
-    constexpr int HB = FM / 2;
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      float4 res[HB][4][2];
-#pragma unroll
-      for (int b = 0; b < HB; ++b)
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-          const int m = m_base + (half * HB + b) * 32 + it * 8 + r8;
-          const float4 *src = (const float4 *)(cbase + (int64_t)(m < p.M ? m : p.M - 1) * p.ldc + ch * 8);
-          res[b][it][0] = src[0];
-          res[b][it][1] = src[1];
-        }
-#pragma unroll
-      for (int b = 0; b < HB; ++b) {
-        const int bm = half * HB + b;
-#pragma unroll
-        for (int bn = 0; bn < 2; ++bn)
-#pragma unroll
-          for (int jg = 0; jg < 4; ++jg)
-            *(float4 *)(slab + l32 * RS + (bn * 32 + 8 * jg + 4 * g) * 4) =
-                make_float4(acc[bn][bm][4 * jg], acc[bn][bm][4 * jg + 1], acc[bn][bm][4 * jg + 2], acc[bn][bm][4 * jg + 3]);
-        // a wave's LDS operations execute in order: the reads below see the writes above
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-          const int row = it * 8 + r8;
-          const int m = m_base + bm * 32 + row;
-          const float4 lo = *(const float4 *)(slab + row * RS + ch * 32), hi = *(const float4 *)(slab + row * RS + ch * 32 + 16);
-          const float4 r0 = res[b][it][0], r1 = res[b][it][1];
-          const float x[8] = {r0.x + lo.x, r0.y + lo.y, r0.z + lo.z, r0.w + lo.w, r1.x + hi.x, r1.y + hi.y, r1.z + hi.z, r1.w + hi.w};
-          if (m < p.M) {
-            float4 *dst = (float4 *)(cbase + (int64_t)m * p.ldc + ch * 8);
-            dst[0] = make_float4(x[0], x[1], x[2], x[3]);
-            dst[1] = make_float4(x[4], x[5], x[6], x[7]);
-            if constexpr (NORM_OUT)
-              *(uint4 *)(p.hb + (int64_t)m * p.ldc + n_base + ch * 8) =
-                  make_uint4(pack_bf16x2(x[0] * gv[0], x[1] * gv[1]), pack_bf16x2(x[2] * gv[2], x[3] * gv[3]),
-                             pack_bf16x2(x[4] * gv[4], x[5] * gv[5]), pack_bf16x2(x[6] * gv[6], x[7] * gv[7]));
-          }
-          if constexpr (NORM_OUT) {   // fixed order: the lane's 8 columns left to right, then a butterfly over the row's 8 lanes
-            float sq = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sq += x[e] * x[e];
-            sq += __shfl_xor(sq, 1);
-            sq += __shfl_xor(sq, 2);
-            sq += __shfl_xor(sq, 4);
-            if (ch == 0 && m < p.M) p.ssq[(int64_t)m * (p.N >> 6) + (n_base >> 6)] = sq;
-          }
-        }
-      }
-    }
-  } else if constexpr (EPI == EPI_QKV || EPI == EPI_KV) {
-    // The wave's 64 (virtual) columns are one head (head_dim 64: blocks = first / second half) or, for
-    // head_dim 128, half a head in the packed order: block 0 = columns s*32.. of the first half, block 1
-    // = their rotary partners s*32 + 64.. (s = parity of the wave tile inside the head).  Either way
-    // element v of block 0 and element v of block 1 are rotary partners.
-    const int hd = p.head_dim;
-    const int head_base = hd == 128 ? (n_base & ~127) : n_base;
-    const int s = hd == 128 ? ((n_base >> 6) & 1) : 0;
-    int kind, col0, proj = 0;                          // kind 0 = q, 1 = k, 2 = v; col0 = head's first column in its output
-    if constexpr (EPI == EPI_QKV) {
-      if (head_base < p.q_dim) { kind = 0; col0 = head_base; }
-      else if (head_base < p.q_dim + p.kv_dim) { kind = 1; col0 = head_base - p.q_dim; }
-      else { kind = 2; col0 = head_base - p.q_dim - p.kv_dim; }
-    } else {
-      proj = head_base / (2 * p.kv_dim);
-      const int within = head_base % (2 * p.kv_dim);
-      kind = within < p.kv_dim ? 1 : 2;
-      col0 = within % p.kv_dim;
-    }
-    const int blk_stride = hd == 128 ? 64 : 32;        // real columns between block 0 and block 1
-    constexpr int RS = 64 * 2 + 16;
-    float amax_h = 0.f;
-    // Destination of this wave's columns, selected once (uniform over the wave): base pointer of the
-    // head's first column and the row stride in elements; rows of the paged cache go through p.slots.
-    // (Selecting per store, through a table indexed by `kind`, cost a private-memory lookup, a full
-    // vmcnt wait and a flat store for each of the 32 stores of a wave tile.)
-    bf16_t *obase;
-    int64_t ostride;
-    bool paged = false;
-    if constexpr (EPI == EPI_QKV) {
-      obase = p.q_out; ostride = p.q_dim;
-      if (kind == 1) { obase = p.k_out; ostride = p.kv_dim; }
-      if (kind == 2) { obase = p.v_out; ostride = p.kv_dim; }
-    } else {
-      obase = p.stage + (int64_t)proj * 2 * p.kv_dim + (kind == 2 ? p.kv_dim : 0); ostride = p.N;
-      if (!p.stage) {
-        obase = p.cache + (int64_t)(p.first_cache_layer + proj) * p.cache_layer_stride + (kind == 2 ? p.cache_kv_stride : 0);
-        ostride = p.kv_dim; paged = true;
-      }
-    }
-    obase += col0 + s * 32;
-    // 1/rms of this lane's rows, all requested before the first use (one latency, not one per 32 rows)
-    float rsv[FM];
-#pragma unroll
-    for (int bm = 0; bm < FM; ++bm) {
-      const int m = m_base + bm * 32 + l32;
-      rsv[bm] = p.rstd ? p.rstd[m < p.M ? m : p.M - 1] : 1.f;
-    }
-    // Two passes, so that no load follows a store: loads and stores share one counter, and with both
-    // kinds pending every wait for a load becomes a wait for everything, stores included (which made
-    // each 32-row block of the epilogue wait for the previous block's stores to reach memory).
-    // Pass 1: per 32-row block the cos/sin pieces (requested CSD - 1 blocks ahead: they are 32-row gathers
-    // that mostly miss L2, and one block of arithmetic covers only a third of their latency) and, for the
-    // paged cache, the rows' slots; rotation, rounding, bf16 rows into the wave's LDS slab (FM blocks of 32 rows).
-    // Pass 2: the slab leaves as 16-byte stores in which consecutive lanes cover a contiguous row piece.
-    constexpr int SLAB_BM = 32 * RS;   // bytes per 32-row block
-    constexpr int CSD = (EPI == EPI_QKV) ? 4 : 2;   // the paged variant keeps 64 registers of slots instead
-    float4 csb[CSD][8];
-    auto load_cs = [&](int bm) {
-      const int m = m_base + bm * 32 + l32;
-      const float2 *cs = p.cos_sin + (int64_t)(m < p.M ? m : p.M - 1) * (hd / 2) + s * 32 + 4 * g;
-#pragma unroll
-      for (int jg = 0; jg < 4; ++jg) {
-        csb[bm % CSD][2 * jg] = *(const float4 *)(cs + 8 * jg);
-        csb[bm % CSD][2 * jg + 1] = *(const float4 *)(cs + 8 * jg + 2);
-      }
-    };
-    if (kind != 2) {
-#pragma unroll
-      for (int b = 0; b < CSD - 1; ++b) load_cs(b);
-    }
-    int64_t orow[FM][4];   // output rows of this lane's stores (the paged cache: their slots)
-#pragma unroll
-    for (int bm = 0; bm < FM; ++bm)
-#pragma unroll
-      for (int it = 0; it < 4; ++it) {
-        const int mm = m_base + bm * 32 + it * 8 + (lane >> 3);
-        orow[bm][it] = mm;
-        if constexpr (EPI == EPI_KV) { if (paged) orow[bm][it] = p.slots[mm < p.M ? mm : p.M - 1]; }
-      }
-#pragma unroll
-    for (int bm = 0; bm < FM; ++bm) {
-      const int m = m_base + bm * 32 + l32;
-      const float rs = rsv[bm];
-      unsigned char *srow = slab + bm * SLAB_BM + l32 * RS;
-      if (kind != 2 && bm + CSD - 1 < FM) load_cs(bm + CSD - 1);
-#pragma unroll
-      for (int jg = 0; jg < 4; ++jg) {
-        float y1[4], y2[4];
-        const int i0 = 8 * jg + 4 * g;
-        float cv[4] = {1.f, 1.f, 1.f, 1.f}, sv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (kind != 2) {
-          const float4 c01 = csb[bm % CSD][2 * jg], c23 = csb[bm % CSD][2 * jg + 1];
-          cv[0] = c01.x; cv[1] = c01.z; cv[2] = c23.x; cv[3] = c23.z;
-          sv[0] = c01.y; sv[1] = c01.w; sv[2] = c23.y; sv[3] = c23.w;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float x1 = acc[0][bm][4 * jg + e] * rs, x2 = acc[1][bm][4 * jg + e] * rs;
-          y1[e] = x1 * cv[e] - x2 * sv[e];
-          y2[e] = x2 * cv[e] + x1 * sv[e];
-        }
-        const uint2 p1 = make_uint2(pack_bf16x2(y1[0], y1[1]), pack_bf16x2(y1[2], y1[3]));
-        const uint2 p2 = make_uint2(pack_bf16x2(y2[0], y2[1]), pack_bf16x2(y2[2], y2[3]));
-        *(uint2 *)(srow + i0 * 2) = p1;
-        *(uint2 *)(srow + (32 + i0) * 2) = p2;
-        if (p.amax && kind != 0 && m < p.M) {   // absmax of the values as stored (bf16-rounded)
-          const float a1 = fmaxf(fmaxf(fabsf(bf16lo(p1.x)), fabsf(bf16hi(p1.x))), fmaxf(fabsf(bf16lo(p1.y)), fabsf(bf16hi(p1.y))));
-          const float a2 = fmaxf(fmaxf(fabsf(bf16lo(p2.x)), fabsf(bf16hi(p2.x))), fmaxf(fabsf(bf16lo(p2.y)), fabsf(bf16hi(p2.y))));
-          amax_h = fmaxf(amax_h, fmaxf(a1, a2));
-        }
-      }
-    }
-    // a wave's LDS operations execute in order: the reads below see the writes above
-#pragma unroll
-    for (int bm = 0; bm < FM; ++bm)
-#pragma unroll
-      for (int it = 0; it < 4; ++it) {   // 8 rows per instruction, chunk ch = 8 local columns; local block ch/4
-        const int row = it * 8 + (lane >> 3), ch = lane & 7;
-        const int mm = m_base + bm * 32 + row;
-        const uint4 val = *(const uint4 *)(slab + bm * SLAB_BM + row * RS + ch * 16);
-        if (mm < p.M) *(uint4 *)(obase + orow[bm][it] * ostride + (ch >> 2) * blk_stride + (ch & 3) * 8) = val;
-      }
-    if (p.amax && kind != 0) {
-      const float a = wave_max(amax_h);
-      if (lane == 0)
-        atomicMax(p.amax + ((int64_t)(p.first_cache_layer + proj) * 2 + (kind == 2 ? 1 : 0)) * (p.kv_dim / hd) + col0 / hd, __float_as_uint(a));
-    }
-  } else {
-    static_assert(EPI == EPI_STORE_BF16 || EPI == EPI_SWIGLU, "epilogues of the 64-column wave tile");
-    constexpr int NC = (EPI == EPI_SWIGLU) ? 32 : 64;   // output columns of the wave tile
-    constexpr int RS = NC * 2 + 16;                      // bf16 row stride in bytes
-    constexpr int CPR = NC / 8, RPI = 64 / CPR;          // 16-byte chunks per row, rows per store instruction
-    float rsv[FM];
-    if constexpr (EPI == EPI_SWIGLU) {   // 1/rms of this lane's rows, all requested before the first use
-#pragma unroll
-      for (int bm = 0; bm < FM; ++bm) {
-        const int m = m_base + bm * 32 + l32;
-        rsv[bm] = p.rstd ? p.rstd[m < p.M ? m : p.M - 1] : 1.f;
-      }
-    }
-#pragma unroll
-    for (int bm = 0; bm < FM; ++bm) {
-      unsigned char *srow = slab + l32 * RS;
-      if constexpr (EPI == EPI_SWIGLU) {
-        const float rs = rsv[bm];
-#pragma unroll
-        for (int bn = 0; bn < 2; ++bn)
-#pragma unroll
-          for (int jg = 0; jg < 2; ++jg) {
-            float o[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float gt = acc[bn][bm][4 * jg + e] * rs, up = acc[bn][bm][4 * (jg + 2) + e] * rs;
-              o[e] = gt * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt)) * up;   // silu(gate) * up
-            }
-            *(uint2 *)(srow + (bn * 16 + 8 * jg + 4 * g) * 2) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
-          }
-      } else {
-#pragma unroll
-        for (int bn = 0; bn < 2; ++bn)
-#pragma unroll
-          for (int jg = 0; jg < 4; ++jg)
-            *(uint2 *)(srow + (bn * 32 + 8 * jg + 4 * g) * 2) =
-                make_uint2(pack_bf16x2(acc[bn][bm][4 * jg], acc[bn][bm][4 * jg + 1]), pack_bf16x2(acc[bn][bm][4 * jg + 2], acc[bn][bm][4 * jg + 3]));
-      }
-      const int ch = lane % CPR;
-#pragma unroll
-      for (int it = 0; it < 32 / RPI; ++it) {
-        const int row = it * RPI + lane / CPR;
-        const int m = m_base + bm * 32 + row;
-        const uint4 val = *(const uint4 *)(slab + row * RS + ch * 16);
-        if (m >= p.M) continue;
-        bf16_t *dst = (bf16_t *)p.C + (int64_t)m * p.ldc + (EPI == EPI_SWIGLU ? n_base / 2 : n_base);
-        *(uint4 *)(dst + ch * 8) = val;
-      }
-    }
-  }
-}
-
-template <int EPI, bool NORM_OUT = false>
-__global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
-  constexpr int BM = 256, BN = 256, FM = 8;
-  constexpr int NSA = 5, STAGE = BM * 128;   // activation stages: 256 rows x 128 bytes (one 64-wide k step)
-  extern __shared__ __align__(16) unsigned char smem[];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, g = lane >> 5;
-
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = p.N / BN;
-  const int total = tiles_m * tiles_n;
-  const int per_xcd = (total + 7) / 8;
-  const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (logical >= total) return;
-  const int GM = p.raster_gm > 0 ? p.raster_gm : 8;
-  const int group = logical / (GM * tiles_n);
-  const int first_m = group * GM;
-  const int gsz = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
-  const int in_group = logical % (GM * tiles_n);
-  const int tm = first_m + in_group % gsz, tn = in_group / gsz;
-  const int m0 = tm * BM, n0 = tn * BN + wave * 64;   // n0: first column of this wave
-
-  // LDS-DMA sources: request i of this wave covers rows (wave*8 + i)*8 .. +7 of the tile, 128 bytes each;
-  // this lane fetches row +(lane>>3), the 16-byte chunk that lands at physical chunk lane&7
-  const bf16_t *a_ptr[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int r = (wave * 8 + i) * 8 + (lane >> 3);
-    int m = m0 + r;
-    m = m < p.M ? m : p.M - 1;
-    a_ptr[i] = p.A + (int64_t)m * p.lda + (((lane & 7) ^ ((r >> 1) & 7)) * 8);
-  }
-  // packed weight fragments of the wave's two 32-row blocks: (block, k16) at ((block * K/16) + k16) * 512 elements
-  const bf16_t *w_ptr[2];
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb) w_ptr[nb] = p.wpack + ((int64_t)(n0 / 32 + nb) * (p.K / 16)) * 512 + lane * 8;
-
-  typedef __attribute__((address_space(3))) void *lds_ptr_t;
-  const unsigned lds_base = (unsigned)(size_t)(lds_ptr_t)smem;
-
-  floatx16 acc[2][FM];
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-    for (int bm = 0; bm < FM; ++bm)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[nb][bm][v] = 0.f;
-
-  // activation fragment of m block bm, sub-step kk: row bm*32 + l32, chunk (2*kk + g) ^ swizzle(row);
-  // the swizzle of a 128-byte row is (row >> 1) & 7, the same for every m block, and kk enters as an XOR with 32*kk
-  const unsigned a_lane = l32 * 128 + ((g ^ ((l32 >> 1) & 7)) << 4);
-
-  bf16x8 wf[4][8];   // [slot of the step][2*kk + nb]
-  bf16x8 af[2][FM];
-  const int nk = p.K / 64;
-
-  auto issue_a = [&](int i, int stage, int step) {
-    lds_dma16(a_ptr[i] + (int64_t)step * 64, lds_base + stage * STAGE + (wave * 8 + i) * 1024);
-  };
-  // Plain loads: the compiler places their vmcnt waits.  It counts only these loads, not the LDS-DMA
-  // requests issued from inline assembly in between, so its waits are stricter than necessary, never
-  // weaker.  (Hand-placed waits that relied on register loads and LDS-DMA completing in one common
-  // order gave results that changed from run to run: the two kinds do not complete in issue order
-  // relative to each other.)
-  auto load_w = [&](bf16x8 &dst, int nb, int kk, int step) {
-    dst = *(const bf16x8 *)(w_ptr[nb] + ((int64_t)step * 4 + kk) * 512);
-  };
-
-  // prologue: steps 0, 1, 2 requested (16 requests per wave and step, activations and weights alternating)
-#pragma unroll
-  for (int s0 = 0; s0 < 3; ++s0) {
-    const int step = s0 < nk ? s0 : nk - 1;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      issue_a(i, s0, step);
-      load_w(wf[s0][i], i & 1, i >> 1, step);
-    }
-  }
-  __builtin_amdgcn_s_waitcnt(0x4F70);   // vmcnt(16): step 0 has landed (this wave's part; at most the 16 LDS-DMA requests of steps 1, 2 remain)
-  __builtin_amdgcn_s_barrier();
-#pragma unroll
-  for (int bm = 0; bm < FM; ++bm) af[0][bm] = *(const bf16x8 *)(smem + a_lane + bm * 4096);
-
-  int sa = 0;   // stage of the current step
-  auto step_fn = [&](auto slot_c, const int it) {
-    constexpr int slot = decltype(slot_c)::value;
-    constexpr int lslot = (slot + 3) & 3;                 // the slot freed by the previous step takes the weights of step it+3
-    const int sn = sa == NSA - 1 ? 0 : sa + 1;            // stage of step it+1
-    const int sld = sa >= 2 ? sa - 2 : sa + 3;            // stage of step it+3 = stage of step it-2 (free)
-    const int kl = it + 3 < nk ? it + 3 : nk - 1;         // clamped: the request count per step stays constant
-    const unsigned char *st = smem + sa * STAGE, *stn = smem + sn * STAGE;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      if (kk == 3) {
-        // Step it+1 (requested during step it-2) must be resident before its first fragments are read.
-        // 14 LDS-DMA requests are younger than it (8 of step it-1, 6 of this step).  Register loads and
-        // LDS-DMA do not complete in one common order, so all 14 requests that may stay in flight could
-        // be LDS-DMA ones: the wait is for 14 in total, not for 14 + the 14 younger weight loads.
-        __builtin_amdgcn_s_waitcnt(0x0F7E);   // vmcnt(14)
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int nb = i / 8, bm = i % 8;
-        acc[nb][bm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[slot][kk * 2 + nb], af[kk & 1][bm], acc[nb][bm], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i < 8) af[(kk + 1) & 1][i] = *(const bf16x8 *)((kk < 3 ? st : stn) + (a_lane ^ (unsigned)(((kk + 1) & 3) * 32)) + i * 4096);
-        if (i % 8 == 3) issue_a(kk * 2 + i / 8, sld, kl);
-        if (i % 8 == 7) load_w(wf[lslot][kk * 2 + i / 8], i / 8, kk, kl);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    sa = sn;
-  };
-  for (int it = 0; it < nk; it += 4) {
-    step_fn(std::integral_constant<int, 0>{}, it);
-    step_fn(std::integral_constant<int, 1>{}, it + 1);
-    step_fn(std::integral_constant<int, 2>{}, it + 2);
-    step_fn(std::integral_constant<int, 3>{}, it + 3);
-  }
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // drain the clamped extra requests ...
-  __builtin_amdgcn_s_barrier();         // ... of every wave, before LDS is reused by the epilogue
-  // per-wave slab: one 32-row block of fp32 (272-byte rows), or, for the rotating epilogues, all eight blocks of bf16 (144-byte rows)
-  unsigned char *slab = smem + wave * ((EPI == EPI_QKV || EPI == EPI_KV) ? FM * 32 * (64 * 2 + 16) : 32 * (64 * 4 + 16));
-  gemm_epilogue_n64<EPI, FM, NORM_OUT>(p, acc, m0, n0, lane, slab);
-}
-
-template <int EPI, bool NORM_OUT>
-int launch_wreg_k(const GemmParams &p, hipStream_t st) {
-  constexpr int SMEM = 5 * 256 * 128;
-  auto kern = gemm_wreg_kernel<EPI, NORM_OUT>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-    if (e != hipSuccess) return (int)e;
-    attr_set = true;
-  }
-  const int tiles = ((p.M + 255) / 256) * (p.N / 256);
-  hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), SMEM, st, p);
-  return 0;
-}
-template <int EPI>
-int launch_wreg(const GemmParams &p, hipStream_t st) {
-  if constexpr (EPI == EPI_RESID) {
-    if (p.hb && p.ssq) return launch_wreg_k<EPI, true>(p, st);
-  }
-  return launch_wreg_k<EPI, false>(p, st);
-}
-
-// variant: 0 = pick by shape; 1 = 256x256 tile, register-staged loads; 2 = 128x128 tile; 14 / 15 = the
-// five-stage direct-to-LDS loop with 4 / 8 waves; 27 = the packed-weight loop (needs p.wpack)
+// variant: 1 = 256x256 tile, register-staged loads; 2 = 128x128 tile; 14 / 15 = the five-stage direct-to-LDS
+// loop with 4 / 8 waves
 template <int EPI>
 int launch_epi(const GemmParams &p, int variant, hipStream_t st) {
-  if (variant == 0) variant = (p.M >= 1024) ? ((p.K % BK) == 0 ? 14 : 1) : 2;
-  if constexpr (EPI != EPI_STORE_F32) {
-    // weights available in fragment order: the loop that keeps them out of LDS
-    if ((variant == 27 || variant == 14) && gemm_uses_packed_weights(p)) return launch_wreg<EPI>(p, st);
-  }
-  if (variant == 27) variant = 14;
   if ((variant == 14 || variant == 15) && (p.K % BK) != 0) variant = 1;
   if (variant == 14) return launch_dlds5<256, 256, 2, 2, EPI>(p, st);
   if (variant == 15) return launch_dlds5<256, 256, 4, 2, EPI>(p, st);
@@ -1163,14 +736,16 @@ int launch_mfma_rate(const bf16_t *operands, float *sink, int32_t n_workgroups, 
   return 0;
 }
 
-// Whether launch_gemm(p, epi, 0, ...) reads the fragment-order copy p.wpack (and not p.W / p.wtab): the
-// driver needs to know, because that copy of a projection behind an RMSNorm has the norm's gain folded in.
-bool gemm_uses_packed_weights(const GemmParams &p) {
-  return p.wpack && p.M >= 1024 && (p.K % 256) == 0 && (p.N % 256) == 0;
-}
-
+// variant 0 picks by shape: the plan of gemm_mid.hip (packed weights at any number of rows, row-major ones below 1024),
+// else the 256 x 256 tile from 1024 rows on and the 128 x 128 tile below
 int launch_gemm(const GemmParams &p, int epi, int variant, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return 0;
+  if (p.n_splits_out) *p.n_splits_out = 1;
+  if (variant == 0) {
+    const MidPlan pl = plan_gemm_mid(p, epi);
+    if (pl.kernel != MID_NONE) return launch_gemm_mid(p, epi, pl, st);
+    variant = p.M >= 1024 ? 14 : 2;
+  }
   switch (epi) {
     case EPI_STORE_BF16: return launch_epi<EPI_STORE_BF16>(p, variant, st);
     case EPI_STORE_F32: return launch_epi<EPI_STORE_F32>(p, variant, st);

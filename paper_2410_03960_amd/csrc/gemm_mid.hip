@@ -1,0 +1,409 @@
+// bf16 MFMA GEMM for tens to thousands of rows:  C[M,N] = A[M,K] * W[N,K]^T.
+//
+// Decode batches beyond 80 rows, short prompts, prompt chunks: too many rows for the weight-streaming
+// kernels, too few 256 x 256 tiles for the 256 CUs.  What bounds these products is the bytes a CU fetches
+// per step: with a bounded number of requests in flight per CU a 64-wide step of a 128 x 256 tile (48 KB)
+// takes 0.65 to 0.85 us of fetching and 0.70 of matrix and LDS work alone, 1.0 together, whatever the
+// prefetch distance (two or four register sets, one or two workgroups per CU measured alike).  So the lever
+// is the shape of the work: the tallest tile whose tiles, times K splits, fill the CUs in whole rounds.
+// plan_gemm_mid chooses kernel, tile height and splits; the splits' fp32 partial sums meet in the norm pass
+// that reads the residual rows anyway or in a finishing pass with the epilogue's arithmetic.
+//
+// gemm_mid_kernel: 4 waves side by side along N (wave tile 32 FM x 64), activations through registers into
+// two LDS stages, weights in fragment order straight into registers, or row-major through a wave-private
+// part of LDS.  Everything is an ordinary load, so loads return in order and the compiler's counted waits are
+// exact.  In fragment order it serves the short tiles (FM = 2, 3: at most 256 registers, two workgroups per
+// CU; 96 x 4096 x 14336 28 us against 33 with the LDS-DMA loop of gemm_wreg.hip, which is ahead from FM = 4
+// on); row-major it serves every height (the tail of more than 80 sequences, contexts without packed copies).
+#include "gemm_epilogue.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace {
+
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+
+template <int EPI, int FM, bool PACKED, bool NORM_OUT>
+__global__ __launch_bounds__(256) void gemm_mid_kernel(GemmParams p) {
+  constexpr int BM = 32 * FM, STAGE = BM * 128;
+  constexpr int W_LDS = PACKED ? 0 : 8192;          // bytes of LDS per wave and stage for row-major weights
+  extern __shared__ __align__(16) unsigned char smem[];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + 255) / 256;
+  const int per_split = tiles_m * tiles_n, total = per_split * p.n_splits;
+  const int per_xcd = (total + 7) / 8;
+  const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (logical >= total) return;
+  const int split = logical / per_split, tile = logical % per_split;
+  constexpr int GM = 8;
+  const int group = tile / (GM * tiles_n);
+  const int first_m = group * GM;
+  const int gsz = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
+  const int in_group = tile % (GM * tiles_n);
+  const int tm = first_m + in_group % gsz, tn = in_group / gsz;
+  const int m0 = tm * BM, n0 = tn * 256 + wave * 64;   // n0: first column of this wave
+
+  const int all_steps = p.K / 64, s0 = split * p.split_steps;
+  const int nk = (all_steps - s0) < p.split_steps ? (all_steps - s0) : p.split_steps;   // >= 1 by the plan
+
+  // Activations: request i of this wave covers rows (wave*FM + i)*8 .. +7, 128 bytes each, 8 lanes to a row; chunk c
+  // of row r sits at LDS chunk c ^ ((r >> 1) & 7).  Addresses are a uniform base plus a 32-bit offset per lane.
+  unsigned a_off[FM];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int m = m0 + (wave * FM + i) * 8 + (lane >> 3);
+    a_off[i] = (unsigned)(m < p.M ? m : p.M - 1) * (unsigned)(p.lda * 2) + (lane & 7) * 16;
+  }
+  const unsigned a_st0 = wave * FM * 1024 + (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 4) ^ ((wave * FM & 1) * 4)) << 4);
+  const unsigned char *a_base = (const unsigned char *)p.A + (int64_t)s0 * 128;
+  // Weights (blocks past N re-read the last one; their results are dropped).  In fragment order a request is one
+  // fragment, 1 KB contiguous: request 2*kk + nb is the sub-step's fragment of the wave's 32-row block nb.  Row-major
+  // rows go through LDS like the activations, but through a part of it that only this wave touches: request i
+  // covers the wave's rows 8 i .. 8 i + 7, 128 bytes each (fetched as fragments, 32 bytes of 32 rows per request,
+  // the same rows took 1.5 to 1.8 times as long).  Bases are wave-uniform.
+  const unsigned char *w_base[PACKED ? 2 : 8];
+#pragma unroll
+  for (int i = 0; i < (PACKED ? 2 : 8); ++i) {
+    int blk = n0 / 32 + (PACKED ? i : i / 4);
+    blk = blk < p.N / 32 ? blk : p.N / 32 - 1;
+    if constexpr (PACKED) {
+      w_base[i] = (const unsigned char *)(p.wpack + ((int64_t)blk * (p.K / 16) + (int64_t)s0 * 4) * 512);
+    } else {
+      if ((EPI == EPI_QKV || EPI == EPI_KV || EPI == EPI_PARTIAL) && p.head_dim == 128) {   // rotary partner blocks side by side, as in the packed order
+        const int b = blk & 3;
+        blk = (blk & ~3) | (b == 1 ? 2 : b == 2 ? 1 : b);
+      }
+      const int n16 = blk * 2 + ((i >> 1) & 1);
+      w_base[i] = (const unsigned char *)((p.wtab ? p.wtab[n16] : p.W + (int64_t)n16 * 16 * p.ldw) + (i & 1) * 8 * p.ldw + (int64_t)s0 * 64);
+    }
+  }
+  const unsigned w_lane = PACKED ? lane * 16 : (lane >> 3) * (unsigned)(p.ldw * 2) + (lane & 7) * 16;
+  unsigned char *w_lds = smem + 2 * STAGE + wave * 8192;
+  const unsigned w_st0 = (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 4)) << 4);
+
+  floatx16 acc[2][FM];
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int bm = 0; bm < FM; ++bm)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[nb][bm][v] = 0.f;
+
+  const unsigned a_lane = l32 * 128 + ((g ^ ((l32 >> 1) & 7)) << 4);
+
+  u32x4_t wr[2][8];       // weights of the step in use and of the next one (fragment order), or of the next two (row-major, on their way to LDS)
+  u32x4_t ar[2][FM];      // activation rows of the next two steps on their way to LDS
+  bf16x8 af[2][FM], wf[2][2];
+
+  auto load_a = [&](u32x4_t &dst, int i, int step) { dst = *(const u32x4_t *)(a_base + (int64_t)step * 128 + (uint64_t)a_off[i]); };
+  auto load_w = [&](u32x4_t &dst, int i, int step) {
+    if constexpr (PACKED) dst = *(const u32x4_t *)(w_base[i & 1] + ((int64_t)step * 4 + (i >> 1)) * 1024 + (uint64_t)w_lane);
+    else dst = *(const u32x4_t *)(w_base[PACKED ? 0 : i] + (int64_t)step * 128 + (uint64_t)w_lane);
+  };
+  auto store_a = [&](int stage, int i, const u32x4_t &v) { *(u32x4_t *)(smem + stage * STAGE + (a_st0 ^ ((i & 1) * 64u)) + i * 1024) = v; };
+  auto store_w = [&](int stage, int i, const u32x4_t &v) { *(u32x4_t *)(w_lds + stage * 4 * W_LDS + (w_st0 ^ ((i & 1) * 64u)) + i * 1024) = v; };
+  auto frag_a = [&](int stage, int kk, int bm) { return *(const bf16x8 *)(smem + stage * STAGE + (a_lane ^ (unsigned)(kk * 32)) + bm * 4096); };
+  auto frag_w = [&](int stage, int kk, int nb) { return *(const bf16x8 *)(w_lds + stage * 4 * W_LDS + (a_lane ^ (unsigned)(kk * 32)) + nb * 4096); };
+
+  // prologue: the activations of steps 0 and 1, the weights of step 0 (row-major: also of step 1) requested, step 0 into LDS
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int step = s < nk ? s : nk - 1;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) load_a(ar[s][i], i, step);
+    if (s == 0 || !PACKED) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) load_w(wr[s][i], i, step);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < FM; ++i) store_a(0, i, ar[0][i]);
+  if constexpr (!PACKED) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) store_w(0, i, wr[0][i]);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+  for (int bm = 0; bm < FM; ++bm) af[0][bm] = frag_a(0, 0, bm);
+  if constexpr (!PACKED) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) wf[0][nb] = frag_w(0, 0, nb);
+  }
+
+  // One 64-wide step in stage `cur` (it mod 2).  Between its MFMAs: the fragments of the next sub-step, the requests of
+  // step it + 2 (fragment-order weights: it + 1), and in the first three sub-steps the LDS writes of step it + 1.
+  // Plain loads and LDS accesses throughout: the compiler places the waits, and loads return in order.
+  auto step_fn = [&](auto cur_c, const int it) __attribute__((always_inline)) {
+    constexpr int cur = decltype(cur_c)::value, nxt = cur ^ 1;
+    const int ka = it + 2 < nk ? it + 2 : nk - 1, kw = PACKED ? (it + 1 < nk ? it + 1 : nk - 1) : ka;   // past the end: repeated, never used
+    constexpr int NMF = 2 * FM, NST = PACKED ? FM : FM + 8;   // LDS writes per step
+    constexpr int SPK = (NST + 2) / 3;                        // ... per sub-step 0..2
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      if (kk == 3) {   // every wave's rows of step it+1 are in LDS, and every read of this step's stage has been issued and has returned
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const int a_lo = kk * FM / 4, a_hi = (kk + 1) * FM / 4;   // activation requests of this sub-step
+#pragma unroll
+      for (int i = 0; i < NMF; ++i) {
+        const int nb = i / FM, bm = i % FM;
+        const bf16x8 w = PACKED ? __builtin_bit_cast(bf16x8, wr[cur][kk * 2 + nb]) : wf[kk & 1][nb];
+        acc[nb][bm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, af[kk & 1][bm], acc[nb][bm], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i < FM) af[(kk + 1) & 1][i] = frag_a(kk < 3 ? cur : nxt, (kk + 1) & 3, i);
+        if constexpr (!PACKED) { if (i == FM || i == FM + 1) wf[(kk + 1) & 1][i - FM] = frag_w(kk < 3 ? cur : nxt, (kk + 1) & 3, i - FM); }
+        if (kk < 3) {   // writes NST per step, spread over the MFMAs of three sub-steps
+#pragma unroll
+          for (int w0 = i * SPK / NMF; w0 < (i + 1) * SPK / NMF; ++w0) {
+            const int j = kk * SPK + w0;
+            if (j < FM) store_a(nxt, j, ar[nxt][j]);
+            else if (j < NST) store_w(nxt, j - FM, wr[nxt][j - FM]);
+          }
+        }
+        if (i == FM / 2 && a_lo < a_hi) load_a(ar[cur][a_lo], a_lo, ka);
+        if (i == FM / 2 + FM && a_lo + 1 < a_hi) load_a(ar[cur][a_lo + 1], a_lo + 1, ka);
+        if (i == FM - 1) load_w(wr[PACKED ? nxt : cur][kk * 2], kk * 2, kw);
+        if (i == NMF - 1) load_w(wr[PACKED ? nxt : cur][kk * 2 + 1], kk * 2 + 1, kw);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  for (int it = 0;; it += 2) {
+    step_fn(std::integral_constant<int, 0>{}, it);
+    if (it + 1 >= nk) break;
+    step_fn(std::integral_constant<int, 1>{}, it + 1);
+    if (it + 2 >= nk) break;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // every wave is done with the stages before the epilogue reuses them
+  if (n0 >= p.N) return;
+  unsigned char *slab = smem + wave * ((EPI == EPI_QKV || EPI == EPI_KV) ? FM * 32 * (64 * 2 + 16) : 32 * (64 * 4 + 16));
+  gemm_epilogue_n64<EPI, FM, NORM_OUT>(p, acc, m0, n0, lane, slab, EPI == EPI_PARTIAL ? (int64_t)split * p.M * p.N : 0);
+}
+
+template <int EPI, int FM, bool PACKED, bool NORM_OUT = false>
+int launch_k(const GemmParams &p, hipStream_t st) {
+  constexpr int SLAB = 4 * ((EPI == EPI_QKV || EPI == EPI_KV) ? FM * 32 * (64 * 2 + 16) : 32 * (64 * 4 + 16));
+  constexpr int STAGES = 2 * 32 * FM * 128 + (PACKED ? 0 : 2 * 4 * 8192);
+  constexpr int SMEM = SLAB > STAGES ? SLAB : STAGES;
+  auto kern = gemm_mid_kernel<EPI, FM, PACKED, NORM_OUT>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+    if (e != hipSuccess) return (int)e;
+    attr_set = true;
+  }
+  const int total = ((p.M + 32 * FM - 1) / (32 * FM)) * ((p.N + 255) / 256) * p.n_splits;
+  hipLaunchKernelGGL(kern, dim3(((total + 7) / 8) * 8), dim3(256), SMEM, st, p);
+  return 0;
+}
+
+template <int EPI, int FM>
+int launch_e(const GemmParams &p, MidKernel k, hipStream_t st) {
+  if (k == MID_PACKED) {
+    if constexpr (EPI != EPI_STORE_F32 && FM <= 3) {
+      if constexpr (EPI == EPI_RESID) {
+        if (p.hb && p.ssq) return launch_k<EPI, FM, true, true>(p, st);
+      }
+      return launch_k<EPI, FM, true>(p, st);
+    }
+    return -1;
+  }
+  return launch_k<EPI, FM, false>(p, st);
+}
+template <int FM>
+int launch_f(const GemmParams &p, int epi, MidKernel k, hipStream_t st) {
+  switch (epi) {
+    case EPI_STORE_BF16: return launch_e<EPI_STORE_BF16, FM>(p, k, st);
+    case EPI_STORE_F32: return launch_e<EPI_STORE_F32, FM>(p, k, st);
+    case EPI_RESID: return launch_e<EPI_RESID, FM>(p, k, st);
+    case EPI_SWIGLU: return launch_e<EPI_SWIGLU, FM>(p, k, st);
+    case EPI_QKV: return launch_e<EPI_QKV, FM>(p, k, st);
+    case EPI_KV: return launch_e<EPI_KV, FM>(p, k, st);
+    case EPI_PARTIAL: return launch_e<EPI_PARTIAL, FM>(p, k, st);
+  }
+  return -1;
+}
+int launch_one(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st) {
+  if (pl.kernel == MID_WREG) return launch_gemm_wreg(p, epi, pl.fm, st);
+  switch (pl.fm) {
+    case 2: return launch_f<2>(p, epi, pl.kernel, st);
+    case 3: return launch_f<3>(p, epi, pl.kernel, st);
+    case 4: return launch_f<4>(p, epi, pl.kernel, st);
+    case 5: return launch_f<5>(p, epi, pl.kernel, st);
+  }
+  return -1;
+}
+
+// ---- K splits added up in split order, then the epilogue; 4 columns of C per thread ----
+__device__ __forceinline__ float4 sum_splits(const float *p, int64_t stride, int n) {
+  float4 s = *(const float4 *)p;
+  for (int k = 1; k < n; ++k) {
+    const float4 v = *(const float4 *)(p + k * stride);
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  }
+  return s;
+}
+template <int EPI>
+__global__ void splits_finish_kernel(GemmParams p) {
+  const int ncol = EPI == EPI_SWIGLU ? p.N / 2 : p.N;   // output columns
+  const int64_t id = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4, stride = (int64_t)p.M * p.N;
+  if (id >= (int64_t)p.M * ncol) return;
+  const int m = (int)(id / ncol), n = (int)(id % ncol);
+  if constexpr (EPI == EPI_SWIGLU) {   // every 32 virtual columns = 16 gate columns, then the matching 16 up columns
+    const float *src = p.partial + (int64_t)m * p.N + (n / 16) * 32 + n % 16;
+    const float rs = p.rstd ? p.rstd[m] : 1.f;
+    const float4 g4 = sum_splits(src, stride, p.n_splits), u4 = sum_splits(src + 16, stride, p.n_splits);
+    const float g[4] = {g4.x * rs, g4.y * rs, g4.z * rs, g4.w * rs}, u[4] = {u4.x * rs, u4.y * rs, u4.z * rs, u4.w * rs};
+    float o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = g[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g[e])) * u[e];   // silu(gate) * up
+    *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.ldc + n) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
+  } else {
+    const float4 s = sum_splits(p.partial + id, stride, p.n_splits);
+    if constexpr (EPI == EPI_STORE_F32) {
+      *(float4 *)((float *)p.C + (int64_t)m * p.ldc + n) = s;
+    } else if constexpr (EPI == EPI_RESID) {
+      float4 *dst = (float4 *)((float *)p.C + (int64_t)m * p.ldc + n);
+      const float4 r = *dst;
+      *dst = make_float4(r.x + s.x, r.y + s.y, r.z + s.z, r.w + s.w);
+    } else {
+      *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.ldc + n) = make_uint2(pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w));
+    }
+  }
+}
+// Q, K, V (EPI_QKV) or the later layers' K, V (EPI_KV): rotation, rounding, destination and absmax as in the GEMM's
+// own epilogue.  grid (rows, groups of 4 heads), one wave per head, a rotary pair per lane (half of them idle at head_dim 64).
+template <int EPI, int HD>
+__global__ __launch_bounds__(256) void rope_finish_kernel(GemmParams p) {
+  const int row = blockIdx.x, hs = blockIdx.y * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int n_kv = p.kv_dim / HD, n_q = EPI == EPI_QKV ? p.q_dim / HD : 0;
+  if (hs >= p.N / HD) return;
+  int kind, head, proj = 0;                              // kind 0 = q, 1 = k, 2 = v
+  if constexpr (EPI == EPI_QKV) {
+    kind = hs < n_q ? 0 : (hs < n_q + n_kv ? 1 : 2);
+    head = kind == 0 ? hs : (hs - n_q) % n_kv;
+  } else {
+    proj = hs / (2 * n_kv);
+    kind = 1 + (hs % (2 * n_kv)) / n_kv;
+    head = hs % n_kv;
+  }
+  bf16_t *dst;
+  if constexpr (EPI == EPI_QKV) dst = (kind == 0 ? p.q_out + (int64_t)row * p.q_dim : (kind == 1 ? p.k_out : p.v_out) + (int64_t)row * p.kv_dim) + head * HD;
+  else if (p.stage) dst = p.stage + (int64_t)row * p.N + hs * HD;
+  else dst = p.cache + (int64_t)(p.first_cache_layer + proj) * p.cache_layer_stride + (kind == 2 ? p.cache_kv_stride : 0) + p.slots[row] * p.kv_dim + head * HD;
+  const float *src = p.partial + (int64_t)row * p.N + hs * HD;
+  const int64_t stride = (int64_t)p.M * p.N;
+  const float rs = p.rstd ? p.rstd[row] : 1.f;
+  float a = 0.f;
+  const int i = lane;
+  if (i < HD / 2) {
+    float x0 = src[i], x1 = src[i + HD / 2];
+    for (int k = 1; k < p.n_splits; ++k) { x0 += src[k * stride + i]; x1 += src[k * stride + i + HD / 2]; }
+    x0 *= rs; x1 *= rs;
+    if (kind != 2) {
+      const float2 cs = p.cos_sin[(int64_t)row * (HD / 2) + i];
+      const float y0 = x0 * cs.x - x1 * cs.y, y1 = x1 * cs.x + x0 * cs.y;
+      x0 = y0; x1 = y1;
+    }
+    const bf16_t b0 = f32_to_bf16(x0), b1 = f32_to_bf16(x1);
+    dst[i] = b0;
+    dst[i + HD / 2] = b1;
+    a = fmaxf(fabsf(bf16_to_f32(b0)), fabsf(bf16_to_f32(b1)));   // absmax of the values as stored
+  }
+  if (p.amax && kind != 0) {
+    a = wave_max(a);
+    if (lane == 0) atomicMax(p.amax + ((int64_t)(p.first_cache_layer + proj) * 2 + (kind == 2 ? 1 : 0)) * n_kv + head, __float_as_uint(a));
+  }
+}
+
+template <int EPI>
+void launch_finish(const GemmParams &p, hipStream_t st) {
+  const int64_t quads = (int64_t)p.M * (EPI == EPI_SWIGLU ? p.N / 2 : p.N) / 4;
+  hipLaunchKernelGGL(splits_finish_kernel<EPI>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p);
+}
+template <int EPI>
+void launch_rope_finish(const GemmParams &p, hipStream_t st) {
+  const dim3 grid(p.M, (p.N / p.head_dim + 3) / 4);
+  if (p.head_dim == 128) hipLaunchKernelGGL((rope_finish_kernel<EPI, 128>), grid, dim3(256), 0, st, p);
+  else hipLaunchKernelGGL((rope_finish_kernel<EPI, 64>), grid, dim3(256), 0, st, p);
+}
+
+constexpr int MID_MAX_SPLIT = 16;
+
+}  // namespace
+
+// Time model, us: a fixed part (launch, the first loads) and, per round of workgroups, its 64-wide steps and its
+// epilogue.  The per-step times are those measured with every CU busy on products of 4096 and 14336 columns of K and
+// 2048 to 28672 columns of N over 96 to 2048 rows, weights from HBM; the epilogues those of 16384 rows.  K splits add
+// the partial sums' trip (written and read once more, about 4 TB/s) and, unless the consumer of the residual rows adds
+// them in a pass it makes anyway, a launch.  What the choice is worth, us (256 x 256 tile only -> this choice): 2048 x
+// 4096 x 14336 264 -> 206, 1024 x 4096 x 14336 265 -> 107, 8831 x 4096 x 14336 1010 -> 765; below 1024 rows (128 x 128
+// tile -> this choice): 333 x 28672 x 4096 160 -> 77, 333 x 4096 x 14336 190 -> 53, 160 x 6144 x 4096 73 -> 22.
+MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
+  MidPlan best{};
+  best.kernel = MID_NONE;
+  const bool packed = p.wpack && p.K % 256 == 0 && p.N % 256 == 0 && epi != EPI_STORE_F32;
+  if (p.M <= 80 || (uint64_t)p.M * (uint64_t)p.lda * 2 >= 0xffffffffull) return best;
+  if (!packed && (p.M >= 1024 || p.K % 64 != 0 || p.N % 64 != 0 || ((epi == EPI_QKV || epi == EPI_KV) && p.N % 128 != 0))) return best;
+  const bool norm_out = epi == EPI_RESID && p.hb && p.ssq;
+  const bool consumer = epi == EPI_RESID && p.n_splits_out;
+  const int all_steps = p.K / 64, unit = packed ? 4 : 1;
+  const int tiles_n = (p.N + 255) / 256;
+  // us per step of a round of up to 256 workgroups (t1); the forms that fit two workgroups to a CU: per 256 of more (t2)
+  struct Form { MidKernel kernel; int fm; double t1, t2; };
+  static const Form forms[] = {
+      {MID_WREG, 8, 1.46, 0}, {MID_WREG, 7, 1.27, 0}, {MID_WREG, 6, 1.12, 0}, {MID_WREG, 5, 0.99, 0}, {MID_WREG, 4, 0.89, 0},
+      {MID_PACKED, 3, 0.82, 0.73}, {MID_PACKED, 2, 0.76, 0.66},
+      {MID_ROWS, 5, 1.45, 0}, {MID_ROWS, 4, 1.33, 0}, {MID_ROWS, 3, 1.27, 0}, {MID_ROWS, 2, 1.20, 0.76}};
+  // epilogue of a 256-row tile
+  const double epi_us = norm_out ? 25 : epi == EPI_RESID || epi == EPI_QKV ? 12 : epi == EPI_KV ? 10 : 4;
+  for (const Form &f : forms) {
+    if ((f.kernel == MID_ROWS) == packed) continue;
+    const int64_t tiles = (int64_t)((p.M + 32 * f.fm - 1) / (32 * f.fm)) * tiles_n;
+    for (int want = 1; want <= std::min(MID_MAX_SPLIT, all_steps / unit); ++want) {
+      if (want > 1 && (!p.partial || norm_out)) break;
+      const int steps = ((all_steps / unit + want - 1) / want) * unit, s = (all_steps + steps - 1) / steps;
+      if (s != want) continue;
+      const size_t bytes = s > 1 ? (size_t)s * p.M * p.N * 4 : 0;
+      if (bytes > p.partial_bytes) break;
+      const double wgs = (double)(tiles * s);
+      const double rounds = f.t2 > 0 && wgs > 256 ? std::max(2.0, wgs / 256) : (double)((tiles * s + 255) / 256);
+      const double round_us = steps * (f.t2 > 0 && wgs > 256 ? f.t2 : f.t1) + 4 + (s > 1 ? 0 : epi_us * f.fm / 8);
+      const double cost = 7 + rounds * round_us + (s > 1 ? 2.0 * bytes / 4.0e6 + (consumer ? 0 : 5) : 0);
+      if (best.kernel == MID_NONE || cost < best.cost) best = MidPlan{f.kernel, f.fm, s, steps, cost};
+    }
+  }
+  // row-major, many columns: the 128 x 128 tile (two workgroups per CU, no K split) keeps up
+  if (!packed && best.kernel != MID_NONE) {
+    const int64_t tiles = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128);
+    if (tiles >= 384 && 10 + (double)((tiles + 511) / 512) * all_steps * 1.22 < best.cost) best.kernel = MID_NONE;
+  }
+  return best;
+}
+
+int launch_gemm_mid(const GemmParams &p0, int epi, const MidPlan &pl, hipStream_t st) {
+  GemmParams p = p0;
+  p.n_splits = pl.n_splits; p.split_steps = pl.split_steps;
+  if (p.n_splits_out) *p.n_splits_out = 1;
+  if (pl.n_splits == 1) return launch_one(p, epi, pl, st);
+  GemmParams q = p;
+  q.C = p.partial; q.ldc = p.N;
+  if (epi != EPI_QKV && epi != EPI_KV) q.head_dim = 0;   // the packed order of rotary operands is theirs alone
+  if (int e = launch_one(q, EPI_PARTIAL, pl, st)) return e;
+  if (epi == EPI_RESID && p.n_splits_out) { *p.n_splits_out = pl.n_splits; return 0; }
+  switch (epi) {
+    case EPI_STORE_BF16: launch_finish<EPI_STORE_BF16>(p, st); return 0;
+    case EPI_STORE_F32: launch_finish<EPI_STORE_F32>(p, st); return 0;
+    case EPI_RESID: launch_finish<EPI_RESID>(p, st); return 0;
+    case EPI_SWIGLU: launch_finish<EPI_SWIGLU>(p, st); return 0;
+    case EPI_QKV: launch_rope_finish<EPI_QKV>(p, st); return 0;
+    case EPI_KV: launch_rope_finish<EPI_KV>(p, st); return 0;
+  }
+  return -1;
+}
