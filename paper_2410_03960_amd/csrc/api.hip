@@ -116,7 +116,8 @@ Layout make_layout(const swiftkv_ctx *c, int64_t T, int32_t B, int64_t vt_ld, in
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
   L.err = take(256);
-  L.meta = take(L.m_words * 4);
+  L.ee_flags = take((size_t)B * 4);
+  L.meta = take(L.m_words * 4);   // err, ee_flags and meta are written by one copy
   L.positions = take(T * 4);
   L.seq_of = take(T * 4);
   L.last_rows = take((size_t)B * 4);
@@ -136,7 +137,6 @@ Layout make_layout(const swiftkv_ctx *c, int64_t T, int32_t B, int64_t vt_ld, in
   L.stage = take(fp8 ? T * (int64_t)c->P * 2 * kvd * 2 : 0);
   L.amax = take(fp8 ? (size_t)c->C * 2 * m.n_kv_heads * 4 : 0);
   L.ee_logits = take(c->ee_head ? (size_t)B * m.vocab * 4 : 0);   // logits of the extra head
-  L.ee_flags = take((size_t)B * 4);
   L.skpart = take(SKINNY_PARTIAL_BYTES);   // K-split partial sums of the weight-streaming GEMMs
   L.qkv32 = take((size_t)std::min<int64_t>(T, SKINNY_MAX_ROWS) * (qd + 2 * kvd) * 4);   // fp32 Q, K, V of few-row batches
   L.th = take((size_t)B * d * 4);
@@ -329,18 +329,20 @@ int run_plan(Run &r, const int32_t *token_ids) {
   swiftkv_ctx *c = r.c;
   // plan words: host vector -> pinned slot -> device, without waiting for the stream (a slot is only
   // waited for when the ring wraps around onto a copy that has not run yet)
-  const size_t bytes = r.hp.meta.size() * 4;
+  // The error flags, the attention kernel's item counters (words 4..12 of err) and the exit flags start at zero: their
+  // words precede the plan's and travel with them.
+  const size_t zeros = r.L.meta - r.L.err, bytes = zeros + r.hp.meta.size() * 4;
   if (int e = pin_reserve(c, bytes)) return e;
   const int slot = c->pin_next;
   c->pin_next = (slot + 1) % PIN_SLOTS;
   if (c->pin_used[slot]) HIP_TRY(hipEventSynchronize(c->pin_ev[slot]));
   unsigned char *stage = c->pin + (size_t)slot * c->pin_slot_bytes;
-  memcpy(stage, r.hp.meta.data(), bytes);
-  HIP_TRY(hipMemcpyAsync(r.ws + r.L.meta, stage, bytes, hipMemcpyHostToDevice, r.st));
+  memset(stage, 0, zeros);
+  memcpy(stage + zeros, r.hp.meta.data(), bytes - zeros);
+  HIP_TRY(hipMemcpyAsync(r.ws + r.L.err, stage, bytes, hipMemcpyHostToDevice, r.st));
   HIP_TRY(hipEventRecord(c->pin_ev[slot], r.st));
   c->pin_used[slot] = true;
-  launch_fill_u32(r.at<uint32_t>(r.L.err), 0, 16, r.st);   // error flags, and (words 4..12) the attention kernel's item counters
-  if (r.fp8) launch_fill_u32(r.at<uint32_t>(r.L.amax), 0, (int64_t)c->C * 2 * c->cfg.n_kv_heads, r.st);
+  if (r.fp8 && r.kv->scale_mode == SWIFTKV_SCALE_COMPUTE_ABSMAX) launch_fill_u32(r.at<uint32_t>(r.L.amax), 0, (int64_t)c->C * 2 * c->cfg.n_kv_heads, r.st);
   PlanParams pp{};
   pp.T = (int32_t)r.L.T; pp.B = r.L.B; pp.head_dim = c->cfg.head_dim; pp.n_blocks = r.kv->n_blocks;
   pp.max_blocks_per_seq = r.kv->max_blocks_per_seq; pp.vocab = c->cfg.vocab; pp.rope_theta = c->cfg.rope_theta;
@@ -377,7 +379,21 @@ int run_fused_kv(Run &r, const bf16_t *hidden, bool rstd_ready, Timer &tm) {
     g.amax = r.kv->scale_mode == SWIFTKV_SCALE_COMPUTE_ABSMAX ? r.at<uint32_t>(r.L.amax) : nullptr;
   }
   tm.begin(TC_KV);
-  if (launch_gemm(g, EPI_KV, 0, r.st) != 0) return fail(SWIFTKV_EHIP, "fused KV GEMM launch failed");
+  // Few rows: the weights stream once through the weight-streaming kernels (fp32 result and K splits in the scratch),
+  // then one pass rotates, rounds and scatters.  Measured with one row, 4096 x 4096: 72 us (a 128-row tile on 32 of
+  // the 256 CUs) -> 12; 64 rows x 32768 x 4096: 94 -> 66.
+  const size_t c_bytes = align_up((size_t)g.M * g.N * 4);
+  if (g.M <= SKINNY_MAX_ROWS && c_bytes <= SKINNY_PARTIAL_BYTES / 2) {
+    float *c32 = g.partial, *splits = c32 + c_bytes / 4;
+    int32_t ns = 1;
+    SkinnyParams sp{hidden, g.M, g.N, g.K, g.W, nullptr, c32, splits, SKINNY_PARTIAL_BYTES - c_bytes, nullptr, &ns};
+    if (launch_skinny(sp, EPI_STORE_F32, r.st)) return fail(SWIFTKV_EHIP, "fused KV GEMM launch failed");
+    g.partial = ns > 1 ? splits : c32;
+    g.n_splits = ns;
+    if (launch_splits_finish(g, EPI_KV, r.st) != 0) return fail(SWIFTKV_EHIP, "fused KV finish launch failed");
+  } else if (launch_gemm(g, EPI_KV, 0, r.st) != 0) {
+    return fail(SWIFTKV_EHIP, "fused KV GEMM launch failed");
+  }
   tm.end();
   if (int e = check_launch("fused KV GEMM")) return e;
   if (r.fp8) {
@@ -912,8 +928,6 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     if (tail_gemm(c, ta, B, m.vocab, d, c->ee_head, nullptr, nullptr, r.at<float>(r.L.ee_logits), EPI_STORE_F32, skp, st))
       return fail(SWIFTKV_EHIP, "early-exit head GEMM failed");
     launch_early_exit_flags(r.at<float>(r.L.ee_logits), B, m.vocab, c->ee_threshold, r.at<int32_t>(r.L.ee_flags), st);
-  } else {
-    launch_fill_u32(r.at<uint32_t>(r.L.ee_flags), 0, B, st);
   }
   int32_t t_pend = 1;   // K splits of the last residual GEMM waiting for the next norm pass over th
   for (int j = c->l; j < m.n_layers; ++j) {

@@ -136,6 +136,7 @@ struct MidPlan {
 MidPlan plan_gemm_mid(const GemmParams &p, int epi);
 int launch_gemm_mid(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st);
 int launch_gemm_wreg(const GemmParams &p, int epi, int fm, hipStream_t st);
+int launch_splits_finish(const GemmParams &p, int epi, hipStream_t st);
 
 // skinny (weight-streaming) GEMM for M <= 80 rows
 struct SkinnyParams {

@@ -397,6 +397,11 @@ int launch_gemm_mid(const GemmParams &p0, int epi, const MidPlan &pl, hipStream_
   if (epi != EPI_QKV && epi != EPI_KV) q.head_dim = 0;   // the packed order of rotary operands is theirs alone
   if (int e = launch_one(q, EPI_PARTIAL, pl, st)) return e;
   if (epi == EPI_RESID && p.n_splits_out) { *p.n_splits_out = pl.n_splits; return 0; }
+  return launch_splits_finish(p, epi, st);
+}
+
+// p.partial holds p.n_splits partial results [split][M][N] of C: added in split order, then the epilogue
+int launch_splits_finish(const GemmParams &p, int epi, hipStream_t st) {
   switch (epi) {
     case EPI_STORE_BF16: launch_finish<EPI_STORE_BF16>(p, st); return 0;
     case EPI_STORE_F32: launch_finish<EPI_STORE_F32>(p, st); return 0;
