@@ -176,23 +176,54 @@ int check_launch(const char *what) {
   return 0;
 }
 
-// Key splits of the single-query attention: about 1024 workgroups (four per CU, all resident at once:
-// measured on 64 rows x 8 KV heads over 2048 keys, 2 splits 118 us, 3 splits 131, 4 splits 125, 1 split
-// 141 per launch), no workgroup walking more than about 2048 keys of the longest row (one long row among
-// short ones would otherwise finish alone), none fewer than 64.
-int pick_split(int rows, int n_kv_heads, int max_keys) {
-  const int want = (1024 + rows * n_kv_heads / 2) / (rows * n_kv_heads);
+// Key splits of the single-query attention over rows of up to max_keys and together sum_keys keys.
+// Vector-unit kernel (min_keys = least keys of a split): about 1024 workgroups (four per CU, all resident at once:
+// measured on 64 rows x 8 KV heads over 2048 keys, 2 splits 118 us, 3 splits 131, 4 splits 125, 1 split 141 per
+// launch), no workgroup walking more than about 2048 keys of the longest row (one long row among short ones would
+// otherwise finish alone), none fewer than 64; where that leaves CUs idle, down to one 32-key iteration (one row over
+// 778 keys: 12 splits 9.6 us, 24 splits 8.6; 4 rows over 150: 2 splits 9.0, 5 splits 7.3).
+// Matrix-unit kernels: three workgroups per CU; a workgroup costs about 8 us besides its 128-key steps of 3.4 us, and
+// rows of one length run in whole rounds of 768 (64 rows x 8 heads over 2048 e4m3 keys: 1 split 62 us, 2 splits 67,
+// 3 splits 59; 160 rows over 900: 1 split 70, 2 splits 75).
+int pick_split(int rows, int n_kv_heads, int max_keys, int64_t sum_keys, bool matrix, int *min_keys) {
+  *min_keys = 128;
+  const int pairs = rows * n_kv_heads;
+  if (matrix) {
+    const double mean = (double)sum_keys / rows;
+    int best = 1;
+    double best_cost = 0;
+    for (int ns = 1; ns <= std::min(MAX_SPLIT, std::max(1, (max_keys + 127) / 128)); ++ns) {
+      const double rounds = (double)pairs * ns / 768;
+      const double first = 8 + 3.4 * ((max_keys + 128 * ns - 1) / (128 * ns)), next = 8 + 3.4 * mean / (128 * ns);
+      const double cost = mean > 0.9 * max_keys ? std::ceil(rounds) * first : first + std::max(0.0, rounds - 1) * next;
+      if (ns == 1 || cost < best_cost) { best = ns; best_cost = cost; }
+    }
+    return best;
+  }
+  const int want = (1024 + pairs / 2) / pairs;
   const int by_len = (max_keys + 1023) / 2048;
-  const int cap = std::max(1, max_keys / 64);
+  int cap = std::max(1, max_keys / 64);
+  if ((int64_t)pairs * ((max_keys + 31) / 32) <= 256) { cap = (max_keys + 31) / 32; *min_keys = 32; }
   return std::max(1, std::min({std::max(want, by_len), cap, MAX_SPLIT}));
+}
+void set_split(AttnDecodeParams &p, int max_keys, int64_t sum_keys) {
+  const bool matrix = p.fp8 != 0 || p.n_q_heads / p.n_kv_heads == 8;   // as launch_attention_decode chooses
+  p.n_split = pick_split(p.n_rows, p.n_kv_heads, max_keys, sum_keys, matrix, &p.min_keys);
 }
 
 struct HostPlan {
   std::vector<int32_t> meta;
   int64_t T = 0, vt_ld = 0, kcat_rows = 0;
   int32_t nqb = 0, nkt = 0, ndec = 0, ngt = 0, max_keys_dec = 0, max_keys_tail = 0;
+  int64_t sum_keys_dec = 0, sum_keys_tail = 0;
   bool chunked = false;   // some sequence brings several new tokens on top of a cached context
 };
+
+// Longest rows first: the rows' workgroups are dealt out in table order, and a long one that starts last finishes alone
+// (160 rows of 300 .. 1500 keys 80 -> 76 us, 24 of 200 .. 4100 53 -> 48 per launch).
+void sort_rows(std::vector<DecodeRow> &rows) {
+  std::stable_sort(rows.begin(), rows.end(), [](const DecodeRow &a, const DecodeRow &b) { return a.n_keys > b.n_keys; });
+}
 
 // Host side of the plan: cumulative lengths, 128-query blocks (longest first),
 // 64-token KV tiles, the decode rows (one new token on a cached context) and the
@@ -207,7 +238,8 @@ int build_host_plan(const swiftkv_ctx *c, const int32_t *seq_lens, const int32_t
   int64_t vt_cols = 0;
   struct QB { int32_t row0, q0, n, seq_row0, vt_col0, q_last_row; };
   std::vector<QB> qbs;
-  std::vector<int32_t> kvt, dec, tail, gt;
+  std::vector<int32_t> kvt, gt;
+  std::vector<DecodeRow> dec, tail;
   int64_t kcat_rows = 0;
   for (int b = 0; b < B; ++b)
     if (ctx_lens && ctx_lens[b] > 0 && seq_lens[b] > 1) hp.chunked = true;
@@ -237,23 +269,27 @@ int build_host_plan(const swiftkv_ctx *c, const int32_t *seq_lens, const int32_t
       for (int64_t q0 = 0; q0 < n; q0 += 128)
         qbs.push_back({(int32_t)(row0 + q0), (int32_t)(ctx + q0), (int32_t)keys, k_row0, vt0[b], (int32_t)(row0 + n - 1)});
     } else {
-      dec.insert(dec.end(), {row0, row0, b, (int32_t)(ctx + 1), -1, 0, 0, 0});
+      dec.push_back(DecodeRow{row0, row0, b, (int32_t)(ctx + 1), -1, {0, 0, 0}});
       hp.max_keys_dec = std::max<int32_t>(hp.max_keys_dec, (int32_t)(ctx + 1));
+      hp.sum_keys_dec += ctx + 1;
     }
     for (int64_t p0 = 0; p0 < n; p0 += 64)
       kvt.insert(kvt.end(), {(int32_t)(row0 + p0), (int32_t)std::min<int64_t>(64, n - p0), (prompt && !hp.chunked) ? (int32_t)(vt0[b] + p0) : -1, 0});
     // tail row: q row b of the tail buffer, rotated with the last token's angles
-    tail.insert(tail.end(), {b, b, b, (int32_t)(ctx + n), (int32_t)(cu[b + 1] - 1), 0, 0, 0});
+    tail.push_back(DecodeRow{b, b, b, (int32_t)(ctx + n), (int32_t)(cu[b + 1] - 1), {0, 0, 0}});
     hp.max_keys_tail = std::max<int32_t>(hp.max_keys_tail, (int32_t)(ctx + n));
+    hp.sum_keys_tail += ctx + n;
   }
   std::stable_sort(qbs.begin(), qbs.end(), [](const QB &a, const QB &b) {
     return std::min(a.q0 + 128, a.n) > std::min(b.q0 + 128, b.n);
   });
+  sort_rows(dec);
+  sort_rows(tail);
   hp.T = cu[B];
   hp.vt_ld = std::max<int64_t>(vt_cols, 64);
   hp.nqb = (int32_t)qbs.size();
   hp.nkt = (int32_t)(kvt.size() / 4);
-  hp.ndec = (int32_t)(dec.size() / 8);
+  hp.ndec = (int32_t)dec.size();
   hp.ngt = (int32_t)(gt.size() / 8);
   hp.kcat_rows = kcat_rows;
   L = make_layout(c, hp.T, B, hp.vt_ld, hp.nqb, hp.nkt, hp.ndec, fp8, kcat_rows, hp.ngt);
@@ -265,8 +301,9 @@ int build_host_plan(const swiftkv_ctx *c, const int32_t *seq_lens, const int32_t
     q[0] = qbs[i].row0; q[1] = qbs[i].q0; q[2] = qbs[i].n; q[3] = qbs[i].seq_row0; q[4] = qbs[i].vt_col0; q[5] = qbs[i].q_last_row;
   }
   std::copy(kvt.begin(), kvt.end(), hp.meta.begin() + L.m_kvtiles);
-  std::copy(dec.begin(), dec.end(), hp.meta.begin() + L.m_dec);
-  std::copy(tail.begin(), tail.end(), hp.meta.begin() + L.m_tail);
+  static_assert(sizeof(DecodeRow) == 8 * sizeof(int32_t), "eight plan words per row");
+  if (!dec.empty()) memcpy(&hp.meta[L.m_dec], dec.data(), dec.size() * sizeof(DecodeRow));
+  memcpy(&hp.meta[L.m_tail], tail.data(), tail.size() * sizeof(DecodeRow));
   std::copy(gt.begin(), gt.end(), hp.meta.begin() + L.m_gtiles);
   return 0;
 }
@@ -845,7 +882,7 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       if (r.fp8) { dp.scale_k = r.layer_scales(j); dp.scale_v = dp.scale_k + (r.per_token ? r.n_slots : (int64_t)m.n_kv_heads); }
       dp.block_tables = kv->block_tables; dp.max_blocks_per_seq = kv->max_blocks_per_seq; dp.n_blocks = kv->n_blocks;
       dp.cos_sin = r.at<float2>(r.L.cos_sin); dp.partial = r.at<float>(r.L.partial);
-      dp.n_split = pick_split(r.L.n_dec, m.n_kv_heads, r.hp.max_keys_dec);
+      set_split(dp, r.hp.max_keys_dec, r.hp.sum_keys_dec);
       tm.begin(TC_OTHER);
       if (launch_attention_decode(dp, st) != 0) return fail(SWIFTKV_EHIP, "decode attention launch failed");
       launch_decode_combine(dp.partial, ob, dp.rows, dp.n_rows, m.n_q_heads, m.head_dim, dp.n_split, st);
@@ -941,7 +978,7 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     if (r.fp8) { dp.scale_k = r.layer_scales(cl); dp.scale_v = dp.scale_k + (r.per_token ? r.n_slots : (int64_t)m.n_kv_heads); }
     dp.block_tables = kv->block_tables; dp.max_blocks_per_seq = kv->max_blocks_per_seq; dp.n_blocks = kv->n_blocks;
     dp.cos_sin = r.at<float2>(r.L.cos_sin); dp.partial = r.at<float>(r.L.partial);
-    dp.n_split = pick_split(B, m.n_kv_heads, r.hp.max_keys_tail);
+    set_split(dp, r.hp.max_keys_tail, r.hp.sum_keys_tail);
     if (launch_attention_decode(dp, st) != 0) return fail(SWIFTKV_EHIP, "tail attention launch failed");
     launch_decode_combine(dp.partial, to, dp.rows, B, m.n_q_heads, m.head_dim, dp.n_split, st);
     if (tail_gemm(c, to, B, d, qd, c->wo[j], nullptr, nullptr, th, EPI_RESID, skp, st, &t_pend)) return fail(SWIFTKV_EHIP, "tail o GEMM failed");
@@ -1150,11 +1187,14 @@ int swiftkv_op_attention_decode(const void *q, void *out, const int32_t *n_keys,
   if (workspace_bytes < swiftkv_op_attention_decode_workspace(n_rows, Hq, hd)) return fail(SWIFTKV_ENOSPC, "workspace too small");
   std::vector<DecodeRow> rows(n_rows);
   int max_keys = 1;
+  int64_t sum_keys = 0;
   for (int r = 0; r < n_rows; ++r) {
     if (n_keys[r] < 1 || (n_keys[r] + SKV_BLOCK - 1) / SKV_BLOCK > max_blocks_per_seq) return fail(SWIFTKV_EINVAL, "n_keys[%d] out of range", r);
     rows[r] = DecodeRow{r, r, r, n_keys[r], -1, {0, 0, 0}};
     max_keys = std::max(max_keys, n_keys[r]);
+    sum_keys += n_keys[r];
   }
+  sort_rows(rows);
   hipStream_t st = (hipStream_t)stream;
   unsigned char *ws = (unsigned char *)workspace;
   HIP_TRY(hipMemcpyAsync(ws, rows.data(), rows.size() * sizeof(DecodeRow), hipMemcpyHostToDevice, st));
@@ -1166,7 +1206,7 @@ int swiftkv_op_attention_decode(const void *q, void *out, const int32_t *n_keys,
   dp.scale_k = scale_k; dp.scale_v = scale_v;
   dp.block_tables = block_tables; dp.max_blocks_per_seq = max_blocks_per_seq; dp.n_blocks = n_blocks;
   dp.partial = (float *)(ws + align_up((size_t)n_rows * sizeof(DecodeRow)));
-  dp.n_split = pick_split(n_rows, Hkv, max_keys);
+  set_split(dp, max_keys, sum_keys);
   if (launch_attention_decode(dp, st)) return fail(SWIFTKV_EHIP, "decode attention launch failed");
   launch_decode_combine(dp.partial, dp.out, dp.rows, n_rows, Hq, hd, dp.n_split, st);
   if (int e = check_launch("single-query attention")) return e;

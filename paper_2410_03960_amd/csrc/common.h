@@ -218,6 +218,7 @@ struct AttnDecodeParams {
   const float2 *cos_sin;  // [T][hd/2]
   float *partial;         // [n_rows][Hq][n_split][hd + 2]
   int32_t n_split;
+  int32_t min_keys;       // least keys of a split (vector-unit kernel; the matrix-unit kernels take whole 128-key steps)
 };
 int launch_attention_decode(const AttnDecodeParams &p, hipStream_t st);
 
