@@ -15,10 +15,12 @@
 // partial sums and a second small kernel (or the consumer of the result) adds
 // them in a fixed order and applies the epilogue (deterministic, unlike atomic
 // accumulation).
-// Three kernels: skinny_kernel (above; any K % 8 == 0, activations from L2),
-// skinny_lds_kernel (K % 512 == 0, up to 32 rows: the activation slice of a
-// workgroup resident in LDS) and skinny_seq_kernel (K % 512 == 0, 33..80 rows:
-// slices walked in sequence behind a producer wave).
+// Four kernels: skinny_kernel (above; any K % 8 == 0, activations from L2),
+// skinny_res_kernel (K % 512 == 0, up to 16 rows, many columns: all activation
+// rows resident in LDS, a wave walks the whole of K), skinny_lds_kernel (K % 512
+// == 0, up to 32 rows: the activation slice of a workgroup resident in LDS) and
+// skinny_seq_kernel (K % 512 == 0, 33..80 rows: slices walked in sequence behind
+// a producer wave).
 #include "common.h"
 
 #include <algorithm>
@@ -293,6 +295,113 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_lds_kernel(SkinnyParams p, 
     c_g += 2;
     if (c_g == groups) { flush(c_nb); ++c_nb; c_g = 0; }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Few rows, many columns: the M rows (not their padding to 16) are resident in LDS over the whole of K, row after
+// row with 64 bytes between them, lanes of columns past M read the last row.  A wave owns one column block and walks
+// K from end to end, two groups of eight 32-wide steps in flight; nothing is split, so there are no partial sums
+// and no second launch.  Taken when the column blocks, four or eight to a workgroup, give the 256 CUs nearly equal
+// shares (launch_res): the stream's rate is then bound by HBM alone.  Measured, us including the reduction of the
+// form used before: 2 x 14336 x 4096 with 1 / 8 / 16 rows 49.8 / 51.2 / 51.9 -> 42.5 / 46.4 / 51.3 (5.5 TB/s with one),
+// 2 x 28672 x 8192 with 1 / 8 rows 197 / 208 -> 170 / 179, 128256 x 4096 with 4 / 16 rows 188 / 205 -> 180 / 202.
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+template <int EPI, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void skinny_res_kernel(SkinnyParams p, int stride) {
+  constexpr int NW = (EPI == EPI_SWIGLU) ? 2 : 1, U = 8;
+  extern __shared__ __align__(16) unsigned char a_lds[];   // [M][stride bytes]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int nblocks = p.N / 16;
+  int nb = blockIdx.x * WAVES + wave;
+  const bool live = nb < nblocks;
+  nb = live ? nb : nblocks - 1;   // (a wave past the end re-reads the last block and stores nothing)
+  const int groups = p.K / (32 * U);   // even
+  const unsigned char *wp[NW];         // uniform; a lane adds its row's offset
+#pragma unroll
+  for (int w = 0; w < NW; ++w) wp[w] = (const unsigned char *)(p.wtab ? p.wtab[nb] : (w ? p.W2 : p.W) + (int64_t)nb * 16 * p.K);
+  const uint64_t w_lane = (uint64_t)l16 * p.K * 2 + kq * 16;
+  auto load_group = [&](u32x4_t (&dst)[NW][U], int g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int u = 0; u < U; ++u) dst[w][u] = *(const u32x4_t *)(wp[w] + (int64_t)(g * U + u) * 64 + w_lane);
+  };
+  u32x4_t wa[NW][U], wb[NW][U];
+  load_group(wa, 0);   // on their way while the activations arrive
+  load_group(wb, 1);
+  const int row_chunks = p.K / 8;
+  for (int i = tid; i < p.M * row_chunks; i += WAVES * 64) {
+    const int r = i / row_chunks, c = i % row_chunks;
+    *(uint4 *)(a_lds + r * stride + c * 16) = *(const uint4 *)(p.A + (int64_t)r * p.K + c * 8);
+  }
+  __syncthreads();
+  floatx4 acc[NW];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) acc[w] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const unsigned char *fr = a_lds + (l16 < p.M ? l16 : p.M - 1) * stride + kq * 16;
+  auto compute_group = [&](const u32x4_t (&src)[NW][U], int g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bf16x8 a = *(const bf16x8 *)(fr + (g * U + u) * 64);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) acc[w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, src[w][u]), a, acc[w], 0, 0, 0);
+    }
+  };
+  for (int g = 0; g < groups; g += 2) {
+    compute_group(wa, g);
+    if (g + 2 < groups) load_group(wa, g + 2);
+    compute_group(wb, g + 1);
+    if (g + 3 < groups) load_group(wb, g + 3);
+  }
+  // acc[w][v] = C[m = l16][n = nb*16 + 4*kq + v] (weight w)
+  const int m = l16, n = nb * 16 + 4 * kq;
+  if (!live || m >= p.M) return;
+  if constexpr (EPI == EPI_STORE_F32) {
+    *(float4 *)((float *)p.C + (int64_t)m * p.N + n) = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
+  } else {
+    float o[4] = {acc[0][0], acc[0][1], acc[0][2], acc[0][3]};
+    if constexpr (EPI == EPI_SWIGLU) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[v] = o[v] / (1.f + __expf(-o[v])) * acc[NW - 1][v];
+    }
+    *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
+  }
+}
+template <int EPI, int WAVES>
+int launch_res_w(const SkinnyParams &p, hipStream_t st) {
+  constexpr int MAX_LDS = 160 * 1024;
+  auto kern = skinny_res_kernel<EPI, WAVES>;
+  static bool attr = false;
+  if (!attr) {
+    if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS) != hipSuccess) return -1;
+    attr = true;
+  }
+  const int stride = p.K * 2 + 64, nblocks = p.N / 16;
+  hipLaunchKernelGGL(kern, dim3((nblocks + WAVES - 1) / WAVES), dim3(WAVES * 64), (size_t)p.M * stride, st, p, stride);
+  return 0;
+}
+// Waves per workgroup of the form above, or 0: not this form.  Eight or four column blocks to a workgroup, where that
+// fills whole rounds of one workgroup per CU to at least four fifths (with half-filled CUs too few loads are in
+// flight: 2 x 8192 x 2048, 128 workgroups of four, 18.0 us against 15.6).  One row of one matrix: the first kernel
+// streams it as fast (128256 x 4096: 168 us against 177).
+int res_waves(const SkinnyParams &p, int epi) {
+  if (p.M > 16 || (p.N % 16) != 0 || (p.K % 512) != 0 || (size_t)p.M * (p.K * 2 + 64) > 160 * 1024) return 0;
+  if (epi != EPI_SWIGLU && epi != EPI_STORE_F32 && epi != EPI_STORE_BF16) return 0;
+  if (epi != EPI_SWIGLU && p.M == 1) return 0;
+  for (int w = 8; w >= 4; w -= 4) {
+    const int wgs = (p.N / 16 + w - 1) / w, rounds = (wgs + 255) / 256;
+    if (wgs * 5 >= rounds * 256 * 4) return w;
+  }
+  return 0;
+}
+int launch_res(const SkinnyParams &p, int epi, int waves, hipStream_t st) {
+  switch (epi) {
+    case EPI_SWIGLU: return waves == 8 ? launch_res_w<EPI_SWIGLU, 8>(p, st) : launch_res_w<EPI_SWIGLU, 4>(p, st);
+    case EPI_STORE_F32: return waves == 8 ? launch_res_w<EPI_STORE_F32, 8>(p, st) : launch_res_w<EPI_STORE_F32, 4>(p, st);
+    case EPI_STORE_BF16: return waves == 8 ? launch_res_w<EPI_STORE_BF16, 8>(p, st) : launch_res_w<EPI_STORE_BF16, 4>(p, st);
+  }
+  return -1;
 }
 
 // ---------------------------------------------------------------------------
@@ -652,9 +761,13 @@ int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
     const SeqPlan sq = plan_seq(p.M, p.N, p.K, epi == EPI_SWIGLU ? 2 : 1, p.n_splits_out != nullptr, p.partial ? p.partial_bytes : 0);
     if (sq.ok) return launch_seq(p, epi, sq, st);
   }
+  if (const int w = res_waves(p, epi)) return launch_res(p, epi, w, st);
   {
     const LdsPlan pl = plan_lds(p.M, p.N, p.K, epi == EPI_SWIGLU ? 2 : 1, p.partial ? p.partial_bytes : 0);
-    if (pl.ok) return launch_lds(p, epi, pl, st);
+    // K slices whose sum needs a launch of its own pay off only from many streams on: 8192 x 4096 (1024 of them) with
+    // 1 / 16 rows 22.1 / 23.6 us, 15.5 / 19.9 on the first kernel
+    const bool reduce = pl.ksplit > 1 && !p.n_splits_out;
+    if (pl.ok && !(reduce && p.M <= 16 && (int64_t)(p.N / 16) * pl.ksplit < 1536)) return launch_lds(p, epi, pl, st);
   }
   if (p.M <= 16) return launch_mb<1, 1>(p, epi, st);
   if (p.M <= 32) return (p.N % 32 == 0) ? launch_mb<2, 2>(p, epi, st) : launch_mb<2, 1>(p, epi, st);
