@@ -15,12 +15,10 @@
 // partial sums and a second small kernel (or the consumer of the result) adds
 // them in a fixed order and applies the epilogue (deterministic, unlike atomic
 // accumulation).
-// Four kernels: skinny_kernel (above; any K % 8 == 0, activations from L2),
-// skinny_res_kernel (K % 512 == 0, up to 16 rows, many columns: all activation
-// rows resident in LDS, a wave walks the whole of K), skinny_lds_kernel (K % 512
-// == 0, up to 32 rows: the activation slice of a workgroup resident in LDS) and
-// skinny_seq_kernel (K % 512 == 0, 33..80 rows: slices walked in sequence behind
-// a producer wave).
+// Three kernels: skinny_kernel (above; any K % 8 == 0, activations from L2),
+// skinny_seq_kernel (K % 512 == 0: slices of K walked in sequence, the activation
+// slice double-buffered in LDS by a producer wave) and skinny_res_kernel (the
+// SwiGLU pair for up to 8 rows: all activation rows resident in LDS).
 #include "common.h"
 
 #include <algorithm>
@@ -168,147 +166,20 @@ __global__ void skinny_reduce_kernel(SkinnyParams p, int ksplit) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// The same product with the activations resident in LDS (K % 512 == 0).
-// Measured on the kernel above: the activation fragments, which every wave
-// fetches from L2 for every k step, take as many vector-memory requests as the
-// weights and cost 20-30 % of the achieved HBM rate.  Here a workgroup owns one
-// K slice; its activation slice sits in LDS in MFMA operand order (filled by
-// LDS-DMA, one 1 KB fragment per request: lane (row l16, quarter kq) lands at
-// 16 * lane), the waves split the output columns (16-column blocks, `nbw` in a
-// row per wave) and stream their weight rows through registers two groups of
-// U k steps ahead, both steps of a 128-byte line in the same wave.  No
-// cross-wave reduction and no barrier after the fill.  K slices go to
-// blockIdx.y and meet in skinny_reduce_kernel in a fixed order.
 __device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory");
 }
 
-template <int MB, int EPI, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void skinny_lds_kernel(SkinnyParams p, int ks_steps, int nbw) {
-  constexpr int NW = (EPI == EPI_SWIGLU) ? 2 : 1;
-  constexpr int U = (NW == 1 && MB <= 2) ? 8 : 4;   // k steps (of 32) per group of loads
-  extern __shared__ __align__(16) unsigned char a_lds[];   // [k step][MB][64 lanes][16 bytes]
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15, kq = lane >> 4;
-  const int all_steps = p.K / 32;
-  const int s_begin = blockIdx.y * ks_steps;
-  const int steps = (all_steps - s_begin) < ks_steps ? (all_steps - s_begin) : ks_steps;   // a multiple of 2U
-  const int k0 = s_begin * 32;
-  const int groups = steps / U;
-
-  const int nblocks = p.N / 16;
-  const int nb0 = (blockIdx.x * WAVES + wave) * nbw;
-  const int nb_end = (nb0 + nbw) < nblocks ? (nb0 + nbw) : nblocks;
-  const int total = nb0 < nblocks ? (nb_end - nb0) * groups : 0;   // groups of this wave, an even number
-
-  // weight rows of this lane: group g of column block nb covers k steps g * U ...; the groups of a wave's
-  // blocks are walked in order, (l_nb, l_g) being the next one to request
-  int l_nb = nb0, l_g = 0;
-  auto load_group = [&](uint4 (&dst)[NW][U]) {
-    const int64_t koff = k0 + l_g * (U * 32) + kq * 8, off = (int64_t)(l_nb * 16 + l16) * p.K + koff;
-    const bf16_t *tsrc = p.wtab ? p.wtab[l_nb] + ((int64_t)l16 * p.K + koff) : nullptr;   // (one weight, never SwiGLU)
-    if (++l_g == groups) { l_g = 0; ++l_nb; }
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const bf16_t *src = tsrc ? tsrc : (w ? p.W2 : p.W) + off;
-#pragma unroll
-      for (int u = 0; u < U; ++u) dst[w][u] = *(const uint4 *)(src + u * 32);
-    }
-  };
-  uint4 wa[NW][U], wb[NW][U];
-  if (total > 0) load_group(wa);   // on its way while the activations arrive
-
-  // activation slice -> LDS: fragment (k step s, row block mb) at (s * MB + mb) * 1024; rows past M repeat row M-1
-  {
-    typedef __attribute__((address_space(3))) void *lds_ptr_t;
-    const unsigned lds_base = (unsigned)(size_t)(lds_ptr_t)a_lds;
-    for (int f = wave; f < steps * MB; f += WAVES) {
-      const int s = f / MB, mb = f % MB;
-      int m = mb * 16 + l16;
-      m = m < p.M ? m : p.M - 1;
-      lds_dma16(p.A + ((int64_t)m * p.K + k0 + s * 32 + kq * 8), lds_base + f * 1024);
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    __syncthreads();
-  }
-  if (total == 0) return;
-
-  floatx4 acc[NW][MB];
-#pragma unroll
-  for (int w = 0; w < NW; ++w)
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[w][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
-  auto compute_group = [&](const uint4 (&src)[NW][U], int g) {
-    const unsigned char *fr = a_lds + (size_t)(g * U) * (MB * 1024) + lane * 16;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      bf16x8 a[MB];
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) a[mb] = *(const bf16x8 *)(fr + (u * MB + mb) * 1024);
-#pragma unroll
-      for (int w = 0; w < NW; ++w)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-          acc[w][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, src[w][u]), a[mb], acc[w][mb], 0, 0, 0);
-    }
-  };
-  // acc[w][mb][v] = C[m = mb*16 + l16][n = nb*16 + 4*kq + v] (weight w), over this K slice
-  auto flush = [&](int nb) {
-    const int n = nb * 16 + 4 * kq;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const int m = mb * 16 + l16;
-      if (m < p.M) {
-        if (gridDim.y > 1) {   // partial[split][w][m][n]
-#pragma unroll
-          for (int w = 0; w < NW; ++w)
-            *(float4 *)(p.partial + (((int64_t)blockIdx.y * NW + w) * p.M + m) * p.N + n) =
-                make_float4(acc[w][mb][0], acc[w][mb][1], acc[w][mb][2], acc[w][mb][3]);
-        } else if constexpr (EPI == EPI_STORE_F32) {
-          *(float4 *)((float *)p.C + (int64_t)m * p.N + n) = make_float4(acc[0][mb][0], acc[0][mb][1], acc[0][mb][2], acc[0][mb][3]);
-        } else if constexpr (EPI == EPI_RESID) {
-          float4 *dst = (float4 *)((float *)p.C + (int64_t)m * p.N + n);
-          const float4 r = *dst;
-          *dst = make_float4(r.x + acc[0][mb][0], r.y + acc[0][mb][1], r.z + acc[0][mb][2], r.w + acc[0][mb][3]);
-        } else {
-          float o[4] = {acc[0][mb][0], acc[0][mb][1], acc[0][mb][2], acc[0][mb][3]};
-          if constexpr (EPI == EPI_SWIGLU) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] = o[v] / (1.f + __expf(-o[v])) * acc[NW - 1][mb][v];
-          }
-          *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
-        }
-      }
-#pragma unroll
-      for (int w = 0; w < NW; ++w) acc[w][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  // two groups per iteration, one register set in flight while the other is consumed; `groups` is even, so
-  // a block ends after the second group of an iteration
-  int c_nb = nb0, c_g = 0;
-  for (int idx = 0; idx < total; idx += 2) {
-    load_group(wb);
-    compute_group(wa, c_g);
-    if (idx + 2 < total) load_group(wa);
-    compute_group(wb, c_g + 1);
-    c_g += 2;
-    if (c_g == groups) { flush(c_nb); ++c_nb; c_g = 0; }
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Few rows, many columns: the M rows (not their padding to 16) are resident in LDS over the whole of K, row after
-// row with 64 bytes between them, lanes of columns past M read the last row.  A wave owns one column block and walks
-// K from end to end, two groups of eight 32-wide steps in flight; nothing is split, so there are no partial sums
-// and no second launch.  Taken when the column blocks, four or eight to a workgroup, give the 256 CUs nearly equal
-// shares (launch_res): the stream's rate is then bound by HBM alone.  Measured, us including the reduction of the
-// form used before: 2 x 14336 x 4096 with 1 / 8 / 16 rows 49.8 / 51.2 / 51.9 -> 42.5 / 46.4 / 51.3 (5.5 TB/s with one),
-// 2 x 28672 x 8192 with 1 / 8 rows 197 / 208 -> 170 / 179, 128256 x 4096 with 4 / 16 rows 188 / 205 -> 180 / 202.
+// The SwiGLU pair for few rows: the M rows (not their padding to 16) are resident in LDS over the whole of K, row
+// after row with 64 bytes between them, lanes of columns past M read the last row.  A wave owns one column block of
+// both weights and walks K from end to end, two groups of eight 32-wide steps in flight; nothing is split, so there are
+// no partial sums and no second launch, and no slice boundary either.  Measured, us: 2 x 14336 x 4096 with 1 / 8 rows
+// 42.5 / 46.4 (5.5 TB/s with one), 46.3 for both with skinny_seq_kernel.
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-template <int EPI, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void skinny_res_kernel(SkinnyParams p, int stride) {
-  constexpr int NW = (EPI == EPI_SWIGLU) ? 2 : 1, U = 8;
+constexpr int RES_WAVES = 4;
+__global__ __launch_bounds__(RES_WAVES * 64) void skinny_res_kernel(SkinnyParams p, int stride) {
+  constexpr int NW = 2, U = 8, WAVES = RES_WAVES;
   extern __shared__ __align__(16) unsigned char a_lds[];   // [M][stride bytes]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kq = lane >> 4;
@@ -319,7 +190,7 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_res_kernel(SkinnyParams p, 
   const int groups = p.K / (32 * U);   // even
   const unsigned char *wp[NW];         // uniform; a lane adds its row's offset
 #pragma unroll
-  for (int w = 0; w < NW; ++w) wp[w] = (const unsigned char *)(p.wtab ? p.wtab[nb] : (w ? p.W2 : p.W) + (int64_t)nb * 16 * p.K);
+  for (int w = 0; w < NW; ++w) wp[w] = (const unsigned char *)((w ? p.W2 : p.W) + (int64_t)nb * 16 * p.K);
   const uint64_t w_lane = (uint64_t)l16 * p.K * 2 + kq * 16;
   auto load_group = [&](u32x4_t (&dst)[NW][U], int g) __attribute__((always_inline)) {
 #pragma unroll
@@ -357,63 +228,39 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_res_kernel(SkinnyParams p, 
   // acc[w][v] = C[m = l16][n = nb*16 + 4*kq + v] (weight w)
   const int m = l16, n = nb * 16 + 4 * kq;
   if (!live || m >= p.M) return;
-  if constexpr (EPI == EPI_STORE_F32) {
-    *(float4 *)((float *)p.C + (int64_t)m * p.N + n) = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
-  } else {
-    float o[4] = {acc[0][0], acc[0][1], acc[0][2], acc[0][3]};
-    if constexpr (EPI == EPI_SWIGLU) {
+  float o[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) o[v] = o[v] / (1.f + __expf(-o[v])) * acc[NW - 1][v];
-    }
-    *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
-  }
+  for (int v = 0; v < 4; ++v) o[v] = acc[0][v] / (1.f + __expf(-acc[0][v])) * acc[1][v];
+  *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
 }
-template <int EPI, int WAVES>
-int launch_res_w(const SkinnyParams &p, hipStream_t st) {
-  constexpr int MAX_LDS = 160 * 1024;
-  auto kern = skinny_res_kernel<EPI, WAVES>;
+// Whether the form above runs this shape: up to 8 rows, and four column blocks to a workgroup fill one round of the 256
+// CUs to at least four fifths (with half of the CUs idle too few loads are in flight: 2 x 8192 x 2048, 128 workgroups,
+// 18.0 us against 15.6 of the first kernel; with several rounds skinny_seq_kernel is ahead: 2 x 28672 x 8192 168
+// against 176).
+bool res_fits(const SkinnyParams &p, int epi) {
+  if (epi != EPI_SWIGLU || p.wtab || p.M > 8 || (p.N % 16) != 0 || (p.K % 512) != 0 || (size_t)p.M * (p.K * 2 + 64) > 160 * 1024) return false;
+  const int wgs = (p.N / 16 + RES_WAVES - 1) / RES_WAVES;
+  return wgs <= 256 && wgs * 5 >= 256 * 4;
+}
+int launch_res(const SkinnyParams &p, hipStream_t st) {
   static bool attr = false;
   if (!attr) {
-    if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS) != hipSuccess) return -1;
+    if (hipFuncSetAttribute((const void *)skinny_res_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return -1;
     attr = true;
   }
   const int stride = p.K * 2 + 64, nblocks = p.N / 16;
-  hipLaunchKernelGGL(kern, dim3((nblocks + WAVES - 1) / WAVES), dim3(WAVES * 64), (size_t)p.M * stride, st, p, stride);
+  hipLaunchKernelGGL(skinny_res_kernel, dim3((nblocks + RES_WAVES - 1) / RES_WAVES), dim3(RES_WAVES * 64), (size_t)p.M * stride, st, p, stride);
   return 0;
-}
-// Waves per workgroup of the form above, or 0: not this form.  Eight or four column blocks to a workgroup, where that
-// fills whole rounds of one workgroup per CU to at least four fifths (with half-filled CUs too few loads are in
-// flight: 2 x 8192 x 2048, 128 workgroups of four, 18.0 us against 15.6).  One row of one matrix: the first kernel
-// streams it as fast (128256 x 4096: 168 us against 177).
-int res_waves(const SkinnyParams &p, int epi) {
-  if (p.M > 16 || (p.N % 16) != 0 || (p.K % 512) != 0 || (size_t)p.M * (p.K * 2 + 64) > 160 * 1024) return 0;
-  if (epi != EPI_SWIGLU && epi != EPI_STORE_F32 && epi != EPI_STORE_BF16) return 0;
-  if (epi != EPI_SWIGLU && p.M == 1) return 0;
-  for (int w = 8; w >= 4; w -= 4) {
-    const int wgs = (p.N / 16 + w - 1) / w, rounds = (wgs + 255) / 256;
-    if (wgs * 5 >= rounds * 256 * 4) return w;
-  }
-  return 0;
-}
-int launch_res(const SkinnyParams &p, int epi, int waves, hipStream_t st) {
-  switch (epi) {
-    case EPI_SWIGLU: return waves == 8 ? launch_res_w<EPI_SWIGLU, 8>(p, st) : launch_res_w<EPI_SWIGLU, 4>(p, st);
-    case EPI_STORE_F32: return waves == 8 ? launch_res_w<EPI_STORE_F32, 8>(p, st) : launch_res_w<EPI_STORE_F32, 4>(p, st);
-    case EPI_STORE_BF16: return waves == 8 ? launch_res_w<EPI_STORE_BF16, 8>(p, st) : launch_res_w<EPI_STORE_BF16, 4>(p, st);
-  }
-  return -1;
 }
 
 // ---------------------------------------------------------------------------
-// The LDS-resident form for many rows (M > 32), where a K slice that fits LDS is
-// short (512 columns at 64 rows) and one slice per workgroup would mean many K
-// splits, i.e. fp32 partial sums of 12-25 % of the weight bytes.  Here a workgroup
-// walks several slices of its K range one after the other: the activation slice
-// is double-buffered in LDS and filled by a producer wave of its own (LDS-DMA,
-// then a wait for everything it requested, then the workgroup barrier), so the
-// consumer waves never wait for an LDS-DMA request and their weight stream runs
-// on across slice boundaries; a consumer keeps the accumulators of its NBW column
-// blocks in registers over the whole K range.  One barrier per slice.
+// The activations through LDS (K % 512 == 0).  Measured on the first kernel: the activation fragments, which every
+// wave fetches from L2 for every k step, take as many vector-memory requests as the weights and cost 20-30 % of the
+// achieved HBM rate.  Here a workgroup walks slices of its K range one after the other: the activation slice sits in
+// LDS in MFMA operand order, double-buffered and filled by a producer wave of its own (LDS-DMA, then a wait for
+// everything it requested, then the workgroup barrier), so the consumer waves never wait for an LDS-DMA request and
+// their weight stream runs on across slice boundaries; a consumer keeps the accumulators of its NBW column blocks in
+// registers over the whole K range.  One barrier per slice.
 template <int MB, int EPI, int WAVES, int NBW>
 __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_seq_kernel(SkinnyParams p, int ks_steps, int n_slices) {
   constexpr int NW = (EPI == EPI_SWIGLU) ? 2 : 1;
@@ -555,45 +402,65 @@ struct SeqPlan {
   bool ok;
   int waves, nbw, ks_steps, n_slices, ksplit;
   size_t lds_bytes, partial_bytes;
+  int64_t wgs;
 };
-// Shape of the launch for M > 32: column blocks per workgroup (waves x nbw) and K ranges, chosen by the
-// bytes that move besides the weights -- every workgroup fetches the activation rows of its K range from
-// L2 (n_cg * M * K * 2 bytes in total over n_cg column groups, whatever the K split), K splits write and
-// re-read fp32 partial sums (2 * ksplit * nw * M * N * 4 bytes) and, for the epilogues that cannot leave
-// the sum to their consumer, need a second launch -- scaled by how evenly the workgroups fill the 256 CUs
-// (one workgroup per CU: the two activation buffers take most of LDS).  Measured at 64 rows (us per call,
-// previous one-slice form -> this one): 128256 x 4096 296 -> 196, 28672 x 4096 64.4 -> 61.2 and no second
-// launch, 4096 x 4096 18.0 -> 16.5, 4096 x 14336 36.8 -> 36.8; at 80 rows 28672 x 4096 97.7 -> 67.1.
+// Shape of the launch: column blocks per workgroup (waves x nbw), slice length and K ranges, chosen by the bytes that
+// move besides the weights -- every workgroup fetches the activation rows of its K range from L2 (n_cg * M * K * 2
+// bytes in total over n_cg column groups, whatever the K split), K splits write and re-read fp32 partial sums (2 *
+// ksplit * nw * M * N * 4 bytes) and, for the epilogues that cannot leave the sum to their consumer, need a second
+// launch.  Beyond 32 rows the two activation buffers take most of LDS, one workgroup runs per CU, and what counts is
+// how evenly the workgroups fill whole rounds of 256.  Up to 32 rows several fit, and what counts is the bytes in
+// flight per CU (two load groups per consumer wave): below 64 KB the stream slows down.
+// Measured, us per call (before -> this form): 64 rows: 128256 x 4096 296 -> 196, 28672 x 4096 64.4 -> 61.2 and no second
+// launch, 4096 x 4096 18.0 -> 16.5, 4096 x 14336 36.8 -> 36.8; 24 rows: 2 x 28672 x 8192 233 -> 171, 128256 x 4096 285 ->
+// 184, 8192 x 28672 101 -> 93, 4096 x 14336 26.4 -> 28.0; 1 row: 6144 x 4096 14.3 -> 11.7, 8192 x 28672 90 -> 82,
+// 2048 x 8192 12.8 -> 9.3, 4096 x 14336 26.6 -> 25.3 (4 ranges of 7 slices, 32 KB in flight per CU: 28.9).
 SeqPlan plan_seq(int M, int N, int K, int nw, bool consumer_sums, size_t partial_cap) {
   SeqPlan best{};
-  if (M <= 32 || M > 80 || (N % 16) != 0 || (K % 512) != 0) return best;
-  const int MB = (M + 15) / 16;
-  const int ks_steps = MB <= 4 ? 16 : 8;                      // 2 x 48-64 KB, 2 x 40 KB of LDS
-  const int all_slices = K / (32 * ks_steps), nblocks = N / 16;
+  if (M < 1 || M > 80 || (N % 16) != 0 || (K % 512) != 0) return best;
+  const int MB = (M + 15) / 16, nblocks = N / 16;
+  const bool few = M <= 32;
   const double w_bytes = 2.0 * nw * N * K;
   double best_cost = 0;
   for (int waves = 4; waves <= 8; waves += 4)
     for (int nbw = 1; nbw <= 4; nbw *= 2) {
       if (nw == 2 && nbw * waves > 8) continue;               // (two weights: register budget of the instantiations below)
       const int n_cg = (nblocks + waves * nbw - 1) / (waves * nbw);
-      for (int want = 1; want <= std::min(SKINNY_MAX_SPLIT, all_slices); ++want) {
-        const int n_slices = (all_slices + want - 1) / want;
-        const int ksplit = (all_slices + n_slices - 1) / n_slices;
-        if (ksplit != want) continue;
-        const int64_t wgs = (int64_t)n_cg * ksplit;
-        const size_t partial = ksplit > 1 ? (size_t)ksplit * nw * M * N * 4 : 0;
-        if (partial > partial_cap) continue;
-        const double a_bytes = 0.75 * (double)n_cg * M * K * 2, p_bytes = 2.0 * partial;   // (L2 hits: cheaper than the partial sums' trip to memory)
-        const double second = (ksplit > 1 && !consumer_sums) ? 25e6 : 0;   // a launch, in bytes at the streaming rate
-        const int64_t n_rounds = (wgs + 255) / 256;   // every further round pays its own fill and uneven end
-        const double rounds = (double)n_rounds * 256.0 / (double)wgs * (1.0 + 0.15 * (double)(n_rounds - 1));
-        const double cost = (w_bytes + a_bytes + p_bytes + second) * rounds;
-        if (!best.ok || cost < best_cost) {
-          best_cost = cost;
-          best = SeqPlan{true, waves, nbw, ks_steps, n_slices, ksplit, (size_t)2 * ks_steps * MB * 1024, partial};
+      for (int ks_steps = 16; ks_steps >= 8; ks_steps /= 2) {
+        if (!few && ks_steps != (MB <= 4 ? 16 : 8)) continue;   // 2 x 48-64 KB, 2 x 40 KB of LDS
+        const int all_slices = K / (32 * ks_steps);
+        const size_t lds = (size_t)2 * ks_steps * MB * 1024;
+        for (int want = 1; want <= std::min(SKINNY_MAX_SPLIT, all_slices); ++want) {
+          const int n_slices = (all_slices + want - 1) / want;
+          const int ksplit = (all_slices + n_slices - 1) / n_slices;
+          if (ksplit != want) continue;
+          const int64_t wgs = (int64_t)n_cg * ksplit;
+          const size_t partial = ksplit > 1 ? (size_t)ksplit * nw * M * N * 4 : 0;
+          if (partial > partial_cap) continue;
+          const double a_bytes = 0.75 * (double)n_cg * M * K * 2, p_bytes = 2.0 * partial;   // (L2 hits: cheaper than the partial sums' trip to memory)
+          const double second = (ksplit > 1 && !consumer_sums) ? 25e6 : 0;   // a launch, in bytes at the streaming rate
+          const int64_t n_rounds = (wgs + 255) / 256;
+          double factor;
+          if (few) {
+            const int resident = (int)std::min<int64_t>(n_rounds, (160 << 10) / lds);
+            const double in_flight = (double)resident * waves * (nbw * nw == 1 ? 8 : 16);   // KB per CU
+            factor = (1 + 0.3 * ((double)n_rounds * 256 / (double)wgs - 1)) * (1 + 0.35 * std::max(0.0, 1 - in_flight / 64));
+          } else {
+            factor = (double)n_rounds * 256.0 / (double)wgs * (1.0 + 0.15 * (double)(n_rounds - 1));   // every further round pays its own fill and uneven end
+          }
+          const double cost = (w_bytes + a_bytes + p_bytes + second) * factor;
+          if (!best.ok || cost < best_cost) {
+            best_cost = cost;
+            best = SeqPlan{true, waves, nbw, ks_steps, n_slices, ksplit, lds, partial};
+            best.wgs = wgs;
+          }
         }
       }
     }
+  // Up to 32 rows the first kernel, which splits K among the waves of a workgroup, is ahead where this one has too few
+  // workgroups (2048 x 2048, 1 row: 6.5 us against 5.5), and up to 16 where it needs a second launch (4096 x 4096
+  // in bf16, 1 row: 13.0 against 9.9; 8192 x 4096 22 against 15.5).
+  if (few && (best.wgs < 192 || (M <= 16 && best.ksplit > 1 && !consumer_sums))) best.ok = false;
   return best;
 }
 template <int MB, int EPI, int WAVES, int NBW>
@@ -601,8 +468,8 @@ int launch_seq_k(const SkinnyParams &p, const SeqPlan &pl, hipStream_t st) {
   auto kern = skinny_seq_kernel<MB, EPI, WAVES, NBW>;
   static bool attr = false;
   if (!attr) {
-    if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_bytes) != hipSuccess) return -1;
-    attr = true;   // (the size depends on MB only)
+    if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 16 * MB * 1024) != hipSuccess) return -1;   // the longest slices
+    attr = true;
   }
   const int nblocks = p.N / 16;
   dim3 grid((nblocks + WAVES * NBW - 1) / (WAVES * NBW), pl.ksplit);
@@ -637,72 +504,12 @@ int launch_seq_m(const SkinnyParams &p, int epi, const SeqPlan &pl, hipStream_t 
 }
 int launch_seq(const SkinnyParams &p, int epi, const SeqPlan &pl, hipStream_t st) {
   switch ((p.M + 15) / 16) {
+    case 1: return launch_seq_m<1>(p, epi, pl, st);
+    case 2: return launch_seq_m<2>(p, epi, pl, st);
     case 3: return launch_seq_m<3>(p, epi, pl, st);
     case 4: return launch_seq_m<4>(p, epi, pl, st);
     default: return launch_seq_m<5>(p, epi, pl, st);
   }
-}
-
-struct LdsPlan {
-  bool ok;
-  int waves, ks_steps, ksplit, nbw;
-  size_t lds_bytes, partial_bytes;
-};
-// How the one-slice LDS-resident form would run this shape (M <= 32); ok = false: it cannot, or the first
-// kernel does better (few column blocks: its workgroups split K among their waves and need no second
-// pass).  Measured on the 8B shapes with 8 rows: slices of 2048 (up to 16 rows) / 1024 columns of K, two
-// column blocks in a row per wave when there are many.
-LdsPlan plan_lds(int M, int N, int K, int nw, size_t partial_cap) {
-  LdsPlan pl{};
-  if (M < 1 || M > 32 || (N % 16) != 0 || (K % 512) != 0) return pl;
-  const int MB = (M + 15) / 16;
-  const int U = (nw == 1) ? 8 : 4;
-  const int all_steps = K / 32, nblocks = N / 16;
-  const int steps_cap = MB == 1 ? 64 : 32;                          // 64 KB of LDS
-  int ksplit = (all_steps + steps_cap - 1) / steps_cap;
-  const int ks_steps = ((all_steps + ksplit - 1) / ksplit + 2 * U - 1) / (2 * U) * (2 * U);
-  ksplit = (all_steps + ks_steps - 1) / ks_steps;
-  pl.ks_steps = ks_steps; pl.ksplit = ksplit;
-  const int64_t streams = (int64_t)nblocks * ksplit;                // (column block, K slice) pairs; a wave takes nbw of them in a row
-  if (streams < 1024) return pl;                                    // too few: the first kernel keeps more CUs busy
-  pl.nbw = streams >= 3200 ? 2 : 1;
-  pl.waves = 8;
-  pl.lds_bytes = (size_t)ks_steps * MB * 1024;
-  pl.partial_bytes = ksplit > 1 ? (size_t)ksplit * nw * M * N * 4 : 0;
-  pl.ok = pl.partial_bytes <= partial_cap && pl.lds_bytes <= 160 * 1024;
-  return pl;
-}
-
-template <int MB, int EPI, int WAVES>
-int launch_lds_w(const SkinnyParams &p, const LdsPlan &pl, hipStream_t st) {
-  auto kern = skinny_lds_kernel<MB, EPI, WAVES>;
-  static size_t attr = 0;
-  if (pl.lds_bytes > attr) {
-    if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_bytes) != hipSuccess) return -1;
-    attr = pl.lds_bytes;
-  }
-  const int nblocks = p.N / 16;
-  dim3 grid((nblocks + WAVES * pl.nbw - 1) / (WAVES * pl.nbw), pl.ksplit);
-  hipLaunchKernelGGL(kern, grid, dim3(WAVES * 64), pl.lds_bytes, st, p, pl.ks_steps, pl.nbw);
-  if (pl.ksplit > 1 && p.n_splits_out) *p.n_splits_out = pl.ksplit;   // the consumer adds the splits
-  else if (pl.ksplit > 1) {
-    const int64_t quads = (int64_t)p.M * p.N / 4;
-    hipLaunchKernelGGL((skinny_reduce_kernel<EPI>), dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p, pl.ksplit);
-  }
-  return 0;
-}
-template <int MB>
-int launch_lds_m(const SkinnyParams &p, int epi, const LdsPlan &pl, hipStream_t st) {
-  switch (epi) {
-    case EPI_STORE_BF16: return launch_lds_w<MB, EPI_STORE_BF16, 8>(p, pl, st);
-    case EPI_STORE_F32: return launch_lds_w<MB, EPI_STORE_F32, 8>(p, pl, st);
-    case EPI_RESID: return launch_lds_w<MB, EPI_RESID, 8>(p, pl, st);
-    case EPI_SWIGLU: return launch_lds_w<MB, EPI_SWIGLU, 8>(p, pl, st);
-  }
-  return -1;
-}
-int launch_lds(const SkinnyParams &p, int epi, const LdsPlan &pl, hipStream_t st) {
-  return p.M <= 16 ? launch_lds_m<1>(p, epi, pl, st) : launch_lds_m<2>(p, epi, pl, st);
 }
 
 template <int MB, int NB, int EPI>
@@ -757,17 +564,10 @@ int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
     if (epi != EPI_STORE_F32 && epi != EPI_RESID) return -1;
     *p.n_splits_out = 1;
   }
+  if (res_fits(p, epi)) return launch_res(p, st);
   {
     const SeqPlan sq = plan_seq(p.M, p.N, p.K, epi == EPI_SWIGLU ? 2 : 1, p.n_splits_out != nullptr, p.partial ? p.partial_bytes : 0);
     if (sq.ok) return launch_seq(p, epi, sq, st);
-  }
-  if (const int w = res_waves(p, epi)) return launch_res(p, epi, w, st);
-  {
-    const LdsPlan pl = plan_lds(p.M, p.N, p.K, epi == EPI_SWIGLU ? 2 : 1, p.partial ? p.partial_bytes : 0);
-    // K slices whose sum needs a launch of its own pay off only from many streams on: 8192 x 4096 (1024 of them) with
-    // 1 / 16 rows 22.1 / 23.6 us, 15.5 / 19.9 on the first kernel
-    const bool reduce = pl.ksplit > 1 && !p.n_splits_out;
-    if (pl.ok && !(reduce && p.M <= 16 && (int64_t)(p.N / 16) * pl.ksplit < 1536)) return launch_lds(p, epi, pl, st);
   }
   if (p.M <= 16) return launch_mb<1, 1>(p, epi, st);
   if (p.M <= 32) return (p.N % 32 == 0) ? launch_mb<2, 2>(p, epi, st) : launch_mb<2, 1>(p, epi, st);

@@ -1,18 +1,22 @@
-"""Weight-streaming GEMM of up to 16 rows with all rows resident in LDS: both
-workgroup widths, ragged last workgroup, the row counts at the edges, the largest
-operand LDS holds, and the shapes next to the rule's line that keep another form."""
+"""Weight-streaming GEMMs of up to 32 rows with the activations in LDS: one and two
+row blocks at their edges, ragged last workgroups, one to eight K ranges, the shapes
+beside the rule's line that keep the first form, and (through a decoder whose MLP is
+wide enough) the SwiGLU pair with all rows resident, up to its 8 rows and past them."""
 import pytest
 import torch
 
 import workloads as WL
+from tests import gpu_helpers as G
 from tests.helpers import rel_err
+from workloads.configs import ModelShape, Workload
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,N,K", [
     (2, 13120, 512), (5, 16384, 1024), (16, 14352, 4096), (8, 28672, 512), (3, 32768, 1024), (16, 32064, 512), (9, 14336, 8704),
-    (1, 14336, 512), (16, 8192, 4096), (2, 12288, 512), (16, 13104, 512), (10, 14336, 8704), (17, 14336, 512)])
+    (1, 14336, 512), (16, 8192, 4096), (2, 12288, 512), (16, 13104, 512), (10, 14336, 8704), (17, 14336, 512),
+    (17, 4096, 4096), (32, 4112, 14336), (31, 6144, 2048), (18, 32784, 1536), (32, 12288, 512), (24, 3056, 512)])
 def test_rows_gemm_at_the_edges(M, N, K):
     from paper_2410_03960_amd import binding as B
     print(f"M={M} N={N} K={K}", flush=True)
@@ -21,3 +25,22 @@ def test_rows_gemm_at_the_edges(M, N, K):
     ref = A.double() @ W.cpu().double().T
     for out_f32, tol in ((True, 1e-5), (False, 4e-3)):     # fp32 sums of exact products / one bf16 rounding
         assert rel_err(B.op_gemm_rows(A.cuda(), W, out_f32=out_f32).cpu(), ref) <= tol
+
+
+@pytest.fixture(scope="module")
+def wide_mlp():
+    wl = Workload("wide_mlp", ModelShape(2, 512, 4, 2, 128, 13136, 512, 1e4, 1e-5), l=1, g=1, seed=2310)   # 821 column blocks
+    store = WL.make_weights(wl, "cpu", keep=True)
+    return wl, store, G.device_weights(store)
+
+
+@pytest.mark.parametrize("lens", [[1], [5, 1, 1], [3, 2, 1, 1, 1], [6, 1, 1, 1], [9, 1, 7], [20, 11, 1]], ids=str)
+def test_wide_mlp_matches_oracle(wide_mlp, lens):
+    from paper_2410_03960_amd import binding as B
+    wl, store, dev_w = wide_mlp
+    print(lens, flush=True)
+    batch = WL.build_batch(wl, lens=lens, shuffled=True)
+    logits, cache, _ = G.run_gpu(B.Context(wl.shape, dev_w, wl.l, wl.g), batch)
+    ologits, ocache, _ = G.run_oracle(wl.shape, store, batch, wl.l, wl.g)
+    G.compare_caches(cache, ocache, batch, label=wl.name)
+    G.compare_logits(logits, ologits, rel=G.BF16_REL, cos=G.BF16_COS, label=wl.name)
