@@ -1159,7 +1159,7 @@ int swiftkv_op_attention_prefill(const void *q, const void *k, const void *v, vo
   ap.qblocks = (const QBlock *)(ws + o_qb); ap.n_qblocks = (int32_t)(qbs.size() / 8);
   ap.n_q_heads = Hq; ap.n_kv_heads = Hkv; ap.head_dim = hd;
   ap.sched = (int32_t *)(ws + o_sched);
-  launch_fill_u32((uint32_t *)(ws + o_sched), 0, 9, st);   // the workspace is the caller's and arrives uninitialised
+  launch_fill_u32((uint32_t *)(ws + o_sched), 0, 8, st);   // the workspace is the caller's and arrives uninitialised
   if (launch_attention_prefill(ap, st)) return fail(SWIFTKV_EHIP, "attention launch failed");
   if (int e = check_launch("attention")) return e;
   HIP_TRY(hipStreamSynchronize(st));   // the tables above were staged from this call's own (pageable) host vectors
