@@ -748,13 +748,15 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   tm.begin(TC_OTHER);
   if (int e = run_plan(r, token_ids)) return e;
   float *h = r.at<float>(r.L.h);             // residual stream, fp32 [T, d]
-  launch_embed(token_ids, c->embed, h, T, d, m.vocab, st);
   tm.end();
   bf16_t *ab = r.at<bf16_t>(r.L.a);          // bf16 operand of the projection behind an RMSNorm
   bf16_t *qb = r.at<bf16_t>(r.L.q), *kb = r.at<bf16_t>(r.L.k), *vb = r.at<bf16_t>(r.L.v), *ob = r.at<bf16_t>(r.L.o);
   bf16_t *vt = r.at<bf16_t>(r.L.vt), *zb = r.at<bf16_t>(r.L.z);
   const bool compute_scale = r.fp8 && kv->scale_mode == SWIFTKV_SCALE_COMPUTE_ABSMAX;
   const bool few_rows = T <= SKINNY_MAX_ROWS;
+  // Decode rows only, and no scale that waits for all of a layer's values: the pass that finishes Q, K and V stores K and
+  // V at their slots, one launch (4.6 us) fewer per layer.
+  const bool commit_in_finish = few_rows && r.L.n_qblocks == 0 && !compute_scale && !r.per_token;
   float *skp = r.at<float>(r.L.skpart);
   float *rstd = r.at<float>(r.L.rstd), *ssq = r.at<float>(r.L.ssq);
 
@@ -780,20 +782,23 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     packed = plan_gemm_mid(go, EPI_RESID).n_splits == 1 && plan_gemm_mid(gd, EPI_RESID).n_splits == 1;
   }
   const int n_ssq = d / 64;
-  if (packed) {
+  // the first norm of the pass takes its rows from the embedding and leaves them in h
+  bool have_h = false;
+  auto norm_h = [&](const bf16_t *gain, float *rstd_out, int32_t pending) {
     tm.begin(TC_NORM);
-    launch_rmsnorm_rows(h, c->norm1[0], ab, T, d, m.rms_eps, rstd, st);
+    if (!have_h) launch_rmsnorm_embed(token_ids, c->embed, m.vocab, h, gain, ab, T, d, m.rms_eps, rstd_out, st);
+    else launch_rmsnorm_rows(h, gain, ab, T, d, m.rms_eps, rstd_out, st, skp, pending);
+    have_h = true;
     tm.end();
-  }
+  };
+  if (packed) norm_h(c->norm1[0], rstd, 1);
   // Without form (a) a residual GEMM that split K leaves the sum of its splits to the RMSNorm pass that
   // reads the residual rows next (h_pend = number of splits waiting in skp; 1 = none).
   int32_t h_pend = 1;
   for (int j = 0; j < c->l; ++j) {
     if (!packed) {
-      tm.begin(TC_NORM);
-      launch_rmsnorm_rows(h, c->norm1[j], ab, T, d, m.rms_eps, nullptr, st, skp, h_pend);
+      norm_h(c->norm1[j], nullptr, h_pend);
       h_pend = 1;
-      tm.end();
     }
     if (few_rows) {
       // decode steps and other few-token batches: weights stream once through the skinny kernel (fp32 out),
@@ -814,6 +819,10 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       fp.T = T; fp.n_q_heads = m.n_q_heads; fp.n_kv_heads = m.n_kv_heads; fp.head_dim = m.head_dim;
       fp.cos_sin = r.at<float2>(r.L.cos_sin);
       fp.amax = compute_scale ? r.at<uint32_t>(r.L.amax) + (int64_t)j * 2 * m.n_kv_heads : nullptr;
+      if (commit_in_finish) {
+        fp.cache_k = r.cache_plane(j, 0); fp.cache_v = r.cache_plane(j, 1); fp.slots = r.at<int64_t>(r.L.slots);
+        fp.scales = r.fp8 ? r.layer_scales(j) : nullptr;
+      }
       launch_qkv_finish(fp, st);
       tm.end();
     } else {
@@ -830,7 +839,7 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       if (launch_gemm(g, EPI_QKV, 0, st) != 0) return fail(SWIFTKV_EHIP, "QKV GEMM launch failed");
       tm.end();
     }
-    {
+    if (!commit_in_finish) {
       CommitParams cp{};
       cp.tiles = (const KVTile *)r.meta(r.L.m_kvtiles); cp.n_tiles = r.L.n_kvtiles;
       cp.n_kv_heads = m.n_kv_heads; cp.head_dim = m.head_dim;
@@ -947,10 +956,8 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   // operand: the layer-l output rounded to bf16 (the leaders' gains live in the packed weight), 1/rms per row
   if (c->P > 0) {
     if (!packed) {
-      tm.begin(TC_NORM);
-      launch_rmsnorm_rows(h, nullptr, ab, T, d, m.rms_eps, rstd, st, skp, h_pend);
+      norm_h(nullptr, rstd, h_pend);
       h_pend = 1;
-      tm.end();
     }
     if (int e = run_fused_kv(r, ab, true, tm)) return e;
   }
@@ -959,17 +966,22 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   tm.begin(TC_TAIL);
   float *th = r.at<float>(r.L.th);
   bf16_t *ta = r.at<bf16_t>(r.L.ta), *tq = r.at<bf16_t>(r.L.tq), *to = r.at<bf16_t>(r.L.to), *tz = r.at<bf16_t>(r.L.tz);
-  launch_gather_rows(h, r.at<int32_t>(r.L.last_rows), th, B, d, st);
+  int32_t t_pend = 1;   // K splits of the last residual GEMM waiting for the next norm pass over th
+  bool have_th = false;   // the tail's first norm takes the last tokens' rows from h and leaves them in th
+  auto norm_th = [&](const bf16_t *gain) {
+    if (!have_th) launch_rmsnorm_gather(h, r.at<int32_t>(r.L.last_rows), th, gain, ta, B, d, m.rms_eps, st);
+    else launch_rmsnorm_rows(th, gain, ta, B, d, m.rms_eps, nullptr, st, skp, t_pend);
+    have_th = true;
+  };
   if (c->ee_head) {   // extra head on the layer-l output; the flagged rows' logits replace the final ones below
-    launch_rmsnorm_rows(th, c->ee_gain, ta, B, d, m.rms_eps, nullptr, st);
+    norm_th(c->ee_gain);
     if (tail_gemm(c, ta, B, m.vocab, d, c->ee_head, nullptr, nullptr, r.at<float>(r.L.ee_logits), EPI_STORE_F32, skp, st))
       return fail(SWIFTKV_EHIP, "early-exit head GEMM failed");
     launch_early_exit_flags(r.at<float>(r.L.ee_logits), B, m.vocab, c->ee_threshold, r.at<int32_t>(r.L.ee_flags), st);
   }
-  int32_t t_pend = 1;   // K splits of the last residual GEMM waiting for the next norm pass over th
   for (int j = c->l; j < m.n_layers; ++j) {
     const int cl = c->l + (j - c->l) / c->g;
-    launch_rmsnorm_rows(th, c->norm1[j], ta, B, d, m.rms_eps, nullptr, st, skp, t_pend);
+    norm_th(c->norm1[j]);
     if (tail_gemm(c, ta, B, qd, d, c->wq[j], nullptr, nullptr, tq, EPI_STORE_BF16, skp, st)) return fail(SWIFTKV_EHIP, "tail q GEMM failed");
     AttnDecodeParams dp{};
     dp.q = tq; dp.out = to; dp.rows = (const DecodeRow *)r.meta(r.L.m_tail); dp.n_rows = B;
@@ -982,11 +994,11 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     if (launch_attention_decode(dp, st) != 0) return fail(SWIFTKV_EHIP, "tail attention launch failed");
     launch_decode_combine(dp.partial, to, dp.rows, B, m.n_q_heads, m.head_dim, dp.n_split, st);
     if (tail_gemm(c, to, B, d, qd, c->wo[j], nullptr, nullptr, th, EPI_RESID, skp, st, &t_pend)) return fail(SWIFTKV_EHIP, "tail o GEMM failed");
-    launch_rmsnorm_rows(th, c->norm2[j], ta, B, d, m.rms_eps, nullptr, st, skp, t_pend);
+    norm_th(c->norm2[j]);
     if (tail_gemm(c, ta, B, m.ffn, d, c->wgate[j], c->wup[j], c->gu_tab[j], tz, EPI_SWIGLU, skp, st)) return fail(SWIFTKV_EHIP, "tail MLP GEMM failed");
     if (tail_gemm(c, tz, B, d, m.ffn, c->wdown[j], nullptr, nullptr, th, EPI_RESID, skp, st, &t_pend)) return fail(SWIFTKV_EHIP, "tail down GEMM failed");
   }
-  launch_rmsnorm_rows(th, c->final_norm, ta, B, d, m.rms_eps, nullptr, st, skp, t_pend);
+  norm_th(c->final_norm);
   if (tail_gemm(c, ta, B, m.vocab, d, c->lm_head, nullptr, nullptr, logits_out, EPI_STORE_F32, skp, st)) return fail(SWIFTKV_EHIP, "LM head GEMM failed");
   if (c->ee_head) launch_early_exit_select(r.at<float>(r.L.ee_logits), r.at<int32_t>(r.L.ee_flags), logits_out, B, m.vocab, st);
   tm.end();

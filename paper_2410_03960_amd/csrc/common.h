@@ -168,6 +168,11 @@ struct QkvFinishParams {
   int32_t T, n_q_heads, n_kv_heads, head_dim;
   const float2 *cos_sin;          // [T][hd/2]
   uint32_t *amax;                 // [2][Hkv] float bits of this cache layer, or null
+  // Decode rows only, whose K and V nobody reads but from the cache: where cache_k is set they go to their paged slots
+  // (bf16, or e4m3 codes under the given scales [2][Hkv]) and not to k and v.
+  void *cache_k, *cache_v;
+  const int64_t *slots;
+  const float *scales;            // null: bf16
 };
 int launch_qkv_finish(const QkvFinishParams &p, hipStream_t st);
 
@@ -249,6 +254,17 @@ int launch_rstd_from_ssq(const float *ssq, int32_t n_blocks, float *rstd, int32_
 int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps, float *rstd_out, hipStream_t st,
                         const float *partial = nullptr, int32_t n_splits = 1);
 int launch_gather_rows(const float *h, const int32_t *rows, float *out, int32_t n_rows, int32_t d, hipStream_t st);
+// The same norm where the rows have yet to be put into h: from the embedding (ids clamped into [0, vocab)), or rows
+// idx[.] of `from`.
+struct RowSource {
+  const void *rows;      // bf16 embedding, or fp32 rows
+  const int32_t *idx;
+  int32_t n;             // rows of the embedding
+};
+int launch_rmsnorm_embed(const int32_t *ids, const bf16_t *E, int32_t vocab, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d,
+                         float eps, float *rstd_out, hipStream_t st);
+int launch_rmsnorm_gather(const float *from, const int32_t *idx, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps,
+                          hipStream_t st);
 int launch_f32_to_bf16(const float *x, bf16_t *out, int64_t n, hipStream_t st);
 int launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st);
 // out[((n/32) * (K/16) + k/16) * 512 + ((k%16)/8 * 32 + n%32) * 8 + k%8] = W row n (through the optional

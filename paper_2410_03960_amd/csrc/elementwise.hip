@@ -168,19 +168,37 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_reg_kernel(const float4 *h, 
 // the row first takes the sums of the K splits a weight-streaming GEMM left in `partial` ([n_splits][rows][d]
 // fp32): the splits are added in order, then to the row, which is written back.  The sum of squares is added
 // over a lane's values in order, then over the wave, then over the four waves in order.
-template <int CQ>
+// SRC: where the row comes from -- h itself; 1: the embedding row of its token id; 2: row idx[row] of another buffer.
+// The latter two leave it in h: the first norm of a pass and of the tail need no launch in front of them that only
+// copies (about 4.5 us each where rows are few; 8831 rows of 4096 from the embedding 70 us in two launches -> 46).
+template <int CQ, int SRC>
 __global__ __launch_bounds__(256) void rmsnorm_row_wg_kernel(float4 *h, const bf16_t *gain, uint2 *out, int rows, float eps, float inv_d,
-                                                             float *rstd_out, const float4 *partial, int n_splits) {
+                                                             float *rstd_out, const float4 *partial, int n_splits, RowSource rs_in) {
   __shared__ float red[4];
   const int row = blockIdx.x, tid = threadIdx.x;
   float4 *r = h + (int64_t)row * (CQ * 256);
   float4 u[CQ];
   uint2 g[CQ];
+  if constexpr (SRC == 1) {
+    int id = rs_in.idx[row];
+    id = id < 0 ? 0 : (id >= rs_in.n ? rs_in.n - 1 : id);   // (the plan reported it)
+    const uint2 *e = (const uint2 *)rs_in.rows + (int64_t)id * (CQ * 256) + tid;
 #pragma unroll
-  for (int i = 0; i < CQ; ++i) u[i] = r[i * 256 + tid];
+    for (int i = 0; i < CQ; ++i) {
+      const uint2 x = e[i * 256];
+      u[i] = make_float4(bf16lo(x.x), bf16hi(x.x), bf16lo(x.y), bf16hi(x.y));
+    }
+  } else {
+    const float4 *from = SRC == 2 ? (const float4 *)rs_in.rows + (int64_t)rs_in.idx[row] * (CQ * 256) : r;
+#pragma unroll
+    for (int i = 0; i < CQ; ++i) u[i] = from[i * 256 + tid];
+  }
 #pragma unroll
   for (int i = 0; i < CQ; ++i) g[i] = gain ? *(const uint2 *)(gain + 4 * (i * 256 + tid)) : make_uint2(0x3f803f80u, 0x3f803f80u);
-  if (n_splits > 1) {
+  if (SRC != 0) {
+#pragma unroll
+    for (int i = 0; i < CQ; ++i) r[i * 256 + tid] = u[i];
+  } else if (n_splits > 1) {
     float4 sum[CQ];
 #pragma unroll
     for (int i = 0; i < CQ; ++i) sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -238,6 +256,32 @@ __global__ void add_splits_kernel(float4 *h, const float4 *partial, int64_t n4, 
   u.x += sum.x; u.y += sum.y; u.z += sum.z; u.w += sum.w;
   h[i] = u;
 }
+namespace {
+template <int SRC>
+bool rmsnorm_from(const RowSource &src, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps, float *rstd_out, hipStream_t st) {
+  if (d % 1024 != 0 || d / 1024 > 8) return false;
+#define SKV_RMS_FROM(CQ_)                                                                                                        \
+  case CQ_:                                                                                                                      \
+    hipLaunchKernelGGL((rmsnorm_row_wg_kernel<CQ_, SRC>), dim3(rows), dim3(256), 0, st, (float4 *)h, gain, (uint2 *)out, rows, eps, \
+                       1.0f / (float)d, rstd_out, (const float4 *)nullptr, 1, src);                                              \
+    break;
+  switch (d / 1024) { SKV_RMS_FROM(1) SKV_RMS_FROM(2) SKV_RMS_FROM(3) SKV_RMS_FROM(4) SKV_RMS_FROM(5) SKV_RMS_FROM(6) SKV_RMS_FROM(7) SKV_RMS_FROM(8) }
+#undef SKV_RMS_FROM
+  return true;
+}
+}  // namespace
+int launch_rmsnorm_embed(const int32_t *ids, const bf16_t *E, int32_t vocab, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d,
+                         float eps, float *rstd_out, hipStream_t st) {
+  if (rows <= 0 || rmsnorm_from<1>(RowSource{E, ids, vocab}, h, gain, out, rows, d, eps, rstd_out, st)) return 0;
+  launch_embed(ids, E, h, rows, d, vocab, st);
+  return launch_rmsnorm_rows(h, gain, out, rows, d, eps, rstd_out, st);
+}
+int launch_rmsnorm_gather(const float *from, const int32_t *idx, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps,
+                          hipStream_t st) {
+  if (rows <= 0 || rmsnorm_from<2>(RowSource{from, idx, 0}, h, gain, out, rows, d, eps, nullptr, st)) return 0;
+  launch_gather_rows(from, idx, h, rows, d, st);
+  return launch_rmsnorm_rows(h, gain, out, rows, d, eps, nullptr, st);
+}
 int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps, float *rstd_out, hipStream_t st,
                         const float *partial, int32_t n_splits) {
   if (rows <= 0) return 0;
@@ -246,8 +290,8 @@ int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows,
   if ((rows <= 256 || n_splits > 1) && d % 1024 == 0 && d / 1024 <= 8) {   // few rows, or K splits to add on the way: a workgroup per row
 #define SKV_RMS_WG(CQ_)                                                                                            \
   case CQ_:                                                                                                        \
-    hipLaunchKernelGGL(rmsnorm_row_wg_kernel<CQ_>, dim3(rows), block, 0, st, (float4 *)h, gain, (uint2 *)out, rows, eps, inv_d, rstd_out, \
-                       (const float4 *)partial, n_splits);                                                        \
+    hipLaunchKernelGGL((rmsnorm_row_wg_kernel<CQ_, 0>), dim3(rows), block, 0, st, (float4 *)h, gain, (uint2 *)out, rows, eps, inv_d, rstd_out, \
+                       (const float4 *)partial, n_splits, RowSource{});                                           \
     return 0;
     switch (d / 1024) {
       SKV_RMS_WG(1) SKV_RMS_WG(2) SKV_RMS_WG(3) SKV_RMS_WG(4) SKV_RMS_WG(5) SKV_RMS_WG(6) SKV_RMS_WG(7) SKV_RMS_WG(8)
@@ -557,6 +601,19 @@ __global__ void qkv_finish_kernel(QkvFinishParams p) {
     x0 = y0; x1 = y1;
   }
   const bf16_t b0 = f32_to_bf16(x0), b1 = f32_to_bf16(x1);
+  if (kind != 0 && p.cache_k) {
+    const int64_t at = (p.slots[row] * p.n_kv_heads + head) * hd + i;
+    void *plane = kind == 1 ? p.cache_k : p.cache_v;
+    if (p.scales) {
+      const float s = p.scales[(kind == 2 ? p.n_kv_heads : 0) + head];
+      ((uint8_t *)plane)[at] = f32_to_e4m3fn(bf16_to_f32(b0) / s);
+      ((uint8_t *)plane)[at + half] = f32_to_e4m3fn(bf16_to_f32(b1) / s);
+    } else {
+      ((bf16_t *)plane)[at] = b0;
+      ((bf16_t *)plane)[at + half] = b1;
+    }
+    return;
+  }
   dst[i] = b0;
   dst[i + half] = b1;
   if (p.amax && kind != 0) {   // absmax of the values as stored (bf16-rounded)
