@@ -422,41 +422,44 @@ SeqPlan plan_seq(int M, int N, int K, int nw, bool consumer_sums, size_t partial
   const bool few = M <= 32;
   const double w_bytes = 2.0 * nw * N * K;
   double best_cost = 0;
-  for (int waves = 4; waves <= 8; waves += 4)
-    for (int nbw = 1; nbw <= 4; nbw *= 2) {
-      if (nw == 2 && nbw * waves > 8) continue;               // (two weights: register budget of the instantiations below)
-      const int n_cg = (nblocks + waves * nbw - 1) / (waves * nbw);
-      for (int ks_steps = 16; ks_steps >= 8; ks_steps /= 2) {
-        if (!few && ks_steps != (MB <= 4 ? 16 : 8)) continue;   // 2 x 48-64 KB, 2 x 40 KB of LDS
-        const int all_slices = K / (32 * ks_steps);
-        const size_t lds = (size_t)2 * ks_steps * MB * 1024;
-        for (int want = 1; want <= std::min(SKINNY_MAX_SPLIT, all_slices); ++want) {
-          const int n_slices = (all_slices + want - 1) / want;
-          const int ksplit = (all_slices + n_slices - 1) / n_slices;
-          if (ksplit != want) continue;
-          const int64_t wgs = (int64_t)n_cg * ksplit;
-          const size_t partial = ksplit > 1 ? (size_t)ksplit * nw * M * N * 4 : 0;
-          if (partial > partial_cap) continue;
-          const double a_bytes = 0.75 * (double)n_cg * M * K * 2, p_bytes = 2.0 * partial;   // (L2 hits: cheaper than the partial sums' trip to memory)
-          const double second = (ksplit > 1 && !consumer_sums) ? 25e6 : 0;   // a launch, in bytes at the streaming rate
-          const int64_t n_rounds = (wgs + 255) / 256;
-          double factor;
-          if (few) {
-            const int resident = (int)std::min<int64_t>(n_rounds, (160 << 10) / lds);
-            const double in_flight = (double)resident * waves * (nbw * nw == 1 ? 8 : 16);   // KB per CU
-            factor = (1 + 0.3 * ((double)n_rounds * 256 / (double)wgs - 1)) * (1 + 0.35 * std::max(0.0, 1 - in_flight / 64));
-          } else {
-            factor = (double)n_rounds * 256.0 / (double)wgs * (1.0 + 0.15 * (double)(n_rounds - 1));   // every further round pays its own fill and uneven end
-          }
-          const double cost = (w_bytes + a_bytes + p_bytes + second) * factor;
-          if (!best.ok || cost < best_cost) {
-            best_cost = cost;
-            best = SeqPlan{true, waves, nbw, ks_steps, n_slices, ksplit, lds, partial};
-            best.wgs = wgs;
-          }
+  // The first of equals wins: beyond 32 rows eight waves with a block each are ahead of four with two (64 rows x 6144 x
+  // 4096 18.0 us against 19.0, 4096 x 4096 13.0 / 13.7), four waves with four blocks of eight with two (8192 x 8192 33.4 / 35.3).
+  static const int shapes[][2] = {{8, 1}, {4, 1}, {4, 2}, {4, 4}, {8, 1}, {8, 2}, {8, 4}};
+  for (int i = few ? 1 : 0; i < 7; ++i) {
+    const int waves = shapes[i][0], nbw = shapes[i][1];
+    if (nw == 2 && nbw * waves > 8) continue;               // (two weights: register budget of the instantiations below)
+    const int n_cg = (nblocks + waves * nbw - 1) / (waves * nbw);
+    for (int ks_steps = 16; ks_steps >= 8; ks_steps /= 2) {
+      if (!few && ks_steps != 16) continue;   // 2 x 48-80 KB of LDS (80 rows in slices half as long: 2 x 14336 x 4096 70.6 us, 67.3 so)
+      const int all_slices = K / (32 * ks_steps);
+      const size_t lds = (size_t)2 * ks_steps * MB * 1024;
+      for (int want = 1; want <= std::min(SKINNY_MAX_SPLIT, all_slices); ++want) {
+        const int n_slices = (all_slices + want - 1) / want;
+        const int ksplit = (all_slices + n_slices - 1) / n_slices;
+        if (ksplit != want) continue;
+        const int64_t wgs = (int64_t)n_cg * ksplit;
+        const size_t partial = ksplit > 1 ? (size_t)ksplit * nw * M * N * 4 : 0;
+        if (partial > partial_cap) continue;
+        const double a_bytes = 0.75 * (double)n_cg * M * K * 2, p_bytes = 2.0 * partial;   // (L2 hits: cheaper than the partial sums' trip to memory)
+        const double second = (ksplit > 1 && !consumer_sums) ? 25e6 : 0;   // a launch, in bytes at the streaming rate
+        const int64_t n_rounds = (wgs + 255) / 256;
+        double factor;
+        if (few) {
+          const int resident = (int)std::min<int64_t>(n_rounds, (160 << 10) / lds);
+          const double in_flight = (double)resident * waves * (nbw * nw == 1 ? 8 : 16);   // KB per CU
+          factor = (1 + 0.3 * ((double)n_rounds * 256 / (double)wgs - 1)) * (1 + 0.35 * std::max(0.0, 1 - in_flight / 64));
+        } else {
+          factor = (double)n_rounds * 256.0 / (double)wgs * (1.0 + 0.15 * (double)(n_rounds - 1));   // every further round pays its own fill and uneven end
+        }
+        const double cost = (w_bytes + a_bytes + p_bytes + second) * factor;
+        if (!best.ok || cost < best_cost) {
+          best_cost = cost;
+          best = SeqPlan{true, waves, nbw, ks_steps, n_slices, ksplit, lds, partial};
+          best.wgs = wgs;
         }
       }
     }
+  }
   // Up to 32 rows the first kernel, which splits K among the waves of a workgroup, is ahead where this one has too few
   // workgroups (2048 x 2048, 1 row: 6.5 us against 5.5), and up to 16 where it needs a second launch (4096 x 4096
   // in bf16, 1 row: 13.0 against 9.9; 8192 x 4096 22 against 15.5).
