@@ -115,9 +115,9 @@ Layout make_layout(const swiftkv_ctx *c, int64_t T, int32_t B, int64_t vt_ld, in
   L.m_words = w;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
-  L.err = take(256);
   L.ee_flags = take((size_t)B * 4);
-  L.meta = take(L.m_words * 4);   // err, ee_flags and meta are written by one copy
+  L.err = take(256);
+  L.meta = take(L.m_words * 4);   // ee_flags, err and meta are written by one copy (the K/V step alone: err and meta)
   L.positions = take(T * 4);
   L.seq_of = take(T * 4);
   L.last_rows = take((size_t)B * 4);
@@ -366,9 +366,9 @@ int run_plan(Run &r, const int32_t *token_ids) {
   swiftkv_ctx *c = r.c;
   // plan words: host vector -> pinned slot -> device, without waiting for the stream (a slot is only
   // waited for when the ring wraps around onto a copy that has not run yet)
-  // The error flags, the attention kernel's item counters (words 4..12 of err) and the exit flags start at zero: their
-  // words precede the plan's and travel with them.
-  const size_t zeros = r.L.meta - r.L.err, bytes = zeros + r.hp.meta.size() * 4;
+  // The exit flags, the error flags and the attention kernel's item counters (words 4..11 of err) start at zero: their
+  // words precede the plan's and travel with them.  The K/V step alone leaves the exit flags as the last prefill set them.
+  const size_t first = token_ids ? r.L.ee_flags : r.L.err, zeros = r.L.meta - first, bytes = zeros + r.hp.meta.size() * 4;
   if (int e = pin_reserve(c, bytes)) return e;
   const int slot = c->pin_next;
   c->pin_next = (slot + 1) % PIN_SLOTS;
@@ -376,7 +376,7 @@ int run_plan(Run &r, const int32_t *token_ids) {
   unsigned char *stage = c->pin + (size_t)slot * c->pin_slot_bytes;
   memset(stage, 0, zeros);
   memcpy(stage + zeros, r.hp.meta.data(), bytes - zeros);
-  HIP_TRY(hipMemcpyAsync(r.ws + r.L.err, stage, bytes, hipMemcpyHostToDevice, r.st));
+  HIP_TRY(hipMemcpyAsync(r.ws + first, stage, bytes, hipMemcpyHostToDevice, r.st));
   HIP_TRY(hipEventRecord(c->pin_ev[slot], r.st));
   c->pin_used[slot] = true;
   if (r.fp8 && r.kv->scale_mode == SWIFTKV_SCALE_COMPUTE_ABSMAX) launch_fill_u32(r.at<uint32_t>(r.L.amax), 0, (int64_t)c->C * 2 * c->cfg.n_kv_heads, r.st);

@@ -228,6 +228,26 @@ def test_early_exit_selects_confident_rows(tiny):
     G.compare_logits(logits2, plain, label="early exit off")
 
 
+def test_exit_flags_outlive_the_kv_step(tiny):
+    """swiftkv_export_exit_flags reports the most recent prefill on the workspace: a
+    swiftkv_kv_from_hidden of the same batch in between leaves them as they are."""
+    from paper_2410_03960_amd import binding as B
+    wl, store, dev_w = tiny
+    l, g = 2, 2
+    batch = WL.build_batch(wl, lens=[19, 7, 30, 64], shuffled=True)
+    ctx = _ctx(dev_w, l, g)
+    gain = torch.ones(TINY.hidden, dtype=torch.bfloat16, device="cuda")
+    head = torch.randn((TINY.vocab, TINY.hidden), generator=torch.Generator().manual_seed(8)).to(torch.bfloat16).cuda()
+    ctx.set_early_exit(gain, head, -1.0)          # every row's largest probability exceeds this threshold
+    logits, cache, ws = G.run_gpu(ctx, batch)
+    hidden = ctx.export_hidden(ws, batch.n_tokens)
+    assert ctx.export_exit_flags(ws, batch.n_seqs).tolist() == [1] * batch.n_seqs
+    ctx.kv_from_hidden(hidden, batch.seq_lens.tolist(), cache, ws)
+    assert ctx.export_exit_flags(ws, batch.n_seqs).tolist() == [1] * batch.n_seqs
+    G.check_plan(ctx, ws, batch)
+    ctx.set_early_exit(None, None)
+
+
 @pytest.mark.parametrize("hq,hkv,hd", [(4, 4, 64), (16, 2, 64), (2, 2, 128), (8, 1, 128)])
 def test_head_groupings(hq, hkv, hd):
     """Query heads per KV head 1 (plain multi-head attention), 8, and a single KV
