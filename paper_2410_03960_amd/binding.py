@@ -9,7 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
-from typing import Dict, Optional, Sequence
+from typing import Dict, NamedTuple, Optional, Sequence
 
 import torch
 
@@ -27,7 +27,7 @@ EXPORTS = (
     "swiftkv_pack_bytes", "swiftkv_pack_bytes_min",
     "swiftkv_create", "swiftkv_destroy", "swiftkv_workspace_bytes", "swiftkv_workspace_bytes_prefix", "swiftkv_prefill",
     "swiftkv_kv_from_hidden", "swiftkv_set_early_exit", "swiftkv_export_exit_flags", "swiftkv_export_plan", "swiftkv_export_hidden", "swiftkv_op_gemm",
-    "swiftkv_op_gemm_packed", "swiftkv_op_gemm_rows", "swiftkv_op_gemm_rows_workspace", "swiftkv_op_gemm_rows_static",
+    "swiftkv_op_gemm_packed", "swiftkv_op_gemm_plan", "swiftkv_op_gemm_rows", "swiftkv_op_gemm_rows_workspace", "swiftkv_op_gemm_rows_static",
     "swiftkv_op_attention_prefill", "swiftkv_op_attention_workspace", "swiftkv_op_attention_decode", "swiftkv_op_attention_decode_workspace", "swiftkv_op_fp8_quantize", "swiftkv_op_mfma_rate",
     "swiftkv_flops", "swiftkv_set_timing", "swiftkv_get_timing", "swiftkv_last_error",
     "swiftkv_version",
@@ -92,6 +92,7 @@ def load() -> C.CDLL:
     lib.swiftkv_export_hidden.argtypes = [vp, vp, vp, vp]
     lib.swiftkv_op_gemm.argtypes = [vp, vp, vp, i32, i32, i32, i32, i32, vp]
     lib.swiftkv_op_gemm_packed.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp]
+    lib.swiftkv_op_gemm_plan.argtypes = [i32, i32, i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]
     lib.swiftkv_op_gemm_rows.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp, C.c_size_t, vp]
     lib.swiftkv_op_gemm_rows_static.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp]
     lib.swiftkv_op_gemm_rows_workspace.argtypes = [i32, i32]
@@ -316,6 +317,28 @@ def op_gemm_packed(A: torch.Tensor, W: torch.Tensor, stream=None) -> torch.Tenso
     _check(load().swiftkv_op_gemm_packed(_dev(A, torch.bfloat16), _dev(W, torch.bfloat16), _dev(scratch), _dev(out),
                                          M, N, K, _stream_ptr(stream)))
     return out
+
+
+class GemmPlan(NamedTuple):
+    kernel: str      # GEMM_KERNELS
+    tile: int        # rows of a tile; weight streaming: 16-column blocks per workgroup
+    n_splits: int
+    slice: int
+
+
+GEMM_KERNELS = {0: "stream_first", 1: "stream_seq", 2: "stream_resident", 4: "tile_128", 5: "tile_256", 6: "five_stage",
+                7: "packed_dma", 8: "packed_reg", 9: "rows_reg"}
+GEMM_EPILOGUES = ("bf16", "f32", "resid", "swiglu", "qkv", "kv")
+GEMM_SCRATCH = 16 * 80 * 8192 * 4     # bytes for K splits that swiftkv_prefill and swiftkv_kv_from_hidden have
+
+
+def op_gemm_plan(epilogue: str, M: int, N: int, K: int, packed: bool = False, consumer_adds: bool = False, norm_out: bool = False,
+                 head_dim: int = 0, scratch: int = GEMM_SCRATCH) -> GemmPlan:
+    """The kernel the library runs for a product (host only, no GPU)."""
+    out = (C.c_int32 * 4)()
+    _check(load().swiftkv_op_gemm_plan(GEMM_EPILOGUES.index(epilogue), M, N, K, int(packed) + 2 * int(consumer_adds) + 4 * int(norm_out),
+                                       head_dim, scratch, out))
+    return GemmPlan(GEMM_KERNELS[out[0]], out[1], out[2], out[3])
 
 
 def op_gemm_rows(A: torch.Tensor, W: torch.Tensor, out_f32: bool = False, stream=None) -> torch.Tensor:

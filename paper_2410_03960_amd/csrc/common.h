@@ -135,6 +135,10 @@ struct MidPlan {
 };
 MidPlan plan_gemm_mid(const GemmParams &p, int epi);
 int launch_gemm_mid(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st);
+// What launch_gemm (variant 0) and launch_skinny run, for swiftkv_op_gemm_plan: a SWIFTKV_GEMM_* kernel, the rows of its
+// tile (weight streaming: column blocks of 16 per workgroup), K splits, columns of K to a slice (0: no slices).
+struct GemmRoute { int32_t kernel, tile, n_splits, slice; };
+GemmRoute route_gemm(const GemmParams &p, int epi);
 int launch_gemm_wreg(const GemmParams &p, int epi, int fm, hipStream_t st);
 int launch_splits_finish(const GemmParams &p, int epi, hipStream_t st);
 
@@ -156,6 +160,7 @@ struct SkinnyParams {
 constexpr int SKINNY_MAX_SPLIT = 16;
 constexpr size_t SKINNY_PARTIAL_BYTES = (size_t)SKINNY_MAX_SPLIT * 80 * 8192 * 4;   // the driver's scratch: 16 splits x 80 rows x 8192 columns fp32 (42 MB)
 int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st);
+GemmRoute route_skinny(const SkinnyParams &p, int epi);
 
 // Few-row batches (decode steps): the Q, K, V projections come out of the weight-streaming kernel as
 // fp32; this step rotates q and k (rotate-half, angles of the row's position), rounds to bf16 once and,

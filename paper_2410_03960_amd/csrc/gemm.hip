@@ -18,6 +18,7 @@
 // The weight operand is addressed through a table of row-block pointers (16
 // rows each), which lets [W_Q;W_K;W_V], the 16-row interleave of W_gate/W_up and
 // the concatenated [W_K;W_V] of all AcrossKV group leaders be consumed in place.
+#include "../../include/swiftkv.h"
 #include "common.h"
 
 namespace {
@@ -736,6 +737,13 @@ int launch_mfma_rate(const bf16_t *operands, float *sink, int32_t n_workgroups, 
   return 0;
 }
 
+GemmRoute route_gemm(const GemmParams &p, int epi) {
+  const MidPlan pl = plan_gemm_mid(p, epi);
+  static const int kernel[] = {0, SWIFTKV_GEMM_PACKED_DMA, SWIFTKV_GEMM_PACKED_REG, SWIFTKV_GEMM_ROWS_REG};
+  if (pl.kernel != MID_NONE) return GemmRoute{kernel[pl.kernel], 32 * pl.fm, pl.n_splits, 0};
+  if (p.M < 1024) return GemmRoute{SWIFTKV_GEMM_TILE_128, 128, 1, 0};
+  return GemmRoute{p.K % BK ? SWIFTKV_GEMM_TILE_256 : SWIFTKV_GEMM_FIVE_STAGE, 256, 1, 0};
+}
 // variant 0 picks by shape: the plan of gemm_mid.hip (packed weights at any number of rows, row-major ones below 1024),
 // else the 256 x 256 tile from 1024 rows on and the 128 x 128 tile below
 int launch_gemm(const GemmParams &p, int epi, int variant, hipStream_t st) {

@@ -349,7 +349,8 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   MidPlan best{};
   best.kernel = MID_NONE;
   const bool packed = p.wpack && p.K % 256 == 0 && p.N % 256 == 0 && epi != EPI_STORE_F32;
-  if (p.M <= 80 || (uint64_t)p.M * (uint64_t)p.lda * 2 >= 0xffffffffull) return best;
+  if (p.M <= 80) return best;
+  const bool far = (uint64_t)p.M * (uint64_t)p.lda * 2 >= 0xffffffffull;   // beyond the 32-bit row offsets of gemm_mid_kernel (gemm_wreg_kernel has whole pointers)
   if (!packed && (p.M >= 1024 || p.K % 64 != 0 || p.N % 64 != 0 || ((epi == EPI_QKV || epi == EPI_KV) && p.N % 128 != 0))) return best;
   const bool norm_out = epi == EPI_RESID && p.hb && p.ssq;
   const bool consumer = epi == EPI_RESID && p.n_splits_out;
@@ -368,7 +369,7 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   // 256, 6.02 ms per launch -> 5.85).
   const bool full = packed && ((int64_t)((p.M + 255) / 256) * tiles_n + 255) / 256 > 24;
   for (const Form &f : forms) {
-    if ((f.kernel == MID_ROWS) == packed || (full && f.fm < 8)) continue;
+    if ((f.kernel == MID_ROWS) == packed || (full && f.fm < 8) || (far && f.kernel != MID_WREG)) continue;
     const int64_t tiles = (int64_t)((p.M + 32 * f.fm - 1) / (32 * f.fm)) * tiles_n;
     for (int want = 1; want <= std::min(MID_MAX_SPLIT, all_steps / unit); ++want) {
       if (want > 1 && (!p.partial || norm_out)) break;

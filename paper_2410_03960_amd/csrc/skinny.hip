@@ -19,6 +19,7 @@
 // skinny_seq_kernel (K % 512 == 0: slices of K walked in sequence, the activation
 // slice double-buffered in LDS by a producer wave) and skinny_res_kernel (the
 // SwiGLU pair for up to 8 rows: all activation rows resident in LDS).
+#include "../../include/swiftkv.h"
 #include "common.h"
 
 #include <algorithm>
@@ -515,17 +516,21 @@ int launch_seq(const SkinnyParams &p, int epi, const SeqPlan &pl, hipStream_t st
   }
 }
 
+// The first kernel's shape: column blocks of a workgroup (two weight matrices count double: at most four weight-row
+// blocks), and K splits where the column tiles of more than 32 rows leave CUs idle, each of at least 16 k steps per wave.
+int first_blocks(const SkinnyParams &p, int epi) {
+  if (p.M > 32 && epi != EPI_SWIGLU && p.N % 64 == 0) return 4;
+  return p.M > 16 && p.N % 32 == 0 ? 2 : 1;
+}
+int first_splits(const SkinnyParams &p, int epi, int nb) {
+  const int tiles = p.N / (16 * nb), nw = epi == EPI_SWIGLU ? 2 : 1;
+  if (!p.partial || p.M <= 32 || tiles >= 256) return 1;
+  const int ksplit = std::min({SKINNY_MAX_SPLIT, 256 / tiles, std::max(1, p.K / (32 * SK_WAVES * 4))});
+  return (size_t)ksplit * nw * p.M * p.N * 4 > p.partial_bytes ? 1 : ksplit;
+}
 template <int MB, int NB, int EPI>
 int launch_kernels(const SkinnyParams &p, hipStream_t st) {
-  constexpr int NW = (EPI == EPI_SWIGLU) ? 2 : 1;
-  const int tiles = p.N / (16 * NB);
-  // split K while the column tiles leave CUs idle: up to 4 splits, each at least 16 k steps per wave pass
-  int ksplit = 1;
-  if (p.partial && MB >= 3 && tiles < 256) {
-    ksplit = std::min(SKINNY_MAX_SPLIT, 256 / tiles);
-    ksplit = std::min(ksplit, std::max(1, p.K / (32 * SK_WAVES * 4)));
-    if ((size_t)ksplit * NW * p.M * p.N * 4 > p.partial_bytes) ksplit = 1;
-  }
+  const int tiles = p.N / (16 * NB), ksplit = first_splits(p, EPI, NB);
   dim3 grid(tiles, ksplit), block(SK_WAVES * 64);
   hipLaunchKernelGGL((skinny_kernel<MB, NB, EPI>), grid, block, 0, st, p);
   if (ksplit > 1 && p.n_splits_out) *p.n_splits_out = ksplit;   // the consumer adds the splits
@@ -551,15 +556,23 @@ int launch_mb(const SkinnyParams &p, int epi, hipStream_t st) {
 
 template <int MB>
 int launch_wide(const SkinnyParams &p, int epi, hipStream_t st) {
-  // two weight matrices count double: at most four weight-row blocks per workgroup
-  const int want = epi == EPI_SWIGLU ? 2 : 4;
-  if (want == 4 && p.N % 64 == 0) return launch_mb<MB, 4>(p, epi, st);
-  if (p.N % 32 == 0) return launch_mb<MB, 2>(p, epi, st);
+  switch (first_blocks(p, epi)) {
+    case 4: return launch_mb<MB, 4>(p, epi, st);
+    case 2: return launch_mb<MB, 2>(p, epi, st);
+  }
   return launch_mb<MB, 1>(p, epi, st);
 }
 
 }  // namespace
 
+GemmRoute route_skinny(const SkinnyParams &p, int epi) {
+  const int nw = epi == EPI_SWIGLU ? 2 : 1;
+  if (res_fits(p, epi)) return GemmRoute{SWIFTKV_GEMM_STREAM_RESIDENT, RES_WAVES, 1, 0};
+  const SeqPlan sq = plan_seq(p.M, p.N, p.K, nw, p.n_splits_out != nullptr, p.partial_bytes);
+  if (sq.ok) return GemmRoute{SWIFTKV_GEMM_STREAM_SEQ, sq.waves * sq.nbw, sq.ksplit, sq.ks_steps * 32};
+  const int nb = first_blocks(p, epi);
+  return GemmRoute{SWIFTKV_GEMM_STREAM_FIRST, nb, first_splits(p, epi, nb), 0};
+}
 int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0) return 0;
   if (p.M > 80 || (p.N % 16) != 0 || (p.K % 8) != 0) return -1;
@@ -573,7 +586,7 @@ int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
     if (sq.ok) return launch_seq(p, epi, sq, st);
   }
   if (p.M <= 16) return launch_mb<1, 1>(p, epi, st);
-  if (p.M <= 32) return (p.N % 32 == 0) ? launch_mb<2, 2>(p, epi, st) : launch_mb<2, 1>(p, epi, st);
+  if (p.M <= 32) return first_blocks(p, epi) == 2 ? launch_mb<2, 2>(p, epi, st) : launch_mb<2, 1>(p, epi, st);
   if (p.M <= 48) return launch_wide<3>(p, epi, st);
   if (p.M <= 64) return launch_wide<4>(p, epi, st);
   return launch_wide<5>(p, epi, st);
