@@ -108,7 +108,6 @@ struct GemmParams {
   bf16_t *hb;
   const bf16_t *hb_gain;
   float *ssq;
-  int32_t raster_gm;           // m tiles per rasterisation group (0 = default)
   // K splits (launch_gemm_mid): scratch for the splits' partial sums, [split][M][N] fp32, or null (K is never split)
   float *partial;
   size_t partial_bytes;

@@ -538,7 +538,7 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_dlds5_kernel(GemmParams p)
   const int per_xcd = (total + 7) / 8;
   const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (logical >= total) return;
-  const int GM = p.raster_gm > 0 ? p.raster_gm : 8;
+  constexpr int GM = 8;   // m tiles per rasterisation group
   const int group = logical / (GM * tiles_n);
   const int first_m = group * GM;
   const int gsz = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;

@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
   const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (logical >= total) return;
   const int split = logical / per_split, tile = logical % per_split;
-  const int GM = p.raster_gm > 0 ? p.raster_gm : 8;
+  constexpr int GM = 8;   // m tiles per rasterisation group
   const int group = tile / (GM * tiles_n);
   const int first_m = group * GM;
   const int gsz = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
