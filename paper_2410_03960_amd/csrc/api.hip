@@ -93,7 +93,6 @@ struct swiftkv_ctx {
 
 namespace {
 
-constexpr int MAX_SPLIT = 32;
 constexpr int SKINNY_MAX_ROWS = 80;   // batches up to this many tokens run every GEMM on the weight-streaming kernel
 
 Layout make_layout(const swiftkv_ctx *c, int64_t T, int32_t B, int64_t vt_ld, int32_t nqb, int32_t nkt,
@@ -894,7 +893,7 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       set_split(dp, r.hp.max_keys_dec, r.hp.sum_keys_dec);
       tm.begin(TC_OTHER);
       if (launch_attention_decode(dp, st) != 0) return fail(SWIFTKV_EHIP, "decode attention launch failed");
-      launch_decode_combine(dp.partial, ob, dp.rows, dp.n_rows, m.n_q_heads, m.head_dim, dp.n_split, st);
+      if (launch_decode_combine(dp.partial, ob, dp.rows, dp.n_rows, m.n_q_heads, m.head_dim, dp.n_split, st) != 0) return fail(SWIFTKV_EHIP, "decode combine launch failed");
       tm.end();
     }
     if (few_rows) {
@@ -992,7 +991,7 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     dp.cos_sin = r.at<float2>(r.L.cos_sin); dp.partial = r.at<float>(r.L.partial);
     set_split(dp, r.hp.max_keys_tail, r.hp.sum_keys_tail);
     if (launch_attention_decode(dp, st) != 0) return fail(SWIFTKV_EHIP, "tail attention launch failed");
-    launch_decode_combine(dp.partial, to, dp.rows, B, m.n_q_heads, m.head_dim, dp.n_split, st);
+    if (launch_decode_combine(dp.partial, to, dp.rows, B, m.n_q_heads, m.head_dim, dp.n_split, st) != 0) return fail(SWIFTKV_EHIP, "tail combine launch failed");
     if (tail_gemm(c, to, B, d, qd, c->wo[j], nullptr, nullptr, th, EPI_RESID, skp, st, &t_pend)) return fail(SWIFTKV_EHIP, "tail o GEMM failed");
     norm_th(c->norm2[j]);
     if (tail_gemm(c, ta, B, m.ffn, d, c->wgate[j], c->wup[j], c->gu_tab[j], tz, EPI_SWIGLU, skp, st)) return fail(SWIFTKV_EHIP, "tail MLP GEMM failed");
@@ -1247,7 +1246,7 @@ int swiftkv_op_attention_decode(const void *q, void *out, const int32_t *n_keys,
   dp.partial = (float *)(ws + align_up((size_t)n_rows * sizeof(DecodeRow)));
   set_split(dp, max_keys, sum_keys);
   if (launch_attention_decode(dp, st)) return fail(SWIFTKV_EHIP, "decode attention launch failed");
-  launch_decode_combine(dp.partial, dp.out, dp.rows, n_rows, Hq, hd, dp.n_split, st);
+  if (launch_decode_combine(dp.partial, dp.out, dp.rows, n_rows, Hq, hd, dp.n_split, st)) return fail(SWIFTKV_EHIP, "decode combine launch failed");
   if (int e = check_launch("single-query attention")) return e;
   HIP_TRY(hipStreamSynchronize(st));   // the row table was staged from this call's own (pageable) host vector
   return SWIFTKV_OK;

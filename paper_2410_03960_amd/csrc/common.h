@@ -119,7 +119,7 @@ struct GemmParams {
 // Matrix-instruction rate on given operand data, nothing else in the loop: `iters` x 16 independent
 // v_mfma_f32_32x32x16_bf16 per wave, 4 waves per workgroup, one workgroup per CU.
 int launch_mfma_rate(const bf16_t *operands, float *sink, int32_t n_workgroups, int32_t iters, hipStream_t st);
-int launch_gemm(const GemmParams &p, int epi, int variant, hipStream_t st);
+[[nodiscard]] int launch_gemm(const GemmParams &p, int epi, int variant, hipStream_t st);
 // Choice of kernel, tile height and K splits for more than 80 rows (gemm_mid.hip).
 enum MidKernel {
   MID_NONE = 0,    // not a shape of these kernels
@@ -133,13 +133,13 @@ struct MidPlan {
   double cost;                     // estimated time in us, adding the splits up included
 };
 MidPlan plan_gemm_mid(const GemmParams &p, int epi);
-int launch_gemm_mid(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st);
+[[nodiscard]] int launch_gemm_mid(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st);
 // What launch_gemm (variant 0) and launch_skinny run, for swiftkv_op_gemm_plan: a SWIFTKV_GEMM_* kernel, the rows of its
 // tile (weight streaming: column blocks of 16 per workgroup), K splits, columns of K to a slice (0: no slices).
 struct GemmRoute { int32_t kernel, tile, n_splits, slice; };
 GemmRoute route_gemm(const GemmParams &p, int epi);
 int launch_gemm_wreg(const GemmParams &p, int epi, int fm, hipStream_t st);
-int launch_splits_finish(const GemmParams &p, int epi, hipStream_t st);
+[[nodiscard]] int launch_splits_finish(const GemmParams &p, int epi, hipStream_t st);
 
 // skinny (weight-streaming) GEMM for M <= 80 rows
 struct SkinnyParams {
@@ -158,7 +158,7 @@ struct SkinnyParams {
 };
 constexpr int SKINNY_MAX_SPLIT = 16;
 constexpr size_t SKINNY_PARTIAL_BYTES = (size_t)SKINNY_MAX_SPLIT * 80 * 8192 * 4;   // the driver's scratch: 16 splits x 80 rows x 8192 columns fp32 (42 MB)
-int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st);
+[[nodiscard]] int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st);
 GemmRoute route_skinny(const SkinnyParams &p, int epi);
 
 // Few-row batches (decode steps): the Q, K, V projections come out of the weight-streaming kernel as
@@ -204,7 +204,7 @@ struct AttnPrefillParams {
   int32_t n_qblocks, n_q_heads, n_kv_heads, head_dim;
   int32_t *sched;       // eight device words, zero at launch (the kernel leaves them zero): items pulled from each of 8 queues
 };
-int launch_attention_prefill(const AttnPrefillParams &p, hipStream_t st);
+[[nodiscard]] int launch_attention_prefill(const AttnPrefillParams &p, hipStream_t st);
 
 struct DecodeRow {  // one single-query attention problem
   int32_t q_row;    // row in q buffer
@@ -229,7 +229,10 @@ struct AttnDecodeParams {
   int32_t n_split;
   int32_t min_keys;       // least keys of a split (vector-unit kernel; the matrix-unit kernels take whole 128-key steps)
 };
-int launch_attention_decode(const AttnDecodeParams &p, hipStream_t st);
+// Most key splits of a single-query row: decode_combine_kernel takes a split per lane of a wave and holds one value of each.
+constexpr int MAX_SPLIT = 32;
+static_assert(MAX_SPLIT <= 64 && MAX_SPLIT % 8 == 0, "a lane per split, groups of eight");
+[[nodiscard]] int launch_attention_decode(const AttnDecodeParams &p, hipStream_t st);
 
 // ----------------------------------------------------------- elementwise ----
 struct PlanParams {
@@ -336,5 +339,6 @@ struct GatherParams {
 };
 int launch_kv_gather(const GatherParams &p, hipStream_t st);
 int launch_fp8_quantize(const float *x, float scale, uint8_t *codes, int64_t n, hipStream_t st);
-int launch_decode_combine(const float *partial, bf16_t *out, const DecodeRow *rows, int32_t n_rows,
+// (refuses more than MAX_SPLIT splits)
+[[nodiscard]] int launch_decode_combine(const float *partial, bf16_t *out, const DecodeRow *rows, int32_t n_rows,
                           int32_t n_q_heads, int32_t head_dim, int32_t n_split, hipStream_t st);

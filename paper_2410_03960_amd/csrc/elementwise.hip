@@ -750,7 +750,7 @@ int launch_fp8_quantize(const float *x, float scale, uint8_t *codes, int64_t n, 
 }
 
 // ------------------------------------------------- split-KV combine --------
-// partial layout: [row][head][split][hd + 2] = (o[hd] unnormalised, m, l), m in log2 units; n_split <= 32.
+// partial layout: [row][head][split][hd + 2] = (o[hd] unnormalised, m, l), m in log2 units; n_split <= MAX_SPLIT.
 // One latency-bound pass: every load is requested before the first use.  Lane s of each wave holds split s's m and l,
 // so the weights come from wave reductions and are broadcast lane by lane (no second trip to memory, no barrier):
 // one row of 25 splits 5.8 -> 3.9 us per launch.  An empty split carries m = -inf and enters with weight 0.
@@ -761,9 +761,9 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float *partia
   const int ls = lane < n_split ? lane : n_split - 1;
   float mv = base[ls * (hd + 2) + hd];
   const float lv = base[ls * (hd + 2) + hd + 1];
-  float ov[32];
+  float ov[MAX_SPLIT];
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+  for (int c = 0; c < MAX_SPLIT / 8; ++c)
     if (c * 8 < n_split) {
 #pragma unroll
       for (int i = c * 8; i < c * 8 + 8; ++i) ov[i] = base[(i < n_split ? i : n_split - 1) * (hd + 2) + d];
@@ -774,7 +774,7 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float *partia
   const float l = wave_sum(w * lv);
   float acc = 0.f;
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+  for (int c = 0; c < MAX_SPLIT / 8; ++c)
     if (c * 8 < n_split) {
 #pragma unroll
       for (int i = c * 8; i < c * 8 + 8; ++i) acc += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), i)) * ov[i];   // (weight 0 past the last split)
@@ -784,7 +784,7 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float *partia
 int launch_decode_combine(const float *partial, bf16_t *out, const DecodeRow *rows, int32_t n_rows,
                           int32_t n_q_heads, int32_t head_dim, int32_t n_split, hipStream_t st) {
   if (n_rows <= 0) return 0;
-  if (n_split > 32) return -1;
+  if (n_split > MAX_SPLIT) return -1;
   hipLaunchKernelGGL(decode_combine_kernel, dim3(n_rows, n_q_heads), dim3(head_dim), 0, st, partial, out, rows, n_q_heads, head_dim, n_split);
   return 0;
 }

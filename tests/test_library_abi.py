@@ -89,3 +89,14 @@ def test_header_is_plain_c(tmp_path):
     r = subprocess.run(["gcc", "-std=c11", "-Wall", "-Werror", "-pedantic", "-Wno-pedantic", "-I", os.path.join(ROOT, "include"),
                         "-c", str(src), "-o", str(tmp_path / "use_header.o")], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
+
+
+def test_every_launch_that_can_refuse_is_checked():
+    """The launch functions that can refuse a shape are [[nodiscard]]; a caller that drops their result would report
+    success over stale output.  Host side only, syntax only."""
+    import subprocess
+    from paper_2410_03960_amd import build
+    for src in ("api.hip", "gemm.hip", "gemm_mid.hip"):
+        r = subprocess.run([build._hipcc(), "--cuda-host-only", "--offload-arch=gfx950", "-std=c++17", "-fsyntax-only", "-Werror=unused-result",
+                            "-Wno-unused-command-line-argument", os.path.join(build.CSRC, src)], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
