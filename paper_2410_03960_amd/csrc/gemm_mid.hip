@@ -358,10 +358,10 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   const int tiles_n = (p.N + 255) / 256;
   // us per step of a round of up to 256 workgroups (t1); the forms that fit two workgroups to a CU: per 256 of more (t2)
   struct Form { MidKernel kernel; int fm; double t1, t2; };
-  static const Form forms[] = {
+  const Form forms[] = {
       {MID_WREG, 8, 1.46, 0}, {MID_WREG, 7, 1.27, 0}, {MID_WREG, 6, 1.12, 0}, {MID_WREG, 5, 0.99, 0}, {MID_WREG, 4, 0.89, 0},
       {MID_PACKED, 3, 0.82, 0.73}, {MID_PACKED, 2, 0.76, 0.66},
-      {MID_ROWS, 5, 1.45, 0}, {MID_ROWS, 4, 1.33, 0}, {MID_ROWS, 3, 1.27, 0}, {MID_ROWS, 2, 1.20, 0.76}};
+      {MID_ROWS, 5, 1.45, 0}, {MID_ROWS, 4, 1.33, 0}, {MID_ROWS, 3, 1.27, 0}, {MID_ROWS, 2, 1.20, p.partial ? 0.76 : 0.92}};   // (the last: 0.80 to 0.92 over a whole long K)
   // epilogue of a 256-row tile
   const double epi_us = norm_out ? 25 : epi == EPI_RESID || epi == EPI_QKV ? 12 : epi == EPI_KV ? 10 : 4;
   // Beyond 24 rounds of the full height an uneven last one is under 4 %, less than the lower heights lose in a run that long
@@ -384,10 +384,18 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
       if (best.kernel == MID_NONE || cost < best.cost) best = MidPlan{f.kernel, f.fm, s, steps, cost};
     }
   }
-  // row-major, many columns: the 128 x 128 tile (two workgroups per CU, no K split) keeps up
+  // Row-major weights also have the 128 x 128 tile of gemm.hip (no K splits).  With scratch for splits it keeps up only
+  // over many columns.  Without, it is the better one nearly everywhere: a lone workgroup on a CU takes 1.03 us per step,
+  // the forms above 1.2 and more, two on one CU 1.31 (us, forms above -> tile: 128 x 8192 x 8192 155 -> 137, 333 x 11008 x
+  // 4096 93 -> 78, 1023 x 4096 x 11008 203 -> 179), unless its last round is nearly empty (700 x 11008 x 4096 103 against 138).
   if (!packed && best.kernel != MID_NONE) {
-    const int64_t tiles = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128);
-    if (tiles >= 384 && 10 + (double)((tiles + 511) / 512) * all_steps * 1.22 < best.cost) best.kernel = MID_NONE;
+    const int64_t tiles = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128), last = tiles % 512;
+    if (p.partial) {
+      if (tiles >= 384 && 10 + (double)((tiles + 511) / 512) * all_steps * 1.22 < best.cost) best.kernel = MID_NONE;
+    } else {
+      const double rounds = 1.31 * (tiles / 512) + (last == 0 ? 0 : 1.03 + 0.28 * std::max<int64_t>(0, last - 256) / 256);
+      if (8 + all_steps * rounds < 1.03 * best.cost) best.kernel = MID_NONE;
+    }
   }
   return best;
 }

@@ -21,3 +21,22 @@ def test_packed_loop_beyond_4_gib_of_activations(epilogue, M, N, K):
         for consumer_adds in (False, True):
             plan = B.op_gemm_plan(epilogue, M, N, K, packed=True, norm_out=norm_out, consumer_adds=consumer_adds)
             assert (plan.kernel, plan.tile, plan.n_splits) == ("packed_dma", 256, 1)
+
+
+# Row-major weights and no room for K splits (swiftkv_op_gemm): the 128 x 128 tile, but for shapes whose last round of its
+# tiles is nearly empty (6 x 86 = 512 + 4, 8 x 80 = 512 + 128, 2 x 1002 = 3 x 512 + 468 tiles).
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (81, 4096, 4096, "tile_128"), (128, 8192, 8192, "tile_128"), (160, 8192, 8192, "tile_128"), (333, 11008, 4096, "tile_128"),
+    (420, 10240, 8192, "tile_128"), (512, 4096, 14336, "tile_128"), (700, 6144, 4096, "tile_128"), (1023, 4096, 11008, "tile_128"),
+    (1023, 512, 4096, "tile_128"), (700, 11008, 4096, "rows_reg"), (900, 10240, 8192, "rows_reg"), (160, 128256, 4096, "rows_reg")])
+def test_row_major_products_without_scratch(M, N, K, kernel):
+    for epilogue in ("bf16", "f32"):
+        plan = B.op_gemm_plan(epilogue, M, N, K, scratch=0)
+        assert (plan.kernel, plan.n_splits) == (kernel, 1)
+
+
+# ... and with it: K splits, which fill the CUs
+@pytest.mark.parametrize("M,N,K", [(81, 4096, 4096), (160, 4096, 14336), (333, 8192, 2048)])
+def test_row_major_products_with_scratch_split_k(M, N, K):
+    plan = B.op_gemm_plan("resid", M, N, K, consumer_adds=True)
+    assert plan.kernel == "rows_reg" and plan.n_splits > 1
