@@ -40,3 +40,11 @@ def test_row_major_products_without_scratch(M, N, K, kernel):
 def test_row_major_products_with_scratch_split_k(M, N, K):
     plan = B.op_gemm_plan("resid", M, N, K, consumer_adds=True)
     assert plan.kernel == "rows_reg" and plan.n_splits > 1
+
+
+@pytest.mark.parametrize("M,slice_", [(33, 512), (64, 512), (65, 256), (80, 256)])
+@pytest.mark.parametrize("N,K", [(2048, 2048), (4096, 4096), (13824, 5120), (8192, 28672)])
+def test_slices_of_33_to_80_rows(M, slice_, N, K):
+    for epilogue, adds in (("bf16", False), ("f32", True), ("swiglu", False)):
+        plan = B.op_gemm_plan(epilogue, M, N, K, consumer_adds=adds)
+        assert (plan.kernel, plan.slice) == ("stream_seq", slice_)
