@@ -431,10 +431,10 @@ SeqPlan plan_seq(int M, int N, int K, int nw, bool consumer_sums, size_t partial
     if (nw == 2 && nbw * waves > 8) continue;               // (two weights: register budget of the instantiations below)
     const int n_cg = (nblocks + waves * nbw - 1) / (waves * nbw);
     for (int ks_steps = 16; ks_steps >= 8; ks_steps /= 2) {
-      // 2 x 48 to 64 KB of LDS, at 65 to 80 rows 2 x 40: slices of 512 columns there (2 x 80 KB) gain up to 3 % where the
-      // weights are large (2 x 28672 x 8192 198 -> 197 us) and lose 5 to 15 where they are not, or where a workgroup's K range
-      // is no whole number of them (80 rows: 2048 x 2048 12.1 -> 13.3, 13824 x 5120 47.5 -> 52.4, 8192 x 3072 22.8 -> 24.9)
-      if (!few && ks_steps != (MB <= 4 ? 16 : 8)) continue;
+      // 2 x 48 to 64 KB of LDS; at 65 to 80 rows 2 x 40, where the weights are large 2 x 80 (us per call with 256 / 512
+      // columns, 80 rows: 2048 x 2048 12.1 / 13.3, 8192 x 3072 22.7 / 24.9, 13824 x 5120 47.6 / 52.4, but 8192 x 28672 120.6 /
+      // 113.3; 228 products of 2 to 940 MB: from 430 MB on 512 columns are 1 % slower to 8 % faster)
+      if (!few && ks_steps != (MB <= 4 || w_bytes >= 4.3e8 ? 16 : 8)) continue;
       const int all_slices = K / (32 * ks_steps);
       const size_t lds = (size_t)2 * ks_steps * MB * 1024;
       for (int want = 1; want <= std::min(SKINNY_MAX_SPLIT, all_slices); ++want) {

@@ -43,8 +43,9 @@ def test_row_major_products_with_scratch_split_k(M, N, K):
 
 
 @pytest.mark.parametrize("M,slice_", [(33, 512), (64, 512), (65, 256), (80, 256)])
-@pytest.mark.parametrize("N,K", [(2048, 2048), (4096, 4096), (13824, 5120), (8192, 28672)])
+@pytest.mark.parametrize("N,K", [(2048, 2048), (4096, 4096), (13824, 5120), (20480, 10240)])
 def test_slices_of_33_to_80_rows(M, slice_, N, K):
-    for epilogue, adds in (("bf16", False), ("f32", True), ("swiglu", False)):
+    for epilogue, adds, weights in (("bf16", False, 1), ("f32", True, 1), ("swiglu", False, 2)):
         plan = B.op_gemm_plan(epilogue, M, N, K, consumer_adds=adds)
-        assert (plan.kernel, plan.slice) == ("stream_seq", slice_)
+        large = 2 * weights * N * K >= 430e6          # at 65 to 80 rows too, the longer slices are ahead
+        assert (plan.kernel, plan.slice) == ("stream_seq", 512 if large else slice_)

@@ -27,6 +27,20 @@ def test_rows_gemm_at_the_edges(M, N, K):
         assert rel_err(B.op_gemm_rows(A.cuda(), W, out_f32=out_f32).cpu(), ref) <= tol
 
 
+@pytest.mark.parametrize("M", [65, 80])
+def test_long_slices_of_large_weights(M):
+    """65 to 80 rows over weights of 430 MB and more: two 80 KB activation buffers, all of a CU's LDS."""
+    from paper_2410_03960_amd import binding as B
+    N, K = 8192, 26624
+    for f32 in (True, False):
+        assert B.op_gemm_plan("f32" if f32 else "bf16", M, N, K)[::3] == ("stream_seq", 512)
+    A = WL.seeded_normal_bf16(1, f"A{M}{K}", (M, K), 0.0, 1.0, device="cuda")
+    W = WL.seeded_normal_bf16(2, f"W{N}{K}", (N, K), 0.0, 0.05, device="cuda")
+    ref = torch.cat([A.double() @ w.double().T.contiguous() for w in W.split(1024)], 1)
+    for out_f32, tol in ((True, 1e-5), (False, 4e-3)):     # fp32 sums of exact products / one bf16 rounding
+        assert rel_err(B.op_gemm_rows(A, W, out_f32=out_f32), ref) <= tol
+
+
 @pytest.fixture(scope="module")
 def wide_mlp():
     wl = Workload("wide_mlp", ModelShape(2, 512, 4, 2, 128, 13136, 512, 1e4, 1e-5), l=1, g=1, seed=2310)   # 821 column blocks
