@@ -15,14 +15,16 @@
 // partial sums and a second small kernel (or the consumer of the result) adds
 // them in a fixed order and applies the epilogue (deterministic, unlike atomic
 // accumulation).
-// Three kernels: skinny_kernel (above; any K % 8 == 0, activations from L2),
-// skinny_seq_kernel (K % 512 == 0: slices of K walked in sequence, the activation
-// slice double-buffered in LDS by a producer wave) and skinny_res_kernel (the
-// SwiGLU pair for up to 8 rows: all activation rows resident in LDS).
+// Four kernels: skinny_kernel (above; any K % 8 == 0, activations from L2),
+// skinny_lds_kernel (one weight, up to 32 rows, K % 512 == 0: a workgroup's one slice
+// of K in LDS), skinny_seq_kernel (K % 512 == 0: slices of K walked in sequence, the
+// activation slice double-buffered in LDS by a producer wave) and skinny_res_kernel
+// (the SwiGLU pair for up to 8 rows: all activation rows resident in LDS).
 #include "../../include/swiftkv.h"
 #include "common.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace {
 
@@ -169,6 +171,108 @@ __global__ void skinny_reduce_kernel(SkinnyParams p, int ksplit) {
 
 __device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory");
+}
+
+// ---------------------------------------------------------------------------
+// One K slice per workgroup (one weight, no row-block table, up to 32 rows, K % 512 == 0): the slice's activations sit in LDS in MFMA operand
+// order (filled by LDS-DMA, one 1 KB fragment per request: lane (row l16, quarter kq) lands at 16 * lane), the
+// waves split the output columns (16-column blocks, `nbw` in a row per wave) and stream their weight rows through
+// registers two groups of U k steps ahead, both steps of a 128-byte line in the same wave.  No cross-wave
+// reduction and no barrier after the fill.  K slices go to blockIdx.y and meet in skinny_reduce_kernel in a fixed
+// order.  Against skinny_seq_kernel, whose workgroups walk their slices in sequence: no barrier in
+// the stream and longer load groups, but a slice is a split, so more partial sums (us per call, this form /
+// skinny_seq_kernel at its best shape: 1 row 28672 x 8192 90 / 101, 24 rows 5120 x 5120 17.7 / 20.2, but 12 rows 5120 x
+// 13824 41 / 32).
+constexpr int LDS_WAVES = 8;
+template <int MB, int EPI>
+__global__ __launch_bounds__(LDS_WAVES * 64) void skinny_lds_kernel(SkinnyParams p, int ks_steps, int nbw) {
+  constexpr int U = 8;                                     // k steps (of 32) per group of loads
+  extern __shared__ __align__(16) unsigned char a_lds[];   // [k step][MB][64 lanes][16 bytes]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int all_steps = p.K / 32;
+  const int s_begin = blockIdx.y * ks_steps;
+  const int steps = (all_steps - s_begin) < ks_steps ? (all_steps - s_begin) : ks_steps;   // a multiple of 2U
+  const int k0 = s_begin * 32;
+  const int groups = steps / U;
+
+  const int nblocks = p.N / 16;
+  const int nb0 = (blockIdx.x * LDS_WAVES + wave) * nbw;
+  const int nb_end = (nb0 + nbw) < nblocks ? (nb0 + nbw) : nblocks;
+  const int total = nb0 < nblocks ? (nb_end - nb0) * groups : 0;   // groups of this wave, an even number
+
+  // weight rows of this lane: group g of column block nb covers k steps g * U ...; the groups of a wave's
+  // blocks are walked in order, (l_nb, l_g) being the next one to request
+  int l_nb = nb0, l_g = 0;
+  auto load_group = [&](uint4 (&dst)[U]) {
+    const int64_t koff = k0 + l_g * (U * 32) + kq * 8;
+    const bf16_t *src = p.W + ((int64_t)(l_nb * 16 + l16) * p.K + koff);
+    if (++l_g == groups) { l_g = 0; ++l_nb; }
+#pragma unroll
+    for (int u = 0; u < U; ++u) dst[u] = *(const uint4 *)(src + u * 32);
+  };
+  uint4 wa[U], wb[U];
+  if (total > 0) load_group(wa);   // on its way while the activations arrive
+
+  // activation slice -> LDS: fragment (k step s, row block mb) at (s * MB + mb) * 1024; rows past M repeat row M-1
+  {
+    typedef __attribute__((address_space(3))) void *lds_ptr_t;
+    const unsigned lds_base = (unsigned)(size_t)(lds_ptr_t)a_lds;
+    for (int f = wave; f < steps * MB; f += LDS_WAVES) {
+      const int s = f / MB, mb = f % MB;
+      int m = mb * 16 + l16;
+      m = m < p.M ? m : p.M - 1;
+      lds_dma16(p.A + ((int64_t)m * p.K + k0 + s * 32 + kq * 8), lds_base + f * 1024);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    __syncthreads();
+  }
+  if (total == 0) return;
+
+  floatx4 acc[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto compute_group = [&](const uint4 (&src)[U], int g) {
+    const unsigned char *fr = a_lds + (size_t)(g * U) * (MB * 1024) + lane * 16;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+        acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, src[u]), *(const bf16x8 *)(fr + (u * MB + mb) * 1024), acc[mb], 0, 0, 0);
+  };
+  // acc[mb][v] = C[m = mb*16 + l16][n = nb*16 + 4*kq + v] over this K slice
+  auto flush = [&](int nb) {
+    const int n = nb * 16 + 4 * kq;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const int m = mb * 16 + l16;
+      if (m < p.M) {
+        if (gridDim.y > 1) {   // partial[split][m][n]
+          *(float4 *)(p.partial + ((int64_t)blockIdx.y * p.M + m) * p.N + n) = make_float4(acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]);
+        } else if constexpr (EPI == EPI_STORE_F32) {
+          *(float4 *)((float *)p.C + (int64_t)m * p.N + n) = make_float4(acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]);
+        } else if constexpr (EPI == EPI_RESID) {
+          float4 *dst = (float4 *)((float *)p.C + (int64_t)m * p.N + n);
+          const float4 r = *dst;
+          *dst = make_float4(r.x + acc[mb][0], r.y + acc[mb][1], r.z + acc[mb][2], r.w + acc[mb][3]);
+        } else {
+          *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(acc[mb][0], acc[mb][1]), pack_bf16x2(acc[mb][2], acc[mb][3]));
+        }
+      }
+      acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  // two groups per iteration, one register set in flight while the other is consumed; `groups` is even, so
+  // a block ends after the second group of an iteration
+  int c_nb = nb0, c_g = 0;
+  for (int idx = 0; idx < total; idx += 2) {
+    load_group(wb);
+    compute_group(wa, c_g);
+    if (idx + 2 < total) load_group(wa);
+    compute_group(wb, c_g + 1);
+    c_g += 2;
+    if (c_g == groups) { flush(c_nb); ++c_nb; c_g = 0; }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -399,11 +503,43 @@ __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_seq_kernel(SkinnyPara
   }
 }
 
+struct LdsPlan {
+  bool ok;
+  int ks_steps, ksplit, nbw;
+  size_t lds_bytes, partial_bytes;
+  double cost;   // as SeqPlan's
+};
+// How skinny_lds_kernel would run this shape (up to 32 rows), with slices of up to 2048 columns of K (1024 beyond 16 rows) or
+// of 1024 where those leave one workgroup to a CU (16 rows x 8192 x 8192 33 us -> 28 with 512 workgroups).  ok = false: it
+// cannot, has fewer than 1024 (column block, K slice) pairs, where the first kernel, whose workgroups split K among their
+// waves, keeps more CUs busy, or weights beyond 500 MB (28672 x 8192, 470 MB, is ahead; 24 rows x 128256 x 4096, 1050 MB, 238
+// us against 187 of skinny_seq_kernel).
+LdsPlan plan_lds(int M, int N, int K, size_t partial_cap) {
+  LdsPlan best{};
+  if (M < 1 || M > 32 || (N % 16) != 0 || (K % 512) != 0 || 2.0 * N * K > 0.5e9) return best;
+  const int MB = (M + 15) / 16, all_steps = K / 32, nblocks = N / 16;
+  const int even = (all_steps + 64 / MB - 1) / (64 / MB);   // slices of at most 64 KB of LDS, of one length
+  const int lengths[2] = {((all_steps + even - 1) / even + 15) / 16 * 16, MB == 1 && all_steps % 32 == 0 ? 32 : 0};
+  if ((int64_t)nblocks * ((all_steps + lengths[0] - 1) / lengths[0]) < 1024) return best;
+  for (const int ks_steps : lengths) {
+    if (ks_steps == 0) continue;
+    const int ksplit = (all_steps + ks_steps - 1) / ks_steps;
+    const size_t partial = ksplit > 1 ? (size_t)ksplit * M * N * 4 : 0;
+    if (partial > partial_cap || ksplit > SKINNY_MAX_SPLIT) continue;
+    const int nbw = (int64_t)nblocks * ksplit >= 3200 ? 2 : 1;   // pairs a wave takes in a row
+    const int64_t n_cg = (nblocks + LDS_WAVES * nbw - 1) / (LDS_WAVES * nbw), wgs = n_cg * ksplit;
+    const double uneven = (double)((wgs + 255) / 256) * 256 / (double)wgs - 1;
+    const double cost = (2.0 * N * K + 0.49 * n_cg * M * K * 2 + 1.9 * partial + (ksplit > 1 ? 11e6 : 0)) * (1 + 0.49 * uneven) * (MB == 1 ? 0.873 : 0.84);
+    if (!best.ok || cost < best.cost) best = LdsPlan{true, ks_steps, ksplit, nbw, (size_t)ks_steps * MB * 1024, partial, cost};
+  }
+  return best;
+}
+
 struct SeqPlan {
   bool ok;
   int waves, nbw, ks_steps, n_slices, ksplit;
   size_t lds_bytes, partial_bytes;
-  int64_t wgs;
+  double cost;   // bytes at the streaming rate
 };
 // Shape of the launch: column blocks per workgroup (waves x nbw), slice length and K ranges, chosen by the bytes that
 // move besides the weights -- every workgroup fetches the activation rows of its K range from L2 (n_cg * M * K * 2
@@ -411,7 +547,9 @@ struct SeqPlan {
 // ksplit * nw * M * N * 4 bytes) and, for the epilogues that cannot leave the sum to their consumer, need a second
 // launch.  Beyond 32 rows the two activation buffers take most of LDS, one workgroup runs per CU, and what counts is
 // how evenly the workgroups fill whole rounds of 256.  Up to 32 rows several fit, and what counts is the bytes in
-// flight per CU (two load groups per consumer wave): below 64 KB the stream slows down.
+// flight per CU (two load groups per consumer wave): below 64 KB the stream slows down.  Where the consumer adds the splits
+// (Q/K/V, O, down and the fused K/V projection of a prefill), each one also lengthens the pass that adds them, about 0.25 us;
+// the terms' larger weights there stand for that.
 // Measured, us per call (before -> this form): 64 rows: 128256 x 4096 296 -> 196, 28672 x 4096 64.4 -> 61.2 and no second
 // launch, 4096 x 4096 18.0 -> 16.5, 4096 x 14336 36.8 -> 36.8; 24 rows: 2 x 28672 x 8192 233 -> 171, 128256 x 4096 285 ->
 // 184, 8192 x 28672 101 -> 93, 4096 x 14336 26.4 -> 28.0; 1 row: 6144 x 4096 14.3 -> 11.7, 8192 x 28672 90 -> 82,
@@ -421,8 +559,11 @@ SeqPlan plan_seq(int M, int N, int K, int nw, bool consumer_sums, size_t partial
   if (M < 1 || M > 80 || (N % 16) != 0 || (K % 512) != 0) return best;
   const int MB = (M + 15) / 16, nblocks = N / 16;
   const bool few = M <= 32;
+  // up to 16 rows, where skinny_lds_kernel has too few (column block, K slice) pairs: no second launch (4096 x 4096 in bf16, 1
+  // row: 13.0 us against 9.9 of the first kernel)
+  const bool one_launch = M <= 16 && !consumer_sums && (nw == 2 || !plan_lds(M, N, K, partial_cap).ok);
   const double w_bytes = 2.0 * nw * N * K;
-  double best_cost = 0;
+  int64_t best_wgs = 0;
   // The first of equals wins: beyond 32 rows eight waves with a block each are ahead of four with two (64 rows x 6144 x
   // 4096 18.0 us against 19.0, 4096 x 4096 13.0 / 13.7), four waves with four blocks of eight with two (8192 x 8192 33.4 / 35.3).
   static const int shapes[][2] = {{8, 1}, {4, 1}, {4, 2}, {4, 4}, {8, 1}, {8, 2}, {8, 4}};
@@ -444,30 +585,33 @@ SeqPlan plan_seq(int M, int N, int K, int nw, bool consumer_sums, size_t partial
         const int64_t wgs = (int64_t)n_cg * ksplit;
         const size_t partial = ksplit > 1 ? (size_t)ksplit * nw * M * N * 4 : 0;
         if (partial > partial_cap) continue;
-        const double a_bytes = 0.75 * (double)n_cg * M * K * 2, p_bytes = 2.0 * partial;   // (L2 hits: cheaper than the partial sums' trip to memory)
-        const double second = (ksplit > 1 && !consumer_sums) ? 25e6 : 0;   // a launch, in bytes at the streaming rate
+        const double a_bytes = (double)n_cg * M * K * 2;
+        const bool second = ksplit > 1 && !consumer_sums;   // a launch, below in bytes at the streaming rate
         const int64_t n_rounds = (wgs + 255) / 256;
-        double factor;
+        const double uneven = (double)n_rounds * 256 / (double)wgs - 1;
+        double cost;
         if (few) {
-          const int resident = (int)std::min<int64_t>(n_rounds, (160 << 10) / lds);
-          const double in_flight = (double)resident * waves * (nbw * nw == 1 ? 8 : 16);   // KB per CU
-          factor = (1 + 0.3 * ((double)n_rounds * 256 / (double)wgs - 1)) * (1 + 0.35 * std::max(0.0, 1 - in_flight / 64));
-        } else {
-          factor = (double)n_rounds * 256.0 / (double)wgs * (1.0 + 0.15 * (double)(n_rounds - 1));   // every further round pays its own fill and uneven end
+          if (!consumer_sums && (wgs < 192 || (second && one_launch))) continue;
+          // (resident: by LDS and by the registers of the instantiations)
+          const int per_simd = nbw * nw == 1 ? 8 : nbw * nw == 4 || (nw == 1 && MB == 2) ? 4 : 5;
+          const int64_t fit = (160 << 10) / lds, resident = std::max<int64_t>(1, std::min<int64_t>(fit, 4 * per_simd / (waves + 1)));
+          const double in_flight = (double)std::min(n_rounds, consumer_sums ? fit : resident) * waves * (nbw * nw == 1 ? 8 : 16);   // KB per CU
+          cost = consumer_sums ? (w_bytes + 0.75 * a_bytes + 2.0 * partial) * (1 + 0.3 * uneven) * (1 + 0.35 * std::max(0.0, 1 - in_flight / 64))
+                               : (w_bytes + 0.26 * a_bytes + 1.9 * partial + (second ? 11e6 : 0)) * (1 + 0.31 * uneven) * (1 + 0.19 * std::max(0.0, 1 - in_flight / 52)) +
+                                     0.06e6 * n_slices * ((n_rounds + resident - 1) / resident);
+        } else {   // L2 hits: cheaper than the partial sums' trip to memory; every further round pays its own fill and uneven end
+          cost = (w_bytes + 0.75 * a_bytes + 2.0 * partial + (second ? 25e6 : 0)) * (1 + uneven) * (1.0 + 0.15 * (double)(n_rounds - 1));
         }
-        const double cost = (w_bytes + a_bytes + p_bytes + second) * factor;
-        if (!best.ok || cost < best_cost) {
-          best_cost = cost;
-          best = SeqPlan{true, waves, nbw, ks_steps, n_slices, ksplit, lds, partial};
-          best.wgs = wgs;
+        if (!best.ok || cost < best.cost) {
+          best = SeqPlan{true, waves, nbw, ks_steps, n_slices, ksplit, lds, partial, cost};
+          best_wgs = wgs;
         }
       }
     }
   }
-  // Up to 32 rows the first kernel, which splits K among the waves of a workgroup, is ahead where this one has too few
-  // workgroups (2048 x 2048, 1 row: 6.5 us against 5.5), and up to 16 where it needs a second launch (4096 x 4096
-  // in bf16, 1 row: 13.0 against 9.9; 8192 x 4096 22 against 15.5).
-  if (few && (best.wgs < 192 || (M <= 16 && best.ksplit > 1 && !consumer_sums))) best.ok = false;
+  // too few workgroups: the first kernel is ahead, which splits K among the waves of a workgroup (2048 x 2048, 1 row: 6.5 us
+  // against 5.5)
+  if (few && best_wgs < 192) best.ok = false;
   return best;
 }
 template <int MB, int EPI, int WAVES, int NBW>
@@ -519,6 +663,36 @@ int launch_seq(const SkinnyParams &p, int epi, const SeqPlan &pl, hipStream_t st
   }
 }
 
+template <int MB, int EPI>
+int launch_lds_k(const SkinnyParams &p, const LdsPlan &pl, hipStream_t st) {
+  auto kern = skinny_lds_kernel<MB, EPI>;
+  static bool attr = false;
+  if (!attr) {
+    if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024) != hipSuccess) return -1;   // the longest slices
+    attr = true;
+  }
+  const int nblocks = p.N / 16;
+  dim3 grid((nblocks + LDS_WAVES * pl.nbw - 1) / (LDS_WAVES * pl.nbw), pl.ksplit);
+  hipLaunchKernelGGL(kern, grid, dim3(LDS_WAVES * 64), pl.lds_bytes, st, p, pl.ks_steps, pl.nbw);
+  if (pl.ksplit > 1) {
+    const int64_t quads = (int64_t)p.M * p.N / 4;
+    hipLaunchKernelGGL((skinny_reduce_kernel<EPI>), dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p, pl.ksplit);
+  }
+  return 0;
+}
+template <int EPI>
+int launch_lds_e(const SkinnyParams &p, const LdsPlan &pl, hipStream_t st) {
+  return p.M <= 16 ? launch_lds_k<1, EPI>(p, pl, st) : launch_lds_k<2, EPI>(p, pl, st);
+}
+int launch_lds(const SkinnyParams &p, int epi, const LdsPlan &pl, hipStream_t st) {   // never with n_splits_out
+  switch (epi) {
+    case EPI_STORE_BF16: return launch_lds_e<EPI_STORE_BF16>(p, pl, st);
+    case EPI_STORE_F32: return launch_lds_e<EPI_STORE_F32>(p, pl, st);
+    case EPI_RESID: return launch_lds_e<EPI_RESID>(p, pl, st);
+  }
+  return -1;
+}
+
 // The first kernel's shape: column blocks of a workgroup (two weight matrices count double: at most four weight-row
 // blocks), and K splits where the column tiles of more than 32 rows leave CUs idle, each of at least 16 k steps per wave.
 int first_blocks(const SkinnyParams &p, int epi) {
@@ -566,15 +740,50 @@ int launch_wide(const SkinnyParams &p, int epi, hipStream_t st) {
   return launch_mb<MB, 1>(p, epi, st);
 }
 
+// Which kernel runs this shape.  Up to 32 rows, where the result is final, three of them compete by the bytes they move at
+// the streaming rate: the weights, a share of the activation rows' way from L2, the partial sums' trip to memory, a second
+// launch; times what an uneven last round costs.  The terms' weights are fitted to the times of 565 products (2 to 940 MB of
+// weights, 1 to 32 rows, one weight or two).  us per call, skinny_lds_kernel wherever it has enough pairs and the first kernel
+// elsewhere / skinny_seq_kernel wherever it needs no second launch (up to 16 rows) or at all / this choice: 16 rows 13824 x
+// 5120 37 / 51 / 33, 14336 x 4096 30 / 36 / 26, 8192 x 28672 105 / 129 / 105, 1 row 28672 x 8192 93 / 103 / 91, 24 rows 11008 x
+// 4096 28 / 37 / 28; over 490 products of 1 to 32 rows 6 % ahead of the first and 4 % of the second rule, behind the first by
+// more than 3 % only at 32000 x 2048 in fp32 (28.1 -> 29.0).  Two weights: without skinny_lds_kernel, which is nowhere ahead by
+// more than 5 % there.
+struct SkinnyRoute {
+  int kernel;   // SWIFTKV_GEMM_STREAM_*
+  SeqPlan seq;
+  LdsPlan lds;
+};
+SkinnyRoute plan_skinny(const SkinnyParams &p, int epi) {
+  SkinnyRoute r{};
+  if (res_fits(p, epi)) { r.kernel = SWIFTKV_GEMM_STREAM_RESIDENT; return r; }
+  const int nw = epi == EPI_SWIGLU ? 2 : 1;
+  const bool adds = p.n_splits_out != nullptr;
+  const size_t cap = p.partial ? p.partial_bytes : 0;
+  r.seq = plan_seq(p.M, p.N, p.K, nw, adds, cap);
+  r.kernel = r.seq.ok ? SWIFTKV_GEMM_STREAM_SEQ : SWIFTKV_GEMM_STREAM_FIRST;
+  if (p.M > 32 || adds) return r;
+  const double wgs = p.N / (16.0 * first_blocks(p, epi));   // of the first kernel
+  const double first = (2.0 * nw * p.N * p.K + 0.68 * wgs * p.M * p.K * 2) * (1 + 0.88 * (std::ceil(wgs / 256) * 256 / wgs - 1)) * 0.913;
+  double best = first;
+  if (r.seq.ok && r.seq.cost < first) best = r.seq.cost;
+  else r.kernel = SWIFTKV_GEMM_STREAM_FIRST;
+  if (nw == 1 && !p.wtab) r.lds = plan_lds(p.M, p.N, p.K, cap);
+  if (r.lds.ok && r.lds.cost < best) r.kernel = SWIFTKV_GEMM_STREAM_SLICE;
+  return r;
+}
+
 }  // namespace
 
 GemmRoute route_skinny(const SkinnyParams &p, int epi) {
-  const int nw = epi == EPI_SWIGLU ? 2 : 1;
-  if (res_fits(p, epi)) return GemmRoute{SWIFTKV_GEMM_STREAM_RESIDENT, RES_WAVES, 1, 0};
-  const SeqPlan sq = plan_seq(p.M, p.N, p.K, nw, p.n_splits_out != nullptr, p.partial_bytes);
-  if (sq.ok) return GemmRoute{SWIFTKV_GEMM_STREAM_SEQ, sq.waves * sq.nbw, sq.ksplit, sq.ks_steps * 32};
+  const SkinnyRoute r = plan_skinny(p, epi);
   const int nb = first_blocks(p, epi);
-  return GemmRoute{SWIFTKV_GEMM_STREAM_FIRST, nb, first_splits(p, epi, nb), 0};
+  switch (r.kernel) {
+    case SWIFTKV_GEMM_STREAM_RESIDENT: return GemmRoute{r.kernel, RES_WAVES, 1, 0};
+    case SWIFTKV_GEMM_STREAM_SEQ: return GemmRoute{r.kernel, r.seq.waves * r.seq.nbw, r.seq.ksplit, r.seq.ks_steps * 32};
+    case SWIFTKV_GEMM_STREAM_SLICE: return GemmRoute{r.kernel, LDS_WAVES * r.lds.nbw, r.lds.ksplit, r.lds.ks_steps * 32};
+  }
+  return GemmRoute{r.kernel, nb, first_splits(p, epi, nb), 0};
 }
 int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0) return 0;
@@ -583,10 +792,11 @@ int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
     if (epi != EPI_STORE_F32 && epi != EPI_RESID) return -1;
     *p.n_splits_out = 1;
   }
-  if (res_fits(p, epi)) return launch_res(p, st);
-  {
-    const SeqPlan sq = plan_seq(p.M, p.N, p.K, epi == EPI_SWIGLU ? 2 : 1, p.n_splits_out != nullptr, p.partial ? p.partial_bytes : 0);
-    if (sq.ok) return launch_seq(p, epi, sq, st);
+  const SkinnyRoute r = plan_skinny(p, epi);
+  switch (r.kernel) {
+    case SWIFTKV_GEMM_STREAM_RESIDENT: return launch_res(p, st);
+    case SWIFTKV_GEMM_STREAM_SEQ: return launch_seq(p, epi, r.seq, st);
+    case SWIFTKV_GEMM_STREAM_SLICE: return launch_lds(p, epi, r.lds, st);
   }
   if (p.M <= 16) return launch_mb<1, 1>(p, epi, st);
   if (p.M <= 32) return first_blocks(p, epi) == 2 ? launch_mb<2, 2>(p, epi, st) : launch_mb<2, 1>(p, epi, st);

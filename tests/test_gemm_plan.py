@@ -49,3 +49,15 @@ def test_slices_of_33_to_80_rows(M, slice_, N, K):
         plan = B.op_gemm_plan(epilogue, M, N, K, consumer_adds=adds)
         large = 2 * weights * N * K >= 430e6          # at 65 to 80 rows too, the longer slices are ahead
         assert (plan.kernel, plan.slice) == ("stream_seq", 512 if large else slice_)
+
+
+# Up to 32 rows with a result that is final: shapes that the first kernel (16 rows x 13824 x 5120: 51 us) or one long walk of
+# slices (1 row x 28672 x 8192: 103 us) serves 10 to 50 % slower than the kernel named.
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (16, 13824, 5120, "stream_seq"), (16, 5120, 13824, "stream_seq"), (24, 11008, 4096, "stream_slice"), (32, 11008, 4096, "stream_slice"),
+    (16, 14336, 4096, "stream_slice"), (1, 28672, 8192, "stream_first"), (8, 28672, 8192, "stream_slice"), (1, 32000, 2048, "stream_slice"),
+    (16, 8192, 28672, "stream_slice"), (24, 5120, 5120, "stream_slice"),
+    (1, 4096, 4096, "stream_first"), (1, 8192, 2048, "stream_first"), (24, 128256, 4096, "stream_seq")])
+def test_final_results_of_up_to_32_rows(M, N, K, kernel):
+    plan = B.op_gemm_plan("bf16", M, N, K, scratch=16 * M * N * 4)
+    assert plan.kernel == kernel and (kernel != "stream_seq" or N > 100000 or plan.n_splits > 1)

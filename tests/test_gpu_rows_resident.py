@@ -1,7 +1,8 @@
-"""Weight-streaming GEMMs of up to 32 rows with the activations in LDS: one and two
-row blocks at their edges, ragged last workgroups, one to eight K ranges, the shapes
-beside the rule's line that keep the first form, and (through a decoder whose MLP is
-wide enough) the SwiGLU pair with all rows resident, up to its 8 rows and past them."""
+"""Weight-streaming GEMMs with the activations in LDS.  Up to 32 rows: one and two row
+blocks at their edges, ragged last workgroups, one to nine K ranges or slices, the
+shapes beside the rules' lines that keep another form, and (through a decoder whose
+MLP is wide enough) the SwiGLU pair with all rows resident, up to its 8 rows and past
+them; 65 to 80 rows: the longer slices of large weights."""
 import pytest
 import torch
 
@@ -25,6 +26,21 @@ def test_rows_gemm_at_the_edges(M, N, K):
     ref = A.double() @ W.cpu().double().T
     for out_f32, tol in ((True, 1e-5), (False, 4e-3)):     # fp32 sums of exact products / one bf16 rounding
         assert rel_err(B.op_gemm_rows(A.cuda(), W, out_f32=out_f32).cpu(), ref) <= tol
+
+
+# one slice of K per workgroup: a single one, several of one length, a shorter last one; one and two column blocks in a row
+# per wave; ragged and whole last workgroups; one and two row blocks at their edges
+@pytest.mark.parametrize("M,N,K,blocks,splits", [
+    (5, 16400, 512, 8, 1), (16, 16400, 1536, 8, 1), (1, 8208, 5120, 8, 3), (16, 10256, 8704, 16, 5), (8, 33024, 3072, 16, 3),
+    (17, 16400, 1024, 8, 1), (17, 8208, 2560, 8, 3), (32, 20496, 2560, 16, 3), (24, 33024, 3072, 16, 3), (31, 4112, 7168, 8, 7)])
+def test_one_slice_per_workgroup(M, N, K, blocks, splits):
+    from paper_2410_03960_amd import binding as B
+    A = WL.seeded_normal_bf16(1, f"A{M}{K}", (M, K), 0.0, 1.0, device="cuda")
+    W = WL.seeded_normal_bf16(2, f"W{N}{K}", (N, K), 0.0, 0.05, device="cuda")
+    ref = torch.cat([A.double() @ w.double().T.contiguous() for w in W.split(4096)], 1)
+    for out_f32, tol in ((True, 1e-5), (False, 4e-3)):     # fp32 sums of exact products / one bf16 rounding
+        assert B.op_gemm_plan("f32" if out_f32 else "bf16", M, N, K, scratch=16 * M * N * 4)[:3] == ("stream_slice", blocks, splits)
+        assert rel_err(B.op_gemm_rows(A, W, out_f32=out_f32), ref) <= tol
 
 
 @pytest.mark.parametrize("M", [65, 80])
