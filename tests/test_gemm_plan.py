@@ -4,6 +4,8 @@ import os
 import pytest
 
 from paper_2410_03960_amd import binding as B
+from tests import test_gpu_gemm_heights as H
+from tests import test_gpu_mid as MID
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -61,3 +63,37 @@ def test_slices_of_33_to_80_rows(M, slice_, N, K):
 def test_final_results_of_up_to_32_rows(M, N, K, kernel):
     plan = B.op_gemm_plan("bf16", M, N, K, scratch=16 * M * N * 4)
     assert plan.kernel == kernel and (kernel != "stream_seq" or N > 100000 or plan.n_splits > 1)
+
+
+# The GPU parity tests of the tiled kernels reach the kernels and heights that they are there for.
+def test_parity_cases_reach_every_packed_height():
+    for rows, tile in H.PACKED_HEIGHTS.items():
+        feed = H.planned(H.FEED, rows, True)
+        assert feed["feed"]
+        for plan in (feed["o"], feed["down"], *(H.planned(wl, rows, True)["kv"] for wl in H.KV.values())):
+            assert (plan.kernel, plan.tile, plan.n_splits) == ("packed_dma", tile, 1)
+    for rows, tile in H.BROAD_HEIGHTS.items():
+        for product in ("qkv", "swiglu"):
+            plan = H.planned(H.BROAD, rows, True)[product]
+            assert (plan.kernel, plan.tile, plan.n_splits) == ("packed_dma", tile, 1)
+    assert sorted(set(H.PACKED_HEIGHTS.values())) == sorted(set(H.BROAD_HEIGHTS.values())) == [128, 160, 192, 224, 256]
+
+
+def test_parity_cases_reach_every_row_major_height():
+    reached = set()
+    for (wl, lens), want in H.ROW_HEIGHTS.items():
+        plans = H.planned(wl, sum(lens), False)
+        for product, (tile, splits) in want.items():
+            plan = plans[product]
+            assert (plan.kernel, plan.tile, plan.n_splits) == ("rows_reg", tile, splits), (wl.name, sum(lens), product)
+            reached.add((tile, splits > 1))
+    assert reached == {(tile, split) for tile in (64, 96, 128, 160) for split in (False, True)}
+    assert B.op_gemm_plan("f32", 641, 11008, 512, scratch=0)[:3] == ("rows_reg", 160, 1)
+
+
+def test_parity_cases_of_the_mid_size_decoders():
+    for wl in MID.MID.values():
+        for product, plan in H.planned(wl, sum(MID.LENS), True).items():
+            assert product == "feed" or (plan.kernel, plan.tile) == ("packed_reg", 64)
+        for product, plan in H.planned(wl, sum(MID.LENS), False).items():
+            assert product == "feed" or plan.kernel == "five_stage"

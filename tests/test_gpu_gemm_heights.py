@@ -1,6 +1,9 @@
 """Parity of the GEMMs between the weight-streaming kernels (80 rows) and many
 full rounds of 256-row tiles: every tile height, K splits with each epilogue's
-finishing pass, ragged last tiles, packed and row-major weights."""
+finishing pass, ragged last tiles, packed and row-major weights.  Which kernel
+and height a case reaches is stated beside it (PACKED_HEIGHTS, ROW_HEIGHTS,
+BROAD_HEIGHTS) and checked against the library's plan without a GPU."""
+import functools
 import sys
 
 import pytest
@@ -20,6 +23,46 @@ LONG = {
 }
 # many output columns over a short contraction: the tile height follows the number of rows
 BROAD = Workload("broad", ModelShape(2, 256, 32, 8, 128, 3072, 256, 1e4, 1e-5), l=1, g=1, seed=2203)
+# Fragment-order weights.  FEED: O (K 512) and down (K 256) write 6144 residual columns each, unsplit, so they leave the next
+# projection's operand and the rows' sums of squares.  KV*: three groups of later layers, 6144 columns of K and V over a
+# contraction of 256, unsplit, so K and V leave through the epilogue (bf16 to their slots; FP8 staged, with the heads' absmax).
+FEED = Workload("feed", ModelShape(2, 6144, 4, 2, 128, 256, 256, 1e4, 1e-5), l=1, g=1, seed=2204)
+KV = {
+    "hd128": Workload("kv_hd128", ModelShape(4, 256, 8, 8, 128, 256, 256, 1e4, 1e-5), l=1, g=1, seed=2205),
+    "hd64": Workload("kv_hd64", ModelShape(4, 256, 16, 16, 64, 256, 256, 1e4, 1e-5), l=1, g=1, seed=2206),
+}
+PACKED_HEIGHTS = {1100: 128, 1300: 160, 1700: 192, 2000: 224, 2300: 256}      # rows -> tile of both models' products
+BROAD_HEIGHTS = {1025: 128, 1300: 160, 1700: 192, 2000: 224, 2300: 256, 2561: 128}   # ... of BROAD's Q/K/V and gate/up, unsplit
+# Row-major weights.  TALL splits K, SHORT does not (gate/up of 5632 columns and 6144 columns of K and V over 256).
+TALL = Workload("tall", ModelShape(2, 4096, 32, 8, 128, 3072, 512, 1e4, 1e-5), l=1, g=1, seed=2207)
+SHORT = Workload("short", ModelShape(4, 256, 8, 8, 128, 5632, 256, 1e4, 1e-5), l=1, g=1, seed=2208)
+# (model, tokens per sequence) -> {product: (rows of a tile, K splits)}; sequences of one token run the later layers on every row
+ROW_HEIGHTS = {
+    (TALL, (96,)): {"qkv": (96, 8), "swiglu": (96, 8), "o": (64, 8)},
+    (TALL, (1,) * 97): {"qkv": (128, 8), "swiglu": (128, 8), "o": (64, 8)},
+    (TALL, (1,) * 132): {"qkv": (160, 8), "swiglu": (160, 8), "o": (96, 8), "down": (96, 8), "kv": (96, 13)},
+    (TALL, (140, 67)): {"qkv": (128, 5), "swiglu": (128, 5), "o": (128, 8), "down": (128, 6)},
+    (TALL, (300,)): {"qkv": (160, 5), "swiglu": (160, 5), "o": (128, 5)},
+    (SHORT, (328,)): {"swiglu": (96, 1), "kv": (64, 1)},
+    (SHORT, (401, 89)): {"swiglu": (128, 1), "kv": (64, 1)},
+    (SHORT, (699, 1)): {"swiglu": (160, 1), "kv": (96, 1)},
+}
+
+
+def planned(wl, rows, packed):
+    """The library's choice for each product of the full layers, and for the later layers' K and V, over `rows` tokens."""
+    from paper_2410_03960_amd import binding as B
+    s, later = wl.shape, wl.shape.n_layers - wl.l
+    qd, kvd = s.n_q_heads * s.head_dim, s.n_kv_heads * s.head_dim
+
+    def of(epilogue, n, k, **kw):
+        return B.op_gemm_plan(epilogue, rows, n, k, packed=packed, head_dim=s.head_dim if epilogue in ("qkv", "kv") else 0, **kw)
+    d = s.hidden
+    # both residual products unsplit: they leave the next projection's operand, nobody adds splits
+    feed = packed and rows >= 1024 and all(of("resid", d, k, consumer_adds=True).n_splits == 1 for k in (qd, s.ffn))
+    resid = {"norm_out": True} if feed else {"consumer_adds": True}
+    return {"qkv": of("qkv", qd + 2 * kvd, d), "o": of("resid", d, qd, **resid), "swiglu": of("swiglu", s.ffn, d),
+            "down": of("resid", d, s.ffn, **resid), "kv": of("kv", (later + wl.g - 1) // wl.g * 2 * kvd, d), "feed": feed}
 
 
 def _say(msg):
@@ -27,9 +70,18 @@ def _say(msg):
     sys.stdout.flush()
 
 
+def _lens(rows, each=190):
+    return [each] * (rows // each) + ([rows % each] if rows % each else [])
+
+
+@functools.lru_cache(maxsize=1)
+def _weights(wl):
+    return WL.make_weights(wl, "cpu", keep=True)
+
+
 def _check(wl, lens, fp8, packed, ctx_lens=None):
     from paper_2410_03960_amd import binding as B
-    store = WL.make_weights(wl, "cpu", keep=True)
+    store = _weights(wl)
     ctx = B.Context(wl.shape, G.device_weights(store), wl.l, wl.g, packed_weights=packed)
     batch = WL.build_batch(wl, lens=lens, shuffled=True)
     mode = B.SWIFTKV_SCALE_COMPUTE_ABSMAX if fp8 else 0
@@ -52,18 +104,36 @@ def test_split_k_with_every_epilogue(name, packed, lens):
     _check(LONG[name], lens, fp8=lens == [200, 133], packed=packed)
 
 
-@pytest.mark.parametrize("rows", [1025, 1300, 2000, 2300, 2561])
+@pytest.mark.parametrize("rows", sorted(BROAD_HEIGHTS))
 def test_tile_heights_with_rotating_and_swiglu_epilogues(rows):
     _say(f"rows={rows}")
-    lens = [190] * (rows // 190) + ([rows % 190] if rows % 190 else [])
-    _check(BROAD, lens, fp8=rows == 2000, packed=True)
+    _check(BROAD, _lens(rows), fp8=rows == 2000, packed=True)
 
 
 @pytest.mark.parametrize("rows", [1025, 2561, 4500])
 def test_tile_heights_with_residual_epilogue(rows):
     _say(f"rows={rows}")
-    lens = [256] * (rows // 256) + ([rows % 256] if rows % 256 else [])
-    _check(LONG["hd128"], lens, fp8=False, packed=True)
+    _check(LONG["hd128"], _lens(rows, 256), fp8=False, packed=True)
+
+
+@pytest.mark.parametrize("rows", sorted(PACKED_HEIGHTS))
+def test_residual_epilogue_that_feeds_the_next_projection(rows):
+    _say(f"rows={rows}")
+    _check(FEED, _lens(rows), fp8=False, packed=True)
+
+
+@pytest.mark.parametrize("rows", sorted(PACKED_HEIGHTS))
+@pytest.mark.parametrize("name", sorted(KV))
+def test_unsplit_kv_epilogue(name, rows):
+    _say(f"{name} rows={rows}")
+    for fp8 in (False, True):
+        _check(KV[name], _lens(rows), fp8=fp8, packed=True)
+
+
+@pytest.mark.parametrize("wl,lens", sorted(ROW_HEIGHTS, key=str), ids=lambda v: v.name if isinstance(v, Workload) else f"{len(v)}x{sum(v)}")
+def test_row_major_tile_heights(wl, lens):
+    _say(f"{wl.name} lens={lens}")
+    _check(wl, list(lens), fp8=len(lens) == 2, packed=False)
 
 
 def test_many_continuing_rows():
@@ -83,8 +153,9 @@ def test_packed_gemm_at_every_tile_height(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [
-    (81, 192, 64), (96, 320, 192), (97, 256, 128), (129, 4096, 448), (161, 1088, 1024), (300, 2112, 64), (513, 640, 320), (1023, 64, 192), (160, 28672, 128)])
+    (81, 192, 64), (96, 320, 192), (97, 256, 128), (129, 4096, 448), (161, 1088, 1024), (300, 2112, 64), (513, 640, 320), (1023, 64, 192), (160, 28672, 128), (641, 11008, 512)])
 def test_row_major_gemm_between_81_and_1023_rows(M, N, K):
+    """swiftkv_op_gemm, which has no room for K splits: the 128 x 128 tile but for the last shape."""
     from paper_2410_03960_amd import binding as B
     _say(f"M={M} N={N} K={K}")
     A = WL.seeded_normal_bf16(1, f"A{M}{K}", (M, K), 0.0, 1.0)

@@ -1,8 +1,10 @@
 """Parity with the CPU oracle on two mid-size decoders whose dimensions are
-multiples of 256 and whose batches have more than 1024 tokens: the smallest
-cases that take the large-GEMM paths (fragment-order weights, 64-column wave
+multiples of 256 and whose batches have more than 1024 tokens: fragment-order
+weights in 64-row tiles with activations through registers (64-column wave
 tiles with RoPE inside a wave tile for head_dim 128 and 64, fused KV scatter,
-FP8 staging + absmax) and, with the minimal pack buffer, the LDS-staged loop."""
+FP8 staging + absmax, residual products with K splits) and, with the minimal
+pack buffer, the five-stage loop of 256 x 256 tiles over row-major weights.
+The taller tiles and the LDS-DMA loop: test_gpu_gemm_heights."""
 import sys
 
 import pytest

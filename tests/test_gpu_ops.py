@@ -26,10 +26,9 @@ def _rand_bf16(seed, name, shape, std=1.0):
     (3, 1, 16, 8), (3, 8, 1024, 256), (3, 16, 272, 688), (3, 17, 64, 96), (3, 65, 160, 1000),
     (3, 32, 96, 264), (3, 33, 192, 520), (3, 48, 80, 1000), (3, 49, 1056, 4096), (3, 64, 4096, 688), (3, 80, 144, 72),
     ("rows", 33, 192, 520), ("rows", 49, 1056, 4096), ("rows", 64, 4096, 1376), ("rows", 80, 1024, 4096), ("rows", 16, 1024, 4096),
-    # the forms with the activation slice resident in LDS (K % 512 == 0).  Up to 32 rows (one slice per workgroup, at
-    # least 1024 (column block, K slice) streams): one and several K slices, a ragged last workgroup, one and two
-    # blocks per wave.  Beyond 32 rows (slices walked in sequence behind a producer wave): 3..5 row blocks, one and
-    # several K ranges, 4 and 8 consumer waves with 1, 2 and 4 column blocks each, a ragged last column group
+    # up to 32 rows: K split among the waves, slices walked in sequence behind a producer wave, one slice per workgroup
+    # (their edges: test_gpu_rows_resident).  Beyond 32 rows, K % 512 == 0: slices in sequence, 3..5 row blocks, one and
+    # several K ranges, 4 and 8 consumer waves with 1 and 2 column blocks each, a ragged last column group
     ("rows", 1, 8192, 4096), ("rows", 7, 16384, 2048), ("rows", 8, 8208, 4096), ("rows", 17, 4096, 4096), ("rows", 16, 4096, 14336),
     ("rows", 40, 16384, 1024), ("rows", 64, 6144, 4096), ("rows", 64, 16384, 4096), ("rows", 80, 4096, 4096),
     ("rows", 64, 28672, 4096), ("rows", 48, 32064, 1024), ("rows", 33, 8208, 4096), ("rows", 72, 2048, 14336), ("rows", 64, 4096, 512),
