@@ -225,7 +225,8 @@ int swiftkv_export_hidden(swiftkv_ctx *ctx, const void *workspace, void *hidden_
  * stores fp32, else bf16.  variant: 0 = pick by shape, 1 = 256x256 tile with
  * register-staged loads, 2 = 128x128 tile, 3 = weight-streaming kernel for
  * M <= 80 rows without a K split, 14 / 15 = the five-stage direct-to-LDS loop
- * with 4 / 8 waves (what 0 picks for M >= 1024, K % 64 == 0).  All dev. */
+ * with 4 / 8 waves (what 0 picks for M >= 1024, K % 64 == 0; below, 2 or a loop
+ * of 64- to 160-row tiles, whichever is expected faster).  All dev. */
 int swiftkv_op_gemm(const void *A, const void *W, void *C, int32_t M, int32_t N, int32_t K,
                     int32_t out_f32, int32_t variant, void *stream);
 /* The same product (bf16 out) through the loop that takes the weights in matrix-
@@ -236,8 +237,8 @@ int swiftkv_op_gemm_packed(const void *A, const void *W, void *w_packed, void *C
                            int32_t N, int32_t K, void *stream);
 /* The weight-streaming kernels (M <= 80 rows: decode steps, the last-token tail)
  * with K split over up to 16 workgroups (slices of K whose activation rows a
- * workgroup keeps in LDS, or splits that keep all compute units streaming when
- * there are few column tiles); the splits' fp32 partial sums go through
+ * workgroup keeps in LDS, one or several in sequence, or splits that keep all
+ * compute units streaming when there are few column tiles); the splits' fp32 partial sums go through
  * `workspace` (dev, swiftkv_op_gemm_rows_workspace(M, N) bytes) and are added in
  * a fixed order. */
 int swiftkv_op_gemm_rows(const void *A, const void *W, void *C, int32_t M, int32_t N, int32_t K,
@@ -338,10 +339,11 @@ int swiftkv_flops(const swiftkv_ctx *ctx, const int32_t *seq_lens, const int32_t
  * decode step has ~450 launches); select only the class in question when the
  * call's own duration matters.  Classes:
  * 0 = QKV GEMM, 1 = O GEMM, 2 = gate/up GEMM, 3 = down GEMM (layers 1..l),
- * 4 = fused KV GEMM (Eq. 2), 5 = prefill attention, 6 = plan / embedding /
- * single-query attention of decode rows / gather, 7 = last-token tail,
- * 8 = RMSNorm and 1/rms kernels, 9 = KV commit (paged scatter, FP8 quantise,
- * V transpose).  ms_out / launches_out are host arrays of
+ * 4 = fused KV GEMM (Eq. 2), 5 = prefill attention, 6 = plan / single-query
+ * attention of decode rows / gather, 7 = last-token tail, 8 = RMSNorm and 1/rms
+ * kernels (the first one of a pass reads the embedding), 9 = KV commit (paged
+ * scatter, FP8 quantise, V transpose; of up to 80 decode rows alone, unless
+ * their scales are computed: part of 0).  ms_out / launches_out are host arrays of
  * SWIFTKV_N_TIME_CLASSES.  Reading waits for the last recorded event. */
 #define SWIFTKV_N_TIME_CLASSES 10
 #define SWIFTKV_TIME_ALL ((1 << SWIFTKV_N_TIME_CLASSES) - 1)

@@ -365,8 +365,8 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   // epilogue of a 256-row tile
   const double epi_us = norm_out ? 25 : epi == EPI_RESID || epi == EPI_QKV ? 12 : epi == EPI_KV ? 10 : 4;
   // Beyond 24 rounds of the full height an uneven last one is under 4 %, less than the lower heights lose in a run that long
-  // (more bytes per product on a power-limited chip; gate/up of 32832 rows: 1.34 us per step of 224 rows against 1.45 of
-  // 256, 6.02 ms per launch -> 5.85).
+  // (more bytes per product on a power-limited chip; gate/up of 32832 rows, a whole launch over its steps: 1.34 us per step
+  // of 224 rows against 1.45 of 256, where the table has 1.27 and 1.46; 6.02 ms per launch -> 5.85).
   const bool full = packed && ((int64_t)((p.M + 255) / 256) * tiles_n + 255) / 256 > 24;
   for (const Form &f : forms) {
     if ((f.kernel == MID_ROWS) == packed || (full && f.fm < 8) || (far && f.kernel != MID_WREG)) continue;

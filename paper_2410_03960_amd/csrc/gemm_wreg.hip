@@ -28,12 +28,12 @@ __device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_addr) {
 // N % 256 == 0.
 // The tile height FM and the K splits come from plan_gemm_mid.  What a step costs is the bytes a CU fetches
 // for it, through L2 and with a bounded number of requests in flight, against the MFMAs it hides them under:
-// 0.85 us at FM = 4 (48 KB, 128 rows), 1.12 at 6, 1.50 at 8 (64 KB, 256 rows) with all CUs busy, so a taller
+// 0.89 us at FM = 4 (48 KB, 128 rows), 1.12 at 6, 1.46 at 8 (64 KB, 256 rows) with all CUs busy, so a taller
 // tile is cheaper per row and a shorter one is taken where it fills a last round or leaves room for K splits.
 template <int EPI, int FM, bool NORM_OUT = false>
 __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
   constexpr int BM = 32 * FM, BN = 256;
-  constexpr int NSA = 5, STAGE = BM * 128;   // activation stages: 256 rows x 128 bytes (one 64-wide k step)
+  constexpr int NSA = 5, STAGE = BM * 128;   // activation stages: BM rows x 128 bytes (one 64-wide k step)
   extern __shared__ __align__(16) unsigned char smem[];
 
   const int tid = threadIdx.x;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
     dst = *(const bf16x8 *)(w_ptr[nb] + ((int64_t)step * 4 + kk) * 512);
   };
 
-  // prologue: steps 0, 1, 2 requested (16 requests per wave and step, activations and weights alternating)
+  // prologue: steps 0, 1, 2 requested (FM + 8 requests per wave and step, activations and weights alternating)
 #pragma unroll
   for (int s0 = 0; s0 < 3; ++s0) {
     const int step = s0 < nk ? s0 : nk - 1;
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
     for (int kk = 0; kk < 4; ++kk) {
       if (kk == 3) {
         // Step it+1 (requested during step it-2) must be resident before its first fragments are read.
-        // V1 LDS-DMA requests are younger than it (FM of step it-1, 3/4 FM of this step: 14 at FM = 8).  Register
+        // V1 LDS-DMA requests are younger than it (FM of step it-1, 3 FM / 4 of this step: 7, 8, 10, 12, 14 at FM = 4 .. 8).  Register
         // loads and LDS-DMA do not complete in one common order, so all V1 requests that may stay in flight
         // could be LDS-DMA ones: the wait is for V1 in total, not for V1 + the younger weight loads.
         constexpr int V1 = FM + 3 * FM / 4;
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);   // drain the clamped extra requests ...
   __builtin_amdgcn_s_barrier();         // ... of every wave, before LDS is reused by the epilogue
-  // per-wave slab: one 32-row block of fp32 (272-byte rows), or, for the rotating epilogues, all eight blocks of bf16 (144-byte rows)
+  // per-wave slab: one 32-row block of fp32 (272-byte rows), or, for the rotating epilogues, all FM blocks of bf16 (144-byte rows)
   unsigned char *slab = smem + wave * ((EPI == EPI_QKV || EPI == EPI_KV) ? FM * 32 * (64 * 2 + 16) : 32 * (64 * 4 + 16));
   gemm_epilogue_n64<EPI, FM, NORM_OUT>(p, acc, m0, n0, lane, slab, EPI == EPI_PARTIAL ? (int64_t)split * p.M * p.N : 0);
 }

@@ -279,8 +279,10 @@ __global__ __launch_bounds__(LDS_WAVES * 64) void skinny_lds_kernel(SkinnyParams
 // The SwiGLU pair for few rows: the M rows (not their padding to 16) are resident in LDS over the whole of K, row
 // after row with 64 bytes between them, lanes of columns past M read the last row.  A wave owns one column block of
 // both weights and walks K from end to end, two groups of eight 32-wide steps in flight; nothing is split, so there are
-// no partial sums and no second launch, and no slice boundary either.  Measured, us: 2 x 14336 x 4096 with 1 / 8 rows
-// 42.5 / 46.4 (5.5 TB/s with one), 46.3 for both with skinny_seq_kernel.
+// no partial sums and no second launch, and no slice boundary either.  us per launch with 1 / 2 / 4 / 8 rows, this kernel against
+// what plan_skinny takes without it: 2 x 14336 x 4096 44 / 45 / 46 / 49 (5.3 TB/s with one) against 53 / 56 / 56 / 51, 2 x 13824 x
+// 5120 50 / 50 / 51 / 54 against 58 / 59 / 60 / 61, 2 x 13312 x 8192 82 / 85 / 88 / 95 against 95 / 96 / 100 / 102.  Beyond: 12 rows
+// of 2 x 14336 x 4096 51 against 51, 16 rows 54 against 52.
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int RES_WAVES = 4;
 __global__ __launch_bounds__(RES_WAVES * 64) void skinny_res_kernel(SkinnyParams p, int stride) {
@@ -566,9 +568,10 @@ SeqPlan plan_seq(int M, int N, int K, int nw, bool consumer_sums, size_t partial
   int64_t best_wgs = 0;
   // The first of equals wins: beyond 32 rows eight waves with a block each are ahead of four with two (64 rows x 6144 x
   // 4096 18.0 us against 19.0, 4096 x 4096 13.0 / 13.7), four waves with four blocks of eight with two (8192 x 8192 33.4 / 35.3).
-  static const int shapes[][2] = {{8, 1}, {4, 1}, {4, 2}, {4, 4}, {8, 1}, {8, 2}, {8, 4}};
-  for (int i = few ? 1 : 0; i < 7; ++i) {
-    const int waves = shapes[i][0], nbw = shapes[i][1];
+  static const int few_shapes[6][2] = {{4, 1}, {4, 2}, {4, 4}, {8, 1}, {8, 2}, {8, 4}};
+  static const int many_shapes[6][2] = {{8, 1}, {4, 1}, {4, 2}, {4, 4}, {8, 2}, {8, 4}};
+  for (const auto &shape : few ? few_shapes : many_shapes) {
+    const int waves = shape[0], nbw = shape[1];
     if (nw == 2 && nbw * waves > 8) continue;               // (two weights: register budget of the instantiations below)
     const int n_cg = (nblocks + waves * nbw - 1) / (waves * nbw);
     for (int ks_steps = 16; ks_steps >= 8; ks_steps /= 2) {
