@@ -183,16 +183,20 @@ int check_launch(const char *what) {
 // 778 keys: 12 splits 9.6 us, 24 splits 8.6; 4 rows over 150: 2 splits 9.0, 5 splits 7.3).
 // Matrix-unit kernels: three workgroups per CU; a workgroup costs about 8 us besides its 128-key steps of 3.4 us, and
 // rows of one length run in whole rounds of 768 (64 rows x 8 heads over 2048 e4m3 keys: 1 split 62 us, 2 splits 67,
-// 3 splits 59; 160 rows over 900: 1 split 70, 2 splits 75).
-int pick_split(int rows, int n_kv_heads, int max_keys, int64_t sum_keys, bool matrix, int *min_keys) {
+// 3 splits 59; 160 rows over 900: 1 split 70, 2 splits 75).  With 64-wide heads four workgroups are resident per CU (us per
+// call by rounds of 768 -> 1024, 64 query and 8 KV heads: bf16 160 rows x 900 97.2 -> 93.1, 128 x 2048 140.9 -> 137.3; e4m3
+// 128 x 2048 87.3 -> 83.2, 64 x 4096 85.4 -> 79.1), but fewer than 1024 (row, KV head) pairs over a bf16 cache do not fill
+// them and are better split as for three (64 x 4096 134 -> 139, 64 x 900 53.2 -> 54.6).
+int pick_split(int rows, int n_kv_heads, int head_dim, int max_keys, int64_t sum_keys, bool matrix, bool fp8, int *min_keys) {
   *min_keys = 128;
   const int pairs = rows * n_kv_heads;
   if (matrix) {
     const double mean = (double)sum_keys / rows;
+    const int resident = head_dim == 64 && (fp8 || pairs >= 1024) ? 1024 : 768;
     int best = 1;
     double best_cost = 0;
     for (int ns = 1; ns <= std::min(MAX_SPLIT, std::max(1, (max_keys + 127) / 128)); ++ns) {
-      const double rounds = (double)pairs * ns / 768;
+      const double rounds = (double)pairs * ns / resident;
       const double first = 8 + 3.4 * ((max_keys + 128 * ns - 1) / (128 * ns)), next = 8 + 3.4 * mean / (128 * ns);
       const double cost = mean > 0.9 * max_keys ? std::ceil(rounds) * first : first + std::max(0.0, rounds - 1) * next;
       if (ns == 1 || cost < best_cost) { best = ns; best_cost = cost; }
@@ -207,7 +211,7 @@ int pick_split(int rows, int n_kv_heads, int max_keys, int64_t sum_keys, bool ma
 }
 void set_split(AttnDecodeParams &p, int max_keys, int64_t sum_keys) {
   const bool matrix = p.fp8 != 0 || p.n_q_heads / p.n_kv_heads == 8;   // as launch_attention_decode chooses
-  p.n_split = pick_split(p.n_rows, p.n_kv_heads, max_keys, sum_keys, matrix, &p.min_keys);
+  p.n_split = pick_split(p.n_rows, p.n_kv_heads, p.head_dim, max_keys, sum_keys, matrix, p.fp8 != 0, &p.min_keys);
 }
 
 struct HostPlan {
