@@ -278,10 +278,14 @@ __global__ void splits_finish_kernel(GemmParams p) {
   }
 }
 // Q, K, V (EPI_QKV) or the later layers' K, V (EPI_KV): rotation, rounding, destination and absmax as in the GEMM's
-// own epilogue.  grid (rows, groups of 4 heads), one wave per head, a rotary pair per lane (half of them idle at head_dim 64).
-template <int EPI, int HD>
-__global__ __launch_bounds__(256) void rope_finish_kernel(GemmParams p) {
-  const int row = blockIdx.x, hs = blockIdx.y * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+// own epilogue.  A wave takes one head of a row, a rotary pair per lane (half of them idle at head_dim 64).
+// Without absmax: grid (rows, groups of 4 heads).  With it: grid (groups of `rows` rows, heads), the rows dealt to the four
+// waves, and one atomic per workgroup: all heads' maxima share a few cache lines, and the atomics on them run one after
+// the other at about 5 ns each (one per row and head: 512 rows x 64 heads took 200 us).
+template <int EPI, int HD, bool AMAX>
+__global__ __launch_bounds__(256) void rope_finish_kernel(GemmParams p, int rows) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int hs = AMAX ? blockIdx.y : blockIdx.y * 4 + wave;
   const int n_kv = p.kv_dim / HD, n_q = EPI == EPI_QKV ? p.q_dim / HD : 0;
   if (hs >= p.N / HD) return;
   int kind, head, proj = 0;                              // kind 0 = q, 1 = k, 2 = v
@@ -293,32 +297,40 @@ __global__ __launch_bounds__(256) void rope_finish_kernel(GemmParams p) {
     kind = 1 + (hs % (2 * n_kv)) / n_kv;
     head = hs % n_kv;
   }
-  bf16_t *dst;
-  if constexpr (EPI == EPI_QKV) dst = (kind == 0 ? p.q_out + (int64_t)row * p.q_dim : (kind == 1 ? p.k_out : p.v_out) + (int64_t)row * p.kv_dim) + head * HD;
-  else if (p.stage) dst = p.stage + (int64_t)row * p.N + hs * HD;
-  else dst = p.cache + (int64_t)(p.first_cache_layer + proj) * p.cache_layer_stride + (kind == 2 ? p.cache_kv_stride : 0) + p.slots[row] * p.kv_dim + head * HD;
-  const float *src = p.partial + (int64_t)row * p.N + hs * HD;
   const int64_t stride = (int64_t)p.M * p.N;
-  const float rs = p.rstd ? p.rstd[row] : 1.f;
+  const int i = lane, row0 = blockIdx.x * rows, row_end = row0 + rows < p.M ? row0 + rows : p.M;
   float a = 0.f;
-  const int i = lane;
-  if (i < HD / 2) {
-    float x0 = src[i], x1 = src[i + HD / 2];
-    for (int k = 1; k < p.n_splits; ++k) { x0 += src[k * stride + i]; x1 += src[k * stride + i + HD / 2]; }
-    x0 *= rs; x1 *= rs;
-    if (kind != 2) {
-      const float2 cs = p.cos_sin[(int64_t)row * (HD / 2) + i];
-      const float y0 = x0 * cs.x - x1 * cs.y, y1 = x1 * cs.x + x0 * cs.y;
-      x0 = y0; x1 = y1;
+  for (int row = AMAX ? row0 + wave : row0; row < row_end; row += 4) {
+    bf16_t *dst;
+    if constexpr (EPI == EPI_QKV) dst = (kind == 0 ? p.q_out + (int64_t)row * p.q_dim : (kind == 1 ? p.k_out : p.v_out) + (int64_t)row * p.kv_dim) + head * HD;
+    else if (p.stage) dst = p.stage + (int64_t)row * p.N + hs * HD;
+    else dst = p.cache + (int64_t)(p.first_cache_layer + proj) * p.cache_layer_stride + (kind == 2 ? p.cache_kv_stride : 0) + p.slots[row] * p.kv_dim + head * HD;
+    const float *src = p.partial + (int64_t)row * p.N + hs * HD;
+    const float rs = p.rstd ? p.rstd[row] : 1.f;
+    if (i < HD / 2) {
+      float x0 = src[i], x1 = src[i + HD / 2];
+      for (int k = 1; k < p.n_splits; ++k) { x0 += src[k * stride + i]; x1 += src[k * stride + i + HD / 2]; }
+      x0 *= rs; x1 *= rs;
+      if (kind != 2) {
+        const float2 cs = p.cos_sin[(int64_t)row * (HD / 2) + i];
+        const float y0 = x0 * cs.x - x1 * cs.y, y1 = x1 * cs.x + x0 * cs.y;
+        x0 = y0; x1 = y1;
+      }
+      const bf16_t b0 = f32_to_bf16(x0), b1 = f32_to_bf16(x1);
+      dst[i] = b0;
+      dst[i + HD / 2] = b1;
+      if constexpr (AMAX) a = fmaxf(a, fmaxf(fabsf(bf16_to_f32(b0)), fabsf(bf16_to_f32(b1))));   // absmax of the values as stored
     }
-    const bf16_t b0 = f32_to_bf16(x0), b1 = f32_to_bf16(x1);
-    dst[i] = b0;
-    dst[i + HD / 2] = b1;
-    a = fmaxf(fabsf(bf16_to_f32(b0)), fabsf(bf16_to_f32(b1)));   // absmax of the values as stored
   }
-  if (p.amax && kind != 0) {
+  if constexpr (AMAX) {
+    __shared__ float of_wave[4];
     a = wave_max(a);
-    if (lane == 0) atomicMax(p.amax + ((int64_t)(p.first_cache_layer + proj) * 2 + (kind == 2 ? 1 : 0)) * n_kv + head, __float_as_uint(a));
+    if (lane == 0) of_wave[wave] = a;
+    __syncthreads();
+    if (threadIdx.x == 0 && kind != 0) {
+      a = fmaxf(fmaxf(of_wave[0], of_wave[1]), fmaxf(of_wave[2], of_wave[3]));
+      atomicMax(p.amax + ((int64_t)(p.first_cache_layer + proj) * 2 + (kind == 2 ? 1 : 0)) * n_kv + head, __float_as_uint(a));
+    }
   }
 }
 
@@ -327,11 +339,23 @@ void launch_finish(const GemmParams &p, hipStream_t st) {
   const int64_t quads = (int64_t)p.M * (EPI == EPI_SWIGLU ? p.N / 2 : p.N) / 4;
   hipLaunchKernelGGL(splits_finish_kernel<EPI>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p);
 }
+template <int EPI, int HD>
+void launch_rope_finish_hd(const GemmParams &p, hipStream_t st) {
+  const int heads = p.N / HD;
+  if (!p.amax) {
+    hipLaunchKernelGGL((rope_finish_kernel<EPI, HD, false>), dim3(p.M, (heads + 3) / 4), dim3(256), 0, st, p, 1);
+    return;
+  }
+  // about 1024 workgroups (5 us of atomics), but no wave with more than 8 rows one after the other (2048 and 4096 workgroups: 4
+  // and 15 us slower over 512 rows x 64 heads)
+  const int64_t want = ((int64_t)p.M * heads + 1023) / 1024;
+  const int rows = (int)std::min<int64_t>(32, std::max<int64_t>(4, (want + 3) / 4 * 4));
+  hipLaunchKernelGGL((rope_finish_kernel<EPI, HD, true>), dim3((p.M + rows - 1) / rows, heads), dim3(256), 0, st, p, rows);
+}
 template <int EPI>
 void launch_rope_finish(const GemmParams &p, hipStream_t st) {
-  const dim3 grid(p.M, (p.N / p.head_dim + 3) / 4);
-  if (p.head_dim == 128) hipLaunchKernelGGL((rope_finish_kernel<EPI, 128>), grid, dim3(256), 0, st, p);
-  else hipLaunchKernelGGL((rope_finish_kernel<EPI, 64>), grid, dim3(256), 0, st, p);
+  if (p.head_dim == 128) launch_rope_finish_hd<EPI, 128>(p, st);
+  else launch_rope_finish_hd<EPI, 64>(p, st);
 }
 
 constexpr int MID_MAX_SPLIT = 16;

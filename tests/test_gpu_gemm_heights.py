@@ -163,3 +163,35 @@ def test_row_major_gemm_between_81_and_1023_rows(M, N, K):
     ref = A.double() @ W.double().T
     for out_f32, tol in ((True, 1e-5), (False, 4e-3)):     # fp32 sums of exact products / one bf16 rounding
         assert rel_err(B.op_gemm(A.cuda(), W.cuda(), out_f32=out_f32).cpu(), ref) <= tol
+
+
+@pytest.mark.parametrize("hd,tokens", [(64, 81), (64, 515), (128, 100), (128, 513), (64, 37)])
+def test_computed_scales_of_split_kv_products(hd, tokens):
+    """The finishing pass of a split K/V product takes the heads' absmax over groups of rows: the scales are those of the
+    values that the same call stores into a bf16 cache, bit by bit, and the codes are those values rounded once."""
+    from oracle import swiftkv_oracle as O
+    from paper_2410_03960_amd import binding as B
+    sh = ModelShape(9, 2048, 1024 // hd, 256 // hd, hd, 256, 256, 1e4, 1e-5)
+    kvd = sh.n_kv_heads * hd
+    plan = B.op_gemm_plan("kv", tokens, 8 * 2 * kvd, sh.hidden, packed=True, head_dim=hd)
+    assert plan.n_splits > 1
+    _say(f"hd={hd} tokens={tokens} {plan}")
+    ctx = B.Context(sh, G.device_weights(_weights(Workload(f"scales{hd}", sh, l=1, g=1, seed=2209))), 1, 1)
+    hidden = WL.seeded_normal_bf16(3, f"hidden{tokens}", (tokens, sh.hidden), 0.0, 1.0).cuda()
+    n_blocks = (tokens + 15) // 16
+    table = torch.randperm(n_blocks, generator=torch.Generator().manual_seed(tokens)).int().view(1, -1)
+    caches = []
+    for fp8 in (False, True):
+        cache = B.KVCache(ctx.n_cache_layers, n_blocks, sh.n_kv_heads, hd, table, [0], fp8=fp8,
+                          scale_mode=B.SWIFTKV_SCALE_COMPUTE_ABSMAX if fp8 else 0)
+        kind = B.SWIFTKV_KV_FP8_E4M3 if fp8 else B.SWIFTKV_KV_BF16
+        ctx.kv_from_hidden(hidden, [tokens], cache, torch.empty(ctx.workspace_bytes(tokens, 1, kind, 0), dtype=torch.uint8, device="cuda"))
+        caches.append(cache)
+    pos = torch.arange(tokens)
+    slots = table[0].long()[pos // 16] * 16 + pos % 16
+    stored = caches[0].data[1:, :, slots.cuda()].float().cpu()             # [later layers, K|V, tokens, heads, hd]
+    scales = torch.maximum(stored.abs().amax(dim=(2, 4)), torch.tensor(1e-12)) / 448.0
+    assert torch.equal(caches[1].scales[1:].cpu(), scales)
+    got = O.fp8_e4m3fn_decode_table().float()[caches[1].data[1:, :, slots.cuda()].cpu().long()] * scales[:, :, None, :, None]
+    # three mantissa bits: half a unit is 2^-4 of the value, or 2^-10 of the scale below its normal range
+    assert ((got - stored).abs() <= 2.0 ** -4 * stored.abs() + 2.0 ** -10 * scales[:, :, None, :, None]).all()
