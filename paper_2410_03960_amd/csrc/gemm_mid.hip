@@ -298,32 +298,34 @@ __global__ __launch_bounds__(256) void rope_finish_kernel(GemmParams p, int rows
     head = hs % n_kv;
   }
   const int64_t stride = (int64_t)p.M * p.N;
-  const int i = lane, row0 = blockIdx.x * rows, row_end = row0 + rows < p.M ? row0 + rows : p.M;
-  float a = 0.f;
-  for (int row = AMAX ? row0 + wave : row0; row < row_end; row += 4) {
+  const int i = lane;
+  const auto finish_row = [&](int row) __attribute__((always_inline)) {   // absmax of the lane's pair, as stored
     bf16_t *dst;
     if constexpr (EPI == EPI_QKV) dst = (kind == 0 ? p.q_out + (int64_t)row * p.q_dim : (kind == 1 ? p.k_out : p.v_out) + (int64_t)row * p.kv_dim) + head * HD;
     else if (p.stage) dst = p.stage + (int64_t)row * p.N + hs * HD;
     else dst = p.cache + (int64_t)(p.first_cache_layer + proj) * p.cache_layer_stride + (kind == 2 ? p.cache_kv_stride : 0) + p.slots[row] * p.kv_dim + head * HD;
     const float *src = p.partial + (int64_t)row * p.N + hs * HD;
     const float rs = p.rstd ? p.rstd[row] : 1.f;
-    if (i < HD / 2) {
-      float x0 = src[i], x1 = src[i + HD / 2];
-      for (int k = 1; k < p.n_splits; ++k) { x0 += src[k * stride + i]; x1 += src[k * stride + i + HD / 2]; }
-      x0 *= rs; x1 *= rs;
-      if (kind != 2) {
-        const float2 cs = p.cos_sin[(int64_t)row * (HD / 2) + i];
-        const float y0 = x0 * cs.x - x1 * cs.y, y1 = x1 * cs.x + x0 * cs.y;
-        x0 = y0; x1 = y1;
-      }
-      const bf16_t b0 = f32_to_bf16(x0), b1 = f32_to_bf16(x1);
-      dst[i] = b0;
-      dst[i + HD / 2] = b1;
-      if constexpr (AMAX) a = fmaxf(a, fmaxf(fabsf(bf16_to_f32(b0)), fabsf(bf16_to_f32(b1))));   // absmax of the values as stored
+    if (i >= HD / 2) return 0.f;
+    float x0 = src[i], x1 = src[i + HD / 2];
+    for (int k = 1; k < p.n_splits; ++k) { x0 += src[k * stride + i]; x1 += src[k * stride + i + HD / 2]; }
+    x0 *= rs; x1 *= rs;
+    if (kind != 2) {
+      const float2 cs = p.cos_sin[(int64_t)row * (HD / 2) + i];
+      const float y0 = x0 * cs.x - x1 * cs.y, y1 = x1 * cs.x + x0 * cs.y;
+      x0 = y0; x1 = y1;
     }
-  }
+    const bf16_t b0 = f32_to_bf16(x0), b1 = f32_to_bf16(x1);
+    dst[i] = b0;
+    dst[i + HD / 2] = b1;
+    return fmaxf(fabsf(bf16_to_f32(b0)), fabsf(bf16_to_f32(b1)));
+  };
+  if constexpr (!AMAX) finish_row(blockIdx.x);
   if constexpr (AMAX) {
     __shared__ float of_wave[4];
+    const int row0 = blockIdx.x * rows, row_end = row0 + rows < p.M ? row0 + rows : p.M;
+    float a = 0.f;
+    for (int row = row0 + wave; row < row_end; row += 4) a = fmaxf(a, finish_row(row));
     a = wave_max(a);
     if (lane == 0) of_wave[wave] = a;
     __syncthreads();
