@@ -268,7 +268,7 @@ int swiftkv_op_gemm_rows_static(const void *A, const void *W, void *C, int32_t M
 enum {
   SWIFTKV_GEMM_STREAM_FIRST = 0,    /* weight streaming, K split among the waves of a workgroup */
   SWIFTKV_GEMM_STREAM_SEQ = 1,      /* ... slices of K one after the other behind a producer wave */
-  SWIFTKV_GEMM_STREAM_RESIDENT = 2, /* ... all activation rows resident in LDS */
+  SWIFTKV_GEMM_STREAM_RESIDENT = 2, /* (all activation rows resident in LDS: no product takes this form any more) */
   SWIFTKV_GEMM_STREAM_SLICE = 3,    /* ... one slice of K per workgroup in LDS */
   SWIFTKV_GEMM_TILE_128 = 4,        /* 128 x 128 tile */
   SWIFTKV_GEMM_TILE_256 = 5,        /* 256 x 256 tile, register-staged */

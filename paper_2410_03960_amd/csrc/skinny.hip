@@ -16,10 +16,9 @@
 // them in a fixed order and applies the epilogue (deterministic, unlike atomic
 // accumulation).
 // Four kernels: skinny_kernel (above; any K % 8 == 0, activations from L2),
-// skinny_lds_kernel (one weight, up to 32 rows, K % 512 == 0: a workgroup's one slice
-// of K in LDS), skinny_seq_kernel (K % 512 == 0: slices of K walked in sequence, the
-// activation slice double-buffered in LDS by a producer wave) and skinny_res_kernel
-// (the SwiGLU pair for up to 8 rows: all activation rows resident in LDS).
+// skinny_ring_kernel (K % 512 == 0: weights and activations through LDS, slices of K walked in sequence;
+// everything but final results of up to 32 rows over one weight), and for those skinny_lds_kernel (K % 512 == 0: a
+// workgroup's one slice of K in LDS) and skinny_seq_kernel (K % 512 == 0: slices walked in sequence, weights to registers).
 #include "../../include/swiftkv.h"
 #include "common.h"
 
@@ -173,6 +172,27 @@ __device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory");
 }
 
+// acc[mb][v] = C[m = mb*16 + l16][n + v] of one weight, whole or over K range `split`: to partial[split][m][n] or through the epilogue
+template <int MB, int EPI>
+__device__ __forceinline__ void store_blocks(const SkinnyParams &p, const floatx4 (&acc)[MB], int n, int l16, int split, bool partial) {
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int m = mb * 16 + l16;
+    if (m >= p.M) continue;
+    if (partial) {
+      *(float4 *)(p.partial + ((int64_t)split * p.M + m) * p.N + n) = make_float4(acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]);
+    } else if constexpr (EPI == EPI_STORE_F32) {
+      *(float4 *)((float *)p.C + (int64_t)m * p.N + n) = make_float4(acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]);
+    } else if constexpr (EPI == EPI_RESID) {
+      float4 *dst = (float4 *)((float *)p.C + (int64_t)m * p.N + n);
+      const float4 r = *dst;
+      *dst = make_float4(r.x + acc[mb][0], r.y + acc[mb][1], r.z + acc[mb][2], r.w + acc[mb][3]);
+    } else {
+      *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(acc[mb][0], acc[mb][1]), pack_bf16x2(acc[mb][2], acc[mb][3]));
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // One K slice per workgroup (one weight, no row-block table, up to 32 rows, K % 512 == 0): the slice's activations sit in LDS in MFMA operand
 // order (filled by LDS-DMA, one 1 KB fragment per request: lane (row l16, quarter kq) lands at 16 * lane), the
@@ -242,25 +262,9 @@ __global__ __launch_bounds__(LDS_WAVES * 64) void skinny_lds_kernel(SkinnyParams
   };
   // acc[mb][v] = C[m = mb*16 + l16][n = nb*16 + 4*kq + v] over this K slice
   auto flush = [&](int nb) {
-    const int n = nb * 16 + 4 * kq;
+    store_blocks<MB, EPI>(p, acc, nb * 16 + 4 * kq, l16, blockIdx.y, gridDim.y > 1);
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const int m = mb * 16 + l16;
-      if (m < p.M) {
-        if (gridDim.y > 1) {   // partial[split][m][n]
-          *(float4 *)(p.partial + ((int64_t)blockIdx.y * p.M + m) * p.N + n) = make_float4(acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]);
-        } else if constexpr (EPI == EPI_STORE_F32) {
-          *(float4 *)((float *)p.C + (int64_t)m * p.N + n) = make_float4(acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]);
-        } else if constexpr (EPI == EPI_RESID) {
-          float4 *dst = (float4 *)((float *)p.C + (int64_t)m * p.N + n);
-          const float4 r = *dst;
-          *dst = make_float4(r.x + acc[mb][0], r.y + acc[mb][1], r.z + acc[mb][2], r.w + acc[mb][3]);
-        } else {
-          *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(acc[mb][0], acc[mb][1]), pack_bf16x2(acc[mb][2], acc[mb][3]));
-        }
-      }
-      acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int mb = 0; mb < MB; ++mb) acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
   };
   // two groups per iteration, one register set in flight while the other is consumed; `groups` is even, so
   // a block ends after the second group of an iteration
@@ -276,91 +280,6 @@ __global__ __launch_bounds__(LDS_WAVES * 64) void skinny_lds_kernel(SkinnyParams
 }
 
 // ---------------------------------------------------------------------------
-// The SwiGLU pair for few rows: the M rows (not their padding to 16) are resident in LDS over the whole of K, row
-// after row with 64 bytes between them, lanes of columns past M read the last row.  A wave owns one column block of
-// both weights and walks K from end to end, two groups of eight 32-wide steps in flight; nothing is split, so there are
-// no partial sums and no second launch, and no slice boundary either.  us per launch with 1 / 2 / 4 / 8 rows, this kernel against
-// what plan_skinny takes without it: 2 x 14336 x 4096 44 / 45 / 46 / 49 (5.3 TB/s with one) against 53 / 56 / 56 / 51, 2 x 13824 x
-// 5120 50 / 50 / 51 / 54 against 58 / 59 / 60 / 61, 2 x 13312 x 8192 82 / 85 / 88 / 95 against 95 / 96 / 100 / 102.  Beyond: 12 rows
-// of 2 x 14336 x 4096 51 against 51, 16 rows 54 against 52.
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-constexpr int RES_WAVES = 4;
-__global__ __launch_bounds__(RES_WAVES * 64) void skinny_res_kernel(SkinnyParams p, int stride) {
-  constexpr int NW = 2, U = 8, WAVES = RES_WAVES;
-  extern __shared__ __align__(16) unsigned char a_lds[];   // [M][stride bytes]
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15, kq = lane >> 4;
-  const int nblocks = p.N / 16;
-  int nb = blockIdx.x * WAVES + wave;
-  const bool live = nb < nblocks;
-  nb = live ? nb : nblocks - 1;   // (a wave past the end re-reads the last block and stores nothing)
-  const int groups = p.K / (32 * U);   // even
-  const unsigned char *wp[NW];         // uniform; a lane adds its row's offset
-#pragma unroll
-  for (int w = 0; w < NW; ++w) wp[w] = (const unsigned char *)((w ? p.W2 : p.W) + (int64_t)nb * 16 * p.K);
-  const uint64_t w_lane = (uint64_t)l16 * p.K * 2 + kq * 16;
-  auto load_group = [&](u32x4_t (&dst)[NW][U], int g) __attribute__((always_inline)) {
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-#pragma unroll
-      for (int u = 0; u < U; ++u) dst[w][u] = *(const u32x4_t *)(wp[w] + (int64_t)(g * U + u) * 64 + w_lane);
-  };
-  u32x4_t wa[NW][U], wb[NW][U];
-  load_group(wa, 0);   // on their way while the activations arrive
-  load_group(wb, 1);
-  const int row_chunks = p.K / 8;
-  for (int i = tid; i < p.M * row_chunks; i += WAVES * 64) {
-    const int r = i / row_chunks, c = i % row_chunks;
-    *(uint4 *)(a_lds + r * stride + c * 16) = *(const uint4 *)(p.A + (int64_t)r * p.K + c * 8);
-  }
-  __syncthreads();
-  floatx4 acc[NW];
-#pragma unroll
-  for (int w = 0; w < NW; ++w) acc[w] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const unsigned char *fr = a_lds + (l16 < p.M ? l16 : p.M - 1) * stride + kq * 16;
-  auto compute_group = [&](const u32x4_t (&src)[NW][U], int g) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bf16x8 a = *(const bf16x8 *)(fr + (g * U + u) * 64);
-#pragma unroll
-      for (int w = 0; w < NW; ++w) acc[w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, src[w][u]), a, acc[w], 0, 0, 0);
-    }
-  };
-  for (int g = 0; g < groups; g += 2) {
-    compute_group(wa, g);
-    if (g + 2 < groups) load_group(wa, g + 2);
-    compute_group(wb, g + 1);
-    if (g + 3 < groups) load_group(wb, g + 3);
-  }
-  // acc[w][v] = C[m = l16][n = nb*16 + 4*kq + v] (weight w)
-  const int m = l16, n = nb * 16 + 4 * kq;
-  if (!live || m >= p.M) return;
-  float o[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) o[v] = acc[0][v] / (1.f + __expf(-acc[0][v])) * acc[1][v];
-  *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
-}
-// Whether the form above runs this shape: up to 8 rows, and four column blocks to a workgroup fill one round of the 256
-// CUs to at least four fifths (with half of the CUs idle too few loads are in flight: 2 x 8192 x 2048, 128 workgroups,
-// 18.0 us against 15.6 of the first kernel; with several rounds skinny_seq_kernel is ahead: 2 x 28672 x 8192 168
-// against 176).
-bool res_fits(const SkinnyParams &p, int epi) {
-  if (epi != EPI_SWIGLU || p.wtab || p.M > 8 || (p.N % 16) != 0 || (p.K % 512) != 0 || (size_t)p.M * (p.K * 2 + 64) > 160 * 1024) return false;
-  const int wgs = (p.N / 16 + RES_WAVES - 1) / RES_WAVES;
-  return wgs <= 256 && wgs * 5 >= 256 * 4;
-}
-int launch_res(const SkinnyParams &p, hipStream_t st) {
-  static bool attr = false;
-  if (!attr) {
-    if (hipFuncSetAttribute((const void *)skinny_res_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return -1;
-    attr = true;
-  }
-  const int stride = p.K * 2 + 64, nblocks = p.N / 16;
-  hipLaunchKernelGGL(skinny_res_kernel, dim3((nblocks + RES_WAVES - 1) / RES_WAVES), dim3(RES_WAVES * 64), (size_t)p.M * stride, st, p, stride);
-  return 0;
-}
-
-// ---------------------------------------------------------------------------
 // The activations through LDS (K % 512 == 0).  Measured on the first kernel: the activation fragments, which every
 // wave fetches from L2 for every k step, take as many vector-memory requests as the weights and cost 20-30 % of the
 // achieved HBM rate.  Here a workgroup walks slices of its K range one after the other: the activation slice sits in
@@ -370,8 +289,7 @@ int launch_res(const SkinnyParams &p, hipStream_t st) {
 // registers over the whole K range.  One barrier per slice.
 template <int MB, int EPI, int WAVES, int NBW>
 __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_seq_kernel(SkinnyParams p, int ks_steps, int n_slices) {
-  constexpr int NW = (EPI == EPI_SWIGLU) ? 2 : 1;
-  constexpr int U = (NBW * NW >= 4) ? 2 : 4;                                      // k steps (of 32) per group of loads
+  constexpr int U = NBW >= 4 ? 2 : 4;                                             // k steps (of 32) per group of loads
   extern __shared__ __align__(16) unsigned char a_lds[];   // [2][k step][MB][64 lanes][16 bytes]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kq = lane >> 4;
@@ -405,40 +323,32 @@ __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_seq_kernel(SkinnyPara
   const int nb0 = (blockIdx.x * WAVES + wave) * NBW;
   const int total = my_slices * gps;                                  // groups of this wave
   // weight rows of this lane: a group is U k steps of all NBW column blocks (an activation fragment read from
-  // LDS then feeds NBW * NW products); groups are requested in the order they are consumed.
+  // LDS then feeds NBW products); groups are requested in the order they are consumed.
   // (a column block past N re-reads the last one; its results are dropped)
-  int64_t woff[NBW];
   const bf16_t *wt[NBW];
 #pragma unroll
   for (int b = 0; b < NBW; ++b) {
     int nb = nb0 + b;
     nb = nb < nblocks ? nb : nblocks - 1;
-    woff[b] = (int64_t)(nb * 16 + l16) * p.K + k0 + kq * 8;
-    wt[b] = p.wtab ? p.wtab[nb] + ((int64_t)l16 * p.K + k0 + kq * 8) : nullptr;   // (one weight, never SwiGLU)
+    wt[b] = (p.wtab ? p.wtab[nb] : p.W + (int64_t)nb * 16 * p.K) + ((int64_t)l16 * p.K + k0 + kq * 8);
   }
   int l_idx = 0;
-  auto load_group = [&](uint4 (&dst)[NBW][NW][U]) {
+  auto load_group = [&](uint4 (&dst)[NBW][U]) {
     const int koff = l_idx * (U * 32);
     ++l_idx;
 #pragma unroll
     for (int b = 0; b < NBW; ++b)
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const bf16_t *src = (wt[b] ? wt[b] : (w ? p.W2 : p.W) + woff[b]) + koff;
-#pragma unroll
-        for (int u = 0; u < U; ++u) dst[b][w][u] = *(const uint4 *)(src + u * 32);
-      }
+      for (int u = 0; u < U; ++u) dst[b][u] = *(const uint4 *)(wt[b] + koff + u * 32);
   };
-  uint4 wa[NBW][NW][U], wb[NBW][NW][U];
+  uint4 wa[NBW][U], wb[NBW][U];
   load_group(wa);   // on its way while the first slice arrives
 
-  floatx4 acc[NBW][NW][MB];
+  floatx4 acc[NBW][MB];
 #pragma unroll
   for (int b = 0; b < NBW; ++b)
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) acc[b][w][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int mb = 0; mb < MB; ++mb) acc[b][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   int idx = 0;
   __builtin_amdgcn_s_barrier();   // slice 0 is in LDS
@@ -458,10 +368,8 @@ __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_seq_kernel(SkinnyPara
 #pragma unroll
           for (int b = 0; b < NBW; ++b)
 #pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-              for (int mb = 0; mb < MB; ++mb)
-                acc[b][w][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, half ? wb[b][w][u] : wa[b][w][u]), a[mb], acc[b][w][mb], 0, 0, 0);
+            for (int mb = 0; mb < MB; ++mb)
+              acc[b][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, half ? wb[b][u] : wa[b][u]), a[mb], acc[b][mb], 0, 0, 0);
         }
       }
       idx += 2;
@@ -472,36 +380,10 @@ __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_seq_kernel(SkinnyPara
     __builtin_amdgcn_s_barrier();
   }
 
-  // acc[b][w][mb][v] = C[m = mb*16 + l16][n = (nb0 + b)*16 + 4*kq + v] (weight w), over this K range
+  // acc[b][mb][v] = C[m = mb*16 + l16][n = (nb0 + b)*16 + 4*kq + v], over this K range
 #pragma unroll
   for (int b = 0; b < NBW; ++b) {
-    const int nb = nb0 + b;
-    if (nb >= nblocks) continue;
-    const int n = nb * 16 + 4 * kq;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const int m = mb * 16 + l16;
-      if (m >= p.M) continue;
-      if (gridDim.y > 1) {   // partial[split][w][m][n]
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-          *(float4 *)(p.partial + (((int64_t)blockIdx.y * NW + w) * p.M + m) * p.N + n) =
-              make_float4(acc[b][w][mb][0], acc[b][w][mb][1], acc[b][w][mb][2], acc[b][w][mb][3]);
-      } else if constexpr (EPI == EPI_STORE_F32) {
-        *(float4 *)((float *)p.C + (int64_t)m * p.N + n) = make_float4(acc[b][0][mb][0], acc[b][0][mb][1], acc[b][0][mb][2], acc[b][0][mb][3]);
-      } else if constexpr (EPI == EPI_RESID) {
-        float4 *dst = (float4 *)((float *)p.C + (int64_t)m * p.N + n);
-        const float4 r = *dst;
-        *dst = make_float4(r.x + acc[b][0][mb][0], r.y + acc[b][0][mb][1], r.z + acc[b][0][mb][2], r.w + acc[b][0][mb][3]);
-      } else {
-        float o[4] = {acc[b][0][mb][0], acc[b][0][mb][1], acc[b][0][mb][2], acc[b][0][mb][3]};
-        if constexpr (EPI == EPI_SWIGLU) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) o[v] = o[v] / (1.f + __expf(-o[v])) * acc[b][NW - 1][mb][v];
-        }
-        *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
-      }
-    }
+    if (nb0 + b < nblocks) store_blocks<MB, EPI>(p, acc[b], (nb0 + b) * 16 + 4 * kq, l16, blockIdx.y, gridDim.y > 1);
   }
 }
 
@@ -543,42 +425,24 @@ struct SeqPlan {
   size_t lds_bytes, partial_bytes;
   double cost;   // bytes at the streaming rate
 };
-// Shape of the launch: column blocks per workgroup (waves x nbw), slice length and K ranges, chosen by the bytes that
-// move besides the weights -- every workgroup fetches the activation rows of its K range from L2 (n_cg * M * K * 2
+// Shape of a launch of skinny_seq_kernel: column blocks per workgroup (waves x nbw), slice length and K ranges, chosen by the
+// bytes that move besides the weights -- every workgroup fetches the activation rows of its K range from L2 (n_cg * M * K * 2
 // bytes in total over n_cg column groups, whatever the K split), K splits write and re-read fp32 partial sums (2 *
-// ksplit * nw * M * N * 4 bytes) and, for the epilogues that cannot leave the sum to their consumer, need a second
-// launch.  Beyond 32 rows the two activation buffers take most of LDS, one workgroup runs per CU, and what counts is
-// how evenly the workgroups fill whole rounds of 256.  Up to 32 rows several fit, and what counts is the bytes in
-// flight per CU (two load groups per consumer wave): below 64 KB the stream slows down.  Where the consumer adds the splits
-// (Q/K/V, O, down and the fused K/V projection of a prefill), each one also lengthens the pass that adds them, about 0.25 us;
-// the terms' larger weights there stand for that.
-// Measured, us per call (before -> this form): 64 rows: 128256 x 4096 296 -> 196, 28672 x 4096 64.4 -> 61.2 and no second
-// launch, 4096 x 4096 18.0 -> 16.5, 4096 x 14336 36.8 -> 36.8; 24 rows: 2 x 28672 x 8192 233 -> 171, 128256 x 4096 285 ->
-// 184, 8192 x 28672 101 -> 93, 4096 x 14336 26.4 -> 28.0; 1 row: 6144 x 4096 14.3 -> 11.7, 8192 x 28672 90 -> 82,
-// 2048 x 8192 12.8 -> 9.3, 4096 x 14336 26.6 -> 25.3 (4 ranges of 7 slices, 32 KB in flight per CU: 28.9).
-SeqPlan plan_seq(int M, int N, int K, int nw, bool consumer_sums, size_t partial_cap) {
+// ksplit * M * N * 4 bytes) and need a second launch.  Several workgroups fit a CU, and what counts is the bytes in
+// flight per CU (two load groups per consumer wave): below 52 KB the stream slows down.
+SeqPlan plan_seq(int M, int N, int K, size_t partial_cap) {
   SeqPlan best{};
-  if (M < 1 || M > 80 || (N % 16) != 0 || (K % 512) != 0) return best;
+  if (M < 1 || M > 32 || (N % 16) != 0 || (K % 512) != 0) return best;
   const int MB = (M + 15) / 16, nblocks = N / 16;
-  const bool few = M <= 32;
   // up to 16 rows, where skinny_lds_kernel has too few (column block, K slice) pairs: no second launch (4096 x 4096 in bf16, 1
   // row: 13.0 us against 9.9 of the first kernel)
-  const bool one_launch = M <= 16 && !consumer_sums && (nw == 2 || !plan_lds(M, N, K, partial_cap).ok);
-  const double w_bytes = 2.0 * nw * N * K;
-  int64_t best_wgs = 0;
-  // The first of equals wins: beyond 32 rows eight waves with a block each are ahead of four with two (64 rows x 6144 x
-  // 4096 18.0 us against 19.0, 4096 x 4096 13.0 / 13.7), four waves with four blocks of eight with two (8192 x 8192 33.4 / 35.3).
-  static const int few_shapes[6][2] = {{4, 1}, {4, 2}, {4, 4}, {8, 1}, {8, 2}, {8, 4}};
-  static const int many_shapes[6][2] = {{8, 1}, {4, 1}, {4, 2}, {4, 4}, {8, 2}, {8, 4}};
-  for (const auto &shape : few ? few_shapes : many_shapes) {
+  const bool one_launch = M <= 16 && !plan_lds(M, N, K, partial_cap).ok;
+  const double w_bytes = 2.0 * N * K;
+  static const int shapes[6][2] = {{4, 1}, {4, 2}, {4, 4}, {8, 1}, {8, 2}, {8, 4}};
+  for (const auto &shape : shapes) {
     const int waves = shape[0], nbw = shape[1];
-    if (nw == 2 && nbw * waves > 8) continue;               // (two weights: register budget of the instantiations below)
     const int n_cg = (nblocks + waves * nbw - 1) / (waves * nbw);
     for (int ks_steps = 16; ks_steps >= 8; ks_steps /= 2) {
-      // 2 x 48 to 64 KB of LDS; at 65 to 80 rows 2 x 40, where the weights are large 2 x 80 (us per call with 256 / 512
-      // columns, 80 rows: 2048 x 2048 12.1 / 13.3, 8192 x 3072 22.7 / 24.9, 13824 x 5120 47.6 / 52.4, but 8192 x 28672 120.6 /
-      // 113.3; 228 products of 2 to 940 MB: from 430 MB on 512 columns are 1 % slower to 8 % faster)
-      if (!few && ks_steps != (MB <= 4 || w_bytes >= 4.3e8 ? 16 : 8)) continue;
       const int all_slices = K / (32 * ks_steps);
       const size_t lds = (size_t)2 * ks_steps * MB * 1024;
       for (int want = 1; want <= std::min(SKINNY_MAX_SPLIT, all_slices); ++want) {
@@ -586,36 +450,29 @@ SeqPlan plan_seq(int M, int N, int K, int nw, bool consumer_sums, size_t partial
         const int ksplit = (all_slices + n_slices - 1) / n_slices;
         if (ksplit != want) continue;
         const int64_t wgs = (int64_t)n_cg * ksplit;
-        const size_t partial = ksplit > 1 ? (size_t)ksplit * nw * M * N * 4 : 0;
-        if (partial > partial_cap) continue;
+        const size_t partial = ksplit > 1 ? (size_t)ksplit * M * N * 4 : 0;
+        // (too few workgroups: the first kernel is ahead, which splits K among the waves of a workgroup; 2048 x 2048, 1 row: 6.5 us
+        // against 5.5)
+        if (partial > partial_cap || wgs < 192 || (ksplit > 1 && one_launch)) continue;
         const double a_bytes = (double)n_cg * M * K * 2;
-        const bool second = ksplit > 1 && !consumer_sums;   // a launch, below in bytes at the streaming rate
         const int64_t n_rounds = (wgs + 255) / 256;
         const double uneven = (double)n_rounds * 256 / (double)wgs - 1;
-        double cost;
-        if (few) {
-          if (!consumer_sums && (wgs < 192 || (second && one_launch))) continue;
-          // (resident: by LDS and by the registers of the instantiations)
-          const int per_simd = nbw * nw == 1 ? 8 : nbw * nw == 4 || (nw == 1 && MB == 2) ? 4 : 5;
-          const int64_t fit = (160 << 10) / lds, resident = std::max<int64_t>(1, std::min<int64_t>(fit, 4 * per_simd / (waves + 1)));
-          const double in_flight = (double)std::min(n_rounds, consumer_sums ? fit : resident) * waves * (nbw * nw == 1 ? 8 : 16);   // KB per CU
-          cost = consumer_sums ? (w_bytes + 0.75 * a_bytes + 2.0 * partial) * (1 + 0.3 * uneven) * (1 + 0.35 * std::max(0.0, 1 - in_flight / 64))
-                               : (w_bytes + 0.26 * a_bytes + 1.9 * partial + (second ? 11e6 : 0)) * (1 + 0.31 * uneven) * (1 + 0.19 * std::max(0.0, 1 - in_flight / 52)) +
-                                     0.06e6 * n_slices * ((n_rounds + resident - 1) / resident);
-        } else {   // L2 hits: cheaper than the partial sums' trip to memory; every further round pays its own fill and uneven end
-          cost = (w_bytes + 0.75 * a_bytes + 2.0 * partial + (second ? 25e6 : 0)) * (1 + uneven) * (1.0 + 0.15 * (double)(n_rounds - 1));
-        }
-        if (!best.ok || cost < best.cost) {
-          best = SeqPlan{true, waves, nbw, ks_steps, n_slices, ksplit, lds, partial, cost};
-          best_wgs = wgs;
-        }
+        // (resident: by LDS and by the registers of the instantiations)
+        const int per_simd = nbw == 1 ? 8 : nbw == 4 || MB == 2 ? 4 : 5;
+        const int64_t resident = std::max<int64_t>(1, std::min<int64_t>((160 << 10) / lds, 4 * per_simd / (waves + 1)));
+        const double in_flight = (double)std::min(n_rounds, resident) * waves * (nbw == 1 ? 8 : 16);   // KB per CU
+        const double cost = (w_bytes + 0.26 * a_bytes + 1.9 * partial + (ksplit > 1 ? 11e6 : 0)) * (1 + 0.31 * uneven) * (1 + 0.19 * std::max(0.0, 1 - in_flight / 52)) +
+                            0.06e6 * n_slices * ((n_rounds + resident - 1) / resident);
+        if (!best.ok || cost < best.cost) best = SeqPlan{true, waves, nbw, ks_steps, n_slices, ksplit, lds, partial, cost};
       }
     }
   }
-  // too few workgroups: the first kernel is ahead, which splits K among the waves of a workgroup (2048 x 2048, 1 row: 6.5 us
-  // against 5.5)
-  if (few && best_wgs < 192) best.ok = false;
   return best;
+}
+template <int EPI>
+void launch_reduce(const SkinnyParams &p, int ksplit, hipStream_t st) {
+  const int64_t quads = (int64_t)p.M * p.N / 4;
+  hipLaunchKernelGGL((skinny_reduce_kernel<EPI>), dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p, ksplit);
 }
 template <int MB, int EPI, int WAVES, int NBW>
 int launch_seq_k(const SkinnyParams &p, const SeqPlan &pl, hipStream_t st) {
@@ -628,41 +485,250 @@ int launch_seq_k(const SkinnyParams &p, const SeqPlan &pl, hipStream_t st) {
   const int nblocks = p.N / 16;
   dim3 grid((nblocks + WAVES * NBW - 1) / (WAVES * NBW), pl.ksplit);
   hipLaunchKernelGGL(kern, grid, dim3((WAVES + 1) * 64), pl.lds_bytes, st, p, pl.ks_steps, pl.n_slices);
-  if (pl.ksplit > 1 && p.n_splits_out) *p.n_splits_out = pl.ksplit;   // the consumer adds the splits
-  else if (pl.ksplit > 1) {
-    const int64_t quads = (int64_t)p.M * p.N / 4;
-    hipLaunchKernelGGL((skinny_reduce_kernel<EPI>), dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p, pl.ksplit);
-  }
+  if (pl.ksplit > 1) launch_reduce<EPI>(p, pl.ksplit, st);
   return 0;
 }
 template <int MB, int EPI>
 int launch_seq_e(const SkinnyParams &p, const SeqPlan &pl, hipStream_t st) {
-  if constexpr (EPI != EPI_SWIGLU) {
-    if (pl.nbw == 4) return pl.waves == 4 ? launch_seq_k<MB, EPI, 4, 4>(p, pl, st) : launch_seq_k<MB, EPI, 8, 4>(p, pl, st);
-    if (pl.waves == 8 && pl.nbw == 2) return launch_seq_k<MB, EPI, 8, 2>(p, pl, st);
+  if (pl.nbw == 4) return pl.waves == 4 ? launch_seq_k<MB, EPI, 4, 4>(p, pl, st) : launch_seq_k<MB, EPI, 8, 4>(p, pl, st);
+  if (pl.nbw == 2) return pl.waves == 4 ? launch_seq_k<MB, EPI, 4, 2>(p, pl, st) : launch_seq_k<MB, EPI, 8, 2>(p, pl, st);
+  return pl.waves == 4 ? launch_seq_k<MB, EPI, 4, 1>(p, pl, st) : launch_seq_k<MB, EPI, 8, 1>(p, pl, st);
+}
+template <int EPI>
+int launch_seq_m(const SkinnyParams &p, const SeqPlan &pl, hipStream_t st) {
+  return p.M <= 16 ? launch_seq_e<1, EPI>(p, pl, st) : launch_seq_e<2, EPI>(p, pl, st);
+}
+int launch_seq(const SkinnyParams &p, int epi, const SeqPlan &pl, hipStream_t st) {   // one weight, never with n_splits_out
+  switch (epi) {
+    case EPI_STORE_BF16: return launch_seq_m<EPI_STORE_BF16>(p, pl, st);
+    case EPI_STORE_F32: return launch_seq_m<EPI_STORE_F32>(p, pl, st);
+    case EPI_RESID: return launch_seq_m<EPI_RESID>(p, pl, st);
   }
-  if (pl.waves == 8 && pl.nbw == 1) return launch_seq_k<MB, EPI, 8, 1>(p, pl, st);
-  if (pl.waves == 4 && pl.nbw == 2) return launch_seq_k<MB, EPI, 4, 2>(p, pl, st);
-  if (pl.waves == 4 && pl.nbw == 1) return launch_seq_k<MB, EPI, 4, 1>(p, pl, st);
   return -1;
+}
+
+// ---------------------------------------------------------------------------
+// Weights and activations through LDS (K % 512 == 0).  A wave owns one 16-column block of one weight and streams it through a
+// ring of its own, R steps of 64 columns of K, by LDS-DMA in whole 128-byte pieces of its rows; it issues no other
+// vector-memory request, so they complete in order and a counted wait is exact.  A producer wave brings the
+// activations, 256 columns of K at a time, into two buffers shared by the workgroup; one barrier per buffer.
+// What bounds such a stream, measured on it:
+//  - The address unit serves a request four lanes at a time, one 128-byte line per cycle.  With a row per lane, the
+//    order in which the matrix instruction wants weights in registers, a 1 KB request takes 64 cycles instead of 16: an
+//    L2-resident stream ends at 7.8 TB/s so loaded and at 20 with eight lanes to a row, and the activations' requests come on top.
+//  - Rows 2^13 or 2^14 bytes apart at the same column lie on few memory channels, and all workgroups walk K in step.  So those of
+//    a die start at different columns (`rot` buffers further round their K range): 28672 x 4096, 64 rows, 52.0 -> 42.4 us.
+// With both, us per call (register form before -> this one): 64 rows 2 x 14336 x 4096 58.9 -> 42.0 (5.6 TB/s), 6144 x
+// 4096 17.5 -> 13.8, 4096 x 4096 12.6 -> 9.8, 4096 x 14336 31.3 -> 25.5, 2048 x 2048 9.0 -> 5.4; 24 rows 2 x 28672 x 8192 171 -> 157, 8192 x
+// 28672 92 -> 80; one row 2 x 14336 x 4096 44.6 (all rows resident in LDS) -> 39.5, 4096 x 14336 25.2 -> 21.2.
+// Chunk c (16 bytes) of row r of a 16 x 64 piece lies at chunk c ^ ((r >> 1) & 7) of its 128 bytes, so that fragment reads meet
+// every bank once.
+template <int N>
+__device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
+template <int R>
+__device__ __forceinline__ void wait_ring(int younger) {   // step i is in LDS: no more than the requests of `younger` later steps in flight
+  static_assert(R <= 4, "cases below");
+  if (younger >= R - 1) wait_vm<2 * (R - 1)>();
+  else if (younger == 2) wait_vm<4>();
+  else if (younger == 1) wait_vm<2>();
+  else wait_vm<0>();
+}
+// 64 lanes x 16 bytes from base (uniform) + off (per lane) into the 1 KB of LDS at lds_addr (uniform)
+__device__ __forceinline__ void lds_dma16_at(const void *base, unsigned off, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base) : "memory");
+}
+constexpr int RING_BUF = 256;                                       // columns of K in an activation buffer
+constexpr int ring_steps(int waves) { return waves == 8 ? 3 : 4; }   // 48 and 32 KB per workgroup; more in flight is no faster (8 waves, 64 rows, 6 steps: 51.7 us against 48.8)
+constexpr int ring_lds(int MB, int waves) { return 2 * MB * 16 * RING_BUF * 2 + waves * ring_steps(waves) * 2048; }
+template <int MB, int EPI, int WAVES>
+__global__ __launch_bounds__((WAVES + 1) * 64) void skinny_ring_kernel(SkinnyParams p, int n_bufs, int stride) {
+  constexpr int R = ring_steps(WAVES);
+  constexpr int CW = EPI == EPI_SWIGLU ? WAVES / 2 : WAVES;   // column blocks of a workgroup (SwiGLU: gate waves, then up waves)
+  constexpr int ABUF = MB * 16 * RING_BUF * 2;
+  extern __shared__ __align__(16) unsigned char lds[];   // [2][MB][4 steps][2 KB] activations, [WAVES][R][2 KB] weights
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int b0 = blockIdx.y * n_bufs, all = p.K / RING_BUF;
+  const int bufs = all - b0 < n_bufs ? all - b0 : n_bufs;   // of this K range, >= 1 by the grid
+  const int rot = (blockIdx.x / 8 * stride) % bufs;         // (workgroup ids go round the eight dies)
+  typedef __attribute__((address_space(3))) void *lds_ptr_t;
+  const unsigned lds_base = (unsigned)(size_t)(lds_ptr_t)lds;
+  // request h of a piece: rows 8 h + r8, and the chunk that lies at this lane's place
+  const int r8 = lane >> 3, c0 = (lane & 7) ^ (lane >> 4), c1 = c0 ^ 4;
+  const unsigned row_bytes = p.K * 2;
+
+  if (wave == WAVES) {
+    for (int s = 0; s <= bufs; ++s) {
+      if (s < bufs) {
+        const int at = s + rot < bufs ? s + rot : s + rot - bufs;
+        const unsigned char *base = (const unsigned char *)(p.A + (int64_t)(b0 + at) * RING_BUF);
+        for (int mb = 0; mb < MB; ++mb) {
+          const int m0 = mb * 16 + r8, m1 = m0 + 8;   // rows past M repeat row M - 1
+          const unsigned o0 = (m0 < p.M ? m0 : p.M - 1) * row_bytes + c0 * 16, o1 = (m1 < p.M ? m1 : p.M - 1) * row_bytes + c1 * 16;
+          const unsigned dst = lds_base + (s & 1) * ABUF + mb * 8192;
+#pragma unroll
+          for (int st = 0; st < 4; ++st) {
+            lds_dma16_at(base + st * 128, o0, dst + st * 2048);
+            lds_dma16_at(base + st * 128, o1, dst + st * 2048 + 1024);
+          }
+        }
+        wait_vm<0>();
+      }
+      __builtin_amdgcn_s_barrier();   // buffer s is ready / the consumers have left buffer s - 1
+    }
+    if constexpr (EPI == EPI_SWIGLU) { if (gridDim.y == 1) __builtin_amdgcn_s_barrier(); }
+    return;
+  }
+
+  const int nblocks = p.N / 16;
+  const int my = blockIdx.x * CW + wave % CW, nb = my < nblocks ? my : nblocks - 1;   // (past N: the last block again, results dropped)
+  const bf16_t *w0 = p.wtab ? p.wtab[nb] : (EPI == EPI_SWIGLU && wave >= CW ? p.W2 : p.W) + (int64_t)nb * 16 * p.K;
+  const unsigned char *wbase = (const unsigned char *)(w0 + (int64_t)b0 * RING_BUF);
+  const unsigned o0 = r8 * row_bytes + c0 * 16, o1 = (8 + r8) * row_bytes + c1 * 16;
+  const int ring_off = 2 * ABUF + wave * (R * 2048);
+  const int steps = bufs * 4;
+  int next = rot * 4;   // column (in steps) of the next request
+  auto request = [&](int slot) __attribute__((always_inline)) {
+    const unsigned char *src = wbase + (int64_t)next * 128;
+    lds_dma16_at(src, o0, lds_base + ring_off + slot * 2048);
+    lds_dma16_at(src, o1, lds_base + ring_off + slot * 2048 + 1024);
+    next = next + 1 == steps ? 0 : next + 1;
+  };
+#pragma unroll
+  for (int i = 0; i < R; ++i) request(i);   // (steps >= 4 >= R)
+
+  floatx4 acc[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int frag = l16 * 128 + ((kq ^ (l16 >> 1)) << 4);   // (second half of a step: four chunks on, XOR 64)
+  int slot = 0;
+  __builtin_amdgcn_s_barrier();   // buffer 0 is in LDS
+  for (int s = 0; s < bufs; ++s) {
+    const unsigned char *buf = lds + (s & 1) * ABUF;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int left = steps - 1 - (s * 4 + j);   // steps after this one
+      wait_ring<R>(left);
+      asm volatile("" ::: "memory");
+      bf16x8 w[2], a[2][MB];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) w[u] = *(const bf16x8 *)(lds + ring_off + slot * 2048 + (frag ^ (u * 64)));
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) a[u][mb] = *(const bf16x8 *)(buf + mb * 8192 + j * 2048 + (frag ^ (u * 64)));
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u], a[u][mb], acc[mb], 0, 0, 0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // every read of the slot (and of the buffer) has returned
+      if (left >= R) request(slot);
+      slot = slot + 1 == R ? 0 : slot + 1;
+    }
+    __builtin_amdgcn_s_barrier();
+  }
+  const int n = nb * 16 + 4 * kq;
+  if constexpr (EPI == EPI_SWIGLU) {
+    if (gridDim.y > 1) {   // partial[split][weight][m][n]
+      if (my < nblocks) store_blocks<MB, EPI_STORE_F32>(p, acc, n, l16, blockIdx.y * 2 + (wave >= CW ? 1 : 0), true);
+      return;
+    }
+    // the up waves hand their sums to the gate waves
+    float4 *up = (float4 *)lds + (wave % CW) * (MB * 64) + lane;
+    if (wave >= CW) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) up[mb * 64] = make_float4(acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (wave >= CW || my >= nblocks) return;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const int m = mb * 16 + l16;
+      if (m >= p.M) continue;
+      const float4 u = up[mb * 64];
+      float o[4] = {acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[v] = o[v] / (1.f + __expf(-o[v])) * (v == 0 ? u.x : v == 1 ? u.y : v == 2 ? u.z : u.w);
+      *(uint2 *)((bf16_t *)p.C + (int64_t)m * p.N + n) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
+    }
+  } else {
+    if (my < nblocks) store_blocks<MB, EPI>(p, acc, n, l16, blockIdx.y, gridDim.y > 1);
+  }
+}
+
+struct RingPlan {
+  bool ok;
+  int waves, slice, n_slices, ksplit;   // slice: columns of K; K ranges are whole slices
+  double cost;                          // us
+};
+// Shape of the launch: eight or four waves and the K ranges, by a time model fitted to 29 products of 2 to 1050 MB with 1 to 80 rows in
+// every shape (median error 4 %; the choice costs 1 % against the best of each): launch and first fill; the weights, the
+// activations' way from L2 (n_cg * M * K * 2 bytes over n_cg column groups) and the partial sums' way at 6.7 TB/s, lengthened by
+// an uneven last round; a start for each further round of workgroups that fit; a wave's own chain of fragment reads and
+// products.  K splits whose consumer adds them lengthen its pass by about a third of a microsecond each, others need a launch.
+RingPlan plan_ring(int M, int N, int K, int nw, bool consumer_sums, size_t partial_cap) {
+  RingPlan best{};
+  if (M < 1 || M > 80 || (N % 16) != 0 || (K % 512) != 0) return best;
+  const int MB = (M + 15) / 16, nblocks = N / 16;
+  const double w_bytes = 2.0 * nw * N * K;
+  // K ranges in steps of 512 columns; of 256 at 65 to 80 rows, whose longer rounds of a wave an even split evens out, but for
+  // large weights
+  const int slice = M > 64 && w_bytes < 4.3e8 ? 256 : 512, all_slices = K / slice;
+  for (int waves = 8; waves >= 4; waves -= 4) {
+    const int cw = waves / nw, n_cg = (nblocks + cw - 1) / cw;
+    const int resident = (160 << 10) / ring_lds(MB, waves);
+    for (int want = 1; want <= std::min(SKINNY_MAX_SPLIT, all_slices); ++want) {
+      const int n_slices = (all_slices + want - 1) / want, ksplit = (all_slices + n_slices - 1) / n_slices;
+      if (ksplit != want) continue;
+      const size_t partial = ksplit > 1 ? (size_t)ksplit * nw * M * N * 4 : 0;
+      if (partial > partial_cap) continue;
+      const double wgs = (double)n_cg * ksplit, rounds = std::ceil(wgs / 256);
+      const double bytes = w_bytes + 0.15 * n_cg * M * K * 2 + 1.6 * (double)partial;
+      const double cost = 2.6 + bytes / 6.67e6 * (1 + 0.385 * (rounds * 256 / wgs - 1)) + 1.73 * (std::ceil(rounds / resident) - 1) +
+                          1.33e-6 * w_bytes / wgs * MB * rounds + (ksplit == 1 ? 0 : consumer_sums ? 0.35 * (ksplit - 1) : 3.0);
+      if (!best.ok || cost < best.cost) best = RingPlan{true, waves, slice, n_slices, ksplit, cost};
+    }
+  }
+  return best;
+}
+template <int MB, int EPI, int WAVES>
+int launch_ring_k(const SkinnyParams &p, const RingPlan &pl, hipStream_t st) {
+  auto kern = skinny_ring_kernel<MB, EPI, WAVES>;
+  constexpr int lds = ring_lds(MB, WAVES);
+  static bool attr = false;
+  if (!attr) {
+    if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return -1;
+    attr = true;
+  }
+  constexpr int CW = EPI == EPI_SWIGLU ? WAVES / 2 : WAVES;
+  // Five buffers from one workgroup of a die to its next, where the activations (M rows of K) stay in a die's L2 all the same; else one,
+  // so that neighbours still share them (64 rows: 2 x 28672 x 8192 162 us with five, 169 with one; 8192 x 28672, 3.7 MB, 98 and 89).
+  const int stride = (int64_t)p.M * p.K * 2 <= (3 << 19) ? 5 : 1;
+  const dim3 grid((p.N / 16 + CW - 1) / CW, pl.ksplit);
+  hipLaunchKernelGGL(kern, grid, dim3((WAVES + 1) * 64), lds, st, p, pl.n_slices * (pl.slice / RING_BUF), stride);
+  if (pl.ksplit > 1 && p.n_splits_out) *p.n_splits_out = pl.ksplit;   // the consumer adds the splits
+  else if (pl.ksplit > 1) launch_reduce<EPI>(p, pl.ksplit, st);
+  return 0;
 }
 template <int MB>
-int launch_seq_m(const SkinnyParams &p, int epi, const SeqPlan &pl, hipStream_t st) {
+int launch_ring_m(const SkinnyParams &p, int epi, const RingPlan &pl, hipStream_t st) {
   switch (epi) {
-    case EPI_STORE_BF16: return launch_seq_e<MB, EPI_STORE_BF16>(p, pl, st);
-    case EPI_STORE_F32: return launch_seq_e<MB, EPI_STORE_F32>(p, pl, st);
-    case EPI_RESID: return launch_seq_e<MB, EPI_RESID>(p, pl, st);
-    case EPI_SWIGLU: return launch_seq_e<MB, EPI_SWIGLU>(p, pl, st);
+    case EPI_STORE_BF16: return pl.waves == 8 ? launch_ring_k<MB, EPI_STORE_BF16, 8>(p, pl, st) : launch_ring_k<MB, EPI_STORE_BF16, 4>(p, pl, st);
+    case EPI_STORE_F32: return pl.waves == 8 ? launch_ring_k<MB, EPI_STORE_F32, 8>(p, pl, st) : launch_ring_k<MB, EPI_STORE_F32, 4>(p, pl, st);
+    case EPI_RESID: return pl.waves == 8 ? launch_ring_k<MB, EPI_RESID, 8>(p, pl, st) : launch_ring_k<MB, EPI_RESID, 4>(p, pl, st);
+    case EPI_SWIGLU: return pl.waves == 8 ? launch_ring_k<MB, EPI_SWIGLU, 8>(p, pl, st) : launch_ring_k<MB, EPI_SWIGLU, 4>(p, pl, st);
   }
   return -1;
 }
-int launch_seq(const SkinnyParams &p, int epi, const SeqPlan &pl, hipStream_t st) {
+int launch_ring(const SkinnyParams &p, int epi, const RingPlan &pl, hipStream_t st) {
   switch ((p.M + 15) / 16) {
-    case 1: return launch_seq_m<1>(p, epi, pl, st);
-    case 2: return launch_seq_m<2>(p, epi, pl, st);
-    case 3: return launch_seq_m<3>(p, epi, pl, st);
-    case 4: return launch_seq_m<4>(p, epi, pl, st);
-    default: return launch_seq_m<5>(p, epi, pl, st);
+    case 1: return launch_ring_m<1>(p, epi, pl, st);
+    case 2: return launch_ring_m<2>(p, epi, pl, st);
+    case 3: return launch_ring_m<3>(p, epi, pl, st);
+    case 4: return launch_ring_m<4>(p, epi, pl, st);
+    default: return launch_ring_m<5>(p, epi, pl, st);
   }
 }
 
@@ -677,10 +743,7 @@ int launch_lds_k(const SkinnyParams &p, const LdsPlan &pl, hipStream_t st) {
   const int nblocks = p.N / 16;
   dim3 grid((nblocks + LDS_WAVES * pl.nbw - 1) / (LDS_WAVES * pl.nbw), pl.ksplit);
   hipLaunchKernelGGL(kern, grid, dim3(LDS_WAVES * 64), pl.lds_bytes, st, p, pl.ks_steps, pl.nbw);
-  if (pl.ksplit > 1) {
-    const int64_t quads = (int64_t)p.M * p.N / 4;
-    hipLaunchKernelGGL((skinny_reduce_kernel<EPI>), dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p, pl.ksplit);
-  }
+  if (pl.ksplit > 1) launch_reduce<EPI>(p, pl.ksplit, st);
   return 0;
 }
 template <int EPI>
@@ -714,10 +777,7 @@ int launch_kernels(const SkinnyParams &p, hipStream_t st) {
   dim3 grid(tiles, ksplit), block(SK_WAVES * 64);
   hipLaunchKernelGGL((skinny_kernel<MB, NB, EPI>), grid, block, 0, st, p);
   if (ksplit > 1 && p.n_splits_out) *p.n_splits_out = ksplit;   // the consumer adds the splits
-  else if (ksplit > 1) {
-    const int64_t quads = (int64_t)p.M * p.N / 4;
-    hipLaunchKernelGGL((skinny_reduce_kernel<EPI>), dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p, ksplit);
-  }
+  else if (ksplit > 1) launch_reduce<EPI>(p, ksplit, st);
   return 0;
 }
 
@@ -754,24 +814,29 @@ int launch_wide(const SkinnyParams &p, int epi, hipStream_t st) {
 // more than 5 % there.
 struct SkinnyRoute {
   int kernel;   // SWIFTKV_GEMM_STREAM_*
+  RingPlan ring;
   SeqPlan seq;
   LdsPlan lds;
 };
 SkinnyRoute plan_skinny(const SkinnyParams &p, int epi) {
   SkinnyRoute r{};
-  if (res_fits(p, epi)) { r.kernel = SWIFTKV_GEMM_STREAM_RESIDENT; return r; }
   const int nw = epi == EPI_SWIGLU ? 2 : 1;
-  const bool adds = p.n_splits_out != nullptr;
   const size_t cap = p.partial ? p.partial_bytes : 0;
-  r.seq = plan_seq(p.M, p.N, p.K, nw, adds, cap);
-  r.kernel = r.seq.ok ? SWIFTKV_GEMM_STREAM_SEQ : SWIFTKV_GEMM_STREAM_FIRST;
-  if (p.M > 32 || adds) return r;
+  r.kernel = SWIFTKV_GEMM_STREAM_FIRST;
+  if (p.M > 32 || p.n_splits_out || nw == 2) {
+    // (up to 8 rows of a SwiGLU pair with no more column blocks than CUs the first kernel is ahead, whose workgroups split K among
+    // their waves: one row 2 x 4096 x 4096 15.0 us against 16.2, 2 x 2048 x 2048 7.9 / 8.6)
+    if (nw == 2 && p.M <= 8 && p.N <= 4096) return r;
+    r.ring = plan_ring(p.M, p.N, p.K, nw, p.n_splits_out != nullptr, cap);
+    if (r.ring.ok) r.kernel = SWIFTKV_GEMM_STREAM_SEQ;
+    return r;
+  }
+  r.seq = plan_seq(p.M, p.N, p.K, cap);
   const double wgs = p.N / (16.0 * first_blocks(p, epi));   // of the first kernel
-  const double first = (2.0 * nw * p.N * p.K + 0.68 * wgs * p.M * p.K * 2) * (1 + 0.88 * (std::ceil(wgs / 256) * 256 / wgs - 1)) * 0.913;
+  const double first = (2.0 * p.N * p.K + 0.68 * wgs * p.M * p.K * 2) * (1 + 0.88 * (std::ceil(wgs / 256) * 256 / wgs - 1)) * 0.913;
   double best = first;
-  if (r.seq.ok && r.seq.cost < first) best = r.seq.cost;
-  else r.kernel = SWIFTKV_GEMM_STREAM_FIRST;
-  if (nw == 1 && !p.wtab) r.lds = plan_lds(p.M, p.N, p.K, cap);
+  if (r.seq.ok && r.seq.cost < first) { best = r.seq.cost; r.kernel = SWIFTKV_GEMM_STREAM_SEQ; }
+  if (!p.wtab) r.lds = plan_lds(p.M, p.N, p.K, cap);
   if (r.lds.ok && r.lds.cost < best) r.kernel = SWIFTKV_GEMM_STREAM_SLICE;
   return r;
 }
@@ -782,8 +847,9 @@ GemmRoute route_skinny(const SkinnyParams &p, int epi) {
   const SkinnyRoute r = plan_skinny(p, epi);
   const int nb = first_blocks(p, epi);
   switch (r.kernel) {
-    case SWIFTKV_GEMM_STREAM_RESIDENT: return GemmRoute{r.kernel, RES_WAVES, 1, 0};
-    case SWIFTKV_GEMM_STREAM_SEQ: return GemmRoute{r.kernel, r.seq.waves * r.seq.nbw, r.seq.ksplit, r.seq.ks_steps * 32};
+    case SWIFTKV_GEMM_STREAM_SEQ:
+      if (r.ring.ok) return GemmRoute{r.kernel, r.ring.waves / (epi == EPI_SWIGLU ? 2 : 1), r.ring.ksplit, r.ring.slice};
+      return GemmRoute{r.kernel, r.seq.waves * r.seq.nbw, r.seq.ksplit, r.seq.ks_steps * 32};
     case SWIFTKV_GEMM_STREAM_SLICE: return GemmRoute{r.kernel, LDS_WAVES * r.lds.nbw, r.lds.ksplit, r.lds.ks_steps * 32};
   }
   return GemmRoute{r.kernel, nb, first_splits(p, epi, nb), 0};
@@ -797,8 +863,7 @@ int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
   }
   const SkinnyRoute r = plan_skinny(p, epi);
   switch (r.kernel) {
-    case SWIFTKV_GEMM_STREAM_RESIDENT: return launch_res(p, st);
-    case SWIFTKV_GEMM_STREAM_SEQ: return launch_seq(p, epi, r.seq, st);
+    case SWIFTKV_GEMM_STREAM_SEQ: return r.ring.ok ? launch_ring(p, epi, r.ring, st) : launch_seq(p, epi, r.seq, st);
     case SWIFTKV_GEMM_STREAM_SLICE: return launch_lds(p, epi, r.lds, st);
   }
   if (p.M <= 16) return launch_mb<1, 1>(p, epi, st);
