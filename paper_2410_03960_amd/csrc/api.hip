@@ -476,7 +476,7 @@ int tail_gemm(const swiftkv_ctx *c, const bf16_t *A, int M, int N, int K, const 
   if (epi == EPI_SWIGLU) { g.wtab = gu_tab; g.N = 2 * N; g.ldc = N; }
   else { g.W = W; g.N = N; g.ldc = N; }
   g.partial = partial; g.partial_bytes = SKINNY_PARTIAL_BYTES;
-  if (epi == EPI_RESID) g.n_splits_out = n_splits_out;
+  g.n_splits_out = n_splits_out;
   (void)c;
   return launch_gemm(g, epi, M < 1024 ? 0 : 2, st);
 }
@@ -985,9 +985,9 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   for (int j = c->l; j < m.n_layers; ++j) {
     const int cl = c->l + (j - c->l) / c->g;
     norm_th(c->norm1[j]);
-    if (tail_gemm(c, ta, B, qd, d, c->wq[j], nullptr, nullptr, tq, EPI_STORE_BF16, skp, st)) return fail(SWIFTKV_EHIP, "tail q GEMM failed");
     AttnDecodeParams dp{};
-    dp.q = tq; dp.out = to; dp.rows = (const DecodeRow *)r.meta(r.L.m_tail); dp.n_rows = B;
+    if (tail_gemm(c, ta, B, qd, d, c->wq[j], nullptr, nullptr, tq, EPI_STORE_BF16, skp, st, &dp.q_splits)) return fail(SWIFTKV_EHIP, "tail q GEMM failed");
+    dp.q = tq; dp.q_sums = skp; dp.q_stride = (int64_t)B * qd; dp.out = to; dp.rows = (const DecodeRow *)r.meta(r.L.m_tail); dp.n_rows = B;
     dp.n_q_heads = m.n_q_heads; dp.n_kv_heads = m.n_kv_heads; dp.head_dim = m.head_dim;
     dp.cache_k = r.cache_plane(cl, 0); dp.cache_v = r.cache_plane(cl, 1); dp.fp8 = r.fp8_kind();
     if (r.fp8) { dp.scale_k = r.layer_scales(cl); dp.scale_v = dp.scale_k + (r.per_token ? r.n_slots : (int64_t)m.n_kv_heads); }

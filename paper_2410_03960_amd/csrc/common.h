@@ -111,7 +111,7 @@ struct GemmParams {
   // K splits (launch_gemm_mid): scratch for the splits' partial sums, [split][M][N] fp32, or null (K is never split)
   float *partial;
   size_t partial_bytes;
-  int32_t *n_splits_out;       // HOST, or null.  Given (RESID only), the consumer of C adds the splits: their number goes here
+  int32_t *n_splits_out;       // HOST, or null.  Given (RESID, STORE_BF16), the consumer of C adds the splits: their number goes here
                                // (1 = C is final) and C is untouched when it is larger; null = C is always final
   int32_t n_splits, split_steps;   // set by launch_gemm_mid: K splits and 64-wide k steps of each
 };
@@ -152,7 +152,7 @@ struct SkinnyParams {
   size_t partial_bytes;   // its size; a split whose partial sums would not fit is not taken
   const bf16_t *const *wtab;   // instead of W: device table of N/16 pointers, entry i = rows 16i .. 16i+15 (row stride K),
                                // e.g. [W_Q; W_K; W_V] of a layer as one matrix
-  int32_t *n_splits_out;       // HOST, or null.  Given (STORE_F32 / RESID only), a launch that splits K leaves the sum to its
+  int32_t *n_splits_out;       // HOST, or null.  Given (never with SWIGLU), a launch that splits K leaves the sum to its
                                // consumer: it writes the number of splits here, the splits' sums stay in `partial` as
                                // [split][M][N] fp32 and C is untouched; 1 = nothing left to do (C is final)
 };
@@ -217,6 +217,10 @@ struct DecodeRow {  // one single-query attention problem
 struct AttnDecodeParams {
   const bf16_t *q;  // [*, q_dim]
   bf16_t *out;      // [*, q_dim]
+  // q_splits > 1: instead of q, the fp32 sums of that many K ranges of the projection, q_stride elements apart, [*, q_dim] each; added in order
+  const float *q_sums;
+  int64_t q_stride;
+  int32_t q_splits;
   const DecodeRow *rows;
   int32_t n_rows, n_q_heads, n_kv_heads, head_dim;
   const void *cache_k, *cache_v;  // this cache layer's K and V planes [n_blocks*16][Hkv][hd]
@@ -225,7 +229,7 @@ struct AttnDecodeParams {
   const int32_t *block_tables;
   int32_t max_blocks_per_seq, n_blocks;
   const float2 *cos_sin;  // [T][hd/2]
-  float *partial;         // [n_rows][Hq][n_split][hd + 2]
+  float *partial;         // [n_rows][Hq][n_split][hd + 2] (n_split > 1; one split is the result and goes to `out`)
   int32_t n_split;
   int32_t min_keys;       // least keys of a split (vector-unit kernel; the matrix-unit kernels take whole 128-key steps)
 };

@@ -783,7 +783,7 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float *partia
 }
 int launch_decode_combine(const float *partial, bf16_t *out, const DecodeRow *rows, int32_t n_rows,
                           int32_t n_q_heads, int32_t head_dim, int32_t n_split, hipStream_t st) {
-  if (n_rows <= 0) return 0;
+  if (n_rows <= 0 || n_split == 1) return 0;   // (one split: the attention kernel wrote the result)
   if (n_split > MAX_SPLIT) return -1;
   hipLaunchKernelGGL(decode_combine_kernel, dim3(n_rows, n_q_heads), dim3(head_dim), 0, st, partial, out, rows, n_q_heads, head_dim, n_split);
   return 0;

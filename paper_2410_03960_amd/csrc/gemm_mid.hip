@@ -379,7 +379,7 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   const bool far = (uint64_t)p.M * (uint64_t)p.lda * 2 >= 0xffffffffull;   // beyond the 32-bit row offsets of gemm_mid_kernel (gemm_wreg_kernel has whole pointers)
   if (!packed && (p.M >= 1024 || p.K % 64 != 0 || p.N % 64 != 0 || ((epi == EPI_QKV || epi == EPI_KV) && p.N % 128 != 0))) return best;
   const bool norm_out = epi == EPI_RESID && p.hb && p.ssq;
-  const bool consumer = epi == EPI_RESID && p.n_splits_out;
+  const bool consumer = p.n_splits_out != nullptr;
   const int all_steps = p.K / 64, unit = packed ? 4 : 1;
   const int tiles_n = (p.N + 255) / 256;
   // us per step of a round of up to 256 workgroups (t1); the forms that fit two workgroups to a CU: per 256 of more (t2)
@@ -435,7 +435,7 @@ int launch_gemm_mid(const GemmParams &p0, int epi, const MidPlan &pl, hipStream_
   q.C = p.partial; q.ldc = p.N;
   if (epi != EPI_QKV && epi != EPI_KV) q.head_dim = 0;   // the packed order of rotary operands is theirs alone
   if (int e = launch_one(q, EPI_PARTIAL, pl, st)) return e;
-  if (epi == EPI_RESID && p.n_splits_out) { *p.n_splits_out = pl.n_splits; return 0; }
+  if (p.n_splits_out) { *p.n_splits_out = pl.n_splits; return 0; }
   return launch_splits_finish(p, epi, st);
 }
 

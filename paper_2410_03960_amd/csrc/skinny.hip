@@ -858,7 +858,7 @@ int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0) return 0;
   if (p.M > 80 || (p.N % 16) != 0 || (p.K % 8) != 0) return -1;
   if (p.n_splits_out) {
-    if (epi != EPI_STORE_F32 && epi != EPI_RESID) return -1;
+    if (epi == EPI_SWIGLU) return -1;
     *p.n_splits_out = 1;
   }
   const SkinnyRoute r = plan_skinny(p, epi);
