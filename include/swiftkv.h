@@ -275,7 +275,9 @@ enum {
   SWIFTKV_GEMM_FIVE_STAGE = 6,      /* 256 x 256 tile, five-stage direct-to-LDS loop */
   SWIFTKV_GEMM_PACKED_DMA = 7,      /* fragment-order weights, activations by LDS-DMA */
   SWIFTKV_GEMM_PACKED_REG = 8,      /* fragment-order weights, activations through registers */
-  SWIFTKV_GEMM_ROWS_REG = 9         /* row-major weights, both operands through registers */
+  SWIFTKV_GEMM_ROWS_REG = 9,        /* row-major weights, both operands through registers */
+  SWIFTKV_GEMM_STREAM_TILE = 10     /* 128-column tiles, both operands streamed through LDS (also the products of the last tokens of
+                                       more than 80 sequences, in place of 9) */
 };
 int swiftkv_op_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t flags, int32_t head_dim,
                          size_t scratch_bytes, int32_t plan_out[4]);

@@ -327,7 +327,7 @@ class GemmPlan(NamedTuple):
 
 
 GEMM_KERNELS = {0: "stream_first", 1: "stream_seq", 2: "stream_resident", 3: "stream_slice", 4: "tile_128", 5: "tile_256", 6: "five_stage",
-                7: "packed_dma", 8: "packed_reg", 9: "rows_reg"}
+                7: "packed_dma", 8: "packed_reg", 9: "rows_reg", 10: "stream_tile"}
 GEMM_EPILOGUES = ("bf16", "f32", "resid", "swiglu", "qkv", "kv")
 GEMM_SCRATCH = 16 * 80 * 8192 * 4     # bytes for K splits that swiftkv_prefill and swiftkv_kv_from_hidden have
 

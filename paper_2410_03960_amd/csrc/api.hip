@@ -477,6 +477,7 @@ int tail_gemm(const swiftkv_ctx *c, const bf16_t *A, int M, int N, int K, const 
   else { g.W = W; g.N = N; g.ldc = N; }
   g.partial = partial; g.partial_bytes = SKINNY_PARTIAL_BYTES;
   g.n_splits_out = n_splits_out;
+  g.streamed = 1;
   (void)c;
   return launch_gemm(g, epi, M < 1024 ? 0 : 2, st);
 }

@@ -113,6 +113,7 @@ struct GemmParams {
   size_t partial_bytes;
   int32_t *n_splits_out;       // HOST, or null.  Given (RESID, STORE_BF16), the consumer of C adds the splits: their number goes here
                                // (1 = C is final) and C is untouched when it is larger; null = C is always final
+  int32_t streamed;            // row-major weights of rows that only pass once (the last tokens): gemm_stream_kernel may take them
   int32_t n_splits, split_steps;   // set by launch_gemm_mid: K splits and 64-wide k steps of each
 };
 
@@ -125,11 +126,12 @@ enum MidKernel {
   MID_NONE = 0,    // not a shape of these kernels
   MID_WREG = 1,    // packed weights, activations by LDS-DMA (gemm_wreg.hip)
   MID_PACKED = 2,  // packed weights, activations staged through registers: short tiles, two workgroups per CU
-  MID_ROWS = 3     // row-major weights
+  MID_ROWS = 3,    // row-major weights
+  MID_STREAM = 4   // tiles of 128 columns, weights (either order) and activations by LDS-DMA (gemm_stream.hip)
 };
 struct MidPlan {
   MidKernel kernel;
-  int fm, n_splits, split_steps;   // tile = 32 fm rows x 256 columns; K splits and 64-wide k steps of each
+  int fm, n_splits, split_steps;   // tile = 32 fm rows x 256 columns (MID_STREAM: 128); K splits and 64-wide k steps of each
   double cost;                     // estimated time in us, adding the splits up included
 };
 MidPlan plan_gemm_mid(const GemmParams &p, int epi);
@@ -139,6 +141,7 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi);
 struct GemmRoute { int32_t kernel, tile, n_splits, slice; };
 GemmRoute route_gemm(const GemmParams &p, int epi);
 int launch_gemm_wreg(const GemmParams &p, int epi, int fm, hipStream_t st);
+int launch_gemm_stream(const GemmParams &p, int epi, int fm, bool packed, hipStream_t st);
 [[nodiscard]] int launch_splits_finish(const GemmParams &p, int epi, hipStream_t st);
 
 // skinny (weight-streaming) GEMM for M <= 80 rows

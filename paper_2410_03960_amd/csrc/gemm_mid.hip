@@ -231,6 +231,7 @@ int launch_f(const GemmParams &p, int epi, MidKernel k, hipStream_t st) {
 }
 int launch_one(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st) {
   if (pl.kernel == MID_WREG) return launch_gemm_wreg(p, epi, pl.fm, st);
+  if (pl.kernel == MID_STREAM) return launch_gemm_stream(p, epi, pl.fm, p.wpack != nullptr, st);
   switch (pl.fm) {
     case 2: return launch_f<2>(p, epi, pl.kernel, st);
     case 3: return launch_f<3>(p, epi, pl.kernel, st);
@@ -410,6 +411,36 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
       if (best.kernel == MID_NONE || cost < best.cost) best = MidPlan{f.kernel, f.fm, s, steps, cost};
     }
   }
+  // gemm_stream_kernel: 128-column tiles of 64 to 192 rows, alone on a CU.  A 128-column slice of K takes what its LDS traffic or
+  // the workgroups' share of the weight stream takes (row tiles after the first find most of it in L2); every term fitted to
+  // 5600 timings of 16 products of 81 to 512 rows (median error 5 %).  Rotary operands always leave as partial sums.
+  // What it is worth, us (the forms above -> this one), fragment order: 160 x 28672 x 4096 67 -> 58, 192 x 4096 x 4096 19.2 -> 14.8,
+  // 256 x 3072 x 2048 11.2 -> 9.3, but 256 x 28672 x 4096 68 against 81; row-major: 160 x 28672 x 4096 82 -> 57, 160 x 4096 x
+  // 4096 21 -> 13.5, 160 x 4096 x 14336 39 -> 32, 333 x 8192 x 4096 60 -> 39.
+  if ((packed || p.streamed) && p.M <= 512 && p.K % 128 == 0 && p.N % 32 == 0 && !far && !norm_out && !(packed && epi == EPI_STORE_F32)) {
+    static const double slice_us[] = {0.83, 0.92, 1.09, 1.32, 1.44};
+    const bool rope = epi == EPI_QKV || epi == EPI_KV;
+    const int slices = p.K / 128;
+    // (the fixed part of the packed forms' model is 12 us above what 600 products of these sizes take)
+    const double other = best.kernel == MID_NONE ? 1e30 : packed ? 1.05 * best.cost - 11.5 : best.cost;
+    MidPlan stream{};
+    for (int fm = 2; fm <= 6; ++fm) {
+      const int64_t rows_n = (p.M + 32 * fm - 1) / (32 * fm), tiles = rows_n * ((p.N + 127) / 128);
+      for (int want = 1; want <= std::min(MID_MAX_SPLIT, slices); ++want) {
+        if ((want > 1 || rope) && !p.partial) break;
+        const int per = (slices + want - 1) / want, s = (slices + per - 1) / per;
+        if (s != want) continue;
+        const size_t bytes = s > 1 || rope ? (size_t)s * p.M * p.N * 4 : 0;
+        if (bytes > p.partial_bytes) break;
+        const double wgs = (double)(tiles * s), rounds = std::ceil(wgs / 256);
+        const double hbm_us = std::min(wgs, 256.0) * 32768 * (0.23 + 0.77 / rows_n) / 5.2e6;
+        const double out = bytes ? 1.7 * bytes + (consumer ? 0 : 20e6) : (double)p.M * p.N * (epi == EPI_RESID ? 8 : epi == EPI_STORE_F32 ? 4 : 1);   // at 4 TB/s
+        const double cost = 1.7 + rounds * per * std::max(slice_us[fm - 2], hbm_us) + out / 4.0e6;
+        if (stream.kernel == MID_NONE || cost < stream.cost) stream = MidPlan{MID_STREAM, fm, s, 2 * per, cost};
+      }
+    }
+    if (stream.kernel != MID_NONE && 1.05 * stream.cost < other) return stream;
+  }
   // Row-major weights also have the 128 x 128 tile of gemm.hip (no K splits).  With scratch for splits it keeps up only
   // over many columns.  Without, it is the better one nearly everywhere: a lone workgroup on a CU takes 1.03 us per step,
   // the forms above 1.2 and more, two on one CU 1.31 (us, forms above -> tile: 128 x 8192 x 8192 155 -> 137, 333 x 11008 x
@@ -430,10 +461,11 @@ int launch_gemm_mid(const GemmParams &p0, int epi, const MidPlan &pl, hipStream_
   GemmParams p = p0;
   p.n_splits = pl.n_splits; p.split_steps = pl.split_steps;
   if (p.n_splits_out) *p.n_splits_out = 1;
-  if (pl.n_splits == 1) return launch_one(p, epi, pl, st);
+  const bool rope = epi == EPI_QKV || epi == EPI_KV;
+  if (pl.n_splits == 1 && !(rope && pl.kernel == MID_STREAM)) return launch_one(p, epi, pl, st);
   GemmParams q = p;
   q.C = p.partial; q.ldc = p.N;
-  if (epi != EPI_QKV && epi != EPI_KV) q.head_dim = 0;   // the packed order of rotary operands is theirs alone
+  if (!rope) q.head_dim = 0;   // the packed order of rotary operands is theirs alone
   if (int e = launch_one(q, EPI_PARTIAL, pl, st)) return e;
   if (p.n_splits_out) { *p.n_splits_out = pl.n_splits; return 0; }
   return launch_splits_finish(p, epi, st);
