@@ -417,7 +417,7 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   // What it is worth, us (the forms above -> this one), fragment order: 160 x 28672 x 4096 67 -> 58, 192 x 4096 x 4096 19.2 -> 14.8,
   // 256 x 3072 x 2048 11.2 -> 9.3, but 256 x 28672 x 4096 68 against 81; row-major: 160 x 28672 x 4096 82 -> 57, 160 x 4096 x
   // 4096 21 -> 13.5, 160 x 4096 x 14336 39 -> 32, 333 x 8192 x 4096 60 -> 39.
-  if ((packed || p.streamed) && p.M <= 512 && p.K % 128 == 0 && p.N % 32 == 0 && !far && !norm_out && !(packed && epi == EPI_STORE_F32)) {
+  if ((packed || p.streamed) && p.M < 1024 && p.K % 128 == 0 && p.N % 32 == 0 && !far && !norm_out && !(packed && epi == EPI_STORE_F32)) {
     static const double slice_us[] = {0.83, 0.92, 1.09, 1.32, 1.44};
     const bool rope = epi == EPI_QKV || epi == EPI_KV;
     const int slices = p.K / 128;

@@ -5,8 +5,9 @@
 // skinny_ring_kernel (skinny.hip): everything travels by LDS-DMA in whole 128-byte lines or 1 KB fragments, eight consumer
 // waves each with a ring of its own for the weights, a producer wave for the activations, one barrier per 128
 // columns of K.  Four waves side by side (32 columns each), twice: the two groups take alternate 64-column steps of K and meet in
-// LDS at the end, so that on every SIMD a wave's fragment reads run under the other's products.  The workgroups of a
-// die start at different columns of K (rows 2^13 bytes apart at one column share few memory channels).
+// LDS at the end, so that on every SIMD a wave's fragment reads run under the other's products.
+// Bounds: up to 128 rows the weight stream (128 x 28672 x 4096: 47 us, 5.0 TB/s), above the CU's LDS traffic -- a 128-column
+// slice of 160 rows writes 72 KB and reads 192 KB, 1.0 us at 128 bytes per cycle, and takes 1.3.
 #include "gemm_epilogue.h"
 
 #include <algorithm>
@@ -31,16 +32,25 @@ __global__ __launch_bounds__(9 * 64) void gemm_stream_kernel(GemmParams p) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, g = lane >> 5;
 
-  // Workgroup ids go round the eight dies: each gets a run of (K range, column tile, row tile), so that it needs few K ranges of
-  // the activations and the row tiles of a column tile share its weights in the die's L2.
-  const int tiles_m = (p.M + BM - 1) / BM, tiles = (p.N + 127) / 128 * tiles_m, total = tiles * p.n_splits, per_die = (total + 7) / 8;
-  const int logical = blockIdx.x % 8 * per_die + blockIdx.x / 8;
-  if (logical >= total) return;
-  const int split = logical / tiles, tm = logical % tiles % tiles_m, tn = logical % tiles / tiles_m;
+  // Workgroup ids go round the eight dies.  Without K ranges so do the column tiles (neighbours in memory are read at the same
+  // time; the row tiles of one share a die's L2), and a die's tiles start one slice apart.  With K ranges each die gets a run of
+  // (K range, column tile, row tile), so that it needs few ranges of the activations (160 x 8192 x 28672: 138 -> 105 us; without
+  // ranges the runs cost 2 to 10 %); runs are apart in memory by themselves, row-major ones less so.
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + 127) / 128, tiles = tiles_n * tiles_m;
+  int split = 0, tm, tn, first;
+  if (p.n_splits == 1) {
+    first = blockIdx.x / 8 / tiles_m; tm = blockIdx.x / 8 % tiles_m; tn = first * 8 + blockIdx.x % 8;
+    if (tn >= tiles_n) return;
+  } else {
+    const int total = tiles * p.n_splits, logical = blockIdx.x % 8 * ((total + 7) / 8) + blockIdx.x / 8;
+    if (logical >= total) return;
+    split = logical / tiles; tm = logical % tiles % tiles_m; tn = logical % tiles / tiles_m;
+    first = PACKED ? 0 : tn;
+  }
   const int m0 = tm * BM;
   const int all = p.K / 128, per = p.split_steps / 2, s0 = split * per;
   const int slices = all - s0 < per ? all - s0 : per;   // of 128 columns, >= 1 by the plan
-  const int rot = PACKED ? 0 : tn % slices;
+  const int rot = first % slices;   // slice this workgroup starts with
   typedef __attribute__((address_space(3))) void *lds_ptr_t;
   const unsigned lds_base = (unsigned)(size_t)(lds_ptr_t)lds;
   // a request: 8 rows of 128 bytes; chunk c of row r lies at chunk c ^ ((r >> 1) & 7)
@@ -223,8 +233,9 @@ int launch_k(const GemmParams &p, hipStream_t st) {
     if (hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, st_lds(FM)); e != hipSuccess) return (int)e;
     attr = true;
   }
-  const int total = (p.M + 32 * FM - 1) / (32 * FM) * ((p.N + 127) / 128) * p.n_splits;
-  hipLaunchKernelGGL(kern, dim3((total + 7) / 8 * 8), dim3(9 * 64), st_lds(FM), st, p);
+  const int tiles_m = (p.M + 32 * FM - 1) / (32 * FM), tiles_n = (p.N + 127) / 128;
+  const int dies = p.n_splits == 1 ? (tiles_n + 7) / 8 * tiles_m : (tiles_n * tiles_m * p.n_splits + 7) / 8;   // workgroups of each
+  hipLaunchKernelGGL(kern, dim3(dies * 8), dim3(9 * 64), st_lds(FM), st, p);
   return 0;
 }
 template <int EPI>
