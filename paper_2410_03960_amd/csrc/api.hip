@@ -176,42 +176,28 @@ int check_launch(const char *what) {
 }
 
 // Key splits of the single-query attention over rows of up to max_keys and together sum_keys keys.
-// Vector-unit kernel (min_keys = least keys of a split): about 1024 workgroups (four per CU, all resident at once:
-// measured on 64 rows x 8 KV heads over 2048 keys, 2 splits 118 us, 3 splits 131, 4 splits 125, 1 split 141 per
-// launch), no workgroup walking more than about 2048 keys of the longest row (one long row among short ones would
-// otherwise finish alone), none fewer than 64; where that leaves CUs idle, down to one 32-key iteration (one row over
-// 778 keys: 12 splits 9.6 us, 24 splits 8.6; 4 rows over 150: 2 splits 9.0, 5 splits 7.3).
-// Matrix-unit kernels: about 6 us around the K/V stream at 5.2 TB/s (longer by what an uneven division leaves of the last split)
-// and the longest workgroup's chain of 128-key // steps, which overlap only partly; 3.2 us for every further round of 768 workgroups (three are resident per CU; each starts with
-// three memory latencies in a row); more than one split, the combine launch.  us per launch by splits 1 / 2 / 3 / 4 (combine: 4 more): 64 rows x 8 KV heads x 2048
+// About 6 us around the K/V stream at 5.2 TB/s (longer by what an uneven division leaves of the last split) and the longest
+// workgroup's chain of 128-key steps, which overlap only partly; 3.2 us for every further round of 768 workgroups (three are resident
+// per CU; each starts with three memory latencies in a row); more than one split, the combine launch.  us per launch by
+// splits 1 / 2 / 3 / 4 (combine: 4 more): 64 rows x 8 KV heads x 2048
 // e4m3 keys of 128 dims 54.0 / 57.2 / 57.4 / 60.1, 160 x 900 60.5 / 66.2 / 72.5 / 76.3, 16 x 4096 58.8 / 35.2 / 32.8 / 32.1, 39 rows of 50 to
 // 2050 33.7 / 23.3 / 25.3 / 25.4; bf16, 8 heads per KV head, 24 rows of 200 to 4100 64.6 / 55.5 / 51.2 / 46.8.
-int pick_split(int rows, int n_kv_heads, int head_dim, int max_keys, int64_t sum_keys, bool matrix, bool fp8, int *min_keys) {
-  *min_keys = 128;
+int pick_split(int rows, int n_kv_heads, int head_dim, int max_keys, int64_t sum_keys, bool fp8) {
   const int pairs = rows * n_kv_heads;
-  const double mean = (double)sum_keys / rows;
-  if (matrix) {
-    const double key_bytes = 2.0 * head_dim * (fp8 ? 1 : 2);   // of one KV head
-    const double step_us = 1.1 + 0.45 * key_bytes / 256, stream_us = key_bytes * (double)sum_keys * n_kv_heads / 5.2e6;
-    int best = 1;
-    double best_cost = 0;
-    for (int ns = 1; ns <= std::min(MAX_SPLIT, std::max(1, (max_keys + 127) / 128)); ++ns) {
-      const int steps = (max_keys + 128 * ns - 1) / (128 * ns);
-      const double chain_us = step_us * steps, even_us = stream_us * std::max(1.0, 128.0 * ns * steps / max_keys);
-      const double cost = 6 + std::sqrt(chain_us * chain_us + even_us * even_us) + 3.2 * (std::ceil(pairs * ns / 768.0) - 1) + (ns > 1 ? 4 : 0) + 0.0014 * pairs * (ns - 1);
-      if (ns == 1 || cost < best_cost) { best = ns; best_cost = cost; }
-    }
-    return best;
+  const double key_bytes = 2.0 * head_dim * (fp8 ? 1 : 2);   // of one KV head
+  const double step_us = 1.1 + 0.45 * key_bytes / 256, stream_us = key_bytes * (double)sum_keys * n_kv_heads / 5.2e6;
+  int best = 1;
+  double best_cost = 0;
+  for (int ns = 1; ns <= std::min(MAX_SPLIT, std::max(1, (max_keys + 127) / 128)); ++ns) {
+    const int steps = (max_keys + 128 * ns - 1) / (128 * ns);
+    const double chain_us = step_us * steps, even_us = stream_us * std::max(1.0, 128.0 * ns * steps / max_keys);
+    const double cost = 6 + std::sqrt(chain_us * chain_us + even_us * even_us) + 3.2 * (std::ceil(pairs * ns / 768.0) - 1) + (ns > 1 ? 4 : 0) + 0.0014 * pairs * (ns - 1);
+    if (ns == 1 || cost < best_cost) { best = ns; best_cost = cost; }
   }
-  const int want = (1024 + pairs / 2) / pairs;
-  const int by_len = max_keys > 1.25 * mean ? (max_keys + 1023) / 2048 : 1;   // (rows of one length end together: 64 x 8192 keys, 2 splits 376 us, 4 398)
-  int cap = std::max(1, max_keys / 64);
-  if ((int64_t)pairs * ((max_keys + 31) / 32) <= 256) { cap = (max_keys + 31) / 32; *min_keys = 32; }
-  return std::max(1, std::min({std::max(want, by_len), cap, MAX_SPLIT}));
+  return best;
 }
 void set_split(AttnDecodeParams &p, int max_keys, int64_t sum_keys) {
-  const bool matrix = p.fp8 != 0 || p.n_q_heads / p.n_kv_heads == 8;   // as launch_attention_decode chooses
-  p.n_split = pick_split(p.n_rows, p.n_kv_heads, p.head_dim, max_keys, sum_keys, matrix, p.fp8 != 0, &p.min_keys);
+  p.n_split = pick_split(p.n_rows, p.n_kv_heads, p.head_dim, max_keys, sum_keys, p.fp8 != 0);
 }
 
 struct HostPlan {

@@ -234,7 +234,6 @@ struct AttnDecodeParams {
   const float2 *cos_sin;  // [T][hd/2]
   float *partial;         // [n_rows][Hq][n_split][hd + 2] (n_split > 1; one split is the result and goes to `out`)
   int32_t n_split;
-  int32_t min_keys;       // least keys of a split (vector-unit kernel; the matrix-unit kernels take whole 128-key steps)
 };
 // Most key splits of a single-query row: decode_combine_kernel takes a split per lane of a wave and holds one value of each.
 constexpr int MAX_SPLIT = 32;
