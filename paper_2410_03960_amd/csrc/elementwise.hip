@@ -164,68 +164,71 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_reg_kernel(const float4 *h, 
     out[(int64_t)row * (CH * 64) + i * 64 + lane] =
         make_uint2(pack_bf16x2(u[i].x * f * bf16lo(g[i].x), u[i].y * f * bf16hi(g[i].x)), pack_bf16x2(u[i].z * f * bf16lo(g[i].y), u[i].w * f * bf16hi(g[i].y)));
 }
-// Few rows (decode steps, the tail): one workgroup of four waves per row, d = 1024 * CQ.  With n_splits > 1
+// Few rows (decode steps, the tail): one workgroup per row, d = 256 * WAVES * CQ.  With n_splits > 1
 // the row first takes the sums of the K splits a weight-streaming GEMM left in `partial` ([n_splits][rows][d]
 // fp32): the splits are added in order, then to the row, which is written back.  The sum of squares is added
-// over a lane's values in order, then over the wave, then over the four waves in order.
+// over a lane's values in order, then over the wave, then over the waves in order.
 // SRC: where the row comes from -- h itself; 1: the embedding row of its token id; 2: row idx[row] of another buffer.
 // The latter two leave it in h: the first norm of a pass and of the tail need no launch in front of them that only
 // copies (about 4.5 us each where rows are few; 8831 rows of 4096 from the embedding 70 us in two launches -> 46).
-template <int CQ, int SRC>
-__global__ __launch_bounds__(256) void rmsnorm_row_wg_kernel(float4 *h, const bf16_t *gain, uint2 *out, int rows, float eps, float inv_d,
+template <int CQ, int SRC, int WAVES = 4>
+__global__ __launch_bounds__(WAVES * 64) void rmsnorm_row_wg_kernel(float4 *h, const bf16_t *gain, uint2 *out, int rows, float eps, float inv_d,
                                                              float *rstd_out, const float4 *partial, int n_splits, RowSource rs_in) {
-  __shared__ float red[4];
+  constexpr int TH = WAVES * 64;
+  __shared__ float red[WAVES];
   const int row = blockIdx.x, tid = threadIdx.x;
-  float4 *r = h + (int64_t)row * (CQ * 256);
+  float4 *r = h + (int64_t)row * (CQ * TH);
   float4 u[CQ];
   uint2 g[CQ];
   if constexpr (SRC == 1) {
     int id = rs_in.idx[row];
     id = id < 0 ? 0 : (id >= rs_in.n ? rs_in.n - 1 : id);   // (the plan reported it)
-    const uint2 *e = (const uint2 *)rs_in.rows + (int64_t)id * (CQ * 256) + tid;
+    const uint2 *e = (const uint2 *)rs_in.rows + (int64_t)id * (CQ * TH) + tid;
 #pragma unroll
     for (int i = 0; i < CQ; ++i) {
-      const uint2 x = e[i * 256];
+      const uint2 x = e[i * TH];
       u[i] = make_float4(bf16lo(x.x), bf16hi(x.x), bf16lo(x.y), bf16hi(x.y));
     }
   } else {
-    const float4 *from = SRC == 2 ? (const float4 *)rs_in.rows + (int64_t)rs_in.idx[row] * (CQ * 256) : r;
+    const float4 *from = SRC == 2 ? (const float4 *)rs_in.rows + (int64_t)rs_in.idx[row] * (CQ * TH) : r;
 #pragma unroll
-    for (int i = 0; i < CQ; ++i) u[i] = from[i * 256 + tid];
+    for (int i = 0; i < CQ; ++i) u[i] = from[i * TH + tid];
   }
 #pragma unroll
-  for (int i = 0; i < CQ; ++i) g[i] = gain ? *(const uint2 *)(gain + 4 * (i * 256 + tid)) : make_uint2(0x3f803f80u, 0x3f803f80u);
+  for (int i = 0; i < CQ; ++i) g[i] = gain ? *(const uint2 *)(gain + 4 * (i * TH + tid)) : make_uint2(0x3f803f80u, 0x3f803f80u);
   if (SRC != 0) {
 #pragma unroll
-    for (int i = 0; i < CQ; ++i) r[i * 256 + tid] = u[i];
+    for (int i = 0; i < CQ; ++i) r[i * TH + tid] = u[i];
   } else if (n_splits > 1) {
     float4 sum[CQ];
 #pragma unroll
     for (int i = 0; i < CQ; ++i) sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 *pr = partial + (int64_t)row * (CQ * 256) + tid;
-    const int64_t step = (int64_t)rows * (CQ * 256);
+    const float4 *pr = partial + (int64_t)row * (CQ * TH) + tid;
+    const int64_t step = (int64_t)rows * (CQ * TH);
     int ks = 0;
-    for (; ks + 2 <= n_splits; ks += 2) {   // two splits' loads in flight, added in split order
-      float4 v0[CQ], v1[CQ];
+    constexpr int AT = CQ <= 2 && WAVES > 4 ? 4 : 2;
+    for (; ks + AT <= n_splits; ks += AT) {   // AT splits' loads in flight, added in split order
+      float4 v[AT][CQ];
 #pragma unroll
-      for (int i = 0; i < CQ; ++i) { v0[i] = pr[ks * step + i * 256]; v1[i] = pr[(ks + 1) * step + i * 256]; }
+      for (int j = 0; j < AT; ++j)
 #pragma unroll
-      for (int i = 0; i < CQ; ++i) {
-        sum[i].x += v0[i].x; sum[i].y += v0[i].y; sum[i].z += v0[i].z; sum[i].w += v0[i].w;
-        sum[i].x += v1[i].x; sum[i].y += v1[i].y; sum[i].z += v1[i].z; sum[i].w += v1[i].w;
-      }
+        for (int i = 0; i < CQ; ++i) v[j][i] = pr[(ks + j) * step + i * TH];
+#pragma unroll
+      for (int j = 0; j < AT; ++j)
+#pragma unroll
+        for (int i = 0; i < CQ; ++i) { sum[i].x += v[j][i].x; sum[i].y += v[j][i].y; sum[i].z += v[j][i].z; sum[i].w += v[j][i].w; }
     }
-    if (ks < n_splits) {
+    for (; ks < n_splits; ++ks) {
 #pragma unroll
       for (int i = 0; i < CQ; ++i) {
-        const float4 v = pr[ks * step + i * 256];
+        const float4 v = pr[ks * step + i * TH];
         sum[i].x += v.x; sum[i].y += v.y; sum[i].z += v.z; sum[i].w += v.w;
       }
     }
 #pragma unroll
     for (int i = 0; i < CQ; ++i) {
       u[i].x += sum[i].x; u[i].y += sum[i].y; u[i].z += sum[i].z; u[i].w += sum[i].w;
-      r[i * 256 + tid] = u[i];
+      r[i * TH + tid] = u[i];
     }
   }
   float s = 0.f;
@@ -234,13 +237,15 @@ __global__ __launch_bounds__(256) void rmsnorm_row_wg_kernel(float4 *h, const bf
   s = wave_sum(s);
   if ((tid & 63) == 0) red[tid >> 6] = s;
   __syncthreads();
-  s = ((red[0] + red[1]) + red[2]) + red[3];
+  s = red[0];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) s += red[w];
   const float rs = rsqrtf(s * inv_d + eps);
   if (rstd_out && tid == 0) rstd_out[row] = rs;
   const float f = rstd_out ? 1.f : rs;
 #pragma unroll
   for (int i = 0; i < CQ; ++i)
-    out[(int64_t)row * (CQ * 256) + i * 256 + tid] =
+    out[(int64_t)row * (CQ * TH) + i * TH + tid] =
         make_uint2(pack_bf16x2(u[i].x * f * bf16lo(g[i].x), u[i].y * f * bf16hi(g[i].x)), pack_bf16x2(u[i].z * f * bf16lo(g[i].y), u[i].w * f * bf16hi(g[i].y)));
 }
 // the K-split sums of a weight-streaming GEMM added into fp32 rows (for row widths the kernel above does not cover)
@@ -288,6 +293,20 @@ int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows,
   const dim3 grid((rows + 3) / 4), block(256);
   const float inv_d = 1.0f / (float)d;
   if ((rows <= 256 || n_splits > 1) && d % 1024 == 0 && d / 1024 <= 8) {   // few rows, or K splits to add on the way: a workgroup per row
+    // Bound by the latency of its loads, not by their bytes: up to 1024 rows (four workgroups per CU) one or two float4 per
+    // thread and split, four splits in flight, instead of four waves with d / 1024 float4 and two splits (us, before -> now,
+    // K ranges as the product in front leaves them: 24 rows of 8192 9.6 -> 5.1, 597 of 2048 8.0 -> 6.1, 64 of 4096 4.9 ->
+    // 4.8).  Beyond, four waves: more rows than the CUs hold workgroups keep as many loads in flight.
+#define SKV_RMS_WIDE(D_, CQ_)                                                                                      \
+  case D_ / 1024:                                                                                                  \
+    hipLaunchKernelGGL((rmsnorm_row_wg_kernel<CQ_, 0, D_ / 256 / CQ_>), dim3(rows), dim3(D_ / 4 / CQ_), 0, st, (float4 *)h, gain, (uint2 *)out, rows, \
+                       eps, inv_d, rstd_out, (const float4 *)partial, n_splits, RowSource{});                      \
+    return 0;
+    if (rows <= 1024) switch (d / 1024) {
+      SKV_RMS_WIDE(2048, 1) SKV_RMS_WIDE(3072, 1) SKV_RMS_WIDE(4096, 1) SKV_RMS_WIDE(5120, 2) SKV_RMS_WIDE(6144, 2) SKV_RMS_WIDE(7168, 2) SKV_RMS_WIDE(8192, 2)
+      default: break;
+    }
+#undef SKV_RMS_WIDE
 #define SKV_RMS_WG(CQ_)                                                                                            \
   case CQ_:                                                                                                        \
     hipLaunchKernelGGL((rmsnorm_row_wg_kernel<CQ_, 0>), dim3(rows), block, 0, st, (float4 *)h, gain, (uint2 *)out, rows, eps, inv_d, rstd_out, \

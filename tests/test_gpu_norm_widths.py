@@ -1,0 +1,33 @@
+"""Row norms that add up the K ranges of the residual product in front of them, at every width that
+has a workgroup shape of its own, on few rows and beyond 80; against the oracle."""
+import pytest
+
+import workloads as WL
+from oracle import swiftkv_oracle as O
+from tests import gpu_helpers as G
+from tests.test_gpu_configs import MFMA_INPUTS, SLACK
+from tests.helpers import rel_err
+from workloads.configs import ModelShape, Workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lens", [[3, 1], [100, 7]], ids=str)
+@pytest.mark.parametrize("hidden", [1024, 2048, 3072, 4096, 5120, 6144, 7168, 8192])
+def test_norm_behind_split_products(hidden, lens):
+    from paper_2410_03960_amd import binding as B
+    rows = sum(lens)
+    assert B.op_gemm_plan("resid", rows, hidden, 4096, packed=rows > 80, consumer_adds=True).n_splits > 1     # the down product
+    wl = Workload(f"norm{hidden}", ModelShape(3, hidden, 4, 2, 128, 4096, 256, 1e4, 1e-5), l=2, g=1, seed=2801)
+    store = WL.make_weights(wl, "cpu", keep=True)
+    batch = WL.build_batch(wl, lens=lens, shuffled=True)
+    logits, cache, _ = G.run_gpu(B.Context(wl.shape, G.device_weights(store), wl.l, wl.g), batch)
+    ologits, ocache, _ = G.run_oracle(wl.shape, store, batch, wl.l, wl.g)
+    G.compare_caches(cache, ocache, batch, rel=G.BF16_REL, cos=G.BF16_COS, label=wl.name)
+    # logits: the stated bar, or 1.25 times what rounding the matrix inputs of the oracle to bf16 costs (2.1e-2 at 8192 and 107 rows)
+    rounded = O.PagedKVCache(O.n_cache_layers(3, wl.l, wl.g), batch.n_blocks, 2, 128, batch.block_tables)
+    floor, _ = O.swiftkv_prefill(G.oracle_shape(wl.shape), G.weight_fn(store), batch.token_ids, batch.seq_lens.tolist(),
+                                 batch.context_lens.tolist(), wl.l, wl.g, rounded, act_round=MFMA_INPUTS)
+    for b in range(len(lens)):
+        assert rel_err(logits[b].cpu(), ologits[b]) <= max(G.BF16_REL, SLACK * rel_err(floor[b], ologits[b]))
+    G.compare_logits(logits, ologits, rel=1.0, cos=G.BF16_COS, label=wl.name)
