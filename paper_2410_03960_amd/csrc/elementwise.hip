@@ -785,7 +785,7 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float *partia
   for (int c = 0; c < MAX_SPLIT / 8; ++c)
     if (c * 8 < n_split) {
 #pragma unroll
-      for (int i = c * 8; i < c * 8 + 8; ++i) ov[i] = base[(i < n_split ? i : n_split - 1) * (hd + 2) + d];
+      for (int i = c * 8; i < c * 8 + 8; ++i) ov[i] = i < n_split ? base[i * (hd + 2) + d] : 0.f;   // (0: what weighs nothing must not be infinite)
     }
   if (lane >= n_split) mv = -INFINITY;
   const float m = wave_max(mv);
