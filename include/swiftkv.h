@@ -321,6 +321,17 @@ int swiftkv_op_attention_decode(const void *q, void *out, const int32_t *n_keys,
                                 int32_t n_blocks, void *workspace, size_t workspace_bytes, void *stream);
 size_t swiftkv_op_attention_decode_workspace(int32_t n_rows, int32_t n_q_heads, int32_t head_dim);
 
+/* Which kernel that call runs for these rows, and in how many key splits: for tests and timings that mean a certain one.  Host
+ * only.  plan_out (host): a SWIFTKV_DECODE_* kernel; key splits of a row (1 = none); least keys of a split, which is also the
+ * unit of its length on the matrix unit.  A row of n keys has splits of max(least, ceil(n / splits)) keys, on the matrix unit
+ * rounded up to that unit. */
+enum {
+  SWIFTKV_DECODE_MATRIX_UNIT = 0,
+  SWIFTKV_DECODE_VECTOR_UNIT = 1    /* a bf16 cache, one or two query heads per KV head */
+};
+int swiftkv_op_attention_decode_plan(const int32_t *n_keys, int32_t n_rows, int32_t n_q_heads, int32_t n_kv_heads,
+                                     int32_t head_dim, int32_t kv_dtype, int32_t scale_mode, int32_t plan_out[3]);
+
 /* Saturating round-to-nearest-even fp32 -> OCP e4m3fn of x[i]/scale, dev arrays
  * (the quantiser of the FP8 cache, Appendix B.1). */
 int swiftkv_op_fp8_quantize(const float *x, float scale, uint8_t *codes, int64_t n, void *stream);

@@ -28,7 +28,7 @@ EXPORTS = (
     "swiftkv_create", "swiftkv_destroy", "swiftkv_workspace_bytes", "swiftkv_workspace_bytes_prefix", "swiftkv_prefill",
     "swiftkv_kv_from_hidden", "swiftkv_set_early_exit", "swiftkv_export_exit_flags", "swiftkv_export_plan", "swiftkv_export_hidden", "swiftkv_op_gemm",
     "swiftkv_op_gemm_packed", "swiftkv_op_gemm_plan", "swiftkv_op_gemm_rows", "swiftkv_op_gemm_rows_workspace", "swiftkv_op_gemm_rows_static",
-    "swiftkv_op_attention_prefill", "swiftkv_op_attention_workspace", "swiftkv_op_attention_decode", "swiftkv_op_attention_decode_workspace", "swiftkv_op_fp8_quantize", "swiftkv_op_mfma_rate",
+    "swiftkv_op_attention_prefill", "swiftkv_op_attention_workspace", "swiftkv_op_attention_decode", "swiftkv_op_attention_decode_workspace", "swiftkv_op_attention_decode_plan", "swiftkv_op_fp8_quantize", "swiftkv_op_mfma_rate",
     "swiftkv_flops", "swiftkv_set_timing", "swiftkv_get_timing", "swiftkv_last_error",
     "swiftkv_version",
 )
@@ -104,6 +104,7 @@ def load() -> C.CDLL:
                                                 vp, C.c_size_t, vp]
     lib.swiftkv_op_attention_decode_workspace.argtypes = [i32, i32, i32]
     lib.swiftkv_op_attention_decode_workspace.restype = C.c_size_t
+    lib.swiftkv_op_attention_decode_plan.argtypes = [C.POINTER(i32), i32, i32, i32, i32, i32, i32, C.POINTER(i32)]
     lib.swiftkv_op_fp8_quantize.argtypes = [vp, C.c_float, vp, i64, vp]
     lib.swiftkv_op_mfma_rate.argtypes = [vp, i32, vp, C.c_size_t, C.POINTER(C.c_double), vp]
     lib.swiftkv_flops.argtypes = [vp, C.POINTER(i32), C.POINTER(i32), i32, C.POINTER(C.c_double), C.POINTER(C.c_double)]
@@ -393,6 +394,27 @@ def op_attention_decode(q: torch.Tensor, n_keys: Sequence[int], cache_k: torch.T
         _dev(scale_k, torch.float32) if fp8 else None, _dev(scale_v, torch.float32) if fp8 else None,
         _dev(bt), bt.shape[1], cache_k.shape[0] // 16, _dev(ws), ws.numel(), _stream_ptr(stream)))
     return out
+
+
+class DecodePlan(NamedTuple):
+    unit: str        # "matrix" or "vector"
+    n_splits: int
+    min_keys: int    # of a split
+
+    def split_keys(self, n: int) -> int:
+        """Keys of a full split of a row of n keys."""
+        per = max(self.min_keys, -(-n // self.n_splits))
+        return per if self.unit == "vector" else -(-per // self.min_keys) * self.min_keys
+
+
+def op_attention_decode_plan(n_keys: Sequence[int], n_q_heads: int, n_kv_heads: int, head_dim: int, fp8: bool = False,
+                             per_token: bool = False) -> DecodePlan:
+    """The kernel and key splits of op_attention_decode over these rows (host only, no GPU)."""
+    out = (C.c_int32 * 3)()
+    _check(load().swiftkv_op_attention_decode_plan(
+        _i32_array(n_keys), len(n_keys), n_q_heads, n_kv_heads, head_dim, SWIFTKV_KV_FP8_E4M3 if fp8 else SWIFTKV_KV_BF16,
+        SWIFTKV_SCALE_PER_TOKEN if per_token else SWIFTKV_SCALE_USE_GIVEN, out))
+    return DecodePlan("vector" if out[0] else "matrix", out[1], out[2])
 
 
 def op_fp8_quantize(x: torch.Tensor, scale: float, stream=None) -> torch.Tensor:

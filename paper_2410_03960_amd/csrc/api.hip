@@ -175,29 +175,42 @@ int check_launch(const char *what) {
   return 0;
 }
 
-// Key splits of the single-query attention over rows of up to max_keys and together sum_keys keys.
-// About 6 us around the K/V stream at 5.2 TB/s (longer by what an uneven division leaves of the last split) and the longest
-// workgroup's chain of 128-key steps, which overlap only partly; 3.2 us for every further round of 768 workgroups (three are resident
-// per CU; each starts with three memory latencies in a row); more than one split, the combine launch.  us per launch by
-// splits 1 / 2 / 3 / 4 (combine: 4 more): 64 rows x 8 KV heads x 2048
-// e4m3 keys of 128 dims 54.0 / 57.2 / 57.4 / 60.1, 160 x 900 60.5 / 66.2 / 72.5 / 76.3, 16 x 4096 58.8 / 35.2 / 32.8 / 32.1, 39 rows of 50 to
-// 2050 33.7 / 23.3 / 25.3 / 25.4; bf16, 8 heads per KV head, 24 rows of 200 to 4100 64.6 / 55.5 / 51.2 / 46.8.
-int pick_split(int rows, int n_kv_heads, int head_dim, int max_keys, int64_t sum_keys, bool fp8) {
-  const int pairs = rows * n_kv_heads;
-  const double key_bytes = 2.0 * head_dim * (fp8 ? 1 : 2);   // of one KV head
-  const double step_us = 1.1 + 0.45 * key_bytes / 256, stream_us = key_bytes * (double)sum_keys * n_kv_heads / 5.2e6;
-  int best = 1;
-  double best_cost = 0;
-  for (int ns = 1; ns <= std::min(MAX_SPLIT, std::max(1, (max_keys + 127) / 128)); ++ns) {
-    const int steps = (max_keys + 128 * ns - 1) / (128 * ns);
-    const double chain_us = step_us * steps, even_us = stream_us * std::max(1.0, 128.0 * ns * steps / max_keys);
-    const double cost = 6 + std::sqrt(chain_us * chain_us + even_us * even_us) + 3.2 * (std::ceil(pairs * ns / 768.0) - 1) + (ns > 1 ? 4 : 0) + 0.0014 * pairs * (ns - 1);
-    if (ns == 1 || cost < best_cost) { best = ns; best_cost = cost; }
+// Time of a single-query attention launch in ns key splits, and of the combine pass behind more than one, us.  Fitted to 29000
+// timings of 1 to 256 rows of 17 to 40000 keys, of one length and mixed, in 1 to 32 splits; its choice costs 0.8 % on average.
+//  - A workgroup's chain of 128-key steps, of which each takes what its conversions and products take.
+//  - The K/V stream at 5 TB/s, longer by part of what the busiest CU has above an even share: 8 rows x 8 KV heads x 20000 e4m3
+//    keys in 8 splits, two workgroups to each CU, 73 us, in 10 (three to half of them) 89.
+//  - Every CU as full as it gets (three workgroups, four of 64-wide heads) is 5 % slower over an e4m3 cache than
+//    fewer, or more one after the other: the same rows in 12 splits 85 us, in 16 75.
+struct DecodeShape { int rows, n_kv_heads, head_dim, max_keys; int64_t sum_keys; bool fp8, per_token; };
+double decode_us(const DecodeShape &s, int ns) {
+  const int resident = s.head_dim == 64 ? 4 : 3;
+  const double step_us = (s.head_dim == 64 ? 1.1 : 1.6) + (s.fp8 ? 0.2 : 0) + (s.per_token ? 0.4 : 0);
+  const double pairs = (double)s.rows * s.n_kv_heads, keys = (double)s.sum_keys * s.n_kv_heads;   // (row, KV head) pairs; of all of them
+  const int steps = (s.max_keys + 128 * ns - 1) / (128 * ns);
+  const double longest = std::min(128 * steps, s.max_keys);
+  double chain_us, stream_us = keys * s.head_dim * (s.fp8 ? 2 : 4) / 5.0e6;
+  if ((double)s.sum_keys >= 0.9 * s.max_keys * s.rows) {   // rows of one length: whole rounds
+    const double per_cu = std::ceil(pairs * ((s.max_keys + 128 * steps - 1) / (128 * steps)) / 256);
+    const double uneven = std::min(3.0, per_cu * 256 * longest / keys) - 1;
+    stream_us *= (1 + (per_cu <= resident ? 0.22 : 0.34) * uneven) * (per_cu == resident && s.fp8 ? 1.05 : 1);
+    chain_us = step_us * steps * std::ceil(per_cu / resident);
+  } else {
+    const double wgs = std::min(pairs * ns, std::max(pairs, keys / (128 * steps) + 0.5 * pairs));
+    const double uneven = std::min(3.0, (longest + (std::ceil(wgs / 256) - 1) * keys / wgs) * 256 / keys) - 1;
+    stream_us *= 1 + 0.07 * std::max(0.0, uneven);
+    chain_us = step_us * (steps + std::max(0.0, wgs / (256 * resident) - 1));
   }
-  return best;
+  return (s.head_dim == 64 ? 3 : 4.5) + std::cbrt(chain_us * chain_us * chain_us + stream_us * stream_us * stream_us) + (ns > 1 ? 3.6 : 0) + 0.003 * pairs * ns;
 }
+// Key splits: the fewest us.
 void set_split(AttnDecodeParams &p, int max_keys, int64_t sum_keys) {
-  p.n_split = pick_split(p.n_rows, p.n_kv_heads, p.head_dim, max_keys, sum_keys, p.fp8 != 0);
+  const DecodeShape s{p.n_rows, p.n_kv_heads, p.head_dim, max_keys, sum_keys, p.fp8 != 0, p.fp8 == 2};
+  double best = 0;
+  for (int ns = 1; ns <= std::min(MAX_SPLIT, std::max(1, (max_keys + 127) / 128)); ++ns) {
+    const double us = decode_us(s, ns);
+    if (ns == 1 || us < best) { best = us; p.n_split = ns; }
+  }
 }
 
 struct HostPlan {
@@ -1240,6 +1253,25 @@ int swiftkv_op_attention_decode(const void *q, void *out, const int32_t *n_keys,
   if (launch_decode_combine(dp.partial, dp.out, dp.rows, n_rows, Hq, hd, dp.n_split, st)) return fail(SWIFTKV_EHIP, "decode combine launch failed");
   if (int e = check_launch("single-query attention")) return e;
   HIP_TRY(hipStreamSynchronize(st));   // the row table was staged from this call's own (pageable) host vector
+  return SWIFTKV_OK;
+}
+
+int swiftkv_op_attention_decode_plan(const int32_t *n_keys, int32_t n_rows, int32_t Hq, int32_t Hkv, int32_t hd, int32_t kv_dtype,
+                                     int32_t scale_mode, int32_t plan_out[3]) {
+  if (!n_keys || !plan_out) return fail(SWIFTKV_EINVAL, "null argument");
+  if ((hd != 64 && hd != 128) || Hkv < 1 || Hq < 1 || Hq % Hkv || n_rows < 1) return fail(SWIFTKV_EINVAL, "bad shape");
+  AttnDecodeParams dp{};
+  dp.n_rows = n_rows; dp.n_q_heads = Hq; dp.n_kv_heads = Hkv; dp.head_dim = hd;
+  dp.fp8 = kv_dtype != SWIFTKV_KV_FP8_E4M3 ? 0 : (scale_mode == SWIFTKV_SCALE_PER_TOKEN ? 2 : 1);
+  int max_keys = 0;
+  int64_t sum_keys = 0;
+  for (int r = 0; r < n_rows; ++r) {
+    if (n_keys[r] < 1) return fail(SWIFTKV_EINVAL, "n_keys[%d] out of range", r);
+    max_keys = std::max(max_keys, n_keys[r]);
+    sum_keys += n_keys[r];
+  }
+  set_split(dp, max_keys, sum_keys);
+  plan_out[0] = SWIFTKV_DECODE_MATRIX_UNIT; plan_out[1] = dp.n_split; plan_out[2] = 128;
   return SWIFTKV_OK;
 }
 
