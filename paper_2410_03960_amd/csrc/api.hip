@@ -175,42 +175,76 @@ int check_launch(const char *what) {
   return 0;
 }
 
-// Time of a single-query attention launch in ns key splits, and of the combine pass behind more than one, us.  Fitted to 29000
-// timings of 1 to 256 rows of 17 to 40000 keys, of one length and mixed, in 1 to 32 splits; its choice costs 0.8 % on average.
+// Time of a launch of the matrix-unit single-query attention in ns key splits, and of the combine pass behind more than one, us.
+// Rows of one length, fitted to 17000 timings of 1 to 256 rows of 17 to 40000 keys (its choice costs 0.5 % on average):
 //  - A workgroup's chain of 128-key steps, of which each takes what its conversions and products take.
 //  - The K/V stream at 5 TB/s, longer by part of what the busiest CU has above an even share: 8 rows x 8 KV heads x 20000 e4m3
 //    keys in 8 splits, two workgroups to each CU, 73 us, in 10 (three to half of them) 89.
 //  - Every CU as full as it gets (three workgroups, four of 64-wide heads) is 5 % slower over an e4m3 cache than
 //    fewer, or more one after the other: the same rows in 12 splits 85 us, in 16 75.
+// Mixed lengths: 6 us around the stream (longer by what an uneven division leaves of the last split) and the longest row's chain;
+// 3.2 us for every further round of 768 workgroups (39 rows of 50 to 2050 e4m3 keys in 1 / 2 / 3 / 4 splits 33.7 / 23.3 / 25.3 /
+// 25.4; bf16, 8 heads per KV head, 24 rows of 200 to 4100 64.6 / 55.5 / 51.2 / 46.8).
 struct DecodeShape { int rows, n_kv_heads, head_dim, max_keys; int64_t sum_keys; bool fp8, per_token; };
-double decode_us(const DecodeShape &s, int ns) {
+bool one_length(const DecodeShape &s) { return (double)s.sum_keys >= 0.9 * s.max_keys * s.rows; }
+double matrix_us(const DecodeShape &s, int ns) {
+  const double pairs = (double)s.rows * s.n_kv_heads, keys = (double)s.sum_keys * s.n_kv_heads;   // (row, KV head) pairs; of all of them
+  const double key_bytes = s.head_dim * (s.fp8 ? 2 : 4);
+  const int steps = (s.max_keys + 128 * ns - 1) / (128 * ns);
+  if (!one_length(s)) {
+    const double chain_us = (1.1 + 0.45 * key_bytes / 256) * steps, stream_us = key_bytes * keys / 5.2e6 * std::max(1.0, 128.0 * ns * steps / s.max_keys);
+    return 6 + std::sqrt(chain_us * chain_us + stream_us * stream_us) + 3.2 * (std::ceil(pairs * ns / 768) - 1) + (ns > 1 ? 4 : 0) + 0.0014 * pairs * (ns - 1);
+  }
   const int resident = s.head_dim == 64 ? 4 : 3;
   const double step_us = (s.head_dim == 64 ? 1.1 : 1.6) + (s.fp8 ? 0.2 : 0) + (s.per_token ? 0.4 : 0);
-  const double pairs = (double)s.rows * s.n_kv_heads, keys = (double)s.sum_keys * s.n_kv_heads;   // (row, KV head) pairs; of all of them
-  const int steps = (s.max_keys + 128 * ns - 1) / (128 * ns);
-  const double longest = std::min(128 * steps, s.max_keys);
-  double chain_us, stream_us = keys * s.head_dim * (s.fp8 ? 2 : 4) / 5.0e6;
-  if ((double)s.sum_keys >= 0.9 * s.max_keys * s.rows) {   // rows of one length: whole rounds
-    const double per_cu = std::ceil(pairs * ((s.max_keys + 128 * steps - 1) / (128 * steps)) / 256);
-    const double uneven = std::min(3.0, per_cu * 256 * longest / keys) - 1;
-    stream_us *= (1 + (per_cu <= resident ? 0.22 : 0.34) * uneven) * (per_cu == resident && s.fp8 ? 1.05 : 1);
-    chain_us = step_us * steps * std::ceil(per_cu / resident);
-  } else {
-    const double wgs = std::min(pairs * ns, std::max(pairs, keys / (128 * steps) + 0.5 * pairs));
-    const double uneven = std::min(3.0, (longest + (std::ceil(wgs / 256) - 1) * keys / wgs) * 256 / keys) - 1;
-    stream_us *= 1 + 0.07 * std::max(0.0, uneven);
-    chain_us = step_us * (steps + std::max(0.0, wgs / (256 * resident) - 1));
-  }
-  return (s.head_dim == 64 ? 3 : 4.5) + std::cbrt(chain_us * chain_us * chain_us + stream_us * stream_us * stream_us) + (ns > 1 ? 3.6 : 0) + 0.003 * pairs * ns;
+  const double per_cu = std::ceil(pairs * ((s.max_keys + 128 * steps - 1) / (128 * steps)) / 256);   // workgroups of the busiest CU
+  const double uneven = std::min(3.0, per_cu * 256 * std::min(128 * steps, s.max_keys) / keys) - 1;
+  const double chain_us = step_us * steps * std::ceil(per_cu / resident);
+  const double stream_us = key_bytes * keys / 5.0e6 * (1 + (per_cu <= resident ? 0.22 : 0.34) * uneven) * (per_cu == resident && s.fp8 ? 1.05 : 1);
+  return 4.5 + std::cbrt(chain_us * chain_us * chain_us + stream_us * stream_us * stream_us) + (ns > 1 ? 3.6 : 0) + 0.003 * pairs * ns;
 }
-// Key splits: the fewest us.
+// The vector-unit kernel over a bf16 cache: about 1024 workgroups (four per CU, all resident at once: 64 rows x 8 KV heads over 2048 keys
+// of four query heads 2 splits 118 us, 3 splits 131, 4 splits 125, 1 split 141), no workgroup walking more than about 2048 keys of the
+// longest row (one long row among short ones would otherwise finish alone), none fewer than 64; where that leaves
+// CUs idle, down to one 32-key step (one row over 778 keys: 12 splits 9.6 us, 24 splits 8.6; 4 rows over 150: 2 splits 9.0, 5
+// splits 7.3).
+int vector_split(const DecodeShape &s, int *min_keys) {
+  const int pairs = s.rows * s.n_kv_heads, want = (1024 + pairs / 2) / pairs, by_len = (s.max_keys + 1023) / 2048;
+  int cap = std::max(1, s.max_keys / 64);
+  *min_keys = 128;
+  if ((int64_t)pairs * ((s.max_keys + 31) / 32) <= 256) { cap = (s.max_keys + 31) / 32; *min_keys = 32; }
+  return std::max(1, std::min({std::max(want, by_len), cap, MAX_SPLIT}));
+}
+// ... and its time, as above (median error 3 %): a chain of 32-key steps, of 64 keys of 64-wide heads.
+double vector_us(const DecodeShape &s, int heads, int ns, int min_keys) {
+  const int keys_of_step = s.head_dim == 64 ? 64 : 32, per = std::min(s.max_keys, std::max(min_keys, (s.max_keys + ns - 1) / ns));
+  const double pairs = (double)s.rows * s.n_kv_heads, keys = (double)s.sum_keys * s.n_kv_heads;
+  const bool even = one_length(s);
+  const double wgs = even ? pairs * ((s.max_keys + per - 1) / per) : std::min(pairs * ns, std::max(pairs, keys / per + 0.5 * pairs));
+  const double per_cu = std::ceil(wgs / 256), uneven = std::min(3.0, (per + (per_cu - 1) * (even ? per : keys / wgs)) * 256 / keys) - 1;
+  const double stream_us = keys * s.head_dim * 4 / 6.0e6 * (1 + (even ? 0.13 : 0.43) * std::max(0.0, uneven));
+  const double chain_us = (1.11 + 0.06 * heads) * ((per + keys_of_step - 1) / keys_of_step) * std::max(1.0, per_cu / 8);
+  return 1.3 + 1.36 * heads + std::cbrt(chain_us * chain_us * chain_us + stream_us * stream_us * stream_us) + (ns > 1 ? 3.6 : 0) + 0.001 * pairs * ns;
+}
+// Kernel and key splits.  One query head per KV head over a bf16 cache, or two 128-wide ones: either unit, by the modelled time (the
+// matrix unit's model is above its times by the factors below).  A step of the matrix unit costs the same whatever the heads, but
+// starts later and comes in 128 keys.  us with the combine pass, vector unit / matrix unit, one head of 128: one row x 778
+// keys 7.8 / 9.8, 200 x 40 (32 KV heads) 30.8 / 49, 8 x 500..4000 23.6 / 28.7; 16 x 100 10.7 / 5.9, 64 x 300 20.8 / 18.4, one x 20000 31.6
+// / 21.9.  Two 64-wide heads: the matrix unit, 0.71 of the vector unit's time over 203 shapes (slower by more than 3 % in 5).
 void set_split(AttnDecodeParams &p, int max_keys, int64_t sum_keys) {
   const DecodeShape s{p.n_rows, p.n_kv_heads, p.head_dim, max_keys, sum_keys, p.fp8 != 0, p.fp8 == 2};
   double best = 0;
   for (int ns = 1; ns <= std::min(MAX_SPLIT, std::max(1, (max_keys + 127) / 128)); ++ns) {
-    const double us = decode_us(s, ns);
+    const double us = matrix_us(s, ns);
     if (ns == 1 || us < best) { best = us; p.n_split = ns; }
   }
+  const int heads = p.n_q_heads / p.n_kv_heads;
+  if (p.fp8 || heads > (p.head_dim == 64 ? 1 : 2)) return;
+  int min_keys;
+  const int ns = vector_split(s, &min_keys);
+  const double above = p.head_dim == 64 ? (one_length(s) ? 1.2 : 1.3) : heads == 1 ? 1.1 : 1.05;
+  if (best < above * vector_us(s, heads, ns, min_keys)) return;
+  p.vector_unit = 1; p.n_split = ns; p.min_keys = min_keys;
 }
 
 struct HostPlan {
@@ -1271,7 +1305,8 @@ int swiftkv_op_attention_decode_plan(const int32_t *n_keys, int32_t n_rows, int3
     sum_keys += n_keys[r];
   }
   set_split(dp, max_keys, sum_keys);
-  plan_out[0] = SWIFTKV_DECODE_MATRIX_UNIT; plan_out[1] = dp.n_split; plan_out[2] = 128;
+  plan_out[0] = dp.vector_unit ? SWIFTKV_DECODE_VECTOR_UNIT : SWIFTKV_DECODE_MATRIX_UNIT;
+  plan_out[1] = dp.n_split; plan_out[2] = dp.vector_unit ? dp.min_keys : 128;
   return SWIFTKV_OK;
 }
 

@@ -234,6 +234,8 @@ struct AttnDecodeParams {
   const float2 *cos_sin;  // [T][hd/2]
   float *partial;         // [n_rows][Hq][n_split][hd + 2] (n_split > 1; one split is the result and goes to `out`)
   int32_t n_split;
+  int32_t vector_unit;    // a bf16 cache with one or two query heads per KV head on the vector unit, splits of at least min_keys keys
+  int32_t min_keys;       // (the matrix-unit kernels take whole 128-key steps)
 };
 // Most key splits of a single-query row: decode_combine_kernel takes a split per lane of a wave and holds one value of each.
 constexpr int MAX_SPLIT = 32;
