@@ -413,15 +413,18 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   }
   // gemm_stream_kernel: 128-column tiles of 64 to 192 rows, alone on a CU.  A 128-column slice of K takes what its LDS traffic or
   // the workgroups' share of the weight stream takes (row tiles after the first find most of it in L2); every term fitted to
-  // 5600 timings of 16 products of 81 to 512 rows (median error 5 %).  Rotary operands always leave as partial sums.
+  // 5600 timings of 16 products of 81 to 512 rows (median error 5 %).  Rotary operands always leave as partial sums, so a form that
+  // needs no K ranges and no second pass keeps them (700 x 4096 x 2048, K and V of 8 layers: 35.4 us a call, 38.8 here; 130 x
+  // 8192 x 1024 24.2 and 27.5; with K ranges in the other form this one was ahead in all of 57 products).
   // What it is worth, us (the forms above -> this one), fragment order: 160 x 28672 x 4096 67 -> 58, 192 x 4096 x 4096 19.2 -> 14.8,
   // 256 x 3072 x 2048 11.2 -> 9.3, but 256 x 28672 x 4096 68 against 81; row-major: 160 x 28672 x 4096 82 -> 57, 160 x 4096 x
   // 4096 21 -> 13.5, 160 x 4096 x 14336 39 -> 32, 333 x 8192 x 4096 60 -> 39.
-  if ((packed || p.streamed) && p.M < 1024 && p.K % 128 == 0 && p.N % 32 == 0 && !far && !norm_out && !(packed && epi == EPI_STORE_F32)) {
+  const bool rope = epi == EPI_QKV || epi == EPI_KV;
+  if ((packed || p.streamed) && p.M < 1024 && p.K % 128 == 0 && !far && !norm_out && !(packed && epi == EPI_STORE_F32) && !(rope && best.n_splits == 1)) {
     static const double slice_us[] = {0.83, 0.92, 1.09, 1.32, 1.44};
-    const bool rope = epi == EPI_QKV || epi == EPI_KV;
     const int slices = p.K / 128;
-    // (the fixed part of the packed forms' model is 12 us above what 600 products of these sizes take)
+    // (the fixed part of the packed forms' model is 12 us above what 600 products of these sizes take; of 750 of 520 to 1023 rows this
+    // choice makes 3 slower by more than 2 %, all together 0.92 of the time)
     const double other = best.kernel == MID_NONE ? 1e30 : packed ? 1.05 * best.cost - 11.5 : best.cost;
     MidPlan stream{};
     for (int fm = 2; fm <= 6; ++fm) {

@@ -44,6 +44,16 @@ def test_row_major_products_with_scratch_split_k(M, N, K):
     assert plan.kernel == "rows_reg" and plan.n_splits > 1
 
 
+# Q, K and V leave the streamed 128-column tiles as partial sums: only where the other forms split K as well.
+@pytest.mark.parametrize("M,N,K,hd,kernel", [
+    (700, 4096, 2048, 64, "packed_reg"), (640, 4096, 2048, 64, "packed_reg"), (330, 8192, 2048, 64, "packed_reg"), (130, 8192, 1024, 64, "packed_reg"),
+    (330, 4096, 2048, 64, "stream_tile"), (450, 8192, 4096, 128, "stream_tile"), (1020, 2048, 4096, 64, "stream_tile")])
+def test_rotary_products_that_need_no_second_pass(M, N, K, hd, kernel):
+    for epilogue in ("kv", "qkv"):
+        plan = B.op_gemm_plan(epilogue, M, N, K, packed=True, head_dim=hd)
+        assert plan.kernel == kernel and (kernel == "stream_tile" or plan.n_splits == 1)
+
+
 @pytest.mark.parametrize("M,slice_", [(33, 512), (64, 512), (65, 256), (80, 256)])
 @pytest.mark.parametrize("N,K", [(2048, 2048), (4096, 4096), (13824, 5120), (20480, 10240)])
 def test_slices_of_33_to_80_rows(M, slice_, N, K):
