@@ -671,6 +671,7 @@ struct RingPlan {
 RingPlan plan_ring(int M, int N, int K, int nw, bool consumer_sums, size_t partial_cap) {
   RingPlan best{};
   if (M < 1 || M > 80 || (N % 16) != 0 || (K % 512) != 0) return best;
+  if ((uint64_t)std::max(M, 16) * (uint64_t)K * 2 > 0xffffffffull) return best;   // (32-bit row offsets, of activations and of a block's 16 weight rows)
   const int MB = (M + 15) / 16, nblocks = N / 16;
   const double w_bytes = 2.0 * nw * N * K;
   // K ranges in steps of 512 columns; of 256 at 65 to 80 rows, whose longer rounds of a wave an even split evens out, but for

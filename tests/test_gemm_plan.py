@@ -25,6 +25,15 @@ def test_packed_loop_beyond_4_gib_of_activations(epilogue, M, N, K):
             assert (plan.kernel, plan.tile, plan.n_splits) == ("packed_dma", 256, 1)
 
 
+# Weight streaming beyond 4 GiB of activations: skinny_ring_kernel holds a row's offset in 32 bits.  128 MiB of K lie in a row here.
+@pytest.mark.parametrize("M,K,kernel", [(80, 1 << 26, "stream_first"), (33, 1 << 26, "stream_first"), (31, 1 << 26, "stream_seq"), (80, 1 << 24, "stream_seq")])
+def test_weight_streaming_beyond_4_gib_of_activations(M, K, kernel):
+    assert B.op_gemm_plan("f32", M, 16, K, consumer_adds=True).kernel == kernel
+    assert B.op_gemm_plan("swiglu", M, 16384, K).kernel == kernel
+    if M > 32:
+        assert B.op_gemm_plan("bf16", M, 16, K).kernel == kernel
+
+
 # Row-major weights and no room for K splits (swiftkv_op_gemm): the 128 x 128 tile, but for shapes whose last round of its
 # tiles is nearly empty (6 x 86 = 512 + 4, 8 x 80 = 512 + 128, 2 x 1002 = 3 x 512 + 468 tiles).
 @pytest.mark.parametrize("M,N,K,kernel", [
