@@ -748,6 +748,7 @@ GemmRoute route_gemm(const GemmParams &p, int epi) {
 // else the 256 x 256 tile from 1024 rows on and the 128 x 128 tile below
 int launch_gemm(const GemmParams &p, int epi, int variant, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return 0;
+  if (p.n_splits_out && (epi == EPI_SWIGLU || epi == EPI_QKV || epi == EPI_KV)) return -1;   // their K splits need the finishing pass
   if (p.n_splits_out) *p.n_splits_out = 1;
   if (variant == 0) {
     const MidPlan pl = plan_gemm_mid(p, epi);

@@ -100,3 +100,28 @@ def test_every_launch_that_can_refuse_is_checked():
         r = subprocess.run([build._hipcc(), "--cuda-host-only", "--offload-arch=gfx950", "-std=c++17", "-fsyntax-only", "-Werror=unused-result",
                             "-Wno-unused-command-line-argument", os.path.join(build.CSRC, src)], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr
+
+
+def test_products_whose_splits_nobody_can_add_are_refused(tmp_path):
+    """Gate/up, Q/K/V and K/V products get their result from a pass behind their K splits: a caller that offers to add the
+    splits itself is turned away before anything is launched.  Host code, linked against the library."""
+    import subprocess
+    from paper_2410_03960_amd import binding as B
+    from paper_2410_03960_amd import build
+    if not os.path.exists(B.LIB_PATH):
+        build.build(verbose=False)
+    src, exe = tmp_path / "refuse.hip", tmp_path / "refuse"
+    src.write_text(f'''#include "{build.CSRC}/common.h"
+#include <cstdio>
+int main() {{
+  int32_t n = 7;
+  GemmParams g{{}};
+  g.M = 700; g.N = 4096; g.K = 2048; g.lda = g.ldw = 2048; g.head_dim = 64; g.n_splits_out = &n;
+  for (int epi : {{EPI_SWIGLU, EPI_QKV, EPI_KV}}) if (launch_gemm(g, epi, 0, nullptr) != -1) return epi + 1;
+  return n != 7;
+}}
+''')
+    r = subprocess.run([build._hipcc(), "--offload-arch=gfx950", "-std=c++17", "-Wno-unused-command-line-argument", str(src), "-o", str(exe),
+                        f"-L{os.path.dirname(B.LIB_PATH)}", "-lswiftkv", f"-Wl,-rpath,{os.path.dirname(B.LIB_PATH)}"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    assert subprocess.run([str(exe)], timeout=60).returncode == 0
