@@ -261,14 +261,15 @@ int swiftkv_op_gemm_rows_static(const void *A, const void *W, void *C, int32_t M
  * certain kernel.  Host only: no GPU is needed and nothing is launched.  epilogue: 0 = bf16, 1 = fp32, 2 = added to
  * the fp32 residual stream, 3 = SwiGLU (N = columns of the result; two weights), 4 = Q/K/V of a full layer, 5 = the
  * fused K/V projection.  flags: bit 0 = weights in fragment order are at hand, bit 1 = the reader of the result adds
- * the K splits (1, 2), bit 2 = the residual epilogue also leaves the next projection's operand.  scratch_bytes: room
+ * the K splits (0, 1, 2), bit 2 = the residual epilogue also leaves the next projection's operand, bit 3 = the rows are
+ * the last tokens of more than 80 sequences, whose row-major weights the later layers read once.  scratch_bytes: room
  * for the K splits' partial sums.  head_dim: 64 or 128 for 4 and 5, else ignored.  plan_out (host): a SWIFTKV_GEMM_*
  * kernel; rows of its tile, or 16-column blocks of a workgroup of the weight-streaming kernels (M <= 80); K splits;
  * columns of K to a slice (0: not in slices). */
 enum {
   SWIFTKV_GEMM_STREAM_FIRST = 0,    /* weight streaming, K split among the waves of a workgroup */
   SWIFTKV_GEMM_STREAM_SEQ = 1,      /* ... slices of K one after the other behind a producer wave */
-  SWIFTKV_GEMM_STREAM_RESIDENT = 2, /* (all activation rows resident in LDS: no product takes this form any more) */
+  /* 2: reserved */
   SWIFTKV_GEMM_STREAM_SLICE = 3,    /* ... one slice of K per workgroup in LDS */
   SWIFTKV_GEMM_TILE_128 = 4,        /* 128 x 128 tile */
   SWIFTKV_GEMM_TILE_256 = 5,        /* 256 x 256 tile, register-staged */
@@ -276,8 +277,7 @@ enum {
   SWIFTKV_GEMM_PACKED_DMA = 7,      /* fragment-order weights, activations by LDS-DMA */
   SWIFTKV_GEMM_PACKED_REG = 8,      /* fragment-order weights, activations through registers */
   SWIFTKV_GEMM_ROWS_REG = 9,        /* row-major weights, both operands through registers */
-  SWIFTKV_GEMM_STREAM_TILE = 10     /* 128-column tiles, both operands streamed through LDS (also the products of the last tokens of
-                                       more than 80 sequences, in place of 9) */
+  SWIFTKV_GEMM_STREAM_TILE = 10     /* 128-column tiles, both operands streamed through LDS */
 };
 int swiftkv_op_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t flags, int32_t head_dim,
                          size_t scratch_bytes, int32_t plan_out[4]);

@@ -327,17 +327,18 @@ class GemmPlan(NamedTuple):
     slice: int
 
 
-GEMM_KERNELS = {0: "stream_first", 1: "stream_seq", 2: "stream_resident", 3: "stream_slice", 4: "tile_128", 5: "tile_256", 6: "five_stage",
+GEMM_KERNELS = {0: "stream_first", 1: "stream_seq", 3: "stream_slice", 4: "tile_128", 5: "tile_256", 6: "five_stage",
                 7: "packed_dma", 8: "packed_reg", 9: "rows_reg", 10: "stream_tile"}
 GEMM_EPILOGUES = ("bf16", "f32", "resid", "swiglu", "qkv", "kv")
 GEMM_SCRATCH = 16 * 80 * 8192 * 4     # bytes for K splits that swiftkv_prefill and swiftkv_kv_from_hidden have
 
 
 def op_gemm_plan(epilogue: str, M: int, N: int, K: int, packed: bool = False, consumer_adds: bool = False, norm_out: bool = False,
-                 head_dim: int = 0, scratch: int = GEMM_SCRATCH) -> GemmPlan:
-    """The kernel the library runs for a product (host only, no GPU)."""
+                 head_dim: int = 0, scratch: int = GEMM_SCRATCH, last_tokens: bool = False) -> GemmPlan:
+    """The kernel the library runs for a product (host only, no GPU).  last_tokens: of the layers that only the last token of
+    each sequence runs."""
     out = (C.c_int32 * 4)()
-    _check(load().swiftkv_op_gemm_plan(GEMM_EPILOGUES.index(epilogue), M, N, K, int(packed) + 2 * int(consumer_adds) + 4 * int(norm_out),
+    _check(load().swiftkv_op_gemm_plan(GEMM_EPILOGUES.index(epilogue), M, N, K, int(packed) + 2 * int(consumer_adds) + 4 * int(norm_out) + 8 * int(last_tokens),
                                        head_dim, scratch, out))
     return GemmPlan(GEMM_KERNELS[out[0]], out[1], out[2], out[3])
 

@@ -1075,13 +1075,13 @@ int swiftkv_export_hidden(swiftkv_ctx *c, const void *workspace, void *hidden_ou
 int swiftkv_op_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t flags, int32_t head_dim, size_t scratch_bytes,
                          int32_t plan_out[4]) {
   if (!plan_out) return fail(SWIFTKV_EINVAL, "null argument");
-  if (epilogue < EPI_STORE_BF16 || epilogue > EPI_KV || flags < 0 || flags > 7) return fail(SWIFTKV_EINVAL, "unknown epilogue or flags");
+  if (epilogue < EPI_STORE_BF16 || epilogue > EPI_KV || flags < 0 || flags > 15) return fail(SWIFTKV_EINVAL, "unknown epilogue or flags");
   if (M < 1 || N < 16 || K < 8 || (N % 16) || (K % 8)) return fail(SWIFTKV_EINVAL, "need M >= 1, N %% 16 == 0, K %% 8 == 0");
   // (pointers that the choice only asks for)
   const bf16_t some = 0;
   float partial = 0;
   int32_t ns;
-  const bool rope = epilogue == EPI_QKV || epilogue == EPI_KV, adds = (flags & 2) && (epilogue == EPI_STORE_F32 || epilogue == EPI_RESID);
+  const bool rope = epilogue == EPI_QKV || epilogue == EPI_KV, adds = (flags & 2) && epilogue <= EPI_RESID;
   GemmRoute r;
   if (M <= SKINNY_MAX_ROWS) {   // Q, K and V leave as fp32 and their splits to the pass that rotates them
     SkinnyParams s{nullptr, M, N, K, nullptr, nullptr, nullptr, scratch_bytes ? &partial : nullptr, scratch_bytes, nullptr, rope || adds ? &ns : nullptr};
@@ -1092,6 +1092,7 @@ int swiftkv_op_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int3
     g.wpack = (flags & 1) ? &some : nullptr;
     g.partial = scratch_bytes ? &partial : nullptr; g.partial_bytes = scratch_bytes;
     g.n_splits_out = adds ? &ns : nullptr;
+    g.streamed = (flags & 8) && !(flags & 1);
     if ((flags & 4) && epilogue == EPI_RESID) { g.hb = (bf16_t *)&some; g.ssq = &partial; }
     r = route_gemm(g, epilogue);
   }

@@ -63,6 +63,18 @@ def test_rotary_products_that_need_no_second_pass(M, N, K, hd, kernel):
         assert plan.kernel == kernel and (kernel == "stream_tile" or plan.n_splits == 1)
 
 
+# The last tokens of more than 80 sequences: 128-column tiles, with K ranges for whoever adds them and for those that nobody does.
+@pytest.mark.parametrize("M,N,K", [(81, 4096, 4096), (160, 4096, 14336), (333, 8192, 2048), (600, 2048, 2048), (1023, 2048, 8192)])
+def test_last_tokens_stream_their_weights(M, N, K):
+    for epilogue in ("bf16", "f32", "resid"):
+        for adds in (False, True):
+            plan = B.op_gemm_plan(epilogue, M, N, K, consumer_adds=adds, last_tokens=True)
+            assert plan.kernel == "stream_tile"
+    assert B.op_gemm_plan("swiglu", M, N, K, last_tokens=True).kernel == "stream_tile"
+    assert B.op_gemm_plan("resid", M, N, K, consumer_adds=True).kernel != "stream_tile"     # row-major weights of a context's full layers
+    assert B.op_gemm_plan("resid", M, N, K + 64, last_tokens=True).kernel != "stream_tile"
+
+
 @pytest.mark.parametrize("M,slice_", [(33, 512), (64, 512), (65, 256), (80, 256)])
 @pytest.mark.parametrize("N,K", [(2048, 2048), (4096, 4096), (13824, 5120), (20480, 10240)])
 def test_slices_of_33_to_80_rows(M, slice_, N, K):

@@ -1,6 +1,6 @@
-"""Last tokens whose q projection leaves its K ranges apart: the attention kernels add them up
-(vector unit, matrix unit over bf16 and e4m3 caches; one row, one and several 16-row blocks,
-more rows than the weight-streaming kernels take), against the oracle."""
+"""Last tokens whose q projection leaves its K ranges apart: the attention kernels of the matrix unit add
+them up (bf16 and e4m3 caches; one row, one and several 16-row blocks, more rows than the
+weight-streaming kernels take), against the oracle.  The vector unit's: test_gpu_decode_units."""
 import pytest
 
 import workloads as WL
@@ -23,8 +23,8 @@ def test_tail_matches_oracle(name, n_seqs, fp8):
     from paper_2410_03960_amd import binding as B
     print(name, n_seqs, fp8, flush=True)
     sh = SHAPES[name]
-    plan = B.op_gemm_plan("f32" if n_seqs <= 80 else "resid", n_seqs, sh.q_dim, sh.hidden, consumer_adds=True)
-    assert plan.n_splits > 1
+    plan = B.op_gemm_plan("bf16", n_seqs, sh.q_dim, sh.hidden, consumer_adds=True, last_tokens=n_seqs > 80)
+    assert plan.kernel == ("stream_seq" if n_seqs <= 80 else "stream_tile") and plan.n_splits > 1
     wl = Workload(f"tailq_{name}", sh, l=1, g=1, seed=2610)
     store = WL.make_weights(wl, "cpu", keep=True)
     batch = WL.build_batch(wl, lens=[1 + (7 * i + 3) % 5 for i in range(n_seqs)] if n_seqs > 3 else [150, 40, 2][:n_seqs], shuffled=True)
