@@ -1,18 +1,26 @@
 """Single-query attention on the matrix unit where one workgroup walks more than the 4096 keys whose
-block ids it looks up at once, and rows that end beside that line; whole result against 64 bits."""
+block ids it looks up at once: rows of so many keys that every split does, one and two look-ups
+later, splits that end just behind one, beside rows that end beside that line; against 64 bits."""
 import pytest
 import torch
 
+from paper_2410_03960_amd import binding as B
 from tests.helpers import rel_err
 
 pytestmark = pytest.mark.gpu
 
+MOST = 32      # splits of a row
 
+
+@pytest.mark.parametrize("n_keys,looks", [
+    ([MOST * 4224, 4095, 4096, 4097], 2),                   # 33 steps of 128 keys to a split: the last one behind the second look-up
+    ([MOST * 8320 + 1, 8191, 8192, 8193, 33], 3),            # 65 steps and a key
+], ids=["two", "three"])
 @pytest.mark.parametrize("fp8", [False, True])
-def test_rows_beyond_one_block_id_load(fp8):
-    from paper_2410_03960_amd import binding as B
-    Hq, Hkv, hd = 64, 8, 64
-    n_keys = [4097 + 13 * i for i in range(90)] + [4095, 4096, 4097, 8192, 8193, 33]      # 768 (row, KV head) pairs: not split
+def test_rows_beyond_one_block_id_load(fp8, n_keys, looks):
+    Hq, Hkv, hd = 8, 1, 64
+    plan = B.op_attention_decode_plan(n_keys, Hq, Hkv, hd, fp8=fp8)
+    assert plan.unit == "matrix" and -(-plan.split_keys(n_keys[0]) // 4096) >= looks     # (split over at most MOST: more keys otherwise)
     need = [(n + 15) // 16 for n in n_keys]
     gen = torch.Generator().manual_seed(27)
     order, at = torch.randperm(sum(need) + 3, generator=gen).int(), 0
@@ -33,8 +41,9 @@ def test_rows_beyond_one_block_id_load(fp8):
         k, v = k.bfloat16(), v.bfloat16()
         kd, vd = k.double(), v.double()
     out = B.op_attention_decode(q, n_keys, k, v, table, Hq, Hkv, hd, **kw)
-    for b in (0, 41, 89, 90, 91, 92, 93, 94, 95):
-        s = (table[b].long()[:, None] * 16 + torch.arange(16)).view(-1)[:n_keys[b]].cuda()
+    for b, n in enumerate(n_keys):
+        s = (table[b].long()[:, None] * 16 + torch.arange(16)).view(-1)[:n].cuda()
         qb = q[b].double().view(Hkv, Hq // Hkv, hd)
         p = torch.softmax(torch.matmul(qb, kd[s].permute(1, 2, 0).contiguous()) / hd ** 0.5, -1)
+        # (the steps behind one look-up read from other blocks: 0.2 of the result and more)
         assert rel_err(out[b].double().cpu(), torch.matmul(p, vd[s].permute(1, 0, 2).contiguous()).view(-1).cpu()) <= 1e-2, b
