@@ -52,6 +52,19 @@ __device__ __forceinline__ float e4m3fn_to_f32(uint8_t c) {
   return __uint_as_float(__float_as_uint(v) | s);
 }
 
+// 16 bytes per lane from global memory straight into LDS: lane i lands at lds_addr + 16 * i (M0 carries the LDS base).  The waits are
+// placed by hand (s_waitcnt vmcnt) because the compiler cannot tell which LDS bytes a request targets.
+__device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory");
+}
+// ... from base (uniform) + off (per lane)
+__device__ __forceinline__ void lds_dma16_at(const void *base, unsigned off, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base) : "memory");
+}
+// at most N of the wave's vector-memory requests in flight
+template <int N>
+__device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
+
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));

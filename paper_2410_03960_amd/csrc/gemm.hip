@@ -504,14 +504,6 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmParams &p, floatx16 
 // A stage row is 64 bytes = four 16-byte chunks; chunk c of row r sits at
 // physical chunk c ^ ((r >> 2) & 3), which makes any 16 consecutive rows of one
 // logical chunk hit 16 different bank groups.
-// One LDS-DMA request: 64 lanes x 16 bytes from per-lane global addresses into the 1 KB of LDS
-// starting at byte offset lds_addr (wave-uniform).  Written as inline assembly because the
-// compiler, not knowing which LDS bytes a DMA targets, would otherwise wait for *all* outstanding
-// loads before the next LDS read; here the waits are placed by hand (s_waitcnt vmcnt).
-__device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory");
-}
-
 template <int BM, int BN, int WGM, int WGN, int EPI>
 __global__ __launch_bounds__(WGM *WGN * 64) void gemm_dlds5_kernel(GemmParams p) {
   constexpr int NW = WGM * WGN;

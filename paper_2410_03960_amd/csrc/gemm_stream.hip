@@ -14,12 +14,6 @@
 
 namespace {
 
-template <int N>
-__device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
-// 64 lanes x 16 bytes from base (uniform) + off (per lane) into the 1 KB of LDS at lds_addr (uniform)
-__device__ __forceinline__ void lds_dma16_at(const void *base, unsigned off, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base) : "memory");
-}
 
 constexpr int ST_R = 2;   // 64-column steps in a wave's ring
 constexpr int st_bufs(int FM) { return FM <= 4 ? 3 : 2; }   // activation buffers of 128 columns

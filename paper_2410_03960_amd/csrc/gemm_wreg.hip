@@ -4,13 +4,6 @@
 
 namespace {
 
-// One LDS-DMA request: 64 lanes x 16 bytes from per-lane global addresses into the 1 KB of LDS starting at byte
-// offset lds_addr (wave-uniform).  Inline assembly because the compiler, not knowing which LDS bytes a DMA
-// targets, would wait for all outstanding loads before the next LDS read; the waits are placed by hand.
-__device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory");
-}
-
 // ---------------------------------------------------------------------------
 // Main loop that keeps the weight operand out of LDS.  The weights are static, so
 // they can be stored once in MFMA fragment order (`wpack`: for every block of 32

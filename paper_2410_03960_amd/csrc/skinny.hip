@@ -168,10 +168,6 @@ __global__ void skinny_reduce_kernel(SkinnyParams p, int ksplit) {
   }
 }
 
-__device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory");
-}
-
 // acc[mb][v] = C[m = mb*16 + l16][n + v] of one weight, whole or over K range `split`: to partial[split][m][n] or through the epilogue
 template <int MB, int EPI>
 __device__ __forceinline__ void store_blocks(const SkinnyParams &p, const floatx4 (&acc)[MB], int n, int l16, int split, bool partial) {
@@ -330,7 +326,7 @@ __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_seq_kernel(SkinnyPara
   for (int b = 0; b < NBW; ++b) {
     int nb = nb0 + b;
     nb = nb < nblocks ? nb : nblocks - 1;
-    wt[b] = (p.wtab ? p.wtab[nb] : p.W + (int64_t)nb * 16 * p.K) + ((int64_t)l16 * p.K + k0 + kq * 8);
+    wt[b] = p.W + ((int64_t)(nb * 16 + l16) * p.K + k0 + kq * 8);
   }
   int l_idx = 0;
   auto load_group = [&](uint4 (&dst)[NBW][U]) {
@@ -523,8 +519,6 @@ int launch_seq(const SkinnyParams &p, int epi, const SeqPlan &pl, hipStream_t st
 // 28672 92 -> 80; one row 2 x 14336 x 4096 44.6 (all rows resident in LDS) -> 39.5, 4096 x 14336 25.2 -> 21.2.
 // Chunk c (16 bytes) of row r of a 16 x 64 piece lies at chunk c ^ ((r >> 1) & 7) of its 128 bytes, so that fragment reads meet
 // every bank once.
-template <int N>
-__device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
 template <int R>
 __device__ __forceinline__ void wait_ring(int younger) {   // step i is in LDS: no more than the requests of `younger` later steps in flight
   static_assert(R <= 4, "cases below");
@@ -532,10 +526,6 @@ __device__ __forceinline__ void wait_ring(int younger) {   // step i is in LDS: 
   else if (younger == 2) wait_vm<4>();
   else if (younger == 1) wait_vm<2>();
   else wait_vm<0>();
-}
-// 64 lanes x 16 bytes from base (uniform) + off (per lane) into the 1 KB of LDS at lds_addr (uniform)
-__device__ __forceinline__ void lds_dma16_at(const void *base, unsigned off, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base) : "memory");
 }
 constexpr int RING_BUF = 256;                                       // columns of K in an activation buffer
 constexpr int ring_steps(int waves) { return waves == 8 ? 3 : 4; }   // 48 and 32 KB per workgroup; more in flight is no faster (8 waves, 64 rows, 6 steps: 51.7 us against 48.8)
@@ -807,12 +797,11 @@ int launch_wide(const SkinnyParams &p, int epi, hipStream_t st) {
 // Which kernel runs this shape.  Up to 32 rows, where the result is final, three of them compete by the bytes they move at
 // the streaming rate: the weights, a share of the activation rows' way from L2, the partial sums' trip to memory, a second
 // launch; times what an uneven last round costs.  The terms' weights are fitted to the times of 565 products (2 to 940 MB of
-// weights, 1 to 32 rows, one weight or two).  us per call, skinny_lds_kernel wherever it has enough pairs and the first kernel
+// weights, 1 to 32 rows).  us per call, skinny_lds_kernel wherever it has enough pairs and the first kernel
 // elsewhere / skinny_seq_kernel wherever it needs no second launch (up to 16 rows) or at all / this choice: 16 rows 13824 x
 // 5120 37 / 51 / 33, 14336 x 4096 30 / 36 / 26, 8192 x 28672 105 / 129 / 105, 1 row 28672 x 8192 93 / 103 / 91, 24 rows 11008 x
 // 4096 28 / 37 / 28; over 490 products of 1 to 32 rows 6 % ahead of the first and 4 % of the second rule, behind the first by
-// more than 3 % only at 32000 x 2048 in fp32 (28.1 -> 29.0).  Two weights: without skinny_lds_kernel, which is nowhere ahead by
-// more than 5 % there.
+// more than 3 % only at 32000 x 2048 in fp32 (28.1 -> 29.0).
 struct SkinnyRoute {
   int kernel;   // SWIFTKV_GEMM_STREAM_*
   RingPlan ring;
@@ -837,7 +826,7 @@ SkinnyRoute plan_skinny(const SkinnyParams &p, int epi) {
   const double first = (2.0 * p.N * p.K + 0.68 * wgs * p.M * p.K * 2) * (1 + 0.88 * (std::ceil(wgs / 256) * 256 / wgs - 1)) * 0.913;
   double best = first;
   if (r.seq.ok && r.seq.cost < first) { best = r.seq.cost; r.kernel = SWIFTKV_GEMM_STREAM_SEQ; }
-  if (!p.wtab) r.lds = plan_lds(p.M, p.N, p.K, cap);
+  r.lds = plan_lds(p.M, p.N, p.K, cap);
   if (r.lds.ok && r.lds.cost < best) r.kernel = SWIFTKV_GEMM_STREAM_SLICE;
   return r;
 }
@@ -858,6 +847,7 @@ GemmRoute route_skinny(const SkinnyParams &p, int epi) {
 int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0) return 0;
   if (p.M > 80 || (p.N % 16) != 0 || (p.K % 8) != 0) return -1;
+  if (p.wtab && !p.n_splits_out) return -1;   // (the kernels of final results know no row-block table)
   if (p.n_splits_out) {
     if (epi == EPI_SWIGLU) return -1;
     *p.n_splits_out = 1;

@@ -1,8 +1,8 @@
 """Weight-streaming GEMMs with the activations in LDS.  Up to 32 rows: one and two row
 blocks at their edges, ragged last workgroups, one to nine K ranges or slices, the
 shapes beside the rules' lines that keep another form, and (through a decoder whose
-MLP is wide enough) the SwiGLU pair with all rows resident, up to its 8 rows and past
-them; 65 to 80 rows: the longer slices of large weights."""
+MLP is wide enough) the SwiGLU pair, whose weights and activations both pass through
+LDS; 65 to 80 rows: the longer slices of large weights."""
 import pytest
 import torch
 
@@ -45,7 +45,7 @@ def test_one_slice_per_workgroup(M, N, K, blocks, splits):
 
 @pytest.mark.parametrize("M", [65, 80])
 def test_long_slices_of_large_weights(M):
-    """65 to 80 rows over weights of 430 MB and more: two 80 KB activation buffers, all of a CU's LDS."""
+    """65 to 80 rows over weights of 430 MB and more: K ranges of whole 512-column slices."""
     from paper_2410_03960_amd import binding as B
     N, K = 8192, 26624
     for f32 in (True, False):

@@ -104,7 +104,8 @@ def test_every_launch_that_can_refuse_is_checked():
 
 def test_products_whose_splits_nobody_can_add_are_refused(tmp_path):
     """Gate/up, Q/K/V and K/V products get their result from a pass behind their K splits: a caller that offers to add the
-    splits itself is turned away before anything is launched.  Host code, linked against the library."""
+    splits itself is turned away before anything is launched; so is a final few-row result over a row-block table.
+    Host code, linked against the library."""
     import subprocess
     from paper_2410_03960_amd import binding as B
     from paper_2410_03960_amd import build
@@ -118,6 +119,10 @@ int main() {{
   GemmParams g{{}};
   g.M = 700; g.N = 4096; g.K = 2048; g.lda = g.ldw = 2048; g.head_dim = 64; g.n_splits_out = &n;
   for (int epi : {{EPI_SWIGLU, EPI_QKV, EPI_KV}}) if (launch_gemm(g, epi, 0, nullptr) != -1) return epi + 1;
+  const bf16_t *table[64] = {{}};
+  SkinnyParams k{{}};
+  k.M = 16; k.N = 1024; k.K = 2048; k.wtab = table;   // a row-block table, and a result that is final
+  for (int epi : {{EPI_STORE_BF16, EPI_STORE_F32, EPI_RESID, EPI_SWIGLU}}) if (launch_skinny(k, epi, nullptr) != -1) return 10 + epi;
   return n != 7;
 }}
 ''')
