@@ -423,8 +423,8 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   if ((packed || p.streamed) && p.M < 1024 && p.K % 128 == 0 && !far && !norm_out && !(packed && epi == EPI_STORE_F32) && !(rope && best.n_splits == 1)) {
     static const double slice_us[] = {0.83, 0.92, 1.09, 1.32, 1.44};
     const int slices = p.K / 128;
-    // (the fixed part of the packed forms' model is 12 us above what 600 products of these sizes take; of 750 of 520 to 1023 rows this
-    // choice makes 3 slower by more than 2 %, all together 0.92 of the time)
+    // (the fixed part of the packed forms' model is 12 us above what 600 products of these sizes take; of 376 of 520 to 1023 rows this
+    // choice makes 3 slower by more than 2 %, all together 0.91 of the time)
     const double other = best.kernel == MID_NONE ? 1e30 : packed ? 1.05 * best.cost - 11.5 : best.cost;
     MidPlan stream{};
     for (int fm = 2; fm <= 6; ++fm) {
