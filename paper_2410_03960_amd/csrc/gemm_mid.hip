@@ -416,9 +416,9 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   // 5600 timings of 16 products of 81 to 512 rows (median error 5 %).  Rotary operands always leave as partial sums, so a form that
   // needs no K ranges and no second pass keeps them (700 x 4096 x 2048, K and V of 8 layers: 35.4 us a call, 38.8 here; 130 x
   // 8192 x 1024 24.2 and 27.5; with K ranges in the other form this one was ahead in all of 57 products).
-  // What it is worth, us (the forms above -> this one), fragment order: 160 x 28672 x 4096 67 -> 58, 192 x 4096 x 4096 19.2 -> 14.8,
-  // 256 x 3072 x 2048 11.2 -> 9.3, but 256 x 28672 x 4096 68 against 81; row-major: 160 x 28672 x 4096 82 -> 57, 160 x 4096 x
-  // 4096 21 -> 13.5, 160 x 4096 x 14336 39 -> 32, 333 x 8192 x 4096 60 -> 39.
+  // What it is worth, us (the forms above -> this one), fragment order: 160 x 28672 x 4096 67 -> 56, 192 x 4096 x 4096 18.9 -> 13.8,
+  // 256 x 3072 x 2048 10.0 -> 8.6, but 256 x 28672 x 4096 68 against 81; row-major: 160 x 28672 x 4096 84 -> 56, 160 x 4096 x
+  // 4096 20.7 -> 13.4, 160 x 4096 x 14336 39 -> 33, 333 x 8192 x 4096 53 -> 32.
   const bool rope = epi == EPI_QKV || epi == EPI_KV;
   if ((packed || p.streamed) && p.M < 1024 && p.K % 128 == 0 && !far && !norm_out && !(packed && epi == EPI_STORE_F32) && !(rope && best.n_splits == 1)) {
     static const double slice_us[] = {0.83, 0.92, 1.09, 1.32, 1.44};
