@@ -375,7 +375,7 @@ constexpr int MID_MAX_SPLIT = 16;
 MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   MidPlan best{};
   best.kernel = MID_NONE;
-  const bool packed = p.wpack && p.K % 256 == 0 && p.N % 256 == 0 && epi != EPI_STORE_F32;
+  const bool packed = p.wpack && p.K % 256 == 0 && p.N % 256 == 0 && epi != EPI_STORE_F32 && (uint64_t)p.lda * 512 <= 0xffffffffull;   // (32-bit row offsets inside a 256-row tile)
   if (p.M <= 80) return best;
   const bool far = (uint64_t)p.M * (uint64_t)p.lda * 2 >= 0xffffffffull;   // beyond the 32-bit row offsets of gemm_mid_kernel (gemm_wreg_kernel has whole pointers)
   if (!packed && (p.M >= 1024 || p.K % 64 != 0 || p.N % 64 != 0 || ((epi == EPI_QKV || epi == EPI_KV) && p.N % 128 != 0))) return best;

@@ -23,6 +23,12 @@ namespace {
 // for it, through L2 and with a bounded number of requests in flight, against the MFMAs it hides them under:
 // 0.89 us at FM = 4 (48 KB, 128 rows), 1.12 at 6, 1.46 at 8 (64 KB, 256 rows) with all CUs busy, so a taller
 // tile is cheaper per row and a shorter one is taken where it fills a last round or leaves room for K splits.
+// The four waves run in step, so their fragment reads are spread over all products of a sub-step (in a burst behind the
+// first half of them they took every LDS cycle of that half).  Together with the uniform bases, us per product before -> now:
+// 16384 x 28672 x 4096 2771 -> 2725, 2048 x 28672 x 4096 in 192-row tiles 386 -> 380, 512 x 28672 x 4096 101.5 -> 98.7, 333 in
+// 192-row tiles 81.9 -> 80.5.  No gain, measured on this loop: six to ten stages where they fit, weights four steps ahead (the wait
+// for a stage then leaves 22 instead of 14 requests in flight), 32 KB of a step's weights in one piece, each wave's requests
+// a product later than its neighbour's; eight waves of 128 x 64, two to a SIMD: 3 % slower, as every wave's wait is stricter.
 template <int EPI, int FM, bool NORM_OUT = false>
 __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
   constexpr int BM = 32 * FM, BN = 256;
@@ -50,19 +56,21 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
   const int nk = (all_steps - s_begin) < p.split_steps ? (all_steps - s_begin) : p.split_steps;   // >= 1 by the plan
 
   // LDS-DMA sources: request i of this wave covers rows (wave*FM + i)*8 .. +7 of the tile, 128 bytes each;
-  // this lane fetches row +(lane>>3), the 16-byte chunk that lands at physical chunk lane&7
-  const bf16_t *a_ptr[FM];
+  // this lane fetches row +(lane>>3), the 16-byte chunk that lands at physical chunk lane&7.  Addresses are a uniform base
+  // plus a 32-bit offset per lane: with whole pointers per lane every request cost two vector adds between the MFMAs.
+  unsigned a_off[FM];
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
     const int r = (wave * FM + i) * 8 + (lane >> 3);
-    int m = m0 + r;
-    m = m < p.M ? m : p.M - 1;
-    a_ptr[i] = p.A + (int64_t)m * p.lda + (int64_t)s_begin * 64 + (((lane & 7) ^ ((r >> 1) & 7)) * 8);
+    const int in_tile = m0 + r < p.M ? r : p.M - 1 - m0;
+    a_off[i] = (unsigned)in_tile * (unsigned)(p.lda * 2) + (((lane & 7) ^ ((r >> 1) & 7)) * 16);
   }
+  const unsigned char *a_base = (const unsigned char *)(p.A + (int64_t)m0 * p.lda + (int64_t)s_begin * 64);
   // packed weight fragments of the wave's two 32-row blocks: (block, k16) at ((block * K/16) + k16) * 512 elements
-  const bf16_t *w_ptr[2];
+  const unsigned char *w_base[2];
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) w_ptr[nb] = p.wpack + ((int64_t)(n0 / 32 + nb) * (p.K / 16) + (int64_t)s_begin * 4) * 512 + lane * 8;
+  for (int nb = 0; nb < 2; ++nb) w_base[nb] = (const unsigned char *)(p.wpack + ((int64_t)(n0 / 32 + nb) * (p.K / 16) + (int64_t)s_begin * 4) * 512);
+  const unsigned w_off = lane * 16;
 
   typedef __attribute__((address_space(3))) void *lds_ptr_t;
   const unsigned lds_base = (unsigned)(size_t)(lds_ptr_t)smem;
@@ -83,7 +91,7 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
   bf16x8 af[2][FM];
 
   auto issue_a = [&](int i, int stage, int step) {
-    lds_dma16(a_ptr[i] + (int64_t)step * 64, lds_base + stage * STAGE + (wave * FM + i) * 1024);
+    lds_dma16_at(a_base + (int64_t)step * 128, a_off[i], lds_base + stage * STAGE + (wave * FM + i) * 1024);
   };
   // Plain loads: the compiler places their vmcnt waits.  It counts only these loads, not the LDS-DMA
   // requests issued from inline assembly in between, so its waits are stricter than necessary, never
@@ -91,7 +99,7 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
   // order gave results that changed from run to run: the two kinds do not complete in issue order
   // relative to each other.)
   auto load_w = [&](bf16x8 &dst, int nb, int kk, int step) {
-    dst = *(const bf16x8 *)(w_ptr[nb] + ((int64_t)step * 4 + kk) * 512);
+    dst = *(const bf16x8 *)(w_base[nb] + ((int64_t)step * 4 + kk) * 1024 + (uint64_t)w_off);
   };
 
   // prologue: steps 0, 1, 2 requested (FM + 8 requests per wave and step, activations and weights alternating)
@@ -135,7 +143,7 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
         const int nb = i / FM, bm = i % FM;
         acc[nb][bm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[slot][kk * 2 + nb], af[kk & 1][bm], acc[nb][bm], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        if (i < FM) af[(kk + 1) & 1][i] = *(const bf16x8 *)((kk < 3 ? st : stn) + (a_lane ^ (unsigned)(((kk + 1) & 3) * 32)) + i * 4096);
+        if (i % 2 == 0) af[(kk + 1) & 1][i / 2] = *(const bf16x8 *)((kk < 3 ? st : stn) + (a_lane ^ (unsigned)(((kk + 1) & 3) * 32)) + (i / 2) * 4096);
         const int a_req = kk * FM / 4 + i / FM;   // one or two activation requests per sub-step, FM per step
         if (i % FM == (FM - 1) / 2 && a_req < (kk + 1) * FM / 4) issue_a(a_req, sld, kl);
         if (i % FM == FM - 1) load_w(wf[lslot][kk * 2 + i / FM], i / FM, kk, kl);
