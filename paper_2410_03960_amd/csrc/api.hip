@@ -382,6 +382,14 @@ struct Run {
   void *cache_plane(int c_layer, int kvsel) const {
     return (unsigned char *)kv->data + ((int64_t)c_layer * layer_stride + (int64_t)kvsel * plane) * esz;
   }
+  // cache layer c (and those behind it) as the destination of a finishing pass
+  KvStore kv_store(int c_layer) const {
+    KvStore s{};
+    s.kind = !fp8 ? KV_STORE_BF16 : per_token ? KV_STORE_PER_TOKEN : KV_STORE_GIVEN;
+    s.cache_k = cache_plane(c_layer, 0); s.cache_v = cache_plane(c_layer, 1); s.layer_bytes = layer_stride * (int64_t)esz;
+    if (fp8) { s.scales = layer_scales(c_layer); s.scale_stride = 2 * (per_token ? n_slots : (int64_t)c->cfg.n_kv_heads); s.n_slots = n_slots; }
+    return s;
+  }
 };
 
 // (Re)allocate the pinned staging ring with slots of at least `need` bytes.  Host memory only.
@@ -451,6 +459,13 @@ int run_fused_kv(Run &r, const bf16_t *hidden, bool rstd_ready, Timer &tm) {
     g.stage = r.at<bf16_t>(r.L.stage);
     g.amax = r.kv->scale_mode == SWIFTKV_SCALE_COMPUTE_ABSMAX ? r.at<uint32_t>(r.L.amax) : nullptr;
   }
+  // e4m3 under given or the tokens' own scales: the finishing pass of K-split sums, if there is one, stores the codes itself
+  KvStore ks{};
+  int32_t sums = 0;
+  if (r.fp8 && !g.amax) {
+    ks = r.kv_store(c->l);
+    if (kv_store_fits(ks, kvd)) { g.store = &ks; g.sums_left = &sums; }
+  }
   tm.begin(TC_KV);
   // Few rows: the weights stream once through the weight-streaming kernels (fp32 result and K splits in the scratch),
   // then one pass rotates, rounds and scatters.  Measured with one row, 4096 x 4096: 72 us (a 128-row tile on 32 of
@@ -462,14 +477,18 @@ int run_fused_kv(Run &r, const bf16_t *hidden, bool rstd_ready, Timer &tm) {
     SkinnyParams sp{hidden, g.M, g.N, g.K, g.W, nullptr, c32, splits, SKINNY_PARTIAL_BYTES - c_bytes, nullptr, &ns};
     if (launch_skinny(sp, EPI_STORE_F32, r.st)) return fail(SWIFTKV_EHIP, "fused KV GEMM launch failed");
     g.partial = ns > 1 ? splits : c32;
-    g.n_splits = ns;
-    if (launch_splits_finish(g, EPI_KV, r.st) != 0) return fail(SWIFTKV_EHIP, "fused KV finish launch failed");
+    sums = ns;
   } else if (launch_gemm(g, EPI_KV, 0, r.st) != 0) {
     return fail(SWIFTKV_EHIP, "fused KV GEMM launch failed");
   }
+  if (sums > 0) {
+    g.n_splits = sums;
+    if (launch_splits_finish(g, EPI_KV, r.st) != 0) return fail(SWIFTKV_EHIP, "fused KV finish launch failed");
+  }
+  const bool stored = sums > 0 && g.store;
   tm.end();
   if (int e = check_launch("fused KV GEMM")) return e;
-  if (r.fp8) {
+  if (r.fp8 && !stored) {
     tm.begin(TC_COMMIT);
     for (int p = 0; p < c->P; ++p) {
       const int cl = c->l + p;
@@ -791,9 +810,12 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   bf16_t *vt = r.at<bf16_t>(r.L.vt), *zb = r.at<bf16_t>(r.L.z);
   const bool compute_scale = r.fp8 && kv->scale_mode == SWIFTKV_SCALE_COMPUTE_ABSMAX;
   const bool few_rows = T <= SKINNY_MAX_ROWS;
-  // Decode rows only, and no scale that waits for all of a layer's values: the pass that finishes Q, K and V stores K and
-  // V at their slots, one launch (4.6 us) fewer per layer.
-  const bool commit_in_finish = few_rows && r.L.n_qblocks == 0 && !compute_scale && !r.per_token;
+  // The pass that finishes Q, K and V of K-split sums stores K and V at their slots, and V^T for the prompts' attention, itself
+  // (a commit pass less, for per-token scales two), unless a scale has to wait for all of a layer's values or fresh prompts
+  // read back what an FP8 cache holds.
+  const bool want_vt = r.L.n_qblocks > 0 && !r.hp.chunked;
+  const bool store_in_finish = !compute_scale && !(r.fp8 && want_vt) && kv_store_fits(r.kv_store(0), kvd);
+  const bool decode_finish = few_rows && r.L.n_qblocks == 0 && !compute_scale && !r.per_token;   // by the pass with a thread per rotary pair
   float *skp = r.at<float>(r.L.skpart);
   float *rstd = r.at<float>(r.L.rstd), *ssq = r.at<float>(r.L.ssq);
 
@@ -832,7 +854,23 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   // Without form (a) a residual GEMM that split K leaves the sum of its splits to the RMSNorm pass that
   // reads the residual rows next (h_pend = number of splits waiting in skp; 1 = none).
   int32_t h_pend = 1;
+  KvStore ks{};
+  int32_t sums = 0;
+  const auto qkv_targets = [&](GemmParams &g, int j) {
+    g.cos_sin = r.at<float2>(r.L.cos_sin);
+    g.head_dim = m.head_dim; g.q_dim = qd; g.kv_dim = kvd;
+    g.q_out = qb; g.k_out = kb; g.v_out = vb; g.slots = r.at<int64_t>(r.L.slots);
+    if (!store_in_finish) return;
+    ks = r.kv_store(j);
+    if (want_vt) {
+      ks.rows = 1;   // (the prompts' attention reads K rows)
+      ks.tiles = (const KVTile *)r.meta(r.L.m_kvtiles); ks.n_tiles = r.L.n_kvtiles; ks.vt = vt; ks.vt_ld = r.L.vt_ld;
+    }
+    g.store = &ks; g.sums_left = &sums;
+  };
   for (int j = 0; j < c->l; ++j) {
+    int stored = 0;   // 1: the finishing pass of the layer's Q, K, V has stored K and V
+    sums = 0;
     if (!packed) {
       norm_h(c->norm1[j], nullptr, h_pend);
       h_pend = 1;
@@ -851,32 +889,48 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
         if (ns > 1) { q32 = skp; k32 = q32 + qd; v32 = k32 + kvd; }
         fp_splits = ns;
       }
-      QkvFinishParams fp{};
-      fp.q32 = q32; fp.k32 = k32; fp.v32 = v32; fp.ld32 = qd + 2 * kvd; fp.n_splits = fp_splits; fp.q = qb; fp.k = kb; fp.v = vb;
-      fp.T = T; fp.n_q_heads = m.n_q_heads; fp.n_kv_heads = m.n_kv_heads; fp.head_dim = m.head_dim;
-      fp.cos_sin = r.at<float2>(r.L.cos_sin);
-      fp.amax = compute_scale ? r.at<uint32_t>(r.L.amax) + (int64_t)j * 2 * m.n_kv_heads : nullptr;
-      if (commit_in_finish) {
-        fp.cache_k = r.cache_plane(j, 0); fp.cache_v = r.cache_plane(j, 1); fp.slots = r.at<int64_t>(r.L.slots);
-        fp.scales = r.fp8 ? r.layer_scales(j) : nullptr;
+      if (store_in_finish && !decode_finish) {
+        tm.end();
+        GemmParams g{};
+        g.M = T; g.N = qd + 2 * kvd; g.partial = q32; g.n_splits = fp_splits;
+        qkv_targets(g, j);
+        tm.begin(TC_COMMIT);
+        launch_kv_finish(g, EPI_QKV, st);
+        stored = 1;
+      } else {
+        QkvFinishParams fp{};
+        fp.q32 = q32; fp.k32 = k32; fp.v32 = v32; fp.ld32 = qd + 2 * kvd; fp.n_splits = fp_splits; fp.q = qb; fp.k = kb; fp.v = vb;
+        fp.T = T; fp.n_q_heads = m.n_q_heads; fp.n_kv_heads = m.n_kv_heads; fp.head_dim = m.head_dim;
+        fp.cos_sin = r.at<float2>(r.L.cos_sin);
+        fp.amax = compute_scale ? r.at<uint32_t>(r.L.amax) + (int64_t)j * 2 * m.n_kv_heads : nullptr;
+        if (decode_finish) {
+          fp.cache_k = r.cache_plane(j, 0); fp.cache_v = r.cache_plane(j, 1); fp.slots = r.at<int64_t>(r.L.slots);
+          fp.scales = r.fp8 ? r.layer_scales(j) : nullptr;
+          stored = 1;
+        }
+        launch_qkv_finish(fp, st);
       }
-      launch_qkv_finish(fp, st);
       tm.end();
     } else {
       GemmParams g{};
       g.A = ab; g.lda = d; g.M = T; g.N = qd + 2 * kvd; g.K = d;
       g.wtab = c->qkv_tab[j]; g.ldw = d; g.wpack = wpacked ? c->qkv_pack[j] : nullptr; g.rstd = packed ? rstd : nullptr;
       g.partial = skp; g.partial_bytes = SKINNY_PARTIAL_BYTES;
-      g.cos_sin = r.at<float2>(r.L.cos_sin);
-      g.head_dim = m.head_dim; g.q_dim = qd; g.kv_dim = kvd;
-      g.q_out = qb; g.k_out = kb; g.v_out = vb;
+      qkv_targets(g, j);
       g.first_cache_layer = j;
       g.amax = compute_scale ? r.at<uint32_t>(r.L.amax) : nullptr;
       tm.begin(TC_QKV);
       if (launch_gemm(g, EPI_QKV, 0, st) != 0) return fail(SWIFTKV_EHIP, "QKV GEMM launch failed");
       tm.end();
+      if (sums > 0) {
+        g.n_splits = sums;
+        tm.begin(TC_COMMIT);
+        launch_kv_finish(g, EPI_QKV, st);
+        tm.end();
+        stored = 1;
+      }
     }
-    if (!commit_in_finish) {
+    if (!stored) {
       CommitParams cp{};
       cp.tiles = (const KVTile *)r.meta(r.L.m_kvtiles); cp.n_tiles = r.L.n_kvtiles;
       cp.n_kv_heads = m.n_kv_heads; cp.head_dim = m.head_dim;
@@ -897,18 +951,18 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       }
       launch_kv_commit(cp, st);
       tm.end();
-      if (r.hp.chunked) {   // cached prefix + the rows just committed -> contiguous K rows and V^T columns
-        GatherParams gp{};
-        gp.tiles = (const GatherTile *)r.meta(r.L.m_gtiles); gp.n_tiles = r.L.n_gtiles;
-        gp.n_kv_heads = m.n_kv_heads; gp.head_dim = m.head_dim;
-        gp.cache_k = r.cache_plane(j, 0); gp.cache_v = r.cache_plane(j, 1); gp.fp8 = r.fp8_kind();
-        gp.scales = r.fp8 ? r.layer_scales(j) : nullptr;
-        gp.block_tables = kv->block_tables; gp.max_blocks_per_seq = kv->max_blocks_per_seq; gp.n_blocks = kv->n_blocks;
-        gp.k_dst = r.at<bf16_t>(r.L.kcat); gp.vt = vt; gp.vt_ld = r.L.vt_ld;
-        tm.begin(TC_OTHER);
-        launch_kv_gather(gp, st);
-        tm.end();
-      }
+    }
+    if (r.hp.chunked) {   // cached prefix + the rows just committed -> contiguous K rows and V^T columns
+      GatherParams gp{};
+      gp.tiles = (const GatherTile *)r.meta(r.L.m_gtiles); gp.n_tiles = r.L.n_gtiles;
+      gp.n_kv_heads = m.n_kv_heads; gp.head_dim = m.head_dim;
+      gp.cache_k = r.cache_plane(j, 0); gp.cache_v = r.cache_plane(j, 1); gp.fp8 = r.fp8_kind();
+      gp.scales = r.fp8 ? r.layer_scales(j) : nullptr;
+      gp.block_tables = kv->block_tables; gp.max_blocks_per_seq = kv->max_blocks_per_seq; gp.n_blocks = kv->n_blocks;
+      gp.k_dst = r.at<bf16_t>(r.L.kcat); gp.vt = vt; gp.vt_ld = r.L.vt_ld;
+      tm.begin(TC_OTHER);
+      launch_kv_gather(gp, st);
+      tm.end();
     }
     if (r.L.n_qblocks > 0) {
       AttnPrefillParams ap{};

@@ -87,6 +87,28 @@ enum GemmEpi {
   EPI_PARTIAL = 6      // fp32 partial sums of one K split (a finishing pass or the consumer adds them up)
 };
 
+struct KVTile {  // 64 consecutive new tokens of one sequence
+  int32_t row0;     // packed row of first token
+  int32_t n_valid;  // tokens present (1..64)
+  int32_t vt_col0;  // V^T column of first token (64-aligned), or -1 when no V^T is wanted
+  int32_t pad;
+};
+// Where the pass that finishes K and V of K-split projections puts them besides, or instead of, their bf16 rows (launch_kv_finish).
+enum KvStoreKind { KV_STORE_BF16 = 0, KV_STORE_GIVEN = 1, KV_STORE_PER_TOKEN = 2 };   // bf16; e4m3 under the scales given per head / computed per token
+struct KvStore {
+  int32_t kind;
+  int32_t rows;               // bit 0: K rows are wanted too (k_out, stage), bit 1: V rows
+  void *cache_k, *cache_v;    // planes of the first cache layer written
+  int64_t layer_bytes;        // from one projection's planes to the next one's
+  float *scales;              // of that layer: [2][Hkv], or [2][n_slots] (written)
+  int64_t scale_stride;       // floats from one projection's to the next one's
+  int64_t n_slots;
+  const KVTile *tiles;        // with vt: the V^T columns of the tiles that want them
+  int32_t n_tiles;
+  bf16_t *vt;                 // [kv_dim, vt_ld], bf16 cache only, or null
+  int64_t vt_ld;
+};
+
 struct GemmParams {
   // activations: A [M, K] bf16 row-major, leading dimension lda
   const bf16_t *A;
@@ -126,6 +148,10 @@ struct GemmParams {
   size_t partial_bytes;
   int32_t *n_splits_out;       // HOST, or null.  Given (RESID, STORE_BF16), the consumer of C adds the splits: their number goes here
                                // (1 = C is final) and C is untouched when it is larger; null = C is always final
+  // HOST, or null (QKV, KV).  sums_left given, a launch whose sums need a finishing pass leaves them to its caller, who runs
+  // launch_kv_finish: their number goes here (0: everything is where it belongs).  store: where that pass puts K and V.
+  int32_t *sums_left;
+  const KvStore *store;
   int32_t streamed;            // row-major weights of rows that only pass once (the last tokens): gemm_stream_kernel may take them
   int32_t n_splits, split_steps;   // set by launch_gemm_mid: K splits and 64-wide k steps of each
 };
@@ -156,6 +182,10 @@ GemmRoute route_gemm(const GemmParams &p, int epi);
 int launch_gemm_wreg(const GemmParams &p, int epi, int fm, hipStream_t st);
 int launch_gemm_stream(const GemmParams &p, int epi, int fm, bool packed, hipStream_t st);
 [[nodiscard]] int launch_splits_finish(const GemmParams &p, int epi, hipStream_t st);
+// Q, K, V (EPI_QKV) or the later layers' K, V (EPI_KV) from p.n_splits partial sums: added in split order, 1/rms, rotation, rounding, and
+// K and V to their rows, slots and V^T columns.  No absmax (p.amax): computed per-head scales need all values first.
+bool kv_store_fits(const KvStore &s, int kv_dim);
+int launch_kv_finish(const GemmParams &p, int epi, hipStream_t st);
 
 // skinny (weight-streaming) GEMM for M <= 80 rows
 struct SkinnyParams {
@@ -179,7 +209,9 @@ GemmRoute route_skinny(const SkinnyParams &p, int epi);
 
 // Few-row batches (decode steps): the Q, K, V projections come out of the weight-streaming kernel as
 // fp32; this step rotates q and k (rotate-half, angles of the row's position), rounds to bf16 once and,
-// for an FP8 cache with computed scales, collects the absmax of the stored K and V values per KV head.
+// for an FP8 cache with computed scales, collects the absmax of the stored K and V values per KV head.  A thread per rotary pair: for
+// decode rows it starts sooner than launch_kv_finish (one row 3.6 us and 4.3, 64 rows 4.2 and 4.4), and it serves the calls whose K and
+// V cannot be stored yet, computed scales and fresh prompts over an FP8 cache.
 struct QkvFinishParams {
   const float *q32, *k32, *v32;   // rows of q_dim / kv_dim / kv_dim columns, row stride ld32 elements (0: dense)
   int32_t ld32;
@@ -304,12 +336,6 @@ int launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st);
 int launch_pack_w(const bf16_t *const *wtab, const bf16_t *W, int64_t ldw, int32_t N, int32_t K, int32_t rope_hd, bf16_t *out, hipStream_t st);
 int launch_fold_gain(const bf16_t *W, const bf16_t *gain, bf16_t *out, int64_t rows, int32_t K, hipStream_t st);
 
-struct KVTile {  // 64 consecutive new tokens of one sequence
-  int32_t row0;     // packed row of first token
-  int32_t n_valid;  // tokens present (1..64)
-  int32_t vt_col0;  // V^T column of first token (64-aligned), or -1 when no V^T is wanted
-  int32_t pad;
-};
 struct CommitParams {
   const KVTile *tiles;
   int32_t n_tiles, n_kv_heads, head_dim;

@@ -620,6 +620,197 @@ int launch_token_scales(const TokenScaleParams &p, hipStream_t st) {
   return 0;
 }
 
+// --------------------------------------------- finishing pass of Q, K and V ----
+// K-split Q, K, V (EPI_QKV) or later layers' K, V (EPI_KV): the partial sums added in split order, 1/rms, rotation, rounding
+// once, and K and V straight to where they are read: bf16 rows, paged slots (bf16, e4m3 under given scales, e4m3 under the token's own
+// scale, which the wave that holds the row finds on the way) and V^T columns.  Bound by the latency of its loads and stores.
+// A wave takes 1024 columns of a row, 8 + 8 values of a rotary pair of chunks per lane, so that a row's partial sums are 32-byte pieces
+// in flight together; V that is wanted transposed goes by 64-token tiles through LDS instead.  Before, a pass with one rotary pair per
+// lane, a pass for the tokens' scales and the commit pass followed one another: 512 rows over an e4m3 cache with per-token scales,
+// Q, K, V and two later layers 102 us in eight launches -> 25 in three, 333 rows in bf16 30 -> 18, 597 rows with 64-wide heads
+// 12.7 a layer -> 6.0.
+// NIT: rounds of 1024 columns a wave holds (per-token scales of more than 1024 K columns).
+template <int EPI, int HD, int NIT>
+__global__ __launch_bounds__(256) void kv_finish_kernel(GemmParams p, KvStore s, int vt_wgs, int q_units, int kv_units) {
+  constexpr int CH = HD / 8, PAIRS = HD / 16;   // 16-byte chunks of a head; pairs of chunks (c, c + CH / 2)
+  __shared__ uint4 sv[EPI == EPI_QKV ? 64 * CH : 1];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int n_kv = p.kv_dim / HD;
+  const int64_t stride = (int64_t)p.M * p.N;
+  // eight columns at each of N places, the splits' loads of all of them in flight together
+  auto add_splits = [&](auto &src, auto &x) __attribute__((always_inline)) {
+    constexpr int N = sizeof(x) / sizeof(x[0]);
+    auto add = [&](int k, bool first) __attribute__((always_inline)) {
+      float4 a[N][2];
+#pragma unroll
+      for (int i = 0; i < N; ++i) { a[i][0] = *(const float4 *)(src[i] + k * stride); a[i][1] = *(const float4 *)(src[i] + k * stride + 4); }
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const float v[8] = {a[i][0].x, a[i][0].y, a[i][0].z, a[i][0].w, a[i][1].x, a[i][1].y, a[i][1].z, a[i][1].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[i][e] = first ? v[e] : x[i][e] + v[e];
+      }
+    };
+    add(0, true);
+    for (int k = 1; k < p.n_splits; ++k) add(k, false);
+  };
+  auto pack8 = [](const float (&x)[8]) __attribute__((always_inline)) {
+    return make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
+  };
+  if constexpr (EPI == EPI_QKV) {
+    if ((int)blockIdx.x < vt_wgs) {   // V of 64 tokens and one head: slots and V^T
+      const KVTile tile = s.tiles[blockIdx.x / n_kv];
+      const int head = blockIdx.x % n_kv;
+      constexpr int NI = 64 * CH / 256;
+      float x[NI][8], rs[NI];
+      int64_t slot[NI];
+      const float *src[NI];   // (rows past the tile's last repeat it)
+#pragma unroll
+      for (int ii = 0; ii < NI; ++ii) {
+        const int i = tid + ii * 256, r = i / CH, c = i % CH, row = tile.row0 + (r < tile.n_valid ? r : tile.n_valid - 1);
+        slot[ii] = p.slots[row];
+        rs[ii] = p.rstd ? p.rstd[row] : 1.f;
+        src[ii] = p.partial + (int64_t)row * p.N + p.q_dim + p.kv_dim + head * HD + c * 8;
+      }
+      add_splits(src, x);
+#pragma unroll
+      for (int ii = 0; ii < NI; ++ii)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[ii][e] = (tid + ii * 256) / CH < tile.n_valid ? x[ii][e] * rs[ii] : 0.f;   // (V^T columns past the sequence are zero)
+#pragma unroll
+      for (int ii = 0; ii < NI; ++ii) {
+        const int i = tid + ii * 256, r = i / CH, c = i % CH;
+        const uint4 v = pack8(x[ii]);
+        if (r < tile.n_valid) {
+          *(uint4 *)((bf16_t *)s.cache_v + (slot[ii] * n_kv + head) * HD + c * 8) = v;
+          if (s.rows & 2) *(uint4 *)(p.v_out + (int64_t)(tile.row0 + r) * p.kv_dim + head * HD + c * 8) = v;
+        }
+        sv[v_chunk<HD>(r, c)] = v;
+      }
+      if (tile.vt_col0 < 0) return;
+      __syncthreads();
+      store_vt<HD>(sv, s.vt + (int64_t)(head * HD) * s.vt_ld + tile.vt_col0, s.vt_ld, tid);
+      return;
+    }
+  }
+  // a wave per (row, unit): units of q, then of K, then (V^T is not wanted) of V; EPI_KV: of K and of V of every projection
+  const int units = EPI == EPI_QKV ? q_units + kv_units * (s.vt ? 1 : 2) : p.N / p.kv_dim * kv_units;
+  const int id = __builtin_amdgcn_readfirstlane(((int)blockIdx.x - vt_wgs) * 4 + (tid >> 6));
+  const int row = id / units, u = id % units;
+  if (row >= p.M) return;
+  int kind, part, proj = 0, col0;   // kind 0 = q, 1 = k, 2 = v; part: which 1024 columns; col0: column of the matrix in the sums
+  if constexpr (EPI == EPI_QKV) {
+    kind = u < q_units ? 0 : u < q_units + kv_units ? 1 : 2;
+    part = u - (kind == 0 ? 0 : kind == 1 ? q_units : q_units + kv_units);
+    col0 = kind == 0 ? 0 : kind == 1 ? p.q_dim : p.q_dim + p.kv_dim;
+  } else {
+    const int m = u / kv_units;
+    proj = m / 2; kind = 1 + m % 2; part = u % kv_units;
+    col0 = m * p.kv_dim;
+  }
+  const int dim = kind == 0 ? p.q_dim : p.kv_dim;
+  const float rs = p.rstd ? p.rstd[row] : 1.f;
+  const int64_t slot = kind == 0 ? 0 : p.slots[row];
+  uint4 lo[NIT], hi[NIT];
+  float amax = 0.f, head_scale = 1.f;   // (given scales: NIT = 1)
+#pragma unroll
+  for (int t = 0; t < NIT; ++t) {
+    const int item = (part * NIT + t) * 64 + lane, head = item / PAIRS, c = item % PAIRS;
+    lo[t] = hi[t] = make_uint4(0, 0, 0, 0);
+    if (item * 16 >= dim) continue;
+    const float *first = p.partial + (int64_t)row * p.N + col0 + head * HD + c * 8, *src[2] = {first, first + HD / 2};
+    float4 cs[4];
+    if (kind != 2) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) cs[e] = ((const float4 *)(p.cos_sin + (int64_t)row * (HD / 2) + c * 8))[e];
+    }
+    if (kind != 0 && s.kind == KV_STORE_GIVEN) head_scale = s.scales[(int64_t)proj * s.scale_stride + (kind == 2 ? n_kv : 0) + head];
+    float x[2][8];
+    add_splits(src, x);
+    float(&x0)[8] = x[0], (&x1)[8] = x[1];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { x0[e] *= rs; x1[e] *= rs; }
+    if (kind != 2) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float4 a = cs[e];
+        const float y0 = x0[2 * e] * a.x - x1[2 * e] * a.y, y1 = x1[2 * e] * a.x + x0[2 * e] * a.y;
+        const float z0 = x0[2 * e + 1] * a.z - x1[2 * e + 1] * a.w, z1 = x1[2 * e + 1] * a.z + x0[2 * e + 1] * a.w;
+        x0[2 * e] = y0; x1[2 * e] = y1; x0[2 * e + 1] = z0; x1[2 * e + 1] = z1;
+      }
+    }
+    lo[t] = pack8(x0); hi[t] = pack8(x1);
+    if (s.kind == KV_STORE_PER_TOKEN) {   // absmax of the values as stored
+      const uint32_t w[8] = {lo[t].x, lo[t].y, lo[t].z, lo[t].w, hi[t].x, hi[t].y, hi[t].z, hi[t].w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fmaxf(fabsf(bf16lo(w[e])), fabsf(bf16hi(w[e]))));
+    }
+  }
+  bf16_t *rows = nullptr;
+  if (kind == 0) rows = p.q_out + (int64_t)row * p.q_dim;
+  else if (EPI == EPI_QKV) rows = (kind == 1 ? p.k_out : p.v_out) + (int64_t)row * p.kv_dim;
+  else if (p.stage) rows = p.stage + (int64_t)row * p.N + col0;
+  const bool put_rows = rows && (kind == 0 || (s.rows & kind));
+  float token_scale = 1.f;
+  if (kind != 0 && s.kind == KV_STORE_PER_TOKEN) {
+    token_scale = fmaxf(wave_max(amax), 1e-12f) / 448.0f;
+    if (lane == 0 && s.cache_k) s.scales[(int64_t)proj * s.scale_stride + (kind == 2 ? s.n_slots : 0) + slot] = token_scale;
+  }
+#pragma unroll
+  for (int t = 0; t < NIT; ++t) {
+    const int item = (part * NIT + t) * 64 + lane, head = item / PAIRS, c = item % PAIRS, at = head * HD + c * 8;
+    if (item * 16 >= dim) continue;
+    if (put_rows) {
+      *(uint4 *)(rows + at) = lo[t];
+      *(uint4 *)(rows + at + HD / 2) = hi[t];
+    }
+    if (kind == 0 || !s.cache_k) continue;
+    unsigned char *plane = (unsigned char *)(kind == 1 ? s.cache_k : s.cache_v) + (int64_t)proj * s.layer_bytes;
+    const int64_t dst = slot * p.kv_dim + at;
+    if (s.kind == KV_STORE_BF16) {
+      *(uint4 *)((bf16_t *)plane + dst) = lo[t];
+      *(uint4 *)((bf16_t *)plane + dst + HD / 2) = hi[t];
+    } else {
+      const float sc = s.kind == KV_STORE_PER_TOKEN ? token_scale : head_scale;
+      const float inv = 1.f / sc;
+      uint2 a, b;
+      if (fast_scale(sc)) { a = quantize8<true>(lo[t], sc, inv); b = quantize8<true>(hi[t], sc, inv); }
+      else { a = quantize8<false>(lo[t], sc, inv); b = quantize8<false>(hi[t], sc, inv); }
+      *(uint2 *)(plane + dst) = a;
+      *(uint2 *)(plane + dst + HD / 2) = b;
+    }
+  }
+}
+template <int EPI, int HD>
+static void launch_kv_finish_hd(const GemmParams &p, const KvStore &s, hipStream_t st) {
+  const bool wide = s.kind == KV_STORE_PER_TOKEN && p.kv_dim > 1024;
+  const int cols = wide ? 4096 : 1024;
+  const int q_units = EPI == EPI_QKV ? (p.q_dim + cols - 1) / cols : 0, kv_units = (p.kv_dim + cols - 1) / cols;
+  const int units = EPI == EPI_QKV ? q_units + kv_units * (s.vt ? 1 : 2) : p.N / p.kv_dim * kv_units;
+  const int vt_wgs = EPI == EPI_QKV && s.vt ? s.n_tiles * (p.kv_dim / HD) : 0;
+  const dim3 grid((unsigned)(vt_wgs + ((int64_t)p.M * units + 3) / 4));
+  if (wide) hipLaunchKernelGGL((kv_finish_kernel<EPI, HD, 4>), grid, dim3(256), 0, st, p, s, vt_wgs, q_units, kv_units);
+  else hipLaunchKernelGGL((kv_finish_kernel<EPI, HD, 1>), grid, dim3(256), 0, st, p, s, vt_wgs, q_units, kv_units);
+}
+// (a token's own scale: its K or V row in one wave)
+bool kv_store_fits(const KvStore &s, int kv_dim) { return s.kind != KV_STORE_PER_TOKEN || kv_dim <= 4096; }
+int launch_kv_finish(const GemmParams &p, int epi, hipStream_t st) {
+  KvStore s{};
+  if (p.store) {
+    s = *p.store;
+  } else {
+    s.rows = 3;
+    if (epi == EPI_KV && !p.stage) {
+      s.cache_k = p.cache + (int64_t)p.first_cache_layer * p.cache_layer_stride;
+      s.cache_v = (bf16_t *)s.cache_k + p.cache_kv_stride;
+      s.layer_bytes = p.cache_layer_stride * 2;
+    }
+  }
+  if (epi == EPI_QKV) p.head_dim == 128 ? launch_kv_finish_hd<EPI_QKV, 128>(p, s, st) : launch_kv_finish_hd<EPI_QKV, 64>(p, s, st);
+  else p.head_dim == 128 ? launch_kv_finish_hd<EPI_KV, 128>(p, s, st) : launch_kv_finish_hd<EPI_KV, 64>(p, s, st);
+  return 0;
+}
+
 // ----------------------------------------------------------- QKV finish ----
 // grid (T, Hq + 2*Hkv), hd/2 threads: thread i owns the rotary pair (i, i + hd/2) of one head of one row.
 __global__ void qkv_finish_kernel(QkvFinishParams p) {

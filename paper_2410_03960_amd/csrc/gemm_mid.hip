@@ -278,17 +278,16 @@ __global__ void splits_finish_kernel(GemmParams p) {
     }
   }
 }
-// Q, K, V (EPI_QKV) or the later layers' K, V (EPI_KV): rotation, rounding, destination and absmax as in the GEMM's
-// own epilogue.  A wave takes one head of a row, a rotary pair per lane (half of them idle at head_dim 64).
-// Without absmax: grid (rows, groups of 4 heads).  With it: grid (groups of `rows` rows, heads), the rows dealt to the four
+// The same where an FP8 cache's scales are computed from all values of a head: rotation, rounding, bf16 rows and the absmax as in the
+// GEMM's own epilogue (without absmax: launch_kv_finish).  A wave takes one head of a row, a rotary pair per lane (half of
+// them idle at head_dim 64).  Grid (groups of `rows` rows, heads), the rows dealt to the four
 // waves, and one atomic per workgroup: all heads' maxima share a few cache lines, and the atomics on them run one after
 // the other at about 5 ns each (one per row and head: 512 rows x 64 heads took 200 us).
-template <int EPI, int HD, bool AMAX>
+template <int EPI, int HD>
 __global__ __launch_bounds__(256) void rope_finish_kernel(GemmParams p, int rows) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int hs = AMAX ? blockIdx.y : blockIdx.y * 4 + wave;
+  const int hs = blockIdx.y;
   const int n_kv = p.kv_dim / HD, n_q = EPI == EPI_QKV ? p.q_dim / HD : 0;
-  if (hs >= p.N / HD) return;
   int kind, head, proj = 0;                              // kind 0 = q, 1 = k, 2 = v
   if constexpr (EPI == EPI_QKV) {
     kind = hs < n_q ? 0 : (hs < n_q + n_kv ? 1 : 2);
@@ -303,8 +302,7 @@ __global__ __launch_bounds__(256) void rope_finish_kernel(GemmParams p, int rows
   const auto finish_row = [&](int row) __attribute__((always_inline)) {   // absmax of the lane's pair, as stored
     bf16_t *dst;
     if constexpr (EPI == EPI_QKV) dst = (kind == 0 ? p.q_out + (int64_t)row * p.q_dim : (kind == 1 ? p.k_out : p.v_out) + (int64_t)row * p.kv_dim) + head * HD;
-    else if (p.stage) dst = p.stage + (int64_t)row * p.N + hs * HD;
-    else dst = p.cache + (int64_t)(p.first_cache_layer + proj) * p.cache_layer_stride + (kind == 2 ? p.cache_kv_stride : 0) + p.slots[row] * p.kv_dim + head * HD;
+    else dst = p.stage + (int64_t)row * p.N + hs * HD;
     const float *src = p.partial + (int64_t)row * p.N + hs * HD;
     const float rs = p.rstd ? p.rstd[row] : 1.f;
     if (i >= HD / 2) return 0.f;
@@ -321,19 +319,16 @@ __global__ __launch_bounds__(256) void rope_finish_kernel(GemmParams p, int rows
     dst[i + HD / 2] = b1;
     return fmaxf(fabsf(bf16_to_f32(b0)), fabsf(bf16_to_f32(b1)));
   };
-  if constexpr (!AMAX) finish_row(blockIdx.x);
-  if constexpr (AMAX) {
-    __shared__ float of_wave[4];
-    const int row0 = blockIdx.x * rows, row_end = row0 + rows < p.M ? row0 + rows : p.M;
-    float a = 0.f;
-    for (int row = row0 + wave; row < row_end; row += 4) a = fmaxf(a, finish_row(row));
-    a = wave_max(a);
-    if (lane == 0) of_wave[wave] = a;
-    __syncthreads();
-    if (threadIdx.x == 0 && kind != 0) {
-      a = fmaxf(fmaxf(of_wave[0], of_wave[1]), fmaxf(of_wave[2], of_wave[3]));
-      atomicMax(p.amax + ((int64_t)(p.first_cache_layer + proj) * 2 + (kind == 2 ? 1 : 0)) * n_kv + head, __float_as_uint(a));
-    }
+  __shared__ float of_wave[4];
+  const int row0 = blockIdx.x * rows, row_end = row0 + rows < p.M ? row0 + rows : p.M;
+  float a = 0.f;
+  for (int row = row0 + wave; row < row_end; row += 4) a = fmaxf(a, finish_row(row));
+  a = wave_max(a);
+  if (lane == 0) of_wave[wave] = a;
+  __syncthreads();
+  if (threadIdx.x == 0 && kind != 0) {
+    a = fmaxf(fmaxf(of_wave[0], of_wave[1]), fmaxf(of_wave[2], of_wave[3]));
+    atomicMax(p.amax + ((int64_t)(p.first_cache_layer + proj) * 2 + (kind == 2 ? 1 : 0)) * n_kv + head, __float_as_uint(a));
   }
 }
 
@@ -345,19 +340,16 @@ void launch_finish(const GemmParams &p, hipStream_t st) {
 template <int EPI, int HD>
 void launch_rope_finish_hd(const GemmParams &p, hipStream_t st) {
   const int heads = p.N / HD;
-  if (!p.amax) {
-    hipLaunchKernelGGL((rope_finish_kernel<EPI, HD, false>), dim3(p.M, (heads + 3) / 4), dim3(256), 0, st, p, 1);
-    return;
-  }
   // about 1024 workgroups (5 us of atomics), but no wave with more than 8 rows one after the other (2048 and 4096 workgroups: 4
   // and 15 us slower over 512 rows x 64 heads)
   const int64_t want = ((int64_t)p.M * heads + 1023) / 1024;
   const int rows = (int)std::min<int64_t>(32, std::max<int64_t>(4, (want + 3) / 4 * 4));
-  hipLaunchKernelGGL((rope_finish_kernel<EPI, HD, true>), dim3((p.M + rows - 1) / rows, heads), dim3(256), 0, st, p, rows);
+  hipLaunchKernelGGL((rope_finish_kernel<EPI, HD>), dim3((p.M + rows - 1) / rows, heads), dim3(256), 0, st, p, rows);
 }
 template <int EPI>
 void launch_rope_finish(const GemmParams &p, hipStream_t st) {
-  if (p.head_dim == 128) launch_rope_finish_hd<EPI, 128>(p, st);
+  if (!p.amax) launch_kv_finish(p, EPI, st);
+  else if (p.head_dim == 128) launch_rope_finish_hd<EPI, 128>(p, st);
   else launch_rope_finish_hd<EPI, 64>(p, st);
 }
 
@@ -471,6 +463,7 @@ int launch_gemm_mid(const GemmParams &p0, int epi, const MidPlan &pl, hipStream_
   if (!rope) q.head_dim = 0;   // the packed order of rotary operands is theirs alone
   if (int e = launch_one(q, EPI_PARTIAL, pl, st)) return e;
   if (p.n_splits_out) { *p.n_splits_out = pl.n_splits; return 0; }
+  if (rope && p.sums_left) { *p.sums_left = pl.n_splits; return 0; }
   return launch_splits_finish(p, epi, st);
 }
 
