@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libswiftkv.so")
-SOURCES = ["api.hip", "gemm.hip", "gemm_wreg.hip", "gemm_mid.hip", "gemm_stream.hip", "attention.hip", "skinny.hip", "elementwise.hip"]
+SOURCES = ["api.hip", "gemm.hip", "gemm_wreg.hip", "gemm_mid.hip", "gemm_stream.hip", "attention.hip", "skinny.hip", "skinny_resid.hip", "elementwise.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]

@@ -47,7 +47,7 @@ struct Layout {  // byte offsets into the workspace
   int32_t n_qblocks = 0, n_kvtiles = 0, n_dec = 0, n_gtiles = 0;
   int64_t kcat_rows = 0;   // rows of the K buffer gathered from the cache (prompt chunks over a cached prefix), else 0
   size_t err, meta, positions, seq_of, last_rows, slots, cos_sin, h, a, rstd, ssq, q, k, v, o, vt, kcat, z, stage, amax, qkv32, skpart, ee_logits, ee_flags;
-  size_t th, ta, tq, to, tz, partial, total;
+  size_t rssq, th, ta, tq, to, tz, partial, total;
   // offsets (in int32 units) inside the meta block copied from the host
   size_t m_cu, m_ctx, m_qblocks, m_kvtiles, m_dec, m_tail, m_gtiles, m_words;
 };
@@ -138,6 +138,7 @@ Layout make_layout(const swiftkv_ctx *c, int64_t T, int32_t B, int64_t vt_ld, in
   L.ee_logits = take(c->ee_head ? (size_t)B * m.vocab * 4 : 0);   // logits of the extra head
   L.skpart = take(SKINNY_PARTIAL_BYTES);   // K-split partial sums of the weight-streaming GEMMs
   L.qkv32 = take((size_t)std::min<int64_t>(T, SKINNY_MAX_ROWS) * (qd + 2 * kvd) * 4);   // fp32 Q, K, V of few-row batches
+  L.rssq = take((size_t)SKINNY_RESID_ROWS * (d / 16) * 4);   // sums of squares per 16-column block of very few rows
   L.th = take((size_t)B * d * 4);
   L.ta = take((size_t)B * std::max<int64_t>(d, qd) * 2);
   L.tq = take((size_t)B * qd * 2);
@@ -437,8 +438,9 @@ int run_plan(Run &r, const int32_t *token_ids) {
 }
 
 // Eq. 2 + AcrossKV: one GEMM over the concatenated leader [W_K;W_V] matrices.
-// `hidden` = the layer-l output rounded to bf16; 1/rms of its rows is already in the workspace when rstd_ready
-int run_fused_kv(Run &r, const bf16_t *hidden, bool rstd_ready, Timer &tm) {
+// `hidden` = the layer-l output rounded to bf16; 1/rms of its rows is already in the workspace when rstd_ready, or follows from
+// `row_ssq` (see SkinnyParams::ssq)
+int run_fused_kv(Run &r, const bf16_t *hidden, bool rstd_ready, Timer &tm, const float *row_ssq = nullptr) {
   swiftkv_ctx *c = r.c;
   const swiftkv_model_cfg &m = c->cfg;
   const int kvd = m.n_kv_heads * m.head_dim;
@@ -450,7 +452,7 @@ int run_fused_kv(Run &r, const bf16_t *hidden, bool rstd_ready, Timer &tm) {
   GemmParams g{};
   g.A = hidden; g.lda = m.hidden; g.M = (int32_t)r.L.T; g.N = c->P * 2 * kvd; g.K = m.hidden;
   g.W = c->kv_pack; g.ldw = m.hidden; g.wpack = c->kvf_pack;   // gains are folded into kv_pack; rstd is applied in the epilogue
-  g.rstd = r.at<float>(r.L.rstd); g.cos_sin = r.at<float2>(r.L.cos_sin);
+  g.rstd = row_ssq ? nullptr : r.at<float>(r.L.rstd); g.cos_sin = r.at<float2>(r.L.cos_sin);
   g.partial = r.at<float>(r.L.skpart); g.partial_bytes = SKINNY_PARTIAL_BYTES;
   g.head_dim = m.head_dim; g.q_dim = m.n_q_heads * m.head_dim; g.kv_dim = kvd;
   g.slots = r.at<int64_t>(r.L.slots); g.cache = (bf16_t *)r.kv->data;
@@ -474,7 +476,7 @@ int run_fused_kv(Run &r, const bf16_t *hidden, bool rstd_ready, Timer &tm) {
   if (g.M <= SKINNY_MAX_ROWS && c_bytes <= SKINNY_PARTIAL_BYTES / 2) {
     float *c32 = g.partial, *splits = c32 + c_bytes / 4;
     int32_t ns = 1;
-    SkinnyParams sp{hidden, g.M, g.N, g.K, g.W, nullptr, c32, splits, SKINNY_PARTIAL_BYTES - c_bytes, nullptr, &ns};
+    SkinnyParams sp{hidden, g.M, g.N, g.K, g.W, nullptr, c32, splits, SKINNY_PARTIAL_BYTES - c_bytes, nullptr, &ns, row_ssq, m.rms_eps};
     if (launch_skinny(sp, EPI_STORE_F32, r.st)) return fail(SWIFTKV_EHIP, "fused KV GEMM launch failed");
     g.partial = ns > 1 ? splits : c32;
     sums = ns;
@@ -517,10 +519,11 @@ int run_fused_kv(Run &r, const bf16_t *hidden, bool rstd_ready, Timer &tm) {
 
 // n_splits_out (host, may be null): see SkinnyParams -- the consumer of C adds the K splits
 int tail_gemm(const swiftkv_ctx *c, const bf16_t *A, int M, int N, int K, const bf16_t *W, const bf16_t *W2,
-              const bf16_t *const *gu_tab, void *C, int epi, float *partial, hipStream_t st, int32_t *n_splits_out = nullptr) {
+              const bf16_t *const *gu_tab, void *C, int epi, float *partial, hipStream_t st, int32_t *n_splits_out = nullptr,
+              const float *row_ssq = nullptr) {
   if (n_splits_out) *n_splits_out = 1;
   if (M <= 80) {
-    SkinnyParams s{A, M, N, K, W, W2, C, partial, SKINNY_PARTIAL_BYTES, nullptr, n_splits_out};
+    SkinnyParams s{A, M, N, K, W, W2, C, partial, SKINNY_PARTIAL_BYTES, nullptr, n_splits_out, row_ssq, c->cfg.rms_eps};
     return launch_skinny(s, epi, st);
   }
   GemmParams g{};
@@ -530,7 +533,6 @@ int tail_gemm(const swiftkv_ctx *c, const bf16_t *A, int M, int N, int K, const 
   g.partial = partial; g.partial_bytes = SKINNY_PARTIAL_BYTES;
   g.n_splits_out = n_splits_out;
   g.streamed = 1;
-  (void)c;
   return launch_gemm(g, epi, M < 1024 ? 0 : 2, st);
 }
 
@@ -820,12 +822,14 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   float *rstd = r.at<float>(r.L.rstd), *ssq = r.at<float>(r.L.ssq);
 
   // ------------------------------------------ layers 1..l on every new token ----
-  // Two forms of the RMSNorm in front of the QKV and gate/up projections.
+  // Three forms of the RMSNorm in front of the QKV and gate/up projections.
   // (a) Fragment-order weights (large batches): the residual epilogue of the O / down GEMM leaves, next to
   //     the fp32 residual stream, ab = bf16(h * gain of the next norm) and the rows' sums of squares; the
   //     next projection reads ab and applies 1/rms as a row factor in its own epilogue.  No pass over h.
   // (b) Otherwise one kernel per norm turns fp32 rows into normed bf16 rows; it also adds up the K splits a
   //     residual GEMM left behind, so (b) is taken whenever the O or the down GEMM is better off split.
+  // (c) Very few rows: as (a), the O / down GEMM being skinny_resid_kernel, and the next projection takes 1/rms from its sums of
+  //     squares itself.
   const bool wpacked = !few_rows && c->have_wpack;   // the large GEMMs read the fragment-order copies
   const auto resid_params = [&](const bf16_t *A, int K, const bf16_t *W, const bf16_t *wpack) {
     GemmParams g{};
@@ -833,6 +837,12 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     g.partial = skp; g.partial_bytes = SKINNY_PARTIAL_BYTES;
     return g;
   };
+  const auto chained = [&](int rows) {   // form (c)
+    return skinny_resid_pays(rows, d, qd) && skinny_resid_pays(rows, d, m.ffn) && skinny_takes_ssq(rows, m.ffn, d) && skinny_takes_ssq(rows, qd, d) &&
+           (size_t)rows * c->P * 2 * kvd * 4 <= SKINNY_PARTIAL_BYTES / 4;   // (the later layers' K, V on the weight-streaming kernels)
+  };
+  const bool chain = chained(T);
+  float *row_ssq = r.at<float>(r.L.rssq);
   bool packed = wpacked && T >= 1024;   // form (a)
   if (packed) {
     int32_t ns;
@@ -871,7 +881,7 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   for (int j = 0; j < c->l; ++j) {
     int stored = 0;   // 1: the finishing pass of the layer's Q, K, V has stored K and V
     sums = 0;
-    if (!packed) {
+    if (!packed && !(chain && j > 0)) {
       norm_h(c->norm1[j], nullptr, h_pend);
       h_pend = 1;
     }
@@ -884,7 +894,8 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       tm.begin(TC_QKV);
       {
         int32_t ns = 1;   // K splits left to the finishing pass (it reads the fp32 values anyway)
-        SkinnyParams sp{ab, T, qd + 2 * kvd, d, nullptr, nullptr, q32, skp, SKINNY_PARTIAL_BYTES, c->qkv_tab[j], &ns};
+        SkinnyParams sp{ab, T, qd + 2 * kvd, d, nullptr, nullptr, q32, skp, SKINNY_PARTIAL_BYTES, c->qkv_tab[j], &ns,
+                        chain && j > 0 ? row_ssq : nullptr, m.rms_eps};
         if (launch_skinny(sp, EPI_STORE_F32, st)) return fail(SWIFTKV_EHIP, "QKV GEMM launch failed");
         if (ns > 1) { q32 = skp; k32 = q32 + qd; v32 = k32 + kvd; }
         fp_splits = ns;
@@ -988,7 +999,12 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       if (launch_decode_combine(dp.partial, ob, dp.rows, dp.n_rows, m.n_q_heads, m.head_dim, dp.n_split, st) != 0) return fail(SWIFTKV_EHIP, "decode combine launch failed");
       tm.end();
     }
-    if (few_rows) {
+    if (chain) {
+      tm.begin(TC_O);
+      const SkinnyResidParams rp{ob, T, d, qd, c->wo[j], h, c->norm2[j], ab, row_ssq};
+      if (launch_skinny_resid(rp, st)) return fail(SWIFTKV_EHIP, "O GEMM launch failed");
+      tm.end();
+    } else if (few_rows) {
       tm.begin(TC_O);
       if (tail_gemm(c, ob, T, d, qd, c->wo[j], nullptr, nullptr, h, EPI_RESID, skp, st, &h_pend)) return fail(SWIFTKV_EHIP, "O GEMM launch failed");
       tm.end();
@@ -1000,15 +1016,22 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       if (launch_gemm(g, EPI_RESID, 0, st) != 0) return fail(SWIFTKV_EHIP, "O GEMM launch failed");
       tm.end();
     }
-    tm.begin(TC_NORM);
-    if (packed) launch_rstd_from_ssq(ssq, n_ssq, rstd, T, d, m.rms_eps, st);
-    else { launch_rmsnorm_rows(h, c->norm2[j], ab, T, d, m.rms_eps, nullptr, st, skp, h_pend); h_pend = 1; }
-    tm.end();
+    if (!chain) {
+      tm.begin(TC_NORM);
+      if (packed) launch_rstd_from_ssq(ssq, n_ssq, rstd, T, d, m.rms_eps, st);
+      else { launch_rmsnorm_rows(h, c->norm2[j], ab, T, d, m.rms_eps, nullptr, st, skp, h_pend); h_pend = 1; }
+      tm.end();
+    }
     if (few_rows) {
       tm.begin(TC_GATEUP);
-      if (tail_gemm(c, ab, T, m.ffn, d, c->wgate[j], c->wup[j], c->gu_tab[j], zb, EPI_SWIGLU, skp, st)) return fail(SWIFTKV_EHIP, "gate/up GEMM launch failed");
+      if (tail_gemm(c, ab, T, m.ffn, d, c->wgate[j], c->wup[j], c->gu_tab[j], zb, EPI_SWIGLU, skp, st, nullptr, chain ? row_ssq : nullptr))
+        return fail(SWIFTKV_EHIP, "gate/up GEMM launch failed");
       tm.end();
       tm.begin(TC_DOWN);
+      if (chain) {   // the operand of the next layer, or (gain one) of the fused K/V projection
+        const SkinnyResidParams rp{zb, T, d, m.ffn, c->wdown[j], h, j + 1 < c->l ? c->norm1[j + 1] : nullptr, ab, row_ssq};
+        if (launch_skinny_resid(rp, st)) return fail(SWIFTKV_EHIP, "down GEMM launch failed");
+      } else
       // (the next reader of h is a norm pass: the next layer's, or the one in front of the later layers' K/V projection)
       if (tail_gemm(c, zb, T, d, m.ffn, c->wdown[j], nullptr, nullptr, h, EPI_RESID, skp, st, (j + 1 < c->l || c->P > 0) ? &h_pend : nullptr))
         return fail(SWIFTKV_EHIP, "down GEMM launch failed");
@@ -1046,11 +1069,11 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   // -------------------------- later layers' K/V from the layer-l output ----
   // operand: the layer-l output rounded to bf16 (the leaders' gains live in the packed weight), 1/rms per row
   if (c->P > 0) {
-    if (!packed) {
+    if (!packed && !chain) {
       norm_h(nullptr, rstd, h_pend);
       h_pend = 1;
     }
-    if (int e = run_fused_kv(r, ab, true, tm)) return e;
+    if (int e = run_fused_kv(r, ab, true, tm, chain ? row_ssq : nullptr)) return e;
   }
 
   // ----------------------------- last token of every sequence: layers l+1..L ----
@@ -1070,11 +1093,13 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       return fail(SWIFTKV_EHIP, "early-exit head GEMM failed");
     launch_early_exit_flags(r.at<float>(r.L.ee_logits), B, m.vocab, c->ee_threshold, r.at<int32_t>(r.L.ee_flags), st);
   }
+  const bool t_chain = chained(B);
   for (int j = c->l; j < m.n_layers; ++j) {
     const int cl = c->l + (j - c->l) / c->g;
-    norm_th(c->norm1[j]);
+    const float *in_ssq = t_chain && j > c->l ? row_ssq : nullptr;
+    if (!in_ssq) norm_th(c->norm1[j]);
     AttnDecodeParams dp{};
-    if (tail_gemm(c, ta, B, qd, d, c->wq[j], nullptr, nullptr, tq, EPI_STORE_BF16, skp, st, &dp.q_splits)) return fail(SWIFTKV_EHIP, "tail q GEMM failed");
+    if (tail_gemm(c, ta, B, qd, d, c->wq[j], nullptr, nullptr, tq, EPI_STORE_BF16, skp, st, &dp.q_splits, in_ssq)) return fail(SWIFTKV_EHIP, "tail q GEMM failed");
     dp.q = tq; dp.q_sums = skp; dp.q_stride = (int64_t)B * qd; dp.out = to; dp.rows = (const DecodeRow *)r.meta(r.L.m_tail); dp.n_rows = B;
     dp.n_q_heads = m.n_q_heads; dp.n_kv_heads = m.n_kv_heads; dp.head_dim = m.head_dim;
     dp.cache_k = r.cache_plane(cl, 0); dp.cache_v = r.cache_plane(cl, 1); dp.fp8 = r.fp8_kind();
@@ -1084,6 +1109,15 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     set_split(dp, r.hp.max_keys_tail, r.hp.sum_keys_tail);
     if (launch_attention_decode(dp, st) != 0) return fail(SWIFTKV_EHIP, "tail attention launch failed");
     if (launch_decode_combine(dp.partial, to, dp.rows, B, m.n_q_heads, m.head_dim, dp.n_split, st) != 0) return fail(SWIFTKV_EHIP, "tail combine launch failed");
+    if (t_chain) {
+      const bool more = j + 1 < m.n_layers;
+      const SkinnyResidParams ro{to, B, d, qd, c->wo[j], th, c->norm2[j], ta, row_ssq};
+      const SkinnyResidParams rd{tz, B, d, m.ffn, c->wdown[j], th, more ? c->norm1[j + 1] : nullptr, more ? ta : nullptr, more ? row_ssq : nullptr};
+      if (launch_skinny_resid(ro, st)) return fail(SWIFTKV_EHIP, "tail o GEMM failed");
+      if (tail_gemm(c, ta, B, m.ffn, d, c->wgate[j], c->wup[j], c->gu_tab[j], tz, EPI_SWIGLU, skp, st, nullptr, row_ssq)) return fail(SWIFTKV_EHIP, "tail MLP GEMM failed");
+      if (launch_skinny_resid(rd, st)) return fail(SWIFTKV_EHIP, "tail down GEMM failed");
+      continue;
+    }
     if (tail_gemm(c, to, B, d, qd, c->wo[j], nullptr, nullptr, th, EPI_RESID, skp, st, &t_pend)) return fail(SWIFTKV_EHIP, "tail o GEMM failed");
     norm_th(c->norm2[j]);
     if (tail_gemm(c, ta, B, m.ffn, d, c->wgate[j], c->wup[j], c->gu_tab[j], tz, EPI_SWIGLU, skp, st)) return fail(SWIFTKV_EHIP, "tail MLP GEMM failed");

@@ -201,11 +201,31 @@ struct SkinnyParams {
   int32_t *n_splits_out;       // HOST, or null.  Given (never with SWIGLU), a launch that splits K leaves the sum to its
                                // consumer: it writes the number of splits here, the splits' sums stay in `partial` as
                                // [split][M][N] fp32 and C is untouched; 1 = nothing left to do (C is final)
+  // Given (up to SKINNY_RESID_ROWS rows, K % 512 == 0), the rows of A still lack the factor 1/rms of an RMSNorm over their K columns: it is
+  // taken from the sums of squares launch_skinny_resid left, [M][K / 16], and multiplies the result (all of its K ranges)
+  const float *ssq;
+  float eps;
 };
+bool skinny_takes_ssq(int M, int N, int K);
 constexpr int SKINNY_MAX_SPLIT = 16;
 constexpr size_t SKINNY_PARTIAL_BYTES = (size_t)SKINNY_MAX_SPLIT * 80 * 8192 * 4;   // the driver's scratch: 16 splits x 80 rows x 8192 columns fp32 (42 MB)
 [[nodiscard]] int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st);
 GemmRoute route_skinny(const SkinnyParams &p, int epi);
+
+// h[M, N] += A[M, K] W[N, K]^T of very few rows, final (skinny_resid.hip), and with it the operand of the next projection and the
+// rows' sums of squares over each 16 columns.
+constexpr int SKINNY_RESID_ROWS = 8;
+struct SkinnyResidParams {
+  const bf16_t *A;
+  int32_t M, N, K;
+  const bf16_t *W;
+  float *h;
+  const bf16_t *gain;   // of the next norm, or null (1)
+  bf16_t *out;          // bf16(h * gain), or null
+  float *ssq;           // [M][N / 16], or null
+};
+bool skinny_resid_pays(int M, int N, int K);
+[[nodiscard]] int launch_skinny_resid(const SkinnyResidParams &p, hipStream_t st);
 
 // Few-row batches (decode steps): the Q, K, V projections come out of the weight-streaming kernel as
 // fp32; this step rotates q and k (rotate-half, angles of the row's position), rounds to bf16 once and,

@@ -529,13 +529,13 @@ __device__ __forceinline__ void wait_ring(int younger) {   // step i is in LDS: 
 }
 constexpr int RING_BUF = 256;                                       // columns of K in an activation buffer
 constexpr int ring_steps(int waves) { return waves == 8 ? 3 : 4; }   // 48 and 32 KB per workgroup; more in flight is no faster (8 waves, 64 rows, 6 steps: 51.7 us against 48.8)
-constexpr int ring_lds(int MB, int waves) { return 2 * MB * 16 * RING_BUF * 2 + waves * ring_steps(waves) * 2048; }
+constexpr int ring_lds(int MB, int waves) { return 2 * MB * 16 * RING_BUF * 2 + waves * ring_steps(waves) * 2048 + (MB == 1 ? SKINNY_RESID_ROWS * 4 : 0); }
 template <int MB, int EPI, int WAVES>
 __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_ring_kernel(SkinnyParams p, int n_bufs, int stride) {
   constexpr int R = ring_steps(WAVES);
   constexpr int CW = EPI == EPI_SWIGLU ? WAVES / 2 : WAVES;   // column blocks of a workgroup (SwiGLU: gate waves, then up waves)
   constexpr int ABUF = MB * 16 * RING_BUF * 2;
-  extern __shared__ __align__(16) unsigned char lds[];   // [2][MB][4 steps][2 KB] activations, [WAVES][R][2 KB] weights
+  extern __shared__ __align__(16) unsigned char lds[];   // [2][MB][4 steps][2 KB] activations, [WAVES][R][2 KB] weights, 1/rms of up to 8 rows
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, kq = lane >> 4;
   const int b0 = blockIdx.y * n_bufs, all = p.K / RING_BUF;
@@ -587,6 +587,23 @@ __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_ring_kernel(SkinnyPar
 #pragma unroll
   for (int i = 0; i < R; ++i) request(i);   // (steps >= 4 >= R)
 
+  // 1/rms of the rows, where A lacks it: two rows to a wave at most, while the ring fills
+  float *const rms = (float *)(lds + 2 * ABUF + WAVES * R * 2048);
+  if (MB == 1 && p.ssq) {
+    static_assert(2 * WAVES >= SKINNY_RESID_ROWS, "two rows to a wave");
+    const int m0 = wave, m1 = wave + WAVES, n = p.K / 16;
+    float q0 = 0.f, q1 = 0.f;
+    for (int i = lane; i < n; i += 64) {
+      if (m0 < p.M) q0 += p.ssq[m0 * n + i];
+      if (m1 < p.M) q1 += p.ssq[m1 * n + i];
+    }
+    q0 = wave_sum(q0); q1 = wave_sum(q1);
+    if (lane == 0) {
+      if (m0 < p.M) rms[m0] = rsqrtf(q0 / (float)p.K + p.eps);
+      if (m1 < p.M) rms[m1] = rsqrtf(q1 / (float)p.K + p.eps);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (read behind the barriers below)
+  }
   floatx4 acc[MB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -616,6 +633,12 @@ __global__ __launch_bounds__((WAVES + 1) * 64) void skinny_ring_kernel(SkinnyPar
       slot = slot + 1 == R ? 0 : slot + 1;
     }
     __builtin_amdgcn_s_barrier();
+  }
+  if (MB == 1 && p.ssq) {
+    asm volatile("" ::: "memory");
+    const float f = rms[l16 < p.M ? l16 : 0];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[0][v] *= f;
   }
   const int n = nb * 16 + 4 * kq;
   if constexpr (EPI == EPI_SWIGLU) {
@@ -813,6 +836,11 @@ SkinnyRoute plan_skinny(const SkinnyParams &p, int epi) {
   const int nw = epi == EPI_SWIGLU ? 2 : 1;
   const size_t cap = p.partial ? p.partial_bytes : 0;
   r.kernel = SWIFTKV_GEMM_STREAM_FIRST;
+  if (p.ssq) {   // (the one kernel that takes the rows' factor)
+    r.ring = plan_ring(p.M, p.N, p.K, nw, p.n_splits_out != nullptr, cap);
+    if (r.ring.ok) r.kernel = SWIFTKV_GEMM_STREAM_SEQ;
+    return r;
+  }
   if (p.M > 32 || p.n_splits_out || nw == 2) {
     // (up to 8 rows of a SwiGLU pair with no more column blocks than CUs the first kernel is ahead, whose workgroups split K among
     // their waves: one row 2 x 4096 x 4096 15.0 us against 16.2, 2 x 2048 x 2048 7.9 / 8.6)
@@ -844,8 +872,12 @@ GemmRoute route_skinny(const SkinnyParams &p, int epi) {
   }
   return GemmRoute{r.kernel, nb, first_splits(p, epi, nb), 0};
 }
+bool skinny_takes_ssq(int M, int N, int K) {
+  return M <= SKINNY_RESID_ROWS && plan_ring(M, N, K, 1, true, 0).ok;
+}
 int launch_skinny(const SkinnyParams &p, int epi, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0) return 0;
+  if (p.ssq && !skinny_takes_ssq(p.M, p.N, p.K)) return -1;
   if (p.M > 80 || (p.N % 16) != 0 || (p.K % 8) != 0) return -1;
   if (p.wtab && !p.n_splits_out) return -1;   // (the kernels of final results know no row-block table)
   if (p.n_splits_out) {
