@@ -154,6 +154,7 @@ struct GemmParams {
   const KvStore *store;
   int32_t streamed;            // row-major weights of rows that only pass once (the last tokens): gemm_stream_kernel may take them
   int32_t n_splits, split_steps;   // set by launch_gemm_mid: K splits and 64-wide k steps of each
+  int32_t low_tiles_n;             // set by launch_gemm_mid: columns of tiles, the last ones, that are of the lower of two heights
 };
 
 // Matrix-instruction rate on given operand data, nothing else in the loop: `iters` x 16 independent
@@ -172,6 +173,7 @@ struct MidPlan {
   MidKernel kernel;
   int fm, n_splits, split_steps;   // tile = 32 fm rows x 256 columns (MID_STREAM: 128); K splits and 64-wide k steps of each
   double cost;                     // estimated time in us, adding the splits up included
+  int fm_low, low_tiles_n;         // MID_WREG, 0 or: the last low_tiles_n columns of tiles are 32 fm_low rows high
 };
 MidPlan plan_gemm_mid(const GemmParams &p, int epi);
 [[nodiscard]] int launch_gemm_mid(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st);
@@ -179,7 +181,7 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi);
 // tile (weight streaming: column blocks of 16 per workgroup), K splits, columns of K to a slice (0: no slices).
 struct GemmRoute { int32_t kernel, tile, n_splits, slice; };
 GemmRoute route_gemm(const GemmParams &p, int epi);
-int launch_gemm_wreg(const GemmParams &p, int epi, int fm, hipStream_t st);
+int launch_gemm_wreg(const GemmParams &p, int epi, int fm, int fm_low, hipStream_t st);
 int launch_gemm_stream(const GemmParams &p, int epi, int fm, bool packed, hipStream_t st);
 [[nodiscard]] int launch_splits_finish(const GemmParams &p, int epi, hipStream_t st);
 // Q, K, V (EPI_QKV) or the later layers' K, V (EPI_KV) from p.n_splits partial sums: added in split order, 1/rms, rotation, rounding, and

@@ -230,7 +230,7 @@ int launch_f(const GemmParams &p, int epi, MidKernel k, hipStream_t st) {
   return -1;
 }
 int launch_one(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st) {
-  if (pl.kernel == MID_WREG) return launch_gemm_wreg(p, epi, pl.fm, st);
+  if (pl.kernel == MID_WREG) return launch_gemm_wreg(p, epi, pl.fm, pl.fm_low, st);
   if (pl.kernel == MID_STREAM) return launch_gemm_stream(p, epi, pl.fm, p.wpack != nullptr, st);
   switch (pl.fm) {
     case 2: return launch_f<2>(p, epi, pl.kernel, st);
@@ -403,6 +403,25 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
       if (best.kernel == MID_NONE || cost < best.cost) best = MidPlan{f.kernel, f.fm, s, steps, cost};
     }
   }
+  // Two tile heights in a launch (gate and up, the widest product of a layer: without K splits its rounds rarely come out even): 256-row
+  // tiles over the first columns fill whole rounds, lower ones the time that is left.  By the same table: `tall` rounds of the full
+  // height hold some columns of tiles, the rest go to CUs that have no tile of the last tall round and then to rounds of their own.
+  // us per launch, 28672 columns, K 4096, one height -> two: 900 rows 203 -> 189, 1300 266 -> 262, 2048 421 -> 393, 3300 638 -> 617,
+  // 4700 878 -> 853, 13000 2278 -> 2207; 16384 columns, K 2048, 5000 rows 299 and 308 were about the worst of the others (not taken).
+  if (packed && epi == EPI_SWIGLU && best.kernel == MID_WREG && best.n_splits == 1) {
+    const int rows_n = (p.M + 255) / 256, most = (int)std::min<int64_t>((int64_t)rows_n * tiles_n / 256, 1 << 20);
+    const double a = all_steps * forms[0].t1 + 4 + epi_us;
+    for (const Form &f : {forms[2], forms[4]}) {
+      const double b = all_steps * f.t1 + 4 + epi_us * f.fm / 8;
+      for (int tall = std::max(1, most - 2); tall <= most; ++tall) {
+        const int cols = tall * 256 / rows_n, spare = tall * 256 - cols * rows_n;
+        if (cols < 1 || cols >= tiles_n) continue;
+        const int64_t low = (int64_t)((p.M + 32 * f.fm - 1) / (32 * f.fm)) * (tiles_n - cols) - (int64_t)spare * (int)(a / b);
+        const double cost = 7 + tall * a + (double)((std::max<int64_t>(low, 0) + 255) / 256) * b;
+        if (cost < best.cost) best = MidPlan{MID_WREG, 8, 1, all_steps, cost, f.fm, tiles_n - cols};
+      }
+    }
+  }
   // gemm_stream_kernel: 128-column tiles of 64 to 192 rows, alone on a CU.  A 128-column slice of K takes what its LDS traffic or
   // the workgroups' share of the weight stream takes (row tiles after the first find most of it in L2); every term fitted to
   // 5600 timings of 16 products of 81 to 512 rows (median error 5 %).  Rotary operands always leave as partial sums, so a form that
@@ -454,7 +473,7 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
 
 int launch_gemm_mid(const GemmParams &p0, int epi, const MidPlan &pl, hipStream_t st) {
   GemmParams p = p0;
-  p.n_splits = pl.n_splits; p.split_steps = pl.split_steps;
+  p.n_splits = pl.n_splits; p.split_steps = pl.split_steps; p.low_tiles_n = pl.low_tiles_n;
   if (p.n_splits_out) *p.n_splits_out = 1;
   const bool rope = epi == EPI_QKV || epi == EPI_KV;
   if (pl.n_splits == 1 && !(rope && pl.kernel == MID_STREAM)) return launch_one(p, epi, pl, st);

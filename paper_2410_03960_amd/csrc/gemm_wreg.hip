@@ -29,20 +29,19 @@ namespace {
 // 192-row tiles 81.9 -> 80.5.  No gain, measured on this loop: six to ten stages where they fit, weights four steps ahead (the wait
 // for a stage then leaves 22 instead of 14 requests in flight), 32 KB of a step's weights in one piece, each wave's requests
 // a product later than its neighbour's; eight waves of 128 x 64, two to a SIMD: 3 % slower, as every wave's wait is stricter.
-template <int EPI, int FM, bool NORM_OUT = false>
-__global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
+template <int EPI, int FM, bool NORM_OUT>
+__device__ __forceinline__ void wreg_tile(const GemmParams &p, unsigned char *smem, const int block, const int first_n, const int tiles_n) {
   constexpr int BM = 32 * FM, BN = 256;
   constexpr int NSA = 5, STAGE = BM * 128;   // activation stages: BM rows x 128 bytes (one 64-wide k step)
-  extern __shared__ __align__(16) unsigned char smem[];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
 
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = p.N / BN;
+  const int tiles_m = (p.M + BM - 1) / BM;
   const int per_split = tiles_m * tiles_n, total = per_split * p.n_splits;
   const int per_xcd = (total + 7) / 8;
-  const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  const int logical = (block % 8) * per_xcd + block / 8;
   if (logical >= total) return;
   const int split = logical / per_split, tile = logical % per_split;
   constexpr int GM = 8;   // m tiles per rasterisation group
@@ -50,7 +49,7 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
   const int first_m = group * GM;
   const int gsz = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
   const int in_group = tile % (GM * tiles_n);
-  const int tm = first_m + in_group % gsz, tn = in_group / gsz;
+  const int tm = first_m + in_group % gsz, tn = first_n + in_group / gsz;
   const int m0 = tm * BM, n0 = tn * BN + wave * 64;   // n0: first column of this wave
   const int all_steps = p.K / 64, s_begin = split * p.split_steps;
   const int nk = (all_steps - s_begin) < p.split_steps ? (all_steps - s_begin) : p.split_steps;   // >= 1 by the plan
@@ -165,19 +164,38 @@ __global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
   gemm_epilogue_n64<EPI, FM, NORM_OUT>(p, acc, m0, n0, lane, slab, EPI == EPI_PARTIAL ? (int64_t)split * p.M * p.N : 0);
 }
 
-template <int EPI, int FM, bool NORM_OUT>
+// FL > 0: two tile heights in a launch, 32 FM rows over the first columns of tiles and 32 FL over the last p.low_tiles_n (the rule and
+// what it gives: plan_gemm_mid).  The tall tiles have the lower block ids, so the low ones start as CUs run out of tall ones.
+template <int EPI, int FM, bool NORM_OUT, int FL>
+__global__ __launch_bounds__(256) void gemm_wreg_kernel(GemmParams p) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tiles_n = p.N / 256, block = blockIdx.x;
+  if constexpr (FL > 0) {
+    const int tall_n = tiles_n - p.low_tiles_n, tall = ((p.M + 32 * FM - 1) / (32 * FM) * tall_n + 7) / 8 * 8;
+    if (block >= tall) {
+      wreg_tile<EPI, FL, NORM_OUT>(p, smem, block - tall, tall_n, p.low_tiles_n);
+      return;
+    }
+    wreg_tile<EPI, FM, NORM_OUT>(p, smem, block, 0, tall_n);
+  } else {
+    wreg_tile<EPI, FM, NORM_OUT>(p, smem, block, 0, tiles_n);
+  }
+}
+
+template <int EPI, int FM, bool NORM_OUT, int FL = 0>
 int launch_wreg_k(const GemmParams &p, hipStream_t st) {
   constexpr int SLAB = 4 * ((EPI == EPI_QKV || EPI == EPI_KV) ? FM * 32 * (64 * 2 + 16) : 32 * (64 * 4 + 16));
   constexpr int SMEM = 5 * FM * 32 * 128 > SLAB ? 5 * FM * 32 * 128 : SLAB;
-  auto kern = gemm_wreg_kernel<EPI, FM, NORM_OUT>;
+  auto kern = gemm_wreg_kernel<EPI, FM, NORM_OUT, FL>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
     if (e != hipSuccess) return (int)e;
     attr_set = true;
   }
-  const int tiles = ((p.M + 32 * FM - 1) / (32 * FM)) * (p.N / 256) * p.n_splits;
-  hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), SMEM, st, p);
+  const int tiles = ((p.M + 32 * FM - 1) / (32 * FM)) * (p.N / 256 - p.low_tiles_n) * p.n_splits;
+  const int low = FL > 0 ? ((p.M + 32 * FL - 1) / (32 * FL)) * p.low_tiles_n : 0;
+  hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8 + (low + 7) / 8) * 8), dim3(256), SMEM, st, p);
   return 0;
 }
 template <int EPI, bool NORM_OUT>
@@ -194,8 +212,12 @@ int launch_fm(const GemmParams &p, int fm, hipStream_t st) {
 
 }  // namespace
 
-// tile height 32 * fm, p.n_splits ranges of p.split_steps (a multiple of 4) 64-wide steps
-int launch_gemm_wreg(const GemmParams &p, int epi, int fm, hipStream_t st) {
+// tile height 32 * fm (the last p.low_tiles_n columns of tiles: 32 * fm_low), p.n_splits ranges of p.split_steps (a multiple of 4) 64-wide steps
+int launch_gemm_wreg(const GemmParams &p, int epi, int fm, int fm_low, hipStream_t st) {
+  if (fm_low) {
+    if (epi != EPI_SWIGLU || fm != 8 || p.n_splits != 1) return -1;
+    return fm_low == 6 ? launch_wreg_k<EPI_SWIGLU, 8, false, 6>(p, st) : fm_low == 4 ? launch_wreg_k<EPI_SWIGLU, 8, false, 4>(p, st) : -1;
+  }
   switch (epi) {
     case EPI_STORE_BF16: return launch_fm<EPI_STORE_BF16, false>(p, fm, st);
     case EPI_RESID: return p.hb && p.ssq ? launch_fm<EPI_RESID, true>(p, fm, st) : launch_fm<EPI_RESID, false>(p, fm, st);
