@@ -407,7 +407,8 @@ int pin_reserve(swiftkv_ctx *c, size_t need) {
   return 0;
 }
 
-int run_plan(Run &r, const int32_t *token_ids) {
+// `later` given: the plan's launch is left to its caller (launch_plan_rmsnorm_embed)
+int run_plan(Run &r, const int32_t *token_ids, PlanParams *later = nullptr) {
   swiftkv_ctx *c = r.c;
   // plan words: host vector -> pinned slot -> device, without waiting for the stream (a slot is only
   // waited for when the ring wraps around onto a copy that has not run yet)
@@ -433,7 +434,8 @@ int run_plan(Run &r, const int32_t *token_ids) {
   pp.positions = r.at<int32_t>(r.L.positions); pp.seq_of = r.at<int32_t>(r.L.seq_of);
   pp.last_rows = r.at<int32_t>(r.L.last_rows); pp.err_flag = r.at<int32_t>(r.L.err);
   pp.slots = r.at<int64_t>(r.L.slots); pp.cos_sin = r.at<float2>(r.L.cos_sin);
-  launch_plan(pp, r.st);
+  if (later) *later = pp;
+  else launch_plan(pp, r.st);
   return check_launch("plan");
 }
 
@@ -804,7 +806,8 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   hipStream_t st = r.st;
   Timer tm{c, st};
   tm.begin(TC_OTHER);
-  if (int e = run_plan(r, token_ids)) return e;
+  PlanParams plan;
+  if (int e = run_plan(r, token_ids, &plan)) return e;
   float *h = r.at<float>(r.L.h);             // residual stream, fp32 [T, d]
   tm.end();
   bf16_t *ab = r.at<bf16_t>(r.L.a);          // bf16 operand of the projection behind an RMSNorm
@@ -851,11 +854,11 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     packed = plan_gemm_mid(go, EPI_RESID).n_splits == 1 && plan_gemm_mid(gd, EPI_RESID).n_splits == 1;
   }
   const int n_ssq = d / 64;
-  // the first norm of the pass takes its rows from the embedding and leaves them in h
+  // the first norm of the pass takes its rows from the embedding and leaves them in h; the plan's launch carries it
   bool have_h = false;
   auto norm_h = [&](const bf16_t *gain, float *rstd_out, int32_t pending) {
     tm.begin(TC_NORM);
-    if (!have_h) launch_rmsnorm_embed(token_ids, c->embed, m.vocab, h, gain, ab, T, d, m.rms_eps, rstd_out, st);
+    if (!have_h) launch_plan_rmsnorm_embed(plan, c->embed, h, gain, ab, d, m.rms_eps, rstd_out, st);
     else launch_rmsnorm_rows(h, gain, ab, T, d, m.rms_eps, rstd_out, st, skp, pending);
     have_h = true;
     tm.end();

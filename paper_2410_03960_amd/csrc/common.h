@@ -336,15 +336,15 @@ int launch_rstd_from_ssq(const float *ssq, int32_t n_blocks, float *rstd, int32_
 int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps, float *rstd_out, hipStream_t st,
                         const float *partial = nullptr, int32_t n_splits = 1);
 int launch_gather_rows(const float *h, const int32_t *rows, float *out, int32_t n_rows, int32_t d, hipStream_t st);
-// The same norm where the rows have yet to be put into h: from the embedding (ids clamped into [0, vocab)), or rows
-// idx[.] of `from`.
+// The same norm where the rows have yet to be put into h: from the embedding (ids clamped into [0, vocab)), with the plan in the same
+// launch, or rows idx[.] of `from`.
 struct RowSource {
   const void *rows;      // bf16 embedding, or fp32 rows
   const int32_t *idx;
   int32_t n;             // rows of the embedding
 };
-int launch_rmsnorm_embed(const int32_t *ids, const bf16_t *E, int32_t vocab, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d,
-                         float eps, float *rstd_out, hipStream_t st);
+int launch_plan_rmsnorm_embed(const PlanParams &p, const bf16_t *E, float *h, const bf16_t *gain, bf16_t *out, int32_t d, float eps, float *rstd_out,
+                              hipStream_t st);
 int launch_rmsnorm_gather(const float *from, const int32_t *idx, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps,
                           hipStream_t st);
 int launch_f32_to_bf16(const float *x, bf16_t *out, int64_t n, hipStream_t st);

@@ -11,9 +11,8 @@
 // cu_seqlens, absolute position, paged slot = block_table[b][p/16]*16 + p%16
 // (written by the token's first thread), and the RoPE angle table
 // cos/sin(p * theta^(-2i/hd)) formed in double precision.
-__global__ void plan_kernel(PlanParams p) {
+__device__ __forceinline__ void plan_token(const PlanParams &p, const int64_t gid) {
   const int half = p.head_dim / 2;
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid < p.B) p.last_rows[gid] = p.cu_seqlens[gid + 1] - 1;
   const int t = (int)(gid / half), i = (int)(gid % half);
   if (t >= p.T) return;
@@ -42,9 +41,10 @@ __global__ void plan_kernel(PlanParams p) {
   const double ang = (double)pos * inv_freq;
   p.cos_sin[(int64_t)t * half + i] = make_float2((float)cos(ang), (float)sin(ang));
 }
+__global__ void plan_kernel(PlanParams p) { plan_token(p, (int64_t)blockIdx.x * blockDim.x + threadIdx.x); }
+static unsigned plan_blocks(const PlanParams &p) { return (unsigned)((std::max<int64_t>((int64_t)p.T * (p.head_dim / 2), p.B) + 255) / 256); }
 int launch_plan(const PlanParams &p, hipStream_t st) {
-  const int64_t n = std::max<int64_t>((int64_t)p.T * (p.head_dim / 2), p.B);
-  hipLaunchKernelGGL(plan_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p);
+  hipLaunchKernelGGL(plan_kernel, dim3(plan_blocks(p)), dim3(256), 0, st, p);
   return 0;
 }
 
@@ -174,12 +174,12 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_reg_kernel(const float4 *h, 
 // SRC: where the row comes from -- h itself; 1: the embedding row of its token id; 2: row idx[row] of another buffer.
 // The latter two leave it in h: the first norm of a pass and of the tail need no launch in front of them that only
 // copies (about 4.5 us each where rows are few; 8831 rows of 4096 from the embedding 70 us in two launches -> 46).
-template <int CQ, int SRC, int WAVES = 4>
-__global__ __launch_bounds__(WAVES * 64) void rmsnorm_row_wg_kernel(float4 *h, const bf16_t *gain, uint2 *out, int rows, float eps, float inv_d,
-                                                             float *rstd_out, const float4 *partial, int n_splits, RowSource rs_in) {
+template <int CQ, int SRC, int WAVES>
+__device__ __forceinline__ void rmsnorm_row_wg(const int row, float4 *h, const bf16_t *gain, uint2 *out, int rows, float eps, float inv_d,
+                                               float *rstd_out, const float4 *partial, int n_splits, const RowSource &rs_in) {
   constexpr int TH = WAVES * 64;
   __shared__ float red[WAVES];
-  const int row = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
   float4 *r = h + (int64_t)row * (CQ * TH);
   float4 u[CQ];
   uint2 g[CQ];
@@ -251,6 +251,20 @@ __global__ __launch_bounds__(WAVES * 64) void rmsnorm_row_wg_kernel(float4 *h, c
     out[(int64_t)row * (CQ * TH) + i * TH + tid] =
         make_uint2(pack_bf16x2(u[i].x * f * bf16lo(g[i].x), u[i].y * f * bf16hi(g[i].x)), pack_bf16x2(u[i].z * f * bf16lo(g[i].y), u[i].w * f * bf16hi(g[i].y)));
 }
+template <int CQ, int SRC, int WAVES = 4>
+__global__ __launch_bounds__(WAVES * 64) void rmsnorm_row_wg_kernel(float4 *h, const bf16_t *gain, uint2 *out, int rows, float eps, float inv_d,
+                                                             float *rstd_out, const float4 *partial, int n_splits, RowSource rs_in) {
+  rmsnorm_row_wg<CQ, SRC, WAVES>(blockIdx.x, h, gain, out, rows, eps, inv_d, rstd_out, partial, n_splits, rs_in);
+}
+// The plan and the first norm of a pass in one launch: neither reads what the other writes.  The plan's workgroups come first, as a
+// thread's power, sine and cosine in double precision outlast a row.  us of a whole pass, two launches ->
+// one: one decode row 406.9 -> 404.4, 64 871.4 -> 867.9, 597 rows of 2048 over 16 layers 1350.7 -> 1344.7; 16384 rows of 4096 20 + 89 -> 103.
+template <int CQ>
+__global__ __launch_bounds__(256) void plan_norm_kernel(PlanParams p, int n_plan, float4 *h, const bf16_t *gain, uint2 *out, float eps, float inv_d, float *rstd_out,
+                                                        RowSource rs_in) {
+  if ((int)blockIdx.x < n_plan) plan_token(p, (int64_t)blockIdx.x * 256 + threadIdx.x);
+  else rmsnorm_row_wg<CQ, 1, 4>(blockIdx.x - n_plan, h, gain, out, p.T, eps, inv_d, rstd_out, nullptr, 1, rs_in);
+}
 // the K-split sums of a weight-streaming GEMM added into fp32 rows (for row widths the kernel above does not cover)
 __global__ void add_splits_kernel(float4 *h, const float4 *partial, int64_t n4, int n_splits) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -264,32 +278,37 @@ __global__ void add_splits_kernel(float4 *h, const float4 *partial, int64_t n4, 
   u.x += sum.x; u.y += sum.y; u.z += sum.z; u.w += sum.w;
   h[i] = u;
 }
-namespace {
-template <int SRC>
-bool rmsnorm_from(const RowSource &src, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps, float *rstd_out, hipStream_t st) {
-  if (d % 1024 != 0 || d / 1024 > 8) return false;
-#define SKV_RMS_FROM(CQ_)                                                                                                        \
-  case CQ_:                                                                                                                      \
-    hipLaunchKernelGGL((rmsnorm_row_wg_kernel<CQ_, SRC>), dim3(rows), dim3(256), 0, st, (float4 *)h, gain, (uint2 *)out, rows, eps, \
-                       1.0f / (float)d, rstd_out, (const float4 *)nullptr, 1, src);                                              \
-    break;
-  switch (d / 1024) { SKV_RMS_FROM(1) SKV_RMS_FROM(2) SKV_RMS_FROM(3) SKV_RMS_FROM(4) SKV_RMS_FROM(5) SKV_RMS_FROM(6) SKV_RMS_FROM(7) SKV_RMS_FROM(8) }
-#undef SKV_RMS_FROM
-  return true;
-}
-}  // namespace
-int launch_rmsnorm_embed(const int32_t *ids, const bf16_t *E, int32_t vocab, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d,
-                         float eps, float *rstd_out, hipStream_t st) {
-  if (rows <= 0 || rmsnorm_from<1>(RowSource{E, ids, vocab}, h, gain, out, rows, d, eps, rstd_out, st)) return 0;
-  launch_embed(ids, E, h, rows, d, vocab, st);
-  return launch_rmsnorm_rows(h, gain, out, rows, d, eps, rstd_out, st);
+#define SKV_EACH_CQ(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+int launch_plan_rmsnorm_embed(const PlanParams &p, const bf16_t *E, float *h, const bf16_t *gain, bf16_t *out, int32_t d, float eps, float *rstd_out,
+                              hipStream_t st) {
+  const float inv_d = 1.0f / (float)d;
+  const unsigned n_plan = plan_blocks(p);
+#define SKV_PLAN_NORM(CQ_)                                                                                                               \
+  case CQ_ * 1024:                                                                                                                       \
+    hipLaunchKernelGGL(plan_norm_kernel<CQ_>, dim3(n_plan + p.T), dim3(256), 0, st, p, (int)n_plan, (float4 *)h, gain, (uint2 *)out, eps, inv_d, \
+                       rstd_out, RowSource{E, p.token_ids, p.vocab});                                                                    \
+    return 0;
+  switch (d) { SKV_EACH_CQ(SKV_PLAN_NORM) }
+#undef SKV_PLAN_NORM
+  launch_plan(p, st);   // (other row widths)
+  launch_embed(p.token_ids, E, h, p.T, d, p.vocab, st);
+  return launch_rmsnorm_rows(h, gain, out, p.T, d, eps, rstd_out, st);
 }
 int launch_rmsnorm_gather(const float *from, const int32_t *idx, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps,
                           hipStream_t st) {
-  if (rows <= 0 || rmsnorm_from<2>(RowSource{from, idx, 0}, h, gain, out, rows, d, eps, nullptr, st)) return 0;
+  if (rows <= 0) return 0;
+  const float inv_d = 1.0f / (float)d;
+#define SKV_RMS_GATHER(CQ_)                                                                                                              \
+  case CQ_ * 1024:                                                                                                                       \
+    hipLaunchKernelGGL((rmsnorm_row_wg_kernel<CQ_, 2>), dim3(rows), dim3(256), 0, st, (float4 *)h, gain, (uint2 *)out, rows, eps, inv_d, \
+                       (float *)nullptr, (const float4 *)nullptr, 1, RowSource{from, idx, 0});                                           \
+    return 0;
+  switch (d) { SKV_EACH_CQ(SKV_RMS_GATHER) }
+#undef SKV_RMS_GATHER
   launch_gather_rows(from, idx, h, rows, d, st);
   return launch_rmsnorm_rows(h, gain, out, rows, d, eps, nullptr, st);
 }
+#undef SKV_EACH_CQ
 int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps, float *rstd_out, hipStream_t st,
                         const float *partial, int32_t n_splits) {
   if (rows <= 0) return 0;
