@@ -854,12 +854,19 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
     packed = plan_gemm_mid(go, EPI_RESID).n_splits == 1 && plan_gemm_mid(gd, EPI_RESID).n_splits == 1;
   }
   const int n_ssq = d / 64;
+  // The tail's first operand: with the norm in front of the fused K/V projection, of rows that are a sequence's last, or, form (c) and
+  // one token per sequence, from the last down GEMM (as there, 1/rms then comes from row_ssq; a decode row 405.5 -> 401.4 us a pass);
+  // else by a pass of its own.
+  float *th = r.at<float>(r.L.th);
+  bf16_t *ta = r.at<bf16_t>(r.L.ta);
+  const bool t_chain = chained(B), down_feeds_tail = chain && t_chain && T == B && c->P > 0 && !c->ee_head;
+  bool have_th = false, have_ta = false;
   // the first norm of the pass takes its rows from the embedding and leaves them in h; the plan's launch carries it
   bool have_h = false;
-  auto norm_h = [&](const bf16_t *gain, float *rstd_out, int32_t pending) {
+  auto norm_h = [&](const bf16_t *gain, float *rstd_out, int32_t pending, const TailRows *tail = nullptr, bool *tail_done = nullptr) {
     tm.begin(TC_NORM);
     if (!have_h) launch_plan_rmsnorm_embed(plan, c->embed, h, gain, ab, d, m.rms_eps, rstd_out, st);
-    else launch_rmsnorm_rows(h, gain, ab, T, d, m.rms_eps, rstd_out, st, skp, pending);
+    else launch_rmsnorm_rows(h, gain, ab, T, d, m.rms_eps, rstd_out, st, skp, pending, tail, tail_done);
     have_h = true;
     tm.end();
   };
@@ -1032,7 +1039,8 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       tm.end();
       tm.begin(TC_DOWN);
       if (chain) {   // the operand of the next layer, or (gain one) of the fused K/V projection
-        const SkinnyResidParams rp{zb, T, d, m.ffn, c->wdown[j], h, j + 1 < c->l ? c->norm1[j + 1] : nullptr, ab, row_ssq};
+        SkinnyResidParams rp{zb, T, d, m.ffn, c->wdown[j], h, j + 1 < c->l ? c->norm1[j + 1] : nullptr, ab, row_ssq};
+        if (down_feeds_tail && j + 1 == c->l) { rp.h_tail = th; rp.gain_tail = c->norm1[j + 1]; rp.out_tail = ta; have_th = true; }
         if (launch_skinny_resid(rp, st)) return fail(SWIFTKV_EHIP, "down GEMM launch failed");
       } else
       // (the next reader of h is a norm pass: the next layer's, or the one in front of the later layers' K/V projection)
@@ -1073,7 +1081,9 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
   // operand: the layer-l output rounded to bf16 (the leaders' gains live in the packed weight), 1/rms per row
   if (c->P > 0) {
     if (!packed && !chain) {
-      norm_h(nullptr, rstd, h_pend);
+      const TailRows tail{r.at<int32_t>(r.L.seq_of), r.at<int32_t>(r.L.last_rows), (float4 *)th, c->ee_head ? c->ee_gain : c->norm1[c->l], (uint2 *)ta};
+      norm_h(nullptr, rstd, h_pend, tail.gain ? &tail : nullptr, &have_ta);
+      have_th = have_ta;
       h_pend = 1;
     }
     if (int e = run_fused_kv(r, ab, true, tm, chain ? row_ssq : nullptr)) return e;
@@ -1081,11 +1091,10 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
 
   // ----------------------------- last token of every sequence: layers l+1..L ----
   tm.begin(TC_TAIL);
-  float *th = r.at<float>(r.L.th);
-  bf16_t *ta = r.at<bf16_t>(r.L.ta), *tq = r.at<bf16_t>(r.L.tq), *to = r.at<bf16_t>(r.L.to), *tz = r.at<bf16_t>(r.L.tz);
+  bf16_t *tq = r.at<bf16_t>(r.L.tq), *to = r.at<bf16_t>(r.L.to), *tz = r.at<bf16_t>(r.L.tz);
   int32_t t_pend = 1;   // K splits of the last residual GEMM waiting for the next norm pass over th
-  bool have_th = false;   // the tail's first norm takes the last tokens' rows from h and leaves them in th
-  auto norm_th = [&](const bf16_t *gain) {
+  auto norm_th = [&](const bf16_t *gain) {   // (unless they are there, the first one takes the last tokens' rows from h and leaves them in th)
+    if (have_ta) { have_ta = false; return; }
     if (!have_th) launch_rmsnorm_gather(h, r.at<int32_t>(r.L.last_rows), th, gain, ta, B, d, m.rms_eps, st);
     else launch_rmsnorm_rows(th, gain, ta, B, d, m.rms_eps, nullptr, st, skp, t_pend);
     have_th = true;
@@ -1096,10 +1105,9 @@ int swiftkv_prefill(swiftkv_ctx *c, const int32_t *token_ids, const int32_t *seq
       return fail(SWIFTKV_EHIP, "early-exit head GEMM failed");
     launch_early_exit_flags(r.at<float>(r.L.ee_logits), B, m.vocab, c->ee_threshold, r.at<int32_t>(r.L.ee_flags), st);
   }
-  const bool t_chain = chained(B);
   for (int j = c->l; j < m.n_layers; ++j) {
     const int cl = c->l + (j - c->l) / c->g;
-    const float *in_ssq = t_chain && j > c->l ? row_ssq : nullptr;
+    const float *in_ssq = t_chain && (j > c->l || down_feeds_tail) ? row_ssq : nullptr;
     if (!in_ssq) norm_th(c->norm1[j]);
     AttnDecodeParams dp{};
     if (tail_gemm(c, ta, B, qd, d, c->wq[j], nullptr, nullptr, tq, EPI_STORE_BF16, skp, st, &dp.q_splits, in_ssq)) return fail(SWIFTKV_EHIP, "tail q GEMM failed");

@@ -225,6 +225,9 @@ struct SkinnyResidParams {
   const bf16_t *gain;   // of the next norm, or null (1)
   bf16_t *out;          // bf16(h * gain), or null
   float *ssq;           // [M][N / 16], or null
+  float *h_tail;        // not null: a copy of h, and out_tail = bf16(h * gain_tail): the rows are also the tail's
+  const bf16_t *gain_tail;
+  bf16_t *out_tail;
 };
 bool skinny_resid_pays(int M, int N, int K);
 [[nodiscard]] int launch_skinny_resid(const SkinnyResidParams &p, hipStream_t st);
@@ -333,8 +336,16 @@ int launch_rstd_from_ssq(const float *ssq, int32_t n_blocks, float *rstd, int32_
 // gain == null stands for a gain of one.
 // With n_splits > 1 the rows first take the K-split sums a weight-streaming GEMM left behind: h[row] +=
 // partial[0][row] + partial[1][row] + ... (partial: [n_splits][rows][d] fp32), written back to h.
+// `tail`: rows that are the last of their sequence also go, as fp32 rows and normed with another gain, to the tail's buffers;
+// *tail_done says whether this form of the kernel does that.
+struct TailRows {
+  const int32_t *seq_of, *last_rows;   // sequence of a row, last row of a sequence
+  float4 *h;
+  const bf16_t *gain;
+  uint2 *out;
+};
 int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps, float *rstd_out, hipStream_t st,
-                        const float *partial = nullptr, int32_t n_splits = 1);
+                        const float *partial = nullptr, int32_t n_splits = 1, const TailRows *tail = nullptr, bool *tail_done = nullptr);
 int launch_gather_rows(const float *h, const int32_t *rows, float *out, int32_t n_rows, int32_t d, hipStream_t st);
 // The same norm where the rows have yet to be put into h: from the embedding (ids clamped into [0, vocab)), with the plan in the same
 // launch, or rows idx[.] of `from`.

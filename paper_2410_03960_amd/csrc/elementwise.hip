@@ -174,12 +174,19 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_reg_kernel(const float4 *h, 
 // SRC: where the row comes from -- h itself; 1: the embedding row of its token id; 2: row idx[row] of another buffer.
 // The latter two leave it in h: the first norm of a pass and of the tail need no launch in front of them that only
 // copies (about 4.5 us each where rows are few; 8831 rows of 4096 from the embedding 70 us in two launches -> 46).
-template <int CQ, int SRC, int WAVES>
+// TAIL: rows that are the last of their sequence leave their tail's rows and operand as well, a launch of 4.6 to 5.4 us less (SRC = 2); us
+// per pass: 512 new rows 928.7 -> 924.5, 333 648.6 -> 646.0, 160 decode rows 870.3 -> 868.0, 64 868.1 -> 866.8.
+template <int CQ, int SRC, int WAVES, bool TAIL = false>
 __device__ __forceinline__ void rmsnorm_row_wg(const int row, float4 *h, const bf16_t *gain, uint2 *out, int rows, float eps, float inv_d,
-                                               float *rstd_out, const float4 *partial, int n_splits, const RowSource &rs_in) {
+                                               float *rstd_out, const float4 *partial, int n_splits, const RowSource &rs_in, const TailRows &tail = TailRows{}) {
   constexpr int TH = WAVES * 64;
   __shared__ float red[WAVES];
   const int tid = threadIdx.x;
+  int seq = -1;
+  if constexpr (TAIL) {
+    const int s = tail.seq_of[row];
+    if (tail.last_rows[s] == row) seq = s;
+  }
   float4 *r = h + (int64_t)row * (CQ * TH);
   float4 u[CQ];
   uint2 g[CQ];
@@ -234,6 +241,11 @@ __device__ __forceinline__ void rmsnorm_row_wg(const int row, float4 *h, const b
       r[i * TH + tid] = u[i];
     }
   }
+  uint2 tg[CQ];
+  if (TAIL && seq >= 0) {
+#pragma unroll
+    for (int i = 0; i < CQ; ++i) { tg[i] = *(const uint2 *)(tail.gain + 4 * (i * TH + tid)); tail.h[(int64_t)seq * (CQ * TH) + i * TH + tid] = u[i]; }
+  }
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < CQ; ++i) { s += u[i].x * u[i].x; s += u[i].y * u[i].y; s += u[i].z * u[i].z; s += u[i].w * u[i].w; }
@@ -250,11 +262,22 @@ __device__ __forceinline__ void rmsnorm_row_wg(const int row, float4 *h, const b
   for (int i = 0; i < CQ; ++i)
     out[(int64_t)row * (CQ * TH) + i * TH + tid] =
         make_uint2(pack_bf16x2(u[i].x * f * bf16lo(g[i].x), u[i].y * f * bf16hi(g[i].x)), pack_bf16x2(u[i].z * f * bf16lo(g[i].y), u[i].w * f * bf16hi(g[i].y)));
+  if (TAIL && seq >= 0) {
+#pragma unroll
+    for (int i = 0; i < CQ; ++i)
+      tail.out[(int64_t)seq * (CQ * TH) + i * TH + tid] =
+          make_uint2(pack_bf16x2(u[i].x * rs * bf16lo(tg[i].x), u[i].y * rs * bf16hi(tg[i].x)), pack_bf16x2(u[i].z * rs * bf16lo(tg[i].y), u[i].w * rs * bf16hi(tg[i].y)));
+  }
 }
 template <int CQ, int SRC, int WAVES = 4>
 __global__ __launch_bounds__(WAVES * 64) void rmsnorm_row_wg_kernel(float4 *h, const bf16_t *gain, uint2 *out, int rows, float eps, float inv_d,
                                                              float *rstd_out, const float4 *partial, int n_splits, RowSource rs_in) {
   rmsnorm_row_wg<CQ, SRC, WAVES>(blockIdx.x, h, gain, out, rows, eps, inv_d, rstd_out, partial, n_splits, rs_in);
+}
+template <int CQ, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void rmsnorm_row_tail_kernel(float4 *h, uint2 *out, int rows, float eps, float inv_d, float *rstd_out, const float4 *partial,
+                                                               int n_splits, TailRows tail) {
+  rmsnorm_row_wg<CQ, 0, WAVES, true>(blockIdx.x, h, nullptr, out, rows, eps, inv_d, rstd_out, partial, n_splits, RowSource{}, tail);
 }
 // The plan and the first norm of a pass in one launch: neither reads what the other writes.  The plan's workgroups come first, as a
 // thread's power, sine and cosine in double precision outlast a row.  us of a whole pass, two launches ->
@@ -310,7 +333,7 @@ int launch_rmsnorm_gather(const float *from, const int32_t *idx, float *h, const
 }
 #undef SKV_EACH_CQ
 int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps, float *rstd_out, hipStream_t st,
-                        const float *partial, int32_t n_splits) {
+                        const float *partial, int32_t n_splits, const TailRows *tail, bool *tail_done) {
   if (rows <= 0) return 0;
   const dim3 grid((rows + 3) / 4), block(256);
   const float inv_d = 1.0f / (float)d;
@@ -319,26 +342,32 @@ int launch_rmsnorm_rows(float *h, const bf16_t *gain, bf16_t *out, int32_t rows,
     // thread and split, four splits in flight, instead of four waves with d / 1024 float4 and two splits (us, before -> now,
     // K ranges as the product in front leaves them: 24 rows of 8192 9.6 -> 5.1, 597 of 2048 8.0 -> 6.1, 64 of 4096 4.9 ->
     // 4.8).  Beyond, four waves: more rows than the CUs hold workgroups keep as many loads in flight.
-#define SKV_RMS_WIDE(D_, CQ_)                                                                                      \
-  case D_ / 1024:                                                                                                  \
-    hipLaunchKernelGGL((rmsnorm_row_wg_kernel<CQ_, 0, D_ / 256 / CQ_>), dim3(rows), dim3(D_ / 4 / CQ_), 0, st, (float4 *)h, gain, (uint2 *)out, rows, \
-                       eps, inv_d, rstd_out, (const float4 *)partial, n_splits, RowSource{});                      \
-    return 0;
+    // (the tail's rows with a gain of one only: the norm in front of the fused K/V projection)
+    const bool tails = tail && !gain;
+    if (tails) *tail_done = true;
+#define SKV_RMS_FORM(CQ_, WAVES_)                                                                                                  \
+  do {                                                                                                                             \
+    if (tails)                                                                                                                     \
+      hipLaunchKernelGGL((rmsnorm_row_tail_kernel<CQ_, WAVES_>), dim3(rows), dim3(WAVES_ * 64), 0, st, (float4 *)h, (uint2 *)out, rows, eps, inv_d, rstd_out, \
+                         (const float4 *)partial, n_splits, *tail);                                                                \
+    else                                                                                                                           \
+      hipLaunchKernelGGL((rmsnorm_row_wg_kernel<CQ_, 0, WAVES_>), dim3(rows), dim3(WAVES_ * 64), 0, st, (float4 *)h, gain, (uint2 *)out, rows, eps, inv_d, \
+                         rstd_out, (const float4 *)partial, n_splits, RowSource{});                                                \
+    return 0;                                                                                                                      \
+  } while (0)
+#define SKV_RMS_WIDE(D_, CQ_) case D_ / 1024: SKV_RMS_FORM(CQ_, D_ / 256 / CQ_);
     if (rows <= 1024) switch (d / 1024) {
       SKV_RMS_WIDE(2048, 1) SKV_RMS_WIDE(3072, 1) SKV_RMS_WIDE(4096, 1) SKV_RMS_WIDE(5120, 2) SKV_RMS_WIDE(6144, 2) SKV_RMS_WIDE(7168, 2) SKV_RMS_WIDE(8192, 2)
       default: break;
     }
 #undef SKV_RMS_WIDE
-#define SKV_RMS_WG(CQ_)                                                                                            \
-  case CQ_:                                                                                                        \
-    hipLaunchKernelGGL((rmsnorm_row_wg_kernel<CQ_, 0>), dim3(rows), block, 0, st, (float4 *)h, gain, (uint2 *)out, rows, eps, inv_d, rstd_out, \
-                       (const float4 *)partial, n_splits, RowSource{});                                           \
-    return 0;
+#define SKV_RMS_WG(CQ_) case CQ_: SKV_RMS_FORM(CQ_, 4);
     switch (d / 1024) {
       SKV_RMS_WG(1) SKV_RMS_WG(2) SKV_RMS_WG(3) SKV_RMS_WG(4) SKV_RMS_WG(5) SKV_RMS_WG(6) SKV_RMS_WG(7) SKV_RMS_WG(8)
       default: break;
     }
 #undef SKV_RMS_WG
+#undef SKV_RMS_FORM
   }
   if (n_splits > 1) {   // otherwise: the splits in a pass of their own
     const int64_t n4 = (int64_t)rows * d / 4;

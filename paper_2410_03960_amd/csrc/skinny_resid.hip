@@ -27,10 +27,11 @@ __global__ __launch_bounds__(SR_WAVES * 64) void skinny_resid_kernel(SkinnyResid
   // what the finishing threads need besides the sums: requested first, used last
   const int fm = tid >> 4, fn = n0 + (tid & 15);   // this thread's row and column
   const bool fin = fm < p.M;
-  float h = 0.f, g = 1.f;
+  float h = 0.f, g = 1.f, g_tail = 1.f;
   if (fin) {
     h = p.h[(int64_t)fm * p.N + fn];
     if (p.gain) g = bf16_to_f32(p.gain[fn]);
+    if (p.h_tail) g_tail = bf16_to_f32(p.gain_tail[fn]);
   }
 
   const int all = p.K / 64, per = (all + SR_WAVES - 1) / SR_WAVES, s0 = wave * per;
@@ -86,6 +87,10 @@ __global__ __launch_bounds__(SR_WAVES * 64) void skinny_resid_kernel(SkinnyResid
   h += x;
   p.h[(int64_t)fm * p.N + fn] = h;
   if (p.out) p.out[(int64_t)fm * p.N + fn] = f32_to_bf16(h * g);
+  if (p.h_tail) {
+    p.h_tail[(int64_t)fm * p.N + fn] = h;
+    p.out_tail[(int64_t)fm * p.N + fn] = f32_to_bf16(h * g_tail);
+  }
   if (p.ssq) {
     float q = h * h;
     q += __shfl_xor(q, 1); q += __shfl_xor(q, 2); q += __shfl_xor(q, 4); q += __shfl_xor(q, 8);
