@@ -369,7 +369,7 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   best.kernel = MID_NONE;
   const bool packed = p.wpack && p.K % 256 == 0 && p.N % 256 == 0 && epi != EPI_STORE_F32 && (uint64_t)p.lda * 512 <= 0xffffffffull;   // (32-bit row offsets inside a 256-row tile)
   if (p.M <= 80) return best;
-  const bool far = (uint64_t)p.M * (uint64_t)p.lda * 2 >= 0xffffffffull;   // beyond the 32-bit row offsets of gemm_mid_kernel (gemm_wreg_kernel has whole pointers)
+  const bool far = (uint64_t)p.M * (uint64_t)p.lda * 2 >= 0xffffffffull;   // beyond the 32-bit row offsets of gemm_mid_kernel (gemm_wreg_kernel's start at its tile)
   if (!packed && (p.M >= 1024 || p.K % 64 != 0 || p.N % 64 != 0 || ((epi == EPI_QKV || epi == EPI_KV) && p.N % 128 != 0))) return best;
   const bool norm_out = epi == EPI_RESID && p.hb && p.ssq;
   const bool consumer = p.n_splits_out != nullptr;
