@@ -65,6 +65,14 @@ __device__ __forceinline__ void lds_dma16_at(const void *base, unsigned off, uns
 template <int N>
 __device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
 
+// Rotation of a pair of projected values by (c, s): a c - b s and b c + a s, each one product rounded and the other fused to it.  Which is
+// which is written out: left to the compiler it changed with the kernel, the tile height, the element and the code around, and what lies next
+// to a rounding boundary of bf16 with it.
+__device__ __forceinline__ void rotate_pair(float &a, float &b, const float c, const float s) {
+  const float first = fmaf(a, c, -(b * s));
+  b = fmaf(b, c, a * s);
+  a = first;
+}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));

@@ -781,10 +781,8 @@ __global__ __launch_bounds__(256) void kv_finish_kernel(GemmParams p, KvStore s,
     if (kind != 2) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float4 a = cs[e];
-        const float y0 = x0[2 * e] * a.x - x1[2 * e] * a.y, y1 = x1[2 * e] * a.x + x0[2 * e] * a.y;
-        const float z0 = x0[2 * e + 1] * a.z - x1[2 * e + 1] * a.w, z1 = x1[2 * e + 1] * a.z + x0[2 * e + 1] * a.w;
-        x0[2 * e] = y0; x1[2 * e] = y1; x0[2 * e + 1] = z0; x1[2 * e + 1] = z1;
+        rotate_pair(x0[2 * e], x1[2 * e], cs[e].x, cs[e].y);
+        rotate_pair(x0[2 * e + 1], x1[2 * e + 1], cs[e].z, cs[e].w);
       }
     }
     lo[t] = pack8(x0); hi[t] = pack8(x1);
@@ -876,8 +874,7 @@ __global__ void qkv_finish_kernel(QkvFinishParams p) {
   }
   if (kind != 2) {
     const float2 cs = p.cos_sin[(int64_t)row * half + i];
-    const float y0 = x0 * cs.x - x1 * cs.y, y1 = x1 * cs.x + x0 * cs.y;
-    x0 = y0; x1 = y1;
+    rotate_pair(x0, x1, cs.x, cs.y);
   }
   const bf16_t b0 = f32_to_bf16(x0), b1 = f32_to_bf16(x1);
   if (kind != 0 && p.cache_k) {

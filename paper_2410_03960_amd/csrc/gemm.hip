@@ -147,11 +147,11 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, floatx16 (&ac
                   if (b == blo) x1 = acc[b][bm][4 * jg + e];
                   if (b == bhi) x2 = acc[b][bm][4 * jg + e];
                 }
-                const float y1 = x1 * cv[e] - x2 * sv[e], y2 = x2 * cv[e] + x1 * sv[e];
+                rotate_pair(x1, x2, cv[e], sv[e]);
 #pragma unroll
                 for (int b = 0; b < FN; ++b) {
-                  if (b == blo) acc[b][bm][4 * jg + e] = y1;
-                  if (b == bhi) acc[b][bm][4 * jg + e] = y2;
+                  if (b == blo) acc[b][bm][4 * jg + e] = x1;
+                  if (b == bhi) acc[b][bm][4 * jg + e] = x2;
                 }
               }
             }
@@ -411,11 +411,11 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmParams &p, floatx16 
                       if (b == blo) x1 = acc[b][bm][4 * jg + e];
                       if (b == bhi) x2 = acc[b][bm][4 * jg + e];
                     }
-                    const float y1 = x1 * cv[e] - x2 * sv[e], y2 = x2 * cv[e] + x1 * sv[e];
+                    rotate_pair(x1, x2, cv[e], sv[e]);
 #pragma unroll
                     for (int b = 0; b < FN; ++b) {
-                      if (b == blo) acc[b][bm][4 * jg + e] = y1;
-                      if (b == bhi) acc[b][bm][4 * jg + e] = y2;
+                      if (b == blo) acc[b][bm][4 * jg + e] = x1;
+                      if (b == bhi) acc[b][bm][4 * jg + e] = x2;
                     }
                   }
                 }

@@ -207,9 +207,9 @@ __device__ __forceinline__ void gemm_epilogue_n64(const GemmParams &p, floatx16 
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x1 = acc[0][bm][4 * jg + e] * rs, x2 = acc[1][bm][4 * jg + e] * rs;
-          y1[e] = x1 * cv[e] - x2 * sv[e];
-          y2[e] = x2 * cv[e] + x1 * sv[e];
+          y1[e] = acc[0][bm][4 * jg + e] * rs;
+          y2[e] = acc[1][bm][4 * jg + e] * rs;
+          rotate_pair(y1[e], y2[e], cv[e], sv[e]);
         }
         const uint2 p1 = make_uint2(pack_bf16x2(y1[0], y1[1]), pack_bf16x2(y1[2], y1[3]));
         const uint2 p2 = make_uint2(pack_bf16x2(y2[0], y2[1]), pack_bf16x2(y2[2], y2[3]));

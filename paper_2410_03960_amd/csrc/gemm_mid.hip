@@ -311,8 +311,7 @@ __global__ __launch_bounds__(256) void rope_finish_kernel(GemmParams p, int rows
     x0 *= rs; x1 *= rs;
     if (kind != 2) {
       const float2 cs = p.cos_sin[(int64_t)row * (HD / 2) + i];
-      const float y0 = x0 * cs.x - x1 * cs.y, y1 = x1 * cs.x + x0 * cs.y;
-      x0 = y0; x1 = y1;
+      rotate_pair(x0, x1, cs.x, cs.y);
     }
     const bf16_t b0 = f32_to_bf16(x0), b1 = f32_to_bf16(x1);
     dst[i] = b0;
