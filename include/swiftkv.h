@@ -295,7 +295,7 @@ int swiftkv_op_mfma_rate(const void *operands, int32_t iters, void *sink, size_t
 /* Causal grouped-query attention over packed fresh sequences (Sec. 3.1):
  * q dev bf16 [T, Hq*hd], k, v dev bf16 [T, Hkv*hd] (already rotated), out dev
  * bf16 [T, Hq*hd]; seq_lens host.  workspace as from
- * swiftkv_op_attention_workspace.  Synchronises the stream (long tables are
+ * swiftkv_op_attention_workspace.  Synchronises the stream (its tables are
  * staged from pageable host memory). */
 int swiftkv_op_attention_prefill(const void *q, const void *k, const void *v, void *out,
                                  const int32_t *seq_lens, int32_t n_seqs, int32_t n_q_heads,

@@ -1297,14 +1297,6 @@ size_t swiftkv_op_attention_workspace(int64_t n_tokens, int32_t n_seqs, int32_t 
          align_up((size_t)(n_tokens / 64 + n_seqs) * 16) + 4096;
 }
 
-// The tables of a single operation.  Up to four small launches (5666 tokens in 6 sequences, one launch: 161 -> 158 us per call against
-// two copies from pageable memory and a fill); longer ones by a copy.
-static int stage_words(const std::vector<int32_t> &words, void *dst, hipStream_t st) {
-  if (words.size() <= 4 * (size_t)TABLE_WORDS) return launch_table(words.data(), (int32_t)words.size(), (int32_t *)dst, st);
-  HIP_TRY(hipMemcpyAsync(dst, words.data(), words.size() * 4, hipMemcpyHostToDevice, st));
-  return 0;
-}
-
 int swiftkv_op_attention_prefill(const void *q, const void *k, const void *v, void *out, const int32_t *seq_lens,
                                  int32_t B, int32_t Hq, int32_t Hkv, int32_t hd, void *workspace,
                                  size_t workspace_bytes, void *stream) {
@@ -1331,11 +1323,11 @@ int swiftkv_op_attention_prefill(const void *q, const void *k, const void *v, vo
   size_t o_vt = 0, o_qb = align_up((size_t)Hkv * hd * vt_ld * 2), o_kt = o_qb + align_up(qbs.size() * 4), o_sched = o_kt + align_up(kvt.size() * 4), total = o_sched + 256;
   if (total > workspace_bytes) return fail(SWIFTKV_ENOSPC, "workspace has %zu bytes, %zu needed", workspace_bytes, total);
   unsigned char *ws = (unsigned char *)workspace;
-  // both tables and the work queues' zeros (the workspace is the caller's and arrives uninitialised)
+  // both tables and the work queues' zeros (the workspace is the caller's and arrives uninitialised) in one copy
   std::vector<int32_t> words((o_sched + 32 - o_qb) / 4, 0);
   std::copy(qbs.begin(), qbs.end(), words.begin());
   std::copy(kvt.begin(), kvt.end(), words.begin() + (o_kt - o_qb) / 4);
-  if (int e = stage_words(words, ws + o_qb, st)) return e;
+  HIP_TRY(hipMemcpyAsync(ws + o_qb, words.data(), words.size() * 4, hipMemcpyHostToDevice, st));
   CommitParams cp{};
   cp.tiles = (const KVTile *)(ws + o_kt); cp.n_tiles = (int32_t)(kvt.size() / 4); cp.n_kv_heads = Hkv; cp.head_dim = hd;
   cp.k_src = (bf16_t *)k; cp.v_src = (bf16_t *)v; cp.ld_src = (int64_t)Hkv * hd;
@@ -1348,7 +1340,7 @@ int swiftkv_op_attention_prefill(const void *q, const void *k, const void *v, vo
   ap.sched = (int32_t *)(ws + o_sched);
   if (launch_attention_prefill(ap, st)) return fail(SWIFTKV_EHIP, "attention launch failed");
   if (int e = check_launch("attention")) return e;
-  HIP_TRY(hipStreamSynchronize(st));   // long tables are staged from this call's own (pageable) host vector
+  HIP_TRY(hipStreamSynchronize(st));   // the tables above were staged from this call's own (pageable) host vector
   return SWIFTKV_OK;
 }
 
@@ -1383,9 +1375,7 @@ int swiftkv_op_attention_decode(const void *q, void *out, const int32_t *n_keys,
   sort_rows(rows);
   hipStream_t st = (hipStream_t)stream;
   unsigned char *ws = (unsigned char *)workspace;
-  std::vector<int32_t> words(rows.size() * (sizeof(DecodeRow) / 4));
-  memcpy(words.data(), rows.data(), rows.size() * sizeof(DecodeRow));
-  if (int e = stage_words(words, ws, st)) return e;
+  HIP_TRY(hipMemcpyAsync(ws, rows.data(), rows.size() * sizeof(DecodeRow), hipMemcpyHostToDevice, st));
   AttnDecodeParams dp{};
   dp.q = (const bf16_t *)q; dp.out = (bf16_t *)out; dp.rows = (const DecodeRow *)ws; dp.n_rows = n_rows;
   dp.n_q_heads = Hq; dp.n_kv_heads = Hkv; dp.head_dim = hd;
@@ -1398,7 +1388,7 @@ int swiftkv_op_attention_decode(const void *q, void *out, const int32_t *n_keys,
   if (launch_attention_decode(dp, st)) return fail(SWIFTKV_EHIP, "decode attention launch failed");
   if (launch_decode_combine(dp.partial, dp.out, dp.rows, n_rows, Hq, hd, dp.n_split, st)) return fail(SWIFTKV_EHIP, "decode combine launch failed");
   if (int e = check_launch("single-query attention")) return e;
-  HIP_TRY(hipStreamSynchronize(st));   // a long row table is staged from this call's own (pageable) host vector
+  HIP_TRY(hipStreamSynchronize(st));   // the row table was staged from this call's own (pageable) host vector
   return SWIFTKV_OK;
 }
 

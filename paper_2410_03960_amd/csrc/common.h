@@ -367,9 +367,6 @@ int launch_plan_rmsnorm_embed(const PlanParams &p, const bf16_t *E, float *h, co
 int launch_rmsnorm_gather(const float *from, const int32_t *idx, float *h, const bf16_t *gain, bf16_t *out, int32_t rows, int32_t d, float eps,
                           hipStream_t st);
 int launch_f32_to_bf16(const float *x, bf16_t *out, int64_t n, hipStream_t st);
-// dst[0 .. n) = words[0 .. n) (host), TABLE_WORDS of them to a launch
-constexpr int TABLE_WORDS = 896;
-int launch_table(const int32_t *words, int32_t n, int32_t *dst, hipStream_t st);
 int launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st);
 // out[((n/32) * (K/16) + k/16) * 512 + ((k%16)/8 * 32 + n%32) * 8 + k%8] = W row n (through the optional
 // 16-row block pointer table), element k.  N % 32 == 0, K % 16 == 0.  rope_hd == 128 (N % 128 == 0) takes the

@@ -4,7 +4,6 @@
 #include "common.h"
 
 #include <algorithm>
-#include <cstring>
 
 // ---------------------------------------------------------------- plan -----
 // One thread per (new token, rotary pair): sequence by binary search in
@@ -467,24 +466,6 @@ int launch_pack_w(const bf16_t *const *wtab, const bf16_t *W, int64_t ldw, int32
 int launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st) {
   if (n <= 0) return 0;
   hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, v, n);
-  return 0;
-}
-
-// Host words to device memory inside a launch: they travel in the kernel's arguments, which the launch itself copies, so nothing has
-// to outlive the call and no copy (a launch of its own and, from pageable memory, a staging pass on the host) comes before it.
-struct TableWords { int32_t w[TABLE_WORDS]; };
-static_assert(sizeof(TableWords) + 16 <= 4096, "kernel arguments");
-__global__ void table_kernel(TableWords t, int32_t *dst, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = t.w[i];
-}
-int launch_table(const int32_t *words, int32_t n, int32_t *dst, hipStream_t st) {
-  for (int at = 0; at < n; at += TABLE_WORDS) {
-    const int m = std::min(n - at, TABLE_WORDS);
-    TableWords t;
-    memcpy(t.w, words + at, (size_t)m * 4);
-    hipLaunchKernelGGL(table_kernel, dim3((m + 255) / 256), dim3(256), 0, st, t, dst + at, m);
-  }
   return 0;
 }
 
