@@ -314,6 +314,7 @@ struct AttnDecodeParams {
   int32_t n_split;
   int32_t vector_unit;    // a bf16 cache with one or two query heads per KV head on the vector unit, splits of at least min_keys keys
   int32_t min_keys;       // (the matrix-unit kernels take whole 128-key steps)
+  int32_t head_pairs;     // set by the launch: the grid's order of rows and heads
 };
 // Most key splits of a single-query row: decode_combine_kernel takes a split per lane of a wave and holds one value of each.
 constexpr int MAX_SPLIT = 32;
