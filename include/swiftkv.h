@@ -265,7 +265,8 @@ int swiftkv_op_gemm_rows_static(const void *A, const void *W, void *C, int32_t M
  * the last tokens of more than 80 sequences, whose row-major weights the later layers read once.  scratch_bytes: room
  * for the K splits' partial sums.  head_dim: 64 or 128 for 4 and 5, else ignored.  plan_out (host): a SWIFTKV_GEMM_*
  * kernel; rows of its tile, or 16-column blocks of a workgroup of the weight-streaming kernels (M <= 80); K splits;
- * columns of K to a slice (0: not in slices). */
+ * columns of K to a slice (0: not in slices).  A launch of two tile heights and the form of up to 8 rows without norm
+ * passes are answered for by swiftkv_op_gemm_plan_tiles only. */
 enum {
   SWIFTKV_GEMM_STREAM_FIRST = 0,    /* weight streaming, K split among the waves of a workgroup */
   SWIFTKV_GEMM_STREAM_SEQ = 1,      /* ... slices of K one after the other behind a producer wave */
@@ -277,10 +278,18 @@ enum {
   SWIFTKV_GEMM_PACKED_DMA = 7,      /* fragment-order weights, activations by LDS-DMA */
   SWIFTKV_GEMM_PACKED_REG = 8,      /* fragment-order weights, activations through registers */
   SWIFTKV_GEMM_ROWS_REG = 9,        /* row-major weights, both operands through registers */
-  SWIFTKV_GEMM_STREAM_TILE = 10     /* 128-column tiles, both operands streamed through LDS */
+  SWIFTKV_GEMM_STREAM_TILE = 10,    /* 128-column tiles, both operands streamed through LDS */
+  SWIFTKV_GEMM_STREAM_FOLDED = 11   /* weight streaming of up to 8 rows, final residual sums with the next operand */
 };
 int swiftkv_op_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t flags, int32_t head_dim,
                          size_t scratch_bytes, int32_t plan_out[4]);
+/* The same with two things that the four words have no room for.  flags bit 4 = no norm pass stands between the rows'
+ * projections, the form of a pass of up to 8 rows where all its products allow it: epilogue 2 leaves the operand and
+ * the sums of squares from which the others take 1/rms (a product that does not allow it is answered for as without the
+ * bit).  plan_out[4], [5]: where one launch has tiles of two heights, rows of the lower ones and how many of the
+ * product's columns (SwiGLU: of both weights), the last ones, they cover, else 0; plan_out[1] is the taller. */
+int swiftkv_op_gemm_plan_tiles(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t flags, int32_t head_dim,
+                               size_t scratch_bytes, int32_t plan_out[6]);
 
 /* Measurement aid: the rate (TFLOP/s, host double) at which the chip executes
  * nothing but v_mfma_f32_32x32x16_bf16 on the caller's data -- `operands` is

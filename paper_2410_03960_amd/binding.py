@@ -27,7 +27,7 @@ EXPORTS = (
     "swiftkv_pack_bytes", "swiftkv_pack_bytes_min",
     "swiftkv_create", "swiftkv_destroy", "swiftkv_workspace_bytes", "swiftkv_workspace_bytes_prefix", "swiftkv_prefill",
     "swiftkv_kv_from_hidden", "swiftkv_set_early_exit", "swiftkv_export_exit_flags", "swiftkv_export_plan", "swiftkv_export_hidden", "swiftkv_op_gemm",
-    "swiftkv_op_gemm_packed", "swiftkv_op_gemm_plan", "swiftkv_op_gemm_rows", "swiftkv_op_gemm_rows_workspace", "swiftkv_op_gemm_rows_static",
+    "swiftkv_op_gemm_packed", "swiftkv_op_gemm_plan", "swiftkv_op_gemm_plan_tiles", "swiftkv_op_gemm_rows", "swiftkv_op_gemm_rows_workspace", "swiftkv_op_gemm_rows_static",
     "swiftkv_op_attention_prefill", "swiftkv_op_attention_workspace", "swiftkv_op_attention_decode", "swiftkv_op_attention_decode_workspace", "swiftkv_op_attention_decode_plan", "swiftkv_op_fp8_quantize", "swiftkv_op_mfma_rate",
     "swiftkv_flops", "swiftkv_set_timing", "swiftkv_get_timing", "swiftkv_last_error",
     "swiftkv_version",
@@ -93,6 +93,7 @@ def load() -> C.CDLL:
     lib.swiftkv_op_gemm.argtypes = [vp, vp, vp, i32, i32, i32, i32, i32, vp]
     lib.swiftkv_op_gemm_packed.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp]
     lib.swiftkv_op_gemm_plan.argtypes = [i32, i32, i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]
+    lib.swiftkv_op_gemm_plan_tiles.argtypes = lib.swiftkv_op_gemm_plan.argtypes
     lib.swiftkv_op_gemm_rows.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp, C.c_size_t, vp]
     lib.swiftkv_op_gemm_rows_static.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp]
     lib.swiftkv_op_gemm_rows_workspace.argtypes = [i32, i32]
@@ -328,7 +329,7 @@ class GemmPlan(NamedTuple):
 
 
 GEMM_KERNELS = {0: "stream_first", 1: "stream_seq", 3: "stream_slice", 4: "tile_128", 5: "tile_256", 6: "five_stage",
-                7: "packed_dma", 8: "packed_reg", 9: "rows_reg", 10: "stream_tile"}
+                7: "packed_dma", 8: "packed_reg", 9: "rows_reg", 10: "stream_tile", 11: "stream_folded"}
 GEMM_EPILOGUES = ("bf16", "f32", "resid", "swiglu", "qkv", "kv")
 GEMM_SCRATCH = 16 * 80 * 8192 * 4     # bytes for K splits that swiftkv_prefill and swiftkv_kv_from_hidden have
 
@@ -340,6 +341,20 @@ def op_gemm_plan(epilogue: str, M: int, N: int, K: int, packed: bool = False, co
     out = (C.c_int32 * 4)()
     _check(load().swiftkv_op_gemm_plan(GEMM_EPILOGUES.index(epilogue), M, N, K, int(packed) + 2 * int(consumer_adds) + 4 * int(norm_out) + 8 * int(last_tokens),
                                        head_dim, scratch, out))
+    return GemmPlan(GEMM_KERNELS[out[0]], out[1], out[2], out[3])
+
+
+def op_gemm_low_tiles(M: int, N: int, K: int, scratch: int = GEMM_SCRATCH) -> tuple:
+    """(rows, columns) of the lower tiles of a SwiGLU product with fragment-order weights, whose launch may have two heights; (0, 0): one."""
+    out = (C.c_int32 * 6)()
+    _check(load().swiftkv_op_gemm_plan_tiles(GEMM_EPILOGUES.index("swiglu"), M, N, K, 1, 0, scratch, out))
+    return out[4], out[5]
+
+
+def op_gemm_plan_folded(epilogue: str, M: int, N: int, K: int, consumer_adds: bool = False, scratch: int = GEMM_SCRATCH) -> GemmPlan:
+    """The kernel of a product of up to 8 rows in a pass whose products stand back to back, no norm pass between them."""
+    out = (C.c_int32 * 6)()
+    _check(load().swiftkv_op_gemm_plan_tiles(GEMM_EPILOGUES.index(epilogue), M, N, K, 16 + 2 * int(consumer_adds), 0, scratch, out))
     return GemmPlan(GEMM_KERNELS[out[0]], out[1], out[2], out[3])
 
 

@@ -1171,10 +1171,10 @@ int swiftkv_export_hidden(swiftkv_ctx *c, const void *workspace, void *hidden_ou
 }
 
 // ------------------------------------------------------- single operations ----
-int swiftkv_op_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t flags, int32_t head_dim, size_t scratch_bytes,
-                         int32_t plan_out[4]) {
+int swiftkv_op_gemm_plan_tiles(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t flags, int32_t head_dim, size_t scratch_bytes,
+                               int32_t plan_out[6]) {
   if (!plan_out) return fail(SWIFTKV_EINVAL, "null argument");
-  if (epilogue < EPI_STORE_BF16 || epilogue > EPI_KV || flags < 0 || flags > 15) return fail(SWIFTKV_EINVAL, "unknown epilogue or flags");
+  if (epilogue < EPI_STORE_BF16 || epilogue > EPI_KV || flags < 0 || flags > 31) return fail(SWIFTKV_EINVAL, "unknown epilogue or flags");
   if (M < 1 || N < 16 || K < 8 || (N % 16) || (K % 8)) return fail(SWIFTKV_EINVAL, "need M >= 1, N %% 16 == 0, K %% 8 == 0");
   // (pointers that the choice only asks for)
   const bf16_t some = 0;
@@ -1184,7 +1184,10 @@ int swiftkv_op_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int3
   GemmRoute r;
   if (M <= SKINNY_MAX_ROWS) {   // Q, K and V leave as fp32 and their splits to the pass that rotates them
     SkinnyParams s{nullptr, M, N, K, nullptr, nullptr, nullptr, scratch_bytes ? &partial : nullptr, scratch_bytes, nullptr, rope || adds ? &ns : nullptr};
-    r = route_skinny(s, rope ? EPI_STORE_F32 : epilogue);
+    const bool folded = flags & 16;
+    if (folded && epilogue != EPI_RESID && skinny_takes_ssq(M, N, K)) s.ssq = &partial;
+    if (folded && epilogue == EPI_RESID && skinny_resid_pays(M, N, K)) r = GemmRoute{SWIFTKV_GEMM_STREAM_FOLDED, 1, 1, 0};
+    else r = route_skinny(s, rope ? EPI_STORE_F32 : epilogue);
   } else {
     GemmParams g{};
     g.lda = K; g.M = M; g.N = epilogue == EPI_SWIGLU ? 2 * N : N; g.K = K; g.head_dim = head_dim;
@@ -1196,6 +1199,16 @@ int swiftkv_op_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int3
     r = route_gemm(g, epilogue);
   }
   plan_out[0] = r.kernel; plan_out[1] = r.tile; plan_out[2] = r.n_splits; plan_out[3] = r.slice;
+  plan_out[4] = r.low_tile; plan_out[5] = r.low_columns;
+  return SWIFTKV_OK;
+}
+int swiftkv_op_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t flags, int32_t head_dim, size_t scratch_bytes,
+                         int32_t plan_out[4]) {
+  int32_t plan[6];
+  if (!plan_out) return fail(SWIFTKV_EINVAL, "null argument");
+  if (flags < 0 || flags > 15) return fail(SWIFTKV_EINVAL, "unknown epilogue or flags");
+  if (int e = swiftkv_op_gemm_plan_tiles(epilogue, M, N, K, flags, head_dim, scratch_bytes, plan)) return e;
+  for (int i = 0; i < 4; ++i) plan_out[i] = plan[i];
   return SWIFTKV_OK;
 }
 

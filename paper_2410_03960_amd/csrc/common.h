@@ -186,8 +186,9 @@ struct MidPlan {
 MidPlan plan_gemm_mid(const GemmParams &p, int epi);
 [[nodiscard]] int launch_gemm_mid(const GemmParams &p, int epi, const MidPlan &pl, hipStream_t st);
 // What launch_gemm (variant 0) and launch_skinny run, for swiftkv_op_gemm_plan: a SWIFTKV_GEMM_* kernel, the rows of its
-// tile (weight streaming: column blocks of 16 per workgroup), K splits, columns of K to a slice (0: no slices).
-struct GemmRoute { int32_t kernel, tile, n_splits, slice; };
+// tile (weight streaming: column blocks of 16 per workgroup), K splits, columns of K to a slice (0: no slices); of two tile
+// heights in a launch the taller, and rows and columns of the lower tiles.
+struct GemmRoute { int32_t kernel, tile, n_splits, slice, low_tile, low_columns; };
 GemmRoute route_gemm(const GemmParams &p, int epi);
 int launch_gemm_wreg(const GemmParams &p, int epi, int fm, int fm_low, hipStream_t st);
 int launch_gemm_stream(const GemmParams &p, int epi, int fm, bool packed, hipStream_t st);

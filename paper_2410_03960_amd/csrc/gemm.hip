@@ -732,7 +732,7 @@ int launch_mfma_rate(const bf16_t *operands, float *sink, int32_t n_workgroups, 
 GemmRoute route_gemm(const GemmParams &p, int epi) {
   const MidPlan pl = plan_gemm_mid(p, epi);
   static const int kernel[] = {0, SWIFTKV_GEMM_PACKED_DMA, SWIFTKV_GEMM_PACKED_REG, SWIFTKV_GEMM_ROWS_REG, SWIFTKV_GEMM_STREAM_TILE};
-  if (pl.kernel != MID_NONE) return GemmRoute{kernel[pl.kernel], 32 * pl.fm, pl.n_splits, 0};
+  if (pl.kernel != MID_NONE) return GemmRoute{kernel[pl.kernel], 32 * pl.fm, pl.n_splits, 0, 32 * pl.fm_low, 256 * pl.low_tiles_n};
   if (p.M < 1024) return GemmRoute{SWIFTKV_GEMM_TILE_128, 128, 1, 0};
   return GemmRoute{p.K % BK ? SWIFTKV_GEMM_TILE_256 : SWIFTKV_GEMM_FIVE_STAGE, 256, 1, 0};
 }

@@ -5,6 +5,7 @@ import pytest
 
 from paper_2410_03960_amd import binding as B
 from tests import test_gpu_gemm_heights as H
+from tests import test_gpu_gemm_two_heights as TWO
 from tests import test_gpu_mid as MID
 
 
@@ -128,3 +129,23 @@ def test_parity_cases_of_the_mid_size_decoders():
             assert product == "feed" or (plan.kernel, plan.tile) == ("packed_reg", 64)
         for product, plan in H.planned(wl, sum(MID.LENS), False).items():
             assert product == "feed" or plan.kernel == "five_stage"
+
+
+# Gate and up in two tile heights, as the GPU parity cases say; one height where K is split, and for other products.
+def test_parity_cases_reach_two_tile_heights():
+    for wl in (TWO.FEED, TWO.LONG):
+        for rows, low in TWO.LOW_TILES.items():
+            assert B.op_gemm_low_tiles(rows, wl.shape.ffn, wl.shape.hidden) == low
+    assert {low[0] for low in TWO.LOW_TILES.values()} == {0, 128, 192}
+    assert B.op_gemm_plan("swiglu", 100, 512, 4096, packed=True).n_splits > 1 and B.op_gemm_low_tiles(100, 512, 4096) == (0, 0)
+
+
+# Up to eight rows with no norm pass between the products: the residual one is final, the others take 1/rms in the ring kernel.
+def test_products_of_up_to_eight_rows_without_norm_passes():
+    for rows in (1, 8):
+        assert B.op_gemm_plan_folded("resid", rows, 4096, 14336) == ("stream_folded", 1, 1, 0)
+        for epilogue, N in (("swiglu", 4096), ("qkv", 6144), ("bf16", 4096)):
+            assert B.op_gemm_plan_folded(epilogue, rows, N, 4096, consumer_adds=epilogue == "bf16").kernel == "stream_seq"
+    assert B.op_gemm_plan("swiglu", 8, 4096, 4096).kernel == "stream_first"
+    for rows, N, K in ((9, 4096, 14336), (1, 5120, 13824)):                 # nine rows; 320 blocks of 16 columns over 256 CUs
+        assert B.op_gemm_plan_folded("resid", rows, N, K, consumer_adds=True) == B.op_gemm_plan("resid", rows, N, K, consumer_adds=True)

@@ -11,16 +11,19 @@ from workloads.configs import ModelShape, Workload
 
 pytestmark = pytest.mark.gpu
 FEED = Workload("two_heights", ModelShape(2, 256, 2, 2, 128, 14336, 256, 1e4, 1e-5), l=1, g=1, seed=2311)
+LONG = Workload("two_heights_long", ModelShape(2, 1024, 8, 2, 128, 14336, 256, 1e4, 1e-5), l=1, g=1, seed=2312)   # (16 steps: stages refilled with live data)
+LOW_TILES = {897: (192, 12288), 1000: (0, 0), 2045: (128, 4096), 2048: (128, 4096), 3300: (192, 3584)}            # rows -> rows and columns of the lower tiles
 
 
-@pytest.mark.parametrize("rows", [897, 1000, 2045, 2048, 3300])
-def test_two_heights(rows):
+@pytest.mark.parametrize("wl,rows", [(FEED, r) for r in LOW_TILES] + [(LONG, 897), (LONG, 2045)], ids=lambda v: str(getattr(v, "name", v)))
+def test_two_heights(wl, rows):
     from paper_2410_03960_amd import binding as B
-    store = WL.make_weights(FEED, "cpu", keep=True)
-    ctx = B.Context(FEED.shape, G.device_weights(store), FEED.l, FEED.g, packed_weights=True)
-    batch = WL.build_batch(FEED, lens=[190] * (rows // 190) + [rows % 190], shuffled=True)
+    assert B.op_gemm_low_tiles(rows, wl.shape.ffn, wl.shape.hidden) == LOW_TILES[rows]
+    store = WL.make_weights(wl, "cpu", keep=True)
+    ctx = B.Context(wl.shape, G.device_weights(store), wl.l, wl.g, packed_weights=True)
+    batch = WL.build_batch(wl, lens=[190] * (rows // 190) + [rows % 190], shuffled=True)
     logits, cache, _ = G.run_gpu(ctx, batch)
-    ologits, ocache, _ = G.run_oracle(FEED.shape, store, batch, FEED.l, FEED.g, dtype=torch.float32)
-    G.compare_caches(cache, ocache, batch, label=FEED.name)
-    G.compare_logits(logits, ologits, label=FEED.name)
+    ologits, ocache, _ = G.run_oracle(wl.shape, store, batch, wl.l, wl.g, dtype=torch.float32)
+    G.compare_caches(cache, ocache, batch, label=wl.name)
+    G.compare_logits(logits, ologits, label=wl.name)
     assert all(torch.equal(a, b) for a, b in zip((logits, cache.data), (lambda r: (r[0], r[1].data))(G.run_gpu(ctx, batch))))
