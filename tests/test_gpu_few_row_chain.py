@@ -5,6 +5,7 @@ import pytest
 import workloads as WL
 from workloads.configs import ModelShape, Workload
 from tests import gpu_helpers as G
+from tests.helpers import rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +33,23 @@ def test_rows_through_both_forms(name, l, g, lens):
     ologits, ocache, _ = G.run_oracle(shape, store, batch, l, g)
     G.compare_caches(cache, ocache, batch, label=name)
     G.compare_logits(logits, ologits, label=name)
+
+
+@pytest.mark.parametrize("per_token", [False, True])
+@pytest.mark.parametrize("lens", [[1] * 8, [3, 2, 1, 1], [30] * 7 + [1]])
+def test_codes_and_scales_of_rows_without_a_norm_pass(lens, per_token):
+    """Over an e4m3 cache: the absmax of each head, or of each token, comes from sums that carry the rows' 1/rms."""
+    from paper_2410_03960_amd import binding as B
+    shape = SHAPES["even"]
+    for rows in {min(8, sum(lens)), len(lens)}:
+        assert all(B.op_gemm_plan_folded("resid", rows, shape.hidden, k).kernel == "stream_folded" for k in (shape.q_dim, shape.ffn))
+    wl = Workload("chain_fp8", shape, l=2, g=1, seed=3012)
+    store = WL.make_weights(wl, "cpu", keep=True)
+    batch = WL.build_batch(wl, lens=lens, shuffled=True)
+    ctx = B.Context(shape, G.device_weights(store), 2, 1)
+    logits, cache, ws = G.run_gpu(ctx, batch, fp8=True, scale_mode=B.SWIFTKV_SCALE_PER_TOKEN if per_token else B.SWIFTKV_SCALE_COMPUTE_ABSMAX)
+    G.check_plan(ctx, ws, batch)
+    ologits, ocache, _ = G.run_oracle(shape, store, batch, 2, 1, fp8=True, per_token=per_token)
+    assert rel_err(cache.scales.cpu(), ocache.scales) <= 2e-2
+    G.compare_caches(cache, ocache, batch, rel=G.FP8_REL, cos=G.FP8_COS, label=wl.name)
+    G.compare_logits(logits, ologits, rel=G.FP8_REL, cos=G.FP8_COS, label=wl.name)

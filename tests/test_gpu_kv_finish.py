@@ -15,6 +15,7 @@ SHAPES = {
     "narrow": ModelShape(3, 256, 4, 2, 64, 512, 256, 5e5, 1e-5),
     "hd128": ModelShape(3, 512, 8, 4, 128, 512, 256, 5e5, 1e-5),
     "wide": ModelShape(3, 256, 12, 12, 128, 256, 256, 5e5, 1e-5),
+    "wider": ModelShape(3, 256, 36, 36, 128, 256, 256, 5e5, 1e-5),   # 4608 columns, past what one wave holds: a token's scale by passes of their own
 }
 
 
