@@ -10,6 +10,8 @@
 // barrier until the end.  Every workgroup reads all activation rows (from L2), which is why the rows are few.
 #include "common.h"
 
+#include <cmath>
+
 namespace {
 
 constexpr int SR_WAVES = 8;
@@ -105,10 +107,19 @@ __global__ __launch_bounds__(SR_WAVES * 64) void skinny_resid_kernel(SkinnyResid
 // 5120 x 13824 25.7 -> 30.3: with 320 column blocks 64 CUs have two and the others one.  So the blocks have to be at most one per CU, or
 // their last round nearly full.  Eight rows: 21.8 -> 21.4, 2048 x 8192 8.5 -> 10.5; 16 rows (two requests for activations) 22.0 -> 23.8
 // and 8.7 -> 12.4, not taken.
+// Fewer than 256 blocks leave CUs without work while a wave walks K / 8, which the ring kernel's K ranges do not; more so with more rows
+// in a step.  So K is bounded by the CUs left over and the rows; where K is far longer than N the chain loses whatever the rows.  The
+// norm of a width that 1024 does not divide is two launches here (K ranges added by one), so there more K pays.  A pass of four layers
+// against the form with norm passes, 1, 2, 4, 8 rows, K of down over N: 1024, 8192 0.88 0.83 0.88 0.95, 14336 0.97 0.98 1.00 1.03, 20480
+// 1.03 1.04 1.06 1.11; 2048, 8192 0.92 0.93 0.95 0.97, 16384 0.96 0.97 0.98 1.02, 40960 1.04 1.05 1.06 1.08; 3072, 49152 0.98 0.99 1.00
+// 1.03; 512, 16384 0.85 0.85 0.86 0.89, 32768 1.04 1.05 1.09 1.13; 1536, 32768 0.89 0.89 0.90 0.95, 49152 0.97 0.96 0.97 1.02.
 bool skinny_resid_pays(int M, int N, int K) {
   if (M < 1 || M > SKINNY_RESID_ROWS || N % 16 != 0 || K % 64 != 0 || (uint64_t)16 * (uint64_t)K * 2 > 0xffffffffull) return false;   // (32-bit row offsets)
   const int blocks = N / 16;
-  return blocks <= 256 || (blocks + 255) / 256 * 256 <= 1.15 * blocks;
+  if (blocks > 256) return (blocks + 255) / 256 * 256 <= 1.15 * blocks;
+  const double idle = 1 - blocks / 256.0;
+  const bool one_norm = N % 1024 == 0;
+  return K <= (one_norm ? 16 : 40) * (int64_t)N && K * std::pow(idle, 1.5) * (1 + 0.3 * M) <= (one_norm ? 19500 : 56000);
 }
 int launch_skinny_resid(const SkinnyResidParams &p, hipStream_t st) {
   static bool attr = false;

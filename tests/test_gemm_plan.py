@@ -149,3 +149,12 @@ def test_products_of_up_to_eight_rows_without_norm_passes():
     assert B.op_gemm_plan("swiglu", 8, 4096, 4096).kernel == "stream_first"
     for rows, N, K in ((9, 4096, 14336), (1, 5120, 13824)):                 # nine rows; 320 blocks of 16 columns over 256 CUs
         assert B.op_gemm_plan_folded("resid", rows, N, K, consumer_adds=True) == B.op_gemm_plan("resid", rows, N, K, consumer_adds=True)
+
+
+# ... and only where a wave's walk through K / 8 does not outlast the K ranges of the other kernel on the CUs that few columns leave over.
+@pytest.mark.parametrize("N,K,rows", [      # most rows that take the form
+    (1024, 4096, 8), (1024, 8192, 8), (1024, 14336, 3), (1024, 16384, 2), (1024, 20480, 0), (2048, 8192, 8), (2048, 16384, 7), (2048, 32768, 2), (2048, 40960, 0),
+    (3072, 32768, 8), (3072, 49152, 7), (4096, 49152, 8), (8192, 28672, 8), (512, 16384, 8), (512, 32768, 0), (1536, 32768, 8), (1536, 49152, 4)])
+def test_few_columns_over_a_long_contraction_keep_k_ranges(N, K, rows):
+    taken = [m for m in range(1, 10) if B.op_gemm_plan_folded("resid", m, N, K, consumer_adds=True).kernel == "stream_folded"]
+    assert taken == list(range(1, rows + 1))
