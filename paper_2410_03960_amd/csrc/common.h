@@ -105,7 +105,7 @@ struct KVTile {  // 64 consecutive new tokens of one sequence
 enum KvStoreKind { KV_STORE_BF16 = 0, KV_STORE_GIVEN = 1, KV_STORE_PER_TOKEN = 2 };   // bf16; e4m3 under the scales given per head / computed per token
 struct KvStore {
   int32_t kind;
-  int32_t rows;               // bit 0: K rows are wanted too (k_out, stage), bit 1: V rows
+  int32_t rows;               // bit 0: K rows are wanted too (k_out, stage), bit 1: V rows (not with vt)
   void *cache_k, *cache_v;    // planes of the first cache layer written
   int64_t layer_bytes;        // from one projection's planes to the next one's
   float *scales;              // of that layer: [2][Hkv], or [2][n_slots] (written)

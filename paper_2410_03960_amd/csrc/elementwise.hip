@@ -710,10 +710,7 @@ __global__ __launch_bounds__(256) void kv_finish_kernel(GemmParams p, KvStore s,
       for (int ii = 0; ii < NI; ++ii) {
         const int i = tid + ii * 256, r = i / CH, c = i % CH;
         const uint4 v = pack8(x[ii]);
-        if (r < tile.n_valid) {
-          *(uint4 *)((bf16_t *)s.cache_v + (slot[ii] * n_kv + head) * HD + c * 8) = v;
-          if (s.rows & 2) *(uint4 *)(p.v_out + (int64_t)(tile.row0 + r) * p.kv_dim + head * HD + c * 8) = v;
-        }
+        if (r < tile.n_valid) *(uint4 *)((bf16_t *)s.cache_v + (slot[ii] * n_kv + head) * HD + c * 8) = v;
         sv[v_chunk<HD>(r, c)] = v;
       }
       if (tile.vt_col0 < 0) return;
