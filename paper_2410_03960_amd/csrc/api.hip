@@ -177,7 +177,8 @@ int check_launch(const char *what) {
 }
 
 // Time of a launch of the matrix-unit single-query attention in ns key splits, and of the combine pass behind more than one, us.
-// Rows of one length, fitted to 17000 timings of 1 to 256 rows of 17 to 40000 keys (its choice costs 0.5 % on average):
+// Rows of one length, fitted to 17000 timings of 1 to 256 rows of 17 to 40000 keys when a step's masks still cost what its products do (its
+// choice cost 0.5 % on average; with the present kernels 1.2 % over 424 shapes, and 2.5 % over 149 of mixed lengths):
 //  - A workgroup's chain of 128-key steps, of which each takes what its conversions and products take.
 //  - The K/V stream at 5 TB/s, longer by part of what the busiest CU has above an even share: 8 rows x 8 KV heads x 20000 e4m3
 //    keys in 8 splits, two workgroups to each CU, 73 us, in 10 (three to half of them) 89.

@@ -382,7 +382,7 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
       {MID_ROWS, 5, 1.45, 0}, {MID_ROWS, 4, 1.33, 0}, {MID_ROWS, 3, 1.27, 0}, {MID_ROWS, 2, 1.20, p.partial ? 0.76 : 0.92}};   // (the last: 0.80 to 0.92 over a whole long K)
   // epilogue of a 256-row tile
   const double epi_us = norm_out ? 25 : epi == EPI_RESID || epi == EPI_QKV ? 12 : epi == EPI_KV ? 10 : 4;
-  // Beyond 24 rounds of the full height an uneven last one is under 4 %, less than the lower heights lose in a run that long
+  // Beyond 24 rounds of the full height an uneven last one is under 4 %, less than a lower height throughout loses in a run that long
   // (more bytes per product on a power-limited chip; gate/up of 32832 rows, a whole launch over its steps: 1.34 us per step
   // of 224 rows against 1.45 of 256, where the table has 1.27 and 1.46; 6.02 ms per launch -> 5.85).
   const bool full = packed && ((int64_t)((p.M + 255) / 256) * tiles_n + 255) / 256 > 24;
@@ -407,6 +407,8 @@ MidPlan plan_gemm_mid(const GemmParams &p, int epi) {
   // height hold some columns of tiles, the rest go to CUs that have no tile of the last tall round and then to rounds of their own.
   // us per launch, 28672 columns, K 4096, one height -> two: 900 rows 203 -> 189, 1300 266 -> 262, 2048 421 -> 393, 3300 638 -> 617,
   // 4700 878 -> 853, 13000 2278 -> 2207; 16384 columns, K 2048, 5000 rows 299 and 308 were about the worst of the others (not taken).
+  // Beyond 24 rounds the lower tiles are the last few columns only, and it still pays: 14300 rows 2490 -> 2481, 14600 2587 -> 2562, 15700
+  // 2760 -> 2715, 18000 3171 -> 3129, 24000 4194 -> 4137, 32832 5673 -> 5628, 64000 11347 and 11357.
   if (packed && epi == EPI_SWIGLU && best.kernel == MID_WREG && best.n_splits == 1) {
     const int rows_n = (p.M + 255) / 256, most = (int)std::min<int64_t>((int64_t)rows_n * tiles_n / 256, 1 << 20);
     const double a = all_steps * forms[0].t1 + 4 + epi_us;

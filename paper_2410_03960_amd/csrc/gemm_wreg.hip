@@ -24,9 +24,9 @@ namespace {
 // 0.89 us at FM = 4 (48 KB, 128 rows), 1.12 at 6, 1.46 at 8 (64 KB, 256 rows) with all CUs busy, so a taller
 // tile is cheaper per row and a shorter one is taken where it fills a last round or leaves room for K splits.
 // The four waves run in step, so their fragment reads are spread over all products of a sub-step (in a burst behind the
-// first half of them they took every LDS cycle of that half).  Together with the uniform bases, us per product before -> now:
-// 16384 x 28672 x 4096 2771 -> 2725, 2048 x 28672 x 4096 in 192-row tiles 386 -> 380, 512 x 28672 x 4096 101.5 -> 98.7, 333 in
-// 192-row tiles 81.9 -> 80.5.  No gain, measured on this loop: six to ten stages where they fit, weights four steps ahead (the wait
+// first half of them they took every LDS cycle of that half; gate and up of 16384 rows, K 4096, 2714 -> 2706 us, of 1300 and 6000 level,
+// down 0.3 to 0.6 %).  The uniform bases of the requests are worth more: with a pointer per lane 2739, 6000 rows 1040 -> 1028,
+// 1300 252 -> 249, down of 16384 1439 -> 1424.  No gain, measured on this loop: six to ten stages where they fit, weights four steps ahead (the wait
 // for a stage then leaves 22 instead of 14 requests in flight), 32 KB of a step's weights in one piece, each wave's requests
 // a product later than its neighbour's; eight waves of 128 x 64, two to a SIMD: 3 % slower, as every wave's wait is stricter.
 template <int EPI, int FM, bool NORM_OUT>
